@@ -5,10 +5,10 @@
 //     re-laid into the packed k-major image the MFMA B operand wants (a few hundred KB, one
 //     small kernel into the workspace), then each workgroup multiplies a 32-token tile with
 //     all E columns and reduces each row (max, first arg-max, sum of exponentials) in LDS.
-//   anything else (fp32 tensors, small or odd E): one wavefront per token, lanes over
-//     experts, binary32 FMA in ascending k.
+//   anything else (fp32 tensors, small or odd E): route_direct.h, matrix instructions on the router matrix as it lies.
 #include "gemm_bf16.h"
 #include "route.h"
+#include "route_direct.h"
 #include "route_resident.h"
 
 namespace moe {
@@ -158,99 +158,6 @@ __global__ __launch_bounds__(GEMM_THREADS) void route_mfma_kernel(const bf16_t *
     }
 }
 
-// one wavefront per token; lanes over experts
-template <bool BF16>
-__global__ __launch_bounds__(256) void route_generic_kernel(const void *__restrict__ xv, const void *__restrict__ wv,
-                                                            const float *__restrict__ bias, int T, int d, int E,
-                                                            int top_k, int renormalize,
-                                                            int32_t *__restrict__ idx, float *__restrict__ prob,
-                                                            float *__restrict__ logits_opt)
-{
-    const int lane = threadIdx.x & 63;
-    const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (s >= T) return;
-    constexpr int PER = MOE_MAX_EXPERTS / WAVE;
-    float l[PER];
-    float best = -INFINITY;
-    int bi = 0x7fffffff;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        int e = lane + i * WAVE;
-        l[i] = -INFINITY;
-        if (e < E) {
-            float acc = 0.f;
-            if (BF16) {
-                const bf16_t *x = (const bf16_t *)xv + (size_t)s * d;
-                const bf16_t *w = (const bf16_t *)wv + e;
-                for (int k = 0; k < d; ++k) acc = fmaf(bf16_to_f32(x[k]), bf16_to_f32(w[(size_t)k * E]), acc);
-            } else {
-                const float *x = (const float *)xv + (size_t)s * d;
-                const float *w = (const float *)wv + e;
-                for (int k = 0; k < d; ++k) acc = fmaf(x[k], w[(size_t)k * E], acc);
-            }
-            l[i] = acc + (bias ? bias[e] : 0.f);
-            if (logits_opt) logits_opt[(size_t)s * E + e] = l[i];
-            argmax_merge(best, bi, l[i], e);
-        }
-    }
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        float ov = __shfl_xor(best, o, 64);
-        int oi = __shfl_xor(bi, o, 64);
-        argmax_merge(best, bi, ov, oi);
-    }
-    float z = 0.f;
-#pragma unroll
-    for (int i = 0; i < PER; ++i)
-        if (lane + i * WAVE < E) z += expf(l[i] - best);
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) z += __shfl_xor(z, o, 64);
-    if (top_k == 1) {
-        if (lane == 0) {
-            idx[s] = bi;
-            prob[s] = 1.f / z;
-        }
-        return;
-    }
-    int ci[MOE_MAX_TOPK];
-    float cw[MOE_MAX_TOPK];
-    ci[0] = bi;
-    cw[0] = 1.f / z;
-    float pv = best, wsum = cw[0];
-    int pi = bi;
-#pragma unroll
-    for (int j = 1; j < MOE_MAX_TOPK; ++j) {
-        if (j < top_k) {
-            float v = -INFINITY;
-            int vi = 0x7fffffff;
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                const int e = lane + i * WAVE;
-                if (e < E && (l[i] < pv || (l[i] == pv && e > pi))) argmax_merge(v, vi, l[i], e);
-            }
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                float ov = __shfl_xor(v, o, 64);
-                int oi = __shfl_xor(vi, o, 64);
-                argmax_merge(v, vi, ov, oi);
-            }
-            ci[j] = vi;
-            cw[j] = expf(v - best) / z;
-            wsum += cw[j];
-            pv = v;
-            pi = vi;
-        }
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int j = 0; j < MOE_MAX_TOPK; ++j)
-            if (j < top_k) {
-                idx[(size_t)j * T + s] = ci[j];
-                prob[(size_t)j * T + s] = renormalize ? cw[j] / wsum : cw[j];
-            }
-    }
-}
-
 static inline bool route_uses_mfma(int d, int E, int dtype)
 {
     return dtype == MOE_BF16 && (E == 128 || E == 256) && d % RT_BK == 0;
@@ -321,11 +228,9 @@ int route_launch(const void *x, const void *w_router, int w_layout, const float 
         }
 #undef MOE_ROUTE_LAUNCH
     } else if (dtype == MOE_BF16) {
-        hipLaunchKernelGGL(route_generic_kernel<true>, dim3(ceil_div(T, 4)), dim3(256), 0, st, x, w_router, b_router, T,
-                           d, E, top_k, renormalize, idx, prob, logits_opt);
+        route_direct_launch<true>(x, w_router, b_router, T, d, E, top_k, renormalize, idx, prob, logits_opt, st);
     } else {
-        hipLaunchKernelGGL(route_generic_kernel<false>, dim3(ceil_div(T, 4)), dim3(256), 0, st, x, w_router, b_router,
-                           T, d, E, top_k, renormalize, idx, prob, logits_opt);
+        route_direct_launch<false>(x, w_router, b_router, T, d, E, top_k, renormalize, idx, prob, logits_opt, st);
     }
     MOE_CHECK_LAUNCH(who);
     return MOE_OK;
