@@ -121,11 +121,14 @@ def _ptr(t):
         return None
     if not (t.is_cuda and t.is_contiguous()):
         raise ValueError("device-resident contiguous tensors only")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device as a raw handle.  torch.cuda.current_stream() builds a Stream object
+    around the same handle and takes 7 us for it, more than the rest of a call's marshalling: a layer of four calls
+    was issued in 46-48 us, 29-31 us without it."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _i32(n, dev):
@@ -148,8 +151,7 @@ def moe_route(x, w_router, b_router=None, want_logits=False, out=None, ws=None, 
         raise ValueError("w_router must be [d, E] (or its packed image) in the dtype of x")
     idx, prob = out if out is not None else (_i32(T, dev), torch.empty(T, dtype=torch.float32, device=dev))
     logits = torch.empty(T, E, dtype=torch.float32, device=dev) if want_logits else None
-    need = lib().moe_route_workspace_bytes(T, d, E, dt)
-    ws = ws if ws is not None else _ws(need, dev)
+    ws = ws if ws is not None else _ws(lib().moe_route_workspace_bytes(T, d, E, dt), dev)
     _check(lib().moe_route(_ptr(x), _ptr(w_router), w_layout, _ptr(b_router), T, d, E, dt, _ptr(idx), _ptr(prob),
                            _ptr(logits), _ptr(ws), ws.numel(), _stream()))
     return idx, prob, logits
