@@ -10,16 +10,18 @@
 //   gemm2     y_perm = h * W2[e]
 // At large batch the list cuts every slot into pieces of 256 rows instead and both products run on
 // the persistent 256 x 256 tile kernel (gemm_dense_bf16.h); the 128-column kernel is then not launched.
-// At small batch with short slots the 128-column kernel reads the slot tables itself (no list kernel).
+// At small batch with short slots the 128-column kernel reads the slot tables itself (no list kernel), and so
+// does the binary32 kernel (ffn_f32.h) at any batch.
 // Grids are sized for the worst case on the host (rows and slots are only known on the
 // device); workgroups beyond the list exit at once.  Workgroup ids are remapped so that the
 // column tiles of one row tile, which share the token rows, run on one XCD.
 #include "gemm_bf16.h"
 #include "gemm_dense_bf16.h"
+#include "ffn_f32.h"
 
 namespace moe {
 
-constexpr int FFN_BM = 64;    // rows per tile (fp32 path; short tile of the bf16 path)
+constexpr int FFN_BM = 64;    // rows per tile (short tile of the bf16 path)
 constexpr int FFN_BM_TALL = 128;  // bf16 path: a slot is cut into tiles of up to 128 rows
 constexpr int FFN_BN = 128;   // columns per workgroup (bf16 path)
 constexpr int FFN_BK = 128;   // k chunk of the bf16 path, tiles of up to 64 rows
@@ -245,82 +247,6 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
     }
 }
 
-// ------------------------------------------------------------------ fp32 grouped GEMM (plain weights)
-// 64x64 tile, 256 threads, 4x4 outputs per thread, k ascending.
-template <bool RELU>
-__global__ __launch_bounds__(256) void ffn_gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W,
-                                                           const int32_t *__restrict__ row_index, int n_src_rows,
-                                                           int K, int N, int E,
-                                                           const WorkItem *__restrict__ items,
-                                                           const int32_t *__restrict__ n_items, int max_rows,
-                                                           float *__restrict__ C)
-{
-    __shared__ float As[16][64 + 4];
-    __shared__ float Bs[16][64];
-    const int n_nt = N / 64;
-    const int item = blockIdx.x / n_nt, nt = blockIdx.x - item * n_nt;
-    if (item >= n_items[0]) return;
-    const WorkItem it = items[item];
-    if (it.expert < 0 || it.expert >= E || it.row_begin < 0) return;
-    const float *B = W + (size_t)it.expert * K * N + nt * 64;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int row_end = it.row_end < max_rows ? it.row_end : max_rows;
-    for (int r0 = it.row_begin; r0 < row_end; r0 += FFN_BM) {
-        const int nrows = row_end - r0 < FFN_BM ? row_end - r0 : FFN_BM;
-        float acc[4][4] = {};
-        // this thread's pieces of a 16-deep chunk: 4 consecutive k of token row r, 4 consecutive columns of
-        // weight row kb.  The next chunk is fetched into registers while the current one is multiplied, so a
-        // chunk costs its arithmetic and not a memory round trip.
-        const int r = threadIdx.x >> 2, kq = (threadIdx.x & 3) * 4;
-        const int kb = threadIdx.x >> 4, nb = (threadIdx.x & 15) * 4;
-        const float *a_src = nullptr;
-        if (r < nrows) {
-            const int src = row_index ? row_index[r0 + r] : r0 + r;
-            if (src >= 0 && src < n_src_rows) a_src = A + (size_t)src * K + kq;
-        }
-        auto fetch = [&](int k0, float4 &av, float4 &bv) {
-            av = a_src ? *reinterpret_cast<const float4 *>(a_src + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
-            bv = *reinterpret_cast<const float4 *>(B + (size_t)(k0 + kb) * N + nb);
-        };
-        float4 av, bv;
-        fetch(0, av, bv);
-        for (int k0 = 0; k0 < K; k0 += 16) {
-            As[kq + 0][r] = av.x;
-            As[kq + 1][r] = av.y;
-            As[kq + 2][r] = av.z;
-            As[kq + 3][r] = av.w;
-            *reinterpret_cast<float4 *>(&Bs[kb][nb]) = bv;
-            __syncthreads();
-            if (k0 + 16 < K) fetch(k0 + 16, av, bv);
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                float a[4], b[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-            }
-            __syncthreads();
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int orow = ty * 4 + i;
-            if (orow < nrows) {
-                float4 o;
-                o.x = RELU ? fmaxf(acc[i][0], 0.f) : acc[i][0];
-                o.y = RELU ? fmaxf(acc[i][1], 0.f) : acc[i][1];
-                o.z = RELU ? fmaxf(acc[i][2], 0.f) : acc[i][2];
-                o.w = RELU ? fmaxf(acc[i][3], 0.f) : acc[i][3];
-                *reinterpret_cast<float4 *>(C + (size_t)(r0 + orow) * N + nt * 64 + tx * 4) = o;
-            }
-        }
-    }
-}
-
 static inline int ffn_max_items(int max_rows, int max_slots) { return max_slots + max_rows / FFN_BM + 1; }
 // every dense tile but the last of a slot has 256 rows
 static inline int ffn_max_dense(int max_rows, int max_slots) { return max_rows / DENSE_BM + max_slots + 1; }
@@ -431,7 +357,7 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     // then reads the slot tables itself and the list kernel (a launch of ~5 us in front of the first
     // product) is skipped.  Long slots without the dense kernel keep the list: it cuts them into tiles
     // that run side by side.
-    const bool listless = dtype == MOE_BF16 && !dense && (long long)max_rows <= 64LL * max_slots;
+    const bool listless = dtype == MOE_F32 || (!dense && (long long)max_rows <= 64LL * max_slots);
     if (!listless) {
         hipLaunchKernelGGL(ffn_worklist_kernel, dim3(1), dim3(1024), 0, st, slot_offset, slot_expert, n_slots,
                            max_slots, max_items, schedule, tile_rows, E, dense ? 1 : 0, max_dense, items, dtiles,
@@ -499,14 +425,14 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
                                (bf16_t *)y_perm);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm2");
     } else {
-        int g1 = grid_items * (F / 64), g2 = grid_items * (d / 64);
-        hipLaunchKernelGGL(ffn_gemm_f32_kernel<true>, dim3(g1), dim3(256), 0, st, (const float *)x_perm,
-                           (const float *)w1, row_index, n_x_rows, d, F, E, items, n_items, max_rows, (float *)h);
+        hipLaunchKernelGGL(ffn_gemm_f32_kernel<true>, dim3(f32_grid(max_rows, max_slots, schedule, F)), dim3(F32_THREADS), 0, st,
+                           (const float *)x_perm, (const float *)w1, row_index, n_x_rows, d, F, E, slot_offset, slot_expert,
+                           n_slots, max_slots, schedule, max_rows, (float *)h);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm1");
         if (ev[1]) (void)hipEventRecord(ev[1], st);
-        hipLaunchKernelGGL(ffn_gemm_f32_kernel<false>, dim3(g2), dim3(256), 0, st, (const float *)h,
-                           (const float *)w2, (const int32_t *)nullptr, max_rows, F, d, E, items, n_items, max_rows,
-                           (float *)y_perm);
+        hipLaunchKernelGGL(ffn_gemm_f32_kernel<false>, dim3(f32_grid(max_rows, max_slots, schedule, d)), dim3(F32_THREADS), 0, st,
+                           (const float *)h, (const float *)w2, (const int32_t *)nullptr, max_rows, F, d, E, slot_offset,
+                           slot_expert, n_slots, max_slots, schedule, max_rows, (float *)y_perm);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm2");
     }
     if (ev[2]) (void)hipEventRecord(ev[2], st);
