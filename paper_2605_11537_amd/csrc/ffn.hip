@@ -208,18 +208,20 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
         const int32_t *ri = row_index ? row_index + r0 : nullptr;
         f32x16_t acc[MBT][1];
         zero_acc<MBT, 1>(acc);
-        if (!TALL || nrows <= FFN_BM) {
-            f32x16_t(&acc2)[2][1] = reinterpret_cast<f32x16_t(&)[2][1]>(acc);
-            if (it.reuse)
-                gemm_tile_bf16<2, 1, FFN_BK, false>(a0, K, nrows, Bp, nt * FFN_BN, K, lds, acc2, ri, n_src_rows);
-            else
-                gemm_tile_bf16<2, 1, FFN_BK, true>(a0, K, nrows, Bp, nt * FFN_BN, K, lds, acc2, ri, n_src_rows);
+        // the fewest 32-row blocks that hold the rows: a block less is a matrix instruction, an LDS read and the
+        // token loads of 32 rows less per step
+#define MOE_TILE(MB_, BK_, NT_)                                                                                            gemm_tile_bf16<MB_, 1, BK_, NT_>(a0, K, nrows, Bp, nt * FFN_BN, K, lds,                                                                                 reinterpret_cast<f32x16_t(&)[MB_][1]>(acc), ri, n_src_rows)
+        if (nrows <= 32) {
+            if (it.reuse) MOE_TILE(1, FFN_BK, false);
+            else MOE_TILE(1, FFN_BK, true);
+        } else if (!TALL || nrows <= FFN_BM) {
+            if (it.reuse) MOE_TILE(2, FFN_BK, false);
+            else MOE_TILE(2, FFN_BK, true);
         } else if constexpr (TALL) {
-            if (it.reuse)
-                gemm_tile_bf16<4, 1, FFN_BK_TALL, false>(a0, K, nrows, Bp, nt * FFN_BN, K, lds, acc, ri, n_src_rows);
-            else
-                gemm_tile_bf16<4, 1, FFN_BK_TALL, true>(a0, K, nrows, Bp, nt * FFN_BN, K, lds, acc, ri, n_src_rows);
+            if (it.reuse) MOE_TILE(4, FFN_BK_TALL, false);
+            else MOE_TILE(4, FFN_BK_TALL, true);
         }
+#undef MOE_TILE
         // Epilogue through LDS: an accumulator lane holds single columns of 16 different rows,
         // and 2-byte stores that cover a quarter of a cache line each are slow.  The tile is
         // transposed in LDS (the A buffers are free after the last barrier of the product) and

@@ -14,17 +14,21 @@
 // HBM straight into registers exactly once per workgroup, in DRAM-page order, and never
 // pass through LDS.
 //
-// One workgroup = 4 wavefronts arranged WM x WN (WN = 4 / WM).  Wavefront (wm, wn) owns MB row
-// blocks of 32 rows (rows (wm*MB + mb)*32 ..) and NB column strips (columns
-// n0 + (wn*NB + nb)*32 ..): MB*NB accumulators of 16 VGPRs.  WM = 1 is the weight-streaming
-// shape (every weight byte is loaded by exactly one wavefront); WM = 2 doubles the rows per
-// weight byte for compute-bound tiles.
-// The A rows (tokens) are shared by the four wavefronts and staged through LDS in BK-wide k
-// chunks, double buffered; the global loads of chunk i+1 (A and B) are issued before the
-// matrix instructions of chunk i, B registers ping-pong between two sets so nothing is
-// copied.
+// One workgroup = 4 wavefronts side by side along the columns.  Wavefront w owns MB row blocks of 32 rows and NB
+// column strips (columns n0 + (w*NB + nb)*32 ..): MB*NB accumulators of 16 VGPRs, so every weight byte is loaded by
+// exactly one wavefront.
+// The A rows (tokens) are shared by the four wavefronts and staged through two LDS buffers in BK-wide k
+// chunks.  Both operands are requested two chunks ahead: the registers of chunk i are refilled with chunk i+2 right after
+// its matrix instructions, so two register sets hold two chunks in flight.
+// Every load of the k loop is unconditional and the last chunks are peeled: where a load may or may not have been issued
+// (a lane-masked row, an "if there is another chunk"), the compiler cannot count what is outstanding and waits for the
+// youngest loads with the oldest -- each chunk then stalls for the prefetch it has just issued.  The requests of a chunk go
+// out in one burst: spread between the matrix instructions, the same loads streamed at 5.3 instead of 6.4 TB/s.
+// Measured against that (first, second product, us): 24 experts of 2 rows, 768 x 3072: 25.9, 29.4 -> 24.4, 23.2; 32 x 20 rows,
+// 512 x 2048: 17.9, 21.4 -> 16.2, 17.4; 36 x 100 rows: 47.6, 50.6 -> 44.8, 41.6; 144 x 17 rows: 105, 113 -> 103, 108.
 #pragma once
 #include "common.h"
+#include <type_traits>
 
 namespace moe {
 
@@ -33,25 +37,26 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int GEMM_THREADS = 256;
 
-template <int MB, int BK, int WM = 1>
+template <int MB, int BK>
 constexpr int gemm_lds_elems()
 {
-    return 2 * WM * MB * 32 * (BK + 8);   // row stride BK+8 elements keeps the b128 reads conflict free
+    return 2 * MB * 32 * (BK + 8);   // row stride BK+8 elements keeps the b128 reads conflict free
 }
 
 // Row of accumulator register v (0..15) of a 32x32 block for this lane; its column is lane & 31.
 __device__ __forceinline__ int acc_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 
-// A: pointer to row 0 of the tile (already offset by the tile's first row); rows >= nrows read as 0.
+// A: pointer to row 0 of the tile (already offset by the tile's first row); rows >= nrows repeat row nrows - 1 (the
+// caller does not use what they give).
 // row_idx (optional, already offset to the tile's first row): tile row r is read from
-//   A + row_idx[r]*lda instead of A + r*lda (fused gather of token rows).
+//   A + row_idx[r]*lda instead of A + r*lda (fused gather of token rows); an index outside [0, n_src_rows) reads row 0.
 // Bp: packed matrix (K x N) of this tile's expert; n0 = first column of the tile (multiple of 32).
 // K must be a multiple of BK.
 // STREAM_B: the B operand is read exactly once in the whole launch (expert weights): load it
 // with the non-temporal hint so the stream does not evict the activations the other operand
 // and the epilogue keep in cache.  (Measured on the 604 MB weight stream of a 128-expert
 // layer: 120 -> 110 us for the first FFN product, 111 -> 101 us for the second.)
-template <int MB, int NB, int BK, bool STREAM_B = false, int WM = 1>
+template <int MB, int NB, int BK, bool STREAM_B = false>
 __device__ __forceinline__ void gemm_tile_bf16(const bf16_t *__restrict__ A, int lda, int nrows,
                                                const bf16_t *__restrict__ Bp, int n0, int K,
                                                bf16_t *__restrict__ lds, f32x16_t (&acc)[MB][NB],
@@ -59,101 +64,118 @@ __device__ __forceinline__ void gemm_tile_bf16(const bf16_t *__restrict__ A, int
 {
     constexpr int LDA = BK + 8;
     constexpr int KS = BK / 16;                       // 16-deep MFMA steps per chunk
-    constexpr int WN = 4 / WM;
-    constexpr int BM = WM * MB * 32;                  // rows of the workgroup tile
+    constexpr int BM = MB * 32;                       // rows of the workgroup tile
     constexpr int PIECES = BM * (BK / 8);             // 16-byte pieces of one A chunk
     constexpr int A_PER_THREAD = PIECES / GEMM_THREADS;
     constexpr int ROW_STEP = GEMM_THREADS / (BK / 8);
     static_assert(PIECES % GEMM_THREADS == 0, "A chunk must split evenly over the workgroup");
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int wm = w / WN, wn = w % WN;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nk = K / BK;
     const int KG = K >> 3;
-    uint4 a_reg[A_PER_THREAD];
-    uint4 b0[KS][NB], b1[KS][NB];
+    typedef unsigned u32x4v_t __attribute__((ext_vector_type(4)));
+    u32x4v_t a_reg[2][A_PER_THREAD];
+    u32x4v_t b[2][KS][NB];
     const int a_col = tid % (BK / 8);
     const int a_row = tid / (BK / 8);
-    const uint4 *b_base = reinterpret_cast<const uint4 *>(Bp) + (size_t)((n0 >> 5) + wn * NB) * KG * 32 + lane;
+    // scalar address, the lane's own piece as the offset: one register instead of a pair per load
+    const u32x4v_t *b_base = reinterpret_cast<const u32x4v_t *>(Bp) + (size_t)((n0 >> 5) + w * NB) * KG * 32;
 
     const bf16_t *a_src[A_PER_THREAD];   // this thread's rows stay the same for every k chunk
-    bool a_ok[A_PER_THREAD];             // rows past the tile, or an index outside the source, read as 0
 #pragma unroll
     for (int i = 0; i < A_PER_THREAD; ++i) {
         int r = a_row + i * ROW_STEP;
-        a_ok[i] = r < nrows;
-        int src_row = r;
-        if (row_idx && a_ok[i]) {
-            src_row = row_idx[r];
-            a_ok[i] = src_row >= 0 && src_row < n_src_rows;
+        r = r < nrows ? r : nrows - 1;
+        if (row_idx) {
+            r = row_idx[r];
+            r = (r >= 0 && r < n_src_rows) ? r : 0;
         }
-        a_src[i] = A + (size_t)(a_ok[i] ? src_row : 0) * lda + a_col * 8;
+        a_src[i] = A + (size_t)r * lda + a_col * 8;
     }
-    auto load_a = [&](int kc) {
+    auto load_a = [&](int kc, int set) {
 #pragma unroll
-        for (int i = 0; i < A_PER_THREAD; ++i)
-            a_reg[i] = a_ok[i] ? *reinterpret_cast<const uint4 *>(a_src[i] + kc * BK) : make_uint4(0, 0, 0, 0);
+        for (int i = 0; i < A_PER_THREAD; ++i) a_reg[set][i] = *reinterpret_cast<const u32x4v_t *>(a_src[i] + kc * BK);
     };
-    auto store_a = [&](int buf) {
+    auto load_b = [&](int kc, int set, int ks) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const u32x4v_t *p = b_base + ((size_t)nb * KG + kc * (BK / 8) + ks * 2) * 32 + lane;
+            b[set][ks][nb] = STREAM_B ? __builtin_nontemporal_load(p) : *p;
+        }
+    };
+    auto store_a = [&](int buf, int set) {
         bf16_t *dst = lds + buf * (BM * LDA);
 #pragma unroll
         for (int i = 0; i < A_PER_THREAD; ++i)
-            *reinterpret_cast<uint4 *>(dst + (a_row + i * ROW_STEP) * LDA + a_col * 8) = a_reg[i];
+            *reinterpret_cast<u32x4v_t *>(dst + (a_row + i * ROW_STEP) * LDA + a_col * 8) = a_reg[set][i];
     };
-    auto load_b = [&](int kc, uint4(&b)[KS][NB]) {
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const uint4 *p = b_base + ((size_t)nb * KG + kc * (BK / 8) + ks * 2) * 32;
-                if (STREAM_B) {
-                    typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-                    u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p));
-                    b[ks][nb] = make_uint4(v.x, v.y, v.z, v.w);
-                } else {
-                    b[ks][nb] = *p;
-                }
-            }
-    };
-    auto compute = [&](int kc, const uint4(&b)[KS][NB]) {
-        const bf16_t *src = lds + (kc & 1) * (BM * LDA) + (wm * MB * 32 + (lane & 31)) * LDA + (lane >> 5) * 8;
+    // requests of a chunk, always in this order: the waits are counts, and one count has to fit the way into the loop
+    // and the way round it
+    auto request = [&](int kc, int set) {
+        load_a(kc, set);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
+            load_b(kc, set, ks);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // one pipeline stage: multiply chunk kc (register set and LDS buffer SET = kc & 1), request chunk kc + 2 into the
+    // registers as they fall free, put chunk kc + 1 of the tokens into LDS
+    auto stage = [&](int kc, auto SET, auto ISSUE, auto LAST) {
+        constexpr int set = decltype(SET)::value;
+        constexpr bool issue = decltype(ISSUE)::value;
+        const bf16_t *src = lds + set * (BM * LDA) + (lane & 31) * LDA + (lane >> 5) * 8;
+        u32x4v_t af[2][MB];              // fragments of this 16-deep step and the next
+        auto read_a = [&](int ks) {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                uint4 av = *reinterpret_cast<const uint4 *>(src + mb * 32 * LDA + ks * 16);
-                bf16x8_t a = __builtin_bit_cast(bf16x8_t, av);
+            for (int mb = 0; mb < MB; ++mb) af[ks & 1][mb] = *reinterpret_cast<const u32x4v_t *>(src + mb * 32 * LDA + ks * 16);
+        };
+        read_a(0);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            if (ks + 1 < KS) read_a(ks + 1);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
-                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8_t, b[ks][nb]),
+                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, af[ks & 1][mb]),
+                                                                          __builtin_bit_cast(bf16x8_t, b[set][ks][nb]),
                                                                           acc[mb][nb], 0, 0, 0);
-            }
         }
-    };
-    // one pipeline stage: fetch chunk kc+1 into `nxt`, multiply chunk kc out of `cur`
-    auto stage = [&](int kc, const uint4(&cur)[KS][NB], uint4(&nxt)[KS][NB]) {
-        const bool more = kc + 1 < nk;
-        if (more) {
-            load_a(kc + 1);
-            load_b(kc + 1, nxt);
-        }
-        // keep the prefetch where it is: left alone, the scheduler sinks these loads below the
-        // matrix instructions to save registers, and every chunk then waits a full memory round trip
         __builtin_amdgcn_sched_barrier(0);
-        compute(kc, cur);
-        if (more) store_a((kc + 1) & 1);
+        if constexpr (issue) request(kc + 2, set);
+        if constexpr (!decltype(LAST)::value) store_a(set ^ 1, set ^ 1);
         __syncthreads();
     };
+    using yes = std::true_type;
+    using no = std::false_type;
+    using even = std::integral_constant<int, 0>;
+    using odd = std::integral_constant<int, 1>;
 
-    load_a(0);
-    load_b(0, b0);
-    store_a(0);
+    request(0, 0);
+    request(nk > 1 ? 1 : 0, 1);
+    store_a(0, 0);
     __syncthreads();
     int kc = 0;
-    for (; kc + 1 < nk; kc += 2) {
-        stage(kc, b0, b1);
-        stage(kc + 1, b1, b0);
+    for (; kc + 3 < nk; kc += 2) {
+        stage(kc, even{}, yes{}, no{});
+        stage(kc + 1, odd{}, yes{}, no{});
     }
-    if (kc < nk) stage(kc, b0, b1);
+    // 1 .. 3 chunks are left.  The marks keep the three ways apart: their common first LDS reads would be moved in front
+    // of the branch, into 64 registers that nothing else can spare
+    if (nk - kc == 3) {
+        asm volatile("; three chunks left" ::: "memory");
+        stage(kc, even{}, yes{}, no{});
+        stage(kc + 1, odd{}, no{}, no{});
+        stage(kc + 2, even{}, no{}, yes{});
+    } else if (nk - kc == 2) {
+        asm volatile("; two chunks left" ::: "memory");
+        stage(kc, even{}, no{}, no{});
+        stage(kc + 1, odd{}, no{}, yes{});
+    } else {
+        asm volatile("; one chunk left" ::: "memory");
+        stage(kc, even{}, no{}, yes{});
+    }
 }
 
 template <int MB, int NB>
