@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
     (64, 320, 4, [15, 48, 49, 64, 65, 31, 33, 0, 130], True),        # every block count; a second and third tile
     (448, 192, 2, [200, 3], True),                                   # an odd number of steps
     (64, 128, 40, [(7 * i) % 23 for i in range(600)], False),        # three slots per thread
+    (128, 64, 3, [130, 64, 65, 0, 47, 16, 200], True),               # over 128 rows per expert: tiles of 64 rows
 ])
 def test_ffn_f32_tiles(d, F, E, rows, gather, schedule):
     import paper_2605_11537_amd as moe
