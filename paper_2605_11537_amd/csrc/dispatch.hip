@@ -264,12 +264,18 @@ __global__ __launch_bounds__(DSP_THREADS) void dispatch_permute_kernel(
 
 // x_perm[pos] = x[perm[pos]] for pos < K (K is not read: the permutation ends in -1 entries).  32 lanes per row, 8 rows per workgroup, 16-byte
 // pieces: the scattered row reads and the contiguous writes are both whole lines, the row
-// index is read once per row, and all of a lane's loads are independent.
+// index is read once per row, and a lane's three loads of a trip are independent.
+// STREAM: an output far beyond what the L2s hold is written past them.  Measured, 65536 x 768 bf16: 47 -> 37 us (30 us alone, 6.7 TB/s) on top of
+// the tables; 16384 tokens 16 -> 8.6 us (a trip of four pieces that rows of 96 never fill took the leftover path before).
 constexpr int GATHER_ROWS = DSP_THREADS / 32;
-__global__ __launch_bounds__(DSP_THREADS) void dispatch_gather_kernel(const uint4 *__restrict__ x,
+constexpr size_t GATHER_STREAM_BYTES = (size_t)64 << 20;
+typedef unsigned dsp_u32x4_t __attribute__((ext_vector_type(4)));
+
+template <bool STREAM>
+__global__ __launch_bounds__(DSP_THREADS) void dispatch_gather_kernel(const dsp_u32x4_t *__restrict__ x,
                                                                       const int32_t *__restrict__ perm, int T,
                                                                       int n_tokens, int vec_per_row,
-                                                                      uint4 *__restrict__ x_perm)
+                                                                      dsp_u32x4_t *__restrict__ x_perm)
 {
     const int pos = blockIdx.x * GATHER_ROWS + (threadIdx.x >> 5);
     const int l = threadIdx.x & 31;
@@ -277,23 +283,20 @@ __global__ __launch_bounds__(DSP_THREADS) void dispatch_gather_kernel(const uint
     int row = perm[pos];
     if (row < 0) return;                      // past the kept rows (perm holds -1 there): nothing to copy
     if (row >= n_tokens) row %= n_tokens;     // top-k: assignment -> its token
-    const uint4 *src = x + (size_t)row * vec_per_row;
-    uint4 *dst = x_perm + (size_t)pos * vec_per_row;
-    int c = l;
-    for (; c + 96 < vec_per_row; c += 128) {
-        uint4 v0 = src[c], v1 = src[c + 32], v2 = src[c + 64], v3 = src[c + 96];
-        dst[c] = v0;
-        dst[c + 32] = v1;
-        dst[c + 64] = v2;
-        dst[c + 96] = v3;
+    const dsp_u32x4_t *src = x + (size_t)row * vec_per_row;
+    dsp_u32x4_t *dst = x_perm + (size_t)pos * vec_per_row;
+    for (int c = l; c < vec_per_row; c += 96) {
+        dsp_u32x4_t v[3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+            if (c + u * 32 < vec_per_row) v[u] = src[c + u * 32];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            if (c + u * 32 >= vec_per_row) continue;
+            if (STREAM) __builtin_nontemporal_store(v[u], dst + c + u * 32);
+            else dst[c + u * 32] = v[u];
+        }
     }
-    uint4 v[3];
-#pragma unroll
-    for (int u = 0; u < 3; ++u)
-        if (c + u * 32 < vec_per_row) v[u] = src[c + u * 32];
-#pragma unroll
-    for (int u = 0; u < 3; ++u)
-        if (c + u * 32 < vec_per_row) dst[c + u * 32] = v[u];
 }
 
 size_t dispatch_block_hist_bytes(int T, int E)
@@ -419,8 +422,10 @@ static int dispatch_checked(const char *who, const void *x, const int32_t *exper
         if (x && nb > 0) {
             int vec_per_row = (int)((size_t)d * esz / 16);
             int grid = ceil_div(T, GATHER_ROWS);
-            hipLaunchKernelGGL(dispatch_gather_kernel, dim3(grid), dim3(DSP_THREADS), 0, st, (const uint4 *)x, perm,
-                               T, n_tokens, vec_per_row, (uint4 *)x_perm);
+            auto gather = (size_t)T * vec_per_row * 16 >= GATHER_STREAM_BYTES ? dispatch_gather_kernel<true>
+                                                                              : dispatch_gather_kernel<false>;
+            hipLaunchKernelGGL(gather, dim3(grid), dim3(DSP_THREADS), 0, st, (const dsp_u32x4_t *)x, perm, T, n_tokens,
+                               vec_per_row, (dsp_u32x4_t *)x_perm);
             MOE_CHECK_LAUNCH(who);
         }
     }
