@@ -8,7 +8,7 @@
 // workgroup takes a few channels of one sequence and cuts the time axis into 64 chunks; every thread
 // first composes its chunk into (A, B) with c_out = A c_in + B, the 64 chunk maps of a channel are
 // composed by a scan, and each thread then re-runs its chunk from its true carry-in and writes h_t.
-// For sequences of up to 512 positions steps (2) and (3) are one kernel per layer with the projections
+// For sequences of up to 1024 positions steps (2) and (3) are one kernel per layer with the projections
 // kept in LDS (sru_layer_fused_kernel below); the two-kernel form (sru_proj_kernel, sru_scan_kernel)
 // serves longer sequences.  The head is a router-shaped product + argmax and reuses the router's kernel.
 #include "gemm_bf16.h"
@@ -43,12 +43,20 @@ __global__ __launch_bounds__(GEMM_THREADS) void sru_proj_kernel(const bf16_t *__
         }
 }
 
-// binary32 with the hardware exponential: a few ulp, far inside the bf16 rounding of h
-__device__ __forceinline__ float sigmoidf_(float v) { return 1.f / (1.f + __expf(-v)); }
+// 1 / x for 1 <= x < 2^120: the hardware reciprocal and one Newton step (the full division is ten instructions, and the gates
+// are most of what a layer's recurrence issues)
+__device__ __forceinline__ float recip_(float x)
+{
+    const float r = __builtin_amdgcn_rcpf(x);
+    return fmaf(r, fmaf(-x, r, 1.f), r);
+}
+// binary32 with the hardware exponential: a few ulp, far inside the bf16 rounding of h.  Below -80 the exponential is held where the
+// reciprocal is finite (sigmoid 1e-35); the comparison leaves a NaN a NaN.
+__device__ __forceinline__ float sigmoidf_(float v) { return recip_(1.f + __expf(v < -80.f ? 80.f : -v)); }
 __device__ __forceinline__ float tanhf_(float v)
 {
     float a = fminf(fabsf(v), 15.f);
-    float t = 1.f - 2.f / (1.f + __expf(2.f * a));
+    float t = fmaf(-2.f, recip_(1.f + __expf(2.f * a)), 1.f);
     return copysignf(t, v);
 }
 
@@ -159,37 +167,58 @@ __global__ __launch_bounds__(SRU_CHUNKS * SRU_CHANNELS) void sru_scan_kernel(
     }
 }
 
-// ------------------------------------------------------------------ one SRU layer in one kernel (L <= 512)
+// ------------------------------------------------------------------ one SRU layer in one kernel (L <= 1024)
 // Workgroup (channel block cb of 8 channels, sequence b): the projections of ITS 8 channels for all L
 // positions -- 32 columns of [W | W_f | W_r | (W_h)], one matrix-core column block, gathered from the packed
-// image piece by piece -- land in LDS (L x 32 binary32), and the recurrence runs from there: time chunks
-// x 8 channels (64 chunks), chunk maps composed by a doubling scan across the chunks, every chunk re-run from its true
-// carry-in.  The projections never go to memory (the two-kernel form writes and re-reads 3-4 binary32
-// values per position and channel, and its scan was bound by what one CU can fetch), there is one launch per
-// layer instead of two, and B * n_h / 8 workgroups cover the chip at 8 sequences x 256 channels.
-// The token rows reach the matrix cores without a workgroup barrier (whole lines from memory, a
-// wavefront-private LDS transposition, see below).
+// image piece by piece -- land in LDS (L x 32 binary32), and the recurrence runs from there: 64 time chunks
+// x 8 channels, chunk maps composed by a scan (inside a wavefront by lane exchanges, over the eight wavefronts through
+// LDS), every chunk re-run from its true carry-in.  The projections never go to memory (the two-kernel form writes and
+// re-reads 3-4 binary32 values per position and channel, and its scan was bound by what one CU can fetch), there is one
+// launch per layer instead of two, and B * n_h / 8 workgroups cover the chip at 8 sequences x 256 channels.
+// Between layers the states are kept as matrix-core fragments (packed_piece below): a layer's output piece, 8 channels of one
+// position, is 16 bytes of such a fragment, so the 32 positions of a block leave as a run of 512 bytes, and the next layer's
+// operand load is 1 KB of consecutive memory, straight into registers.  Only the first layer's input (the caller's row-major
+// embeddings) goes through a wavefront-private LDS transposition, which costs as much LDS time per k as the loads take.  All loads are unconditional (rows past the sequence repeat its last
+// row, columns past the gates repeat the first's; neither is used), so that the waits of the chunk pipeline are counts:
+// with conditional ones every chunk waited for the chunk just requested.
+// Measured per layer at 8 x 512, 256 -> 256: 12.4 -> 9.0 us; 5 x 777, 768 -> 256 and 256 -> 256, both layers: 46 us in two
+// launches against 53 us in four (projection and scan kernels, which now serve L > 1024 only).
 constexpr int FUS_CH = 8;              // channels per workgroup
 constexpr int FUS_THREADS = 512;       // 8 wavefronts: 2 per SIMD, so one's loads fly under the other's work
+constexpr int FUS_WAVES = FUS_THREADS / 64;
 constexpr int FUS_CHUNKS = FUS_THREADS / FUS_CH;   // 64 time chunks per sequence
-constexpr int FUS_MAX_L = 512;
-constexpr int FUS_CL = FUS_MAX_L / FUS_CHUNKS;     // steps per chunk at most
+constexpr int FUS_MAX_L = 1024;
 constexpr int FUS_LDU = 33;            // row stride of the LDS tile, binary32 elements
-constexpr int FUS_KC = 64;             // k per register buffer
 
-template <int NRB>                     // 32-row blocks per wavefront: L <= 256 * NRB
+// 16-byte piece of position t, channels 8g .. 8g+7, in the fragment image of a sequence's states (n channels, blocks of 32
+// positions; fragment (block, 16 channels) = 64 lanes x 16 bytes, the lane order of the matrix instruction's operand)
+__device__ __forceinline__ size_t packed_piece(int seq, int n_blocks, int n, int t, int g)
+{
+    return (((size_t)seq * n_blocks + (t >> 5)) * (n >> 4) + (g >> 1)) * 64 + (g & 1) * 32 + (t & 31);
+}
+
+// NRB: 32-row blocks per wavefront, L <= 256 * NRB.  PIN: X is a fragment image (else row-major); packed_out: so is h_out.
+// WF > 0: the weight fragments (K / 16 <= 8 * WF of them) are fetched once per workgroup, WF per wavefront, and read from LDS;
+// loaded by every wavefront for itself they are a third of what the CU's load path carries (45 bytes per clock, the bound of the
+// product here).
+template <int NRB, bool PIN, int WF>
 __global__ __launch_bounds__(FUS_THREADS, 1) void sru_layer_fused_kernel(const bf16_t *__restrict__ X,
                                                                          const bf16_t *__restrict__ Wp, int L, int K,
                                                                          int n_h, int kgates,
                                                                          const float *__restrict__ b_f,
-                                                                         const float *__restrict__ b_r,
+                                                                         const float *__restrict__ b_r, int packed_out,
                                                                          bf16_t *__restrict__ h_out)
 {
-    // the L x 32 tile of projections; during the product, the wavefronts' staging pieces for the token rows
-    constexpr int TILE_FLOATS = FUS_MAX_L * FUS_LDU, STAGE_FLOATS = (FUS_THREADS / 64) * NRB * 32 * (FUS_KC + 8) / 2;
+    constexpr int MAX_L = 256 * NRB, CL = MAX_L / FUS_CHUNKS;
+    constexpr int KC = NRB <= 2 ? 64 : 32;             // k per register buffer: a whole line per row, or half of one for room
+    constexpr int LDA = KC + 8;
+    constexpr int SB = NRB < 2 ? NRB : 2;              // row blocks a wavefront stages at a time
+    // the L x 32 tile of projections; during the product, the weight fragments and the wavefronts' staging pieces for the token rows
+    constexpr int TILE_FLOATS = MAX_L * FUS_LDU, W_FLOATS = WF * FUS_WAVES * 256;
+    constexpr int STAGE_FLOATS = W_FLOATS + (PIN ? 0 : FUS_WAVES * SB * 32 * LDA / 2);
     __shared__ __attribute__((aligned(16))) float u_lds[TILE_FLOATS > STAGE_FLOATS ? TILE_FLOATS : STAGE_FLOATS];
-    __shared__ float car_a[2][FUS_CHUNKS][FUS_CH], car_b[2][FUS_CHUNKS][FUS_CH];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    __shared__ float wave_a[FUS_WAVES][FUS_CH], wave_b[FUS_WAVES][FUS_CH];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroup i runs on XCD i % 8.  All channel blocks of a sequence read the same token rows, written a
     // moment ago by other XCDs: with whole sequences per XCD (sequence b on XCD b % 8, when their number
     // allows) an XCD's L2 fetches 1/8 of the rows instead of all of them.
@@ -206,146 +235,233 @@ __global__ __launch_bounds__(FUS_THREADS, 1) void sru_layer_fused_kernel(const b
         }
     }
     const int KG = K >> 3;
-    // recurrence roles: thread = (chunk q, channel ch)
-    const int ch = tid & (FUS_CH - 1), q = tid / FUS_CH;
+    typedef unsigned u32x4s_t __attribute__((ext_vector_type(4)));
+    const bf16_t *Xs = X + (size_t)b * L * K;
+    const u32x4s_t *Xp = reinterpret_cast<const u32x4s_t *>(X);
+    const int n_blocks = (L + 31) >> 5;
+    const int ch = tid & (FUS_CH - 1), q = tid / FUS_CH;      // recurrence roles: thread = (chunk q, channel ch)
     const int j = cb * FUS_CH + ch;
-    const int cl = (L + FUS_CHUNKS - 1) / FUS_CHUNKS;
-    const int t0 = q * cl < L ? q * cl : L, t1 = t0 + cl < L ? t0 + cl : L;
-    // highway input when the widths are equal (K == n_h): fetched now, used at the very end
-    float hwv[FUS_CL];
+    const float bf = b_f ? b_f[j] : 0.f, br = b_r ? b_r[j] : 0.f;
+    // highway input when the widths are equal (K == n_h): this workgroup's 8 channels of row tid (and tid + 512)
+    constexpr int HROWS = (MAX_L + FUS_THREADS - 1) / FUS_THREADS;
+    u32x4s_t hw_in[HROWS];
     if (kgates == 3) {
-        const bf16_t *xi = X + (size_t)b * L * K + j;
 #pragma unroll
-        for (int i = 0; i < FUS_CL; ++i) hwv[i] = t0 + i < t1 ? bf16_to_f32(xi[(size_t)(t0 + i) * K]) : 0.f;
+        for (int i = 0; i < HROWS; ++i) {
+            int t = tid + i * FUS_THREADS;
+            t = t < L ? t : L - 1;
+            hw_in[i] = PIN ? Xp[packed_piece(b, n_blocks, K, t, cb)]
+                           : *reinterpret_cast<const u32x4s_t *>(Xs + (size_t)t * K + cb * FUS_CH);
+        }
     }
     // ---- projections: U[t][c], c = gate * 8 + channel
     {
         // Token rows: a wavefront fetches its own row blocks in whole 128-byte lines (8 lanes per row, 8 rows
-        // per load), turns them into A fragments through a private piece of LDS (row stride 72 elements, no
-        // barrier: LDS operations of one wavefront execute in order), three register buffers deep.  A lane
+        // per load; half lines for the longest sequences), turns them into A fragments through a private piece of LDS (row stride 72 elements, no
+        // barrier: LDS operations of one wavefront execute in order).  A lane
         // loading its fragment straight from memory touches 32 bytes of 32 different lines per load, and
         // the kernel was bound by those transactions.
-        constexpr int LDA = FUS_KC + 8;
-        bf16_t *stage = reinterpret_cast<bf16_t *>(u_lds) + (size_t)w * (NRB * 32 * LDA);
+        bf16_t *stage = reinterpret_cast<bf16_t *>(u_lds + W_FLOATS) + (size_t)w * (SB * 32 * LDA);
+        u32x4s_t *w_lds = reinterpret_cast<u32x4s_t *>(u_lds);
         const int r = lane & 31, kh = lane >> 5;
-        const int lrow = lane >> 3, lpiece = lane & 7;
-        const bf16_t *a_ptr[NRB][4];
-        bool a_ok[NRB][4];
+        constexpr int PPR = KC / 8, RPL = 64 / PPR, NSB = 32 / RPL;      // pieces per row, rows per load, loads per row block
+        const int lrow = lane / PPR, lpiece = lane % PPR;
+        // this lane's pieces of its rows, elements from the sequence's first; or the first fragment of its row blocks
+        unsigned a_off[NRB][NSB];
+        const u32x4s_t *a_frag[NRB];
 #pragma unroll
         for (int i = 0; i < NRB; ++i)
 #pragma unroll
-            for (int sb = 0; sb < 4; ++sb) {
-                const int t = (w + 8 * i) * 32 + sb * 8 + lrow;   // row blocks dealt to the eight wavefronts in turn
-                a_ok[i][sb] = t < L;
-                a_ptr[i][sb] = X + ((size_t)b * L + (a_ok[i][sb] ? t : 0)) * K + lpiece * 8;
+            for (int sb = 0; sb < NSB; ++sb) {
+                const int t = (w + FUS_WAVES * i) * 32 + sb * RPL + lrow;   // row blocks dealt to the eight wavefronts in turn
+                a_off[i][sb] = (unsigned)(t < L ? t : L - 1) * K + lpiece * 8;
             }
-        const int gate = r >> 3, chn = r & 7;
-        const bool b_ok = gate < kgates;
-        const int col = (b_ok ? gate : 0) * n_h + cb * FUS_CH + chn;
-        const uint4 *b_ptr = reinterpret_cast<const uint4 *>(Wp) + ((size_t)(col >> 5) * KG + kh) * 32 + (col & 31);
+#pragma unroll
+        for (int i = 0; i < NRB; ++i) {
+            const int blk = w + FUS_WAVES * i < n_blocks ? w + FUS_WAVES * i : n_blocks - 1;
+            a_frag[i] = Xp + ((size_t)b * n_blocks + blk) * (K >> 4) * 64;
+        }
+        const int gate = r >> 3 < kgates ? r >> 3 : 0;
+        const int col = gate * n_h + cb * FUS_CH + (r & 7);
+        const u32x4s_t *b_ptr = reinterpret_cast<const u32x4s_t *>(Wp) + ((size_t)(col >> 5) * KG + kh) * 32 + (col & 31);
         f32x16_t acc[NRB][1];
         zero_acc<NRB, 1>(acc);
-        constexpr int KS = FUS_KC / 16;
-        uint4 ga[3][NRB][4], fb[3][KS];
+        constexpr int KS = KC / 16;
+        constexpr int D = 3;                           // chunks in flight
+        constexpr int AR = PIN ? KS : NSB;             // 16-byte pieces per lane, row block and chunk (the same number)
+        u32x4s_t ga[D][NRB][AR], fb[WF ? 1 : D][KS], wf[WF ? WF : 1];
+        const int nkc = K / KC;
         auto load = [&](int kc, int buf) {
-            const int k0 = kc * FUS_KC;
+            const int k0 = (kc < nkc ? kc : nkc - 1) * KC;         // past the end: a harmless re-read
+            if constexpr (WF == 0) {
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                fb[buf][ks] = b_ok ? b_ptr[(size_t)((k0 >> 3) + ks * 2) * 32] : make_uint4(0, 0, 0, 0);
-#pragma unroll
-            for (int i = 0; i < NRB; ++i)
-#pragma unroll
-                for (int sb = 0; sb < 4; ++sb)
-                    ga[buf][i][sb] =
-                        a_ok[i][sb] ? *reinterpret_cast<const uint4 *>(a_ptr[i][sb] + k0) : make_uint4(0, 0, 0, 0);
-        };
-        auto compute = [&](int buf) {
-#pragma unroll
-            for (int i = 0; i < NRB; ++i)
-#pragma unroll
-                for (int sb = 0; sb < 4; ++sb)
-                    *reinterpret_cast<uint4 *>(stage + (i * 32 + sb * 8 + lrow) * LDA + lpiece * 8) = ga[buf][i][sb];
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                for (int i = 0; i < NRB; ++i) {
-                    const uint4 av = *reinterpret_cast<const uint4 *>(stage + (i * 32 + r) * LDA + ks * 16 + kh * 8);
-                    acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av),
-                                                                        __builtin_bit_cast(bf16x8_t, fb[buf][ks]),
-                                                                        acc[i][0], 0, 0, 0);
-                }
-        };
-        const int nkc = K / FUS_KC;
-        load(0, 0);
-        if (nkc > 1) load(1, 1);
-        for (int kc = 0; kc < nkc; kc += 3) {
-            if (kc + 2 < nkc) load(kc + 2, 2);
-            __builtin_amdgcn_sched_barrier(0);
-            compute(0);
-            if (kc + 1 < nkc) {
-                if (kc + 3 < nkc) load(kc + 3, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                compute(1);
+                for (int ks = 0; ks < KS; ++ks) fb[buf][ks] = b_ptr[(size_t)((k0 >> 3) + ks * 2) * 32];
             }
-            if (kc + 2 < nkc) {
-                if (kc + 4 < nkc) load(kc + 4, 1);
+#pragma unroll
+            for (int i = 0; i < NRB; ++i)
+#pragma unroll
+                for (int sb = 0; sb < AR; ++sb)
+                    ga[buf][i][sb] = PIN ? a_frag[i][((k0 >> 4) + sb) * 64 + lane]
+                                         : *reinterpret_cast<const u32x4s_t *>(Xs + k0 + a_off[i][sb]);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto compute = [&](int kc, int buf) {
+            const int fbuf = WF ? 0 : buf;
+            if constexpr (WF > 0) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) fb[0][ks] = w_lds[(kc * KS + ks) * 64 + lane];
+            }
+            if constexpr (PIN) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                    for (int i = 0; i < NRB; ++i)
+                        acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ga[buf][i][ks]),
+                                                                            __builtin_bit_cast(bf16x8_t, fb[fbuf][ks]),
+                                                                            acc[i][0], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                compute(2);
+                return;
+            }
+#pragma unroll
+            for (int i0 = 0; i0 < NRB; i0 += SB) {
+#pragma unroll
+                for (int i = 0; i < SB; ++i)
+#pragma unroll
+                    for (int sb = 0; sb < NSB; ++sb)
+                        *reinterpret_cast<u32x4s_t *>(stage + (i * 32 + sb * RPL + lrow) * LDA + lpiece * 8) = ga[buf][i0 + i][sb];
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                    for (int i = 0; i < SB; ++i) {
+                        const u32x4s_t av = *reinterpret_cast<const u32x4s_t *>(stage + (i * 32 + r) * LDA + ks * 16 + kh * 8);
+                        acc[i0 + i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av),
+                                                                                 __builtin_bit_cast(bf16x8_t, fb[fbuf][ks]),
+                                                                                 acc[i0 + i][0], 0, 0, 0);
+                    }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if constexpr (WF > 0) {
+            const int n_frag = K >> 4;
+#pragma unroll
+            for (int i = 0; i < WF; ++i) {
+                const int fr = w + FUS_WAVES * i < n_frag ? w + FUS_WAVES * i : n_frag - 1;
+                wf[i] = b_ptr[(size_t)(fr * 2) * 32];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int d = 0; d < D; ++d) load(d, d);
+        if constexpr (WF > 0) {
+#pragma unroll
+            for (int i = 0; i < WF; ++i) w_lds[(w + FUS_WAVES * i) * 64 + lane] = wf[i];
+            __syncthreads();
+        }
+        int kc = 0;
+        for (; kc + D < nkc; kc += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                compute(kc + d, d);
+                load(kc + D + d, d);
             }
         }
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (kc + d < nkc) compute(kc + d, d);      // uniform
         __syncthreads();           // the staging pieces alias the tile written next
+        if (r < kgates * FUS_CH) {
 #pragma unroll
-        for (int i = 0; i < NRB; ++i)
+            for (int i = 0; i < NRB; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int t = (w + 8 * i) * 32 + acc_row(v, lane);
-                if (t < FUS_MAX_L) u_lds[t * FUS_LDU + r] = acc[i][0][v];
+                for (int v = 0; v < 16; ++v) u_lds[((w + FUS_WAVES * i) * 32 + acc_row(v, lane)) * FUS_LDU + r] = acc[i][0][v];
+        }
+        if (kgates == 3) {         // the highway input takes the place of the fourth gate
+#pragma unroll
+            for (int i = 0; i < HROWS; ++i) {
+                const int t = tid + i * FUS_THREADS;
+                if (t < MAX_L) {
+                    float *ut = u_lds + t * FUS_LDU + 3 * FUS_CH;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        ut[2 * c] = __uint_as_float(hw_in[i][c] << 16);
+                        ut[2 * c + 1] = __uint_as_float(hw_in[i][c] & 0xffff0000u);
+                    }
+                }
             }
+        }
     }
     __syncthreads();
 
-    // ---- recurrence
-    const float bf = b_f ? b_f[j] : 0.f, br = b_r ? b_r[j] : 0.f;
+    // ---- recurrence: chunk q holds positions q*cl .. ; past the end of the sequence a step is the identity
+    const int cl = (L + FUS_CHUNKS - 1) / FUS_CHUNKS, t0 = q * cl;
+    float f[CL], g[CL], r[CL], hw[CL];
+#pragma unroll
+    for (int i = 0; i < CL; ++i) {
+        const int t = t0 + i;
+        const float *ut = u_lds + (t < MAX_L ? t : MAX_L - 1) * FUS_LDU + ch;
+        g[i] = ut[0];
+        f[i] = ut[FUS_CH];
+        r[i] = ut[2 * FUS_CH];
+        hw[i] = ut[3 * FUS_CH];
+    }
     float a = 1.f, c = 0.f;
 #pragma unroll
-    for (int i = 0; i < FUS_CL; ++i)
-        if (t0 + i < t1) {
-            float *ut = u_lds + (t0 + i) * FUS_LDU;
-            const float f = sigmoidf_(ut[FUS_CH + ch] + bf);
-            ut[FUS_CH + ch] = f;                           // the gate itself from here on
-            a *= f;
-            c = f * c + (1.f - f) * ut[ch];
-        }
-    // inclusive doubling scan of the chunk maps c -> a c + b over the chunks of a channel
-    int cur = 0;
+    for (int i = 0; i < CL; ++i) {
+        const bool in = i < cl && t0 + i < L;
+        f[i] = in ? sigmoidf_(f[i] + bf) : 1.f;
+        g[i] = in ? (1.f - f[i]) * g[i] : 0.f;
+        r[i] = sigmoidf_(r[i] + br);
+        a *= f[i];
+        c = f[i] * c + g[i];
+    }
+    // Inclusive scan of the chunk maps c -> a c + b.  A wavefront holds 8 neighbouring chunks x 8 channels: three
+    // doubling steps over lanes 8, 16, 32 apart; then the eight wavefronts' totals, composed by every thread for itself.
 #pragma unroll
-    for (int o = 1; o < FUS_CHUNKS; o <<= 1) {
-        car_a[cur][q][ch] = a;
-        car_b[cur][q][ch] = c;
-        __syncthreads();
-        if (q >= o) {
-            const float qa = car_a[cur][q - o][ch], qb = car_b[cur][q - o][ch];
+    for (int o = FUS_CH; o < 64; o <<= 1) {
+        const float qa = __shfl_up(a, o, 64), qb = __shfl_up(c, o, 64);
+        if (lane >= o) {
             c = a * qb + c;                                // (this) after (earlier)
             a = a * qa;
         }
-        cur ^= 1;
     }
-    car_b[cur][q][ch] = c;                                 // state after chunks 0..q, starting from 0
-    __syncthreads();
-    c = q > 0 ? car_b[cur][q - 1][ch] : 0.f;
-
-    bf16_t *ho = h_out + (size_t)b * L * n_h + j;
+    if (lane >= 64 - FUS_CH) {
+        wave_a[w][ch] = a;
+        wave_b[w][ch] = c;
+    }
+    // the map of the chunks before this one, inside the wavefront
+    float pa = __shfl_up(a, FUS_CH, 64), pb = __shfl_up(c, FUS_CH, 64);
+    if (lane < FUS_CH) {
+        pa = 1.f;
+        pb = 0.f;
+    }
+    __syncthreads();               // also: every projection has been read, the tile is free for the output rows
+    float cin = 0.f;
 #pragma unroll
-    for (int i = 0; i < FUS_CL; ++i)
-        if (t0 + i < t1) {
-            const float *ut = u_lds + (t0 + i) * FUS_LDU;
-            const float f = ut[FUS_CH + ch];
-            const float r = sigmoidf_(ut[2 * FUS_CH + ch] + br);
-            c = f * c + (1.f - f) * ut[ch];
-            const float hw = kgates == 4 ? ut[3 * FUS_CH + ch] : hwv[i];
-            ho[(size_t)(t0 + i) * n_h] = f32_to_bf16(r * tanhf_(c) + (1.f - r) * hw);
+    for (int i = 0; i < FUS_WAVES - 1; ++i)
+        if (i < w) cin = wave_a[i][ch] * cin + wave_b[i][ch];
+    c = pa * cin + pb;
+
+    // h of 8 channels makes a 16-byte piece per position: through LDS, one store per row instead of eight of 2 bytes
+    bf16_t *h_lds = reinterpret_cast<bf16_t *>(u_lds);
+#pragma unroll
+    for (int i = 0; i < CL; ++i) {
+        c = f[i] * c + g[i];
+        if (i < cl && t0 + i < L) h_lds[(t0 + i) * FUS_CH + ch] = f32_to_bf16(r[i] * tanhf_(c) + (1.f - r[i]) * hw[i]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < HROWS; ++i) {
+        const int t = tid + i * FUS_THREADS;
+        if (t < L) {
+            u32x4s_t *dst = packed_out ? reinterpret_cast<u32x4s_t *>(h_out) + packed_piece(b, n_blocks, n_h, t, cb)
+                                       : reinterpret_cast<u32x4s_t *>(h_out + ((size_t)b * L + t) * n_h + cb * FUS_CH);
+            *dst = *reinterpret_cast<const u32x4s_t *>(h_lds + t * FUS_CH);
         }
+    }
 }
+
+// bytes of the fragment image of B sequences of L states of n channels (at most half of B*L*4*n binary32 values if L >= 8)
+static inline size_t fus_image_bytes(int B, int L, int n) { return (size_t)B * align_up((size_t)L, 32) * n * 2; }
 
 struct SruWs {
     size_t u, h0, h1, wp, rws, prob, ht, total;
@@ -435,6 +551,7 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
     const int head_layout = w->w_layout;
     const bf16_t *cur = (const bf16_t *)emb;
     int nin = w->n_in;
+    bool packed = false;                       // cur is a fragment image
     for (int l = 0; l < w->n_layers; ++l) {
         int k = nin == n_h ? 3 : 4;
         int ncol = k * n_h;
@@ -446,10 +563,21 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
         }
         bf16_t *out = hbuf[l & 1];
         if (L <= FUS_MAX_L) {
-            // the whole layer in one kernel
-            auto fused = L <= 256 ? sru_layer_fused_kernel<1> : sru_layer_fused_kernel<2>;
+            // The whole layer in one kernel.  Every layer but the last hands its states on as a fragment image; the two images
+            // live in the room that the two-kernel form has for its projections, which holds them from 8 positions on (blocks of
+            // 32 positions, padded).
+            const bool pin = packed, pout = l + 1 < w->n_layers && L >= 8;
+            if (pout) out = (bf16_t *)(base + lay.u + (l & 1) * fus_image_bytes(B, L, n_h));
+            packed = pout;
+            // weights through LDS where they fit beside what else is there (K / 16 fragments of 1 KB; the row-major kernel of short
+            // sequences keeps its LDS small, two to four of its workgroups share a CU)
+#define MOE_FUS(N)                                                                                                     \
+    (pin ? (nin <= 256 ? sru_layer_fused_kernel<N, true, 2> : sru_layer_fused_kernel<N, true, 0>)                      \
+         : (N > 1 && nin <= 768 ? sru_layer_fused_kernel<N, false, (N > 1 ? 6 : 0)> : sru_layer_fused_kernel<N, false, 0>))
+            auto fused = L <= 256 ? MOE_FUS(1) : L <= 512 ? MOE_FUS(2) : MOE_FUS(4);
+#undef MOE_FUS
             hipLaunchKernelGGL(fused, dim3((n_h / FUS_CH) * B), dim3(FUS_THREADS), 0, st, cur, (const bf16_t *)wl, L, nin, n_h, k,
-                               w->b_f ? w->b_f[l] : nullptr, w->b_r ? w->b_r[l] : nullptr, out);
+                               w->b_f ? w->b_f[l] : nullptr, w->b_r ? w->b_r[l] : nullptr, pout ? 1 : 0, out);
             MOE_CHECK_LAUNCH("sru_predict/layer");
             cur = out;
             nin = n_h;

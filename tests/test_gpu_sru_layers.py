@@ -1,0 +1,40 @@
+"""The one-kernel SRU layer at the edges of its variants: sequences around 256, 512 and 1024 positions, blocks of 32
+positions part filled, the shortest sequences whose states are handed on as fragments and those that are not, first-layer
+widths with and without room for their weights in LDS, one layer (nothing handed on) and several."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from gpu_util import to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,L,n_in,n_h,layers", [
+    (2, 7, 128, 128, 3),          # too short for the fragment images
+    (3, 8, 128, 256, 3),          # the shortest with them
+    (1, 33, 256, 256, 2),         # one position in the last block; highway input from row-major and from fragments
+    (2, 256, 64, 128, 2),         # the last length of one row block per wavefront
+    (8, 257, 320, 128, 2),        # two row blocks, whole sequences per XCD
+    (1, 512, 832, 256, 2),        # first layer too wide for its weights in LDS
+    (2, 513, 768, 128, 2),        # four row blocks
+    (1, 1024, 128, 384, 3),       # the longest; later layers too wide for their weights in LDS
+    (1, 1025, 128, 128, 2),       # the two-kernel form
+])
+def test_sru_layer_variants(B, L, n_in, n_h, layers):
+    import paper_2605_11537_amd as moe
+    s = synth.sru_inputs(B, L, n_in, n_h, layers, 128, synth.BF16, 4000 + L, bias_std=0.2)
+    w = moe.SruWeights([to_dev(a) for a in s["w_cat"]], [to_dev(a) for a in s["b_f"]], [to_dev(a) for a in s["b_r"]],
+                       to_dev(s["w_head"]), to_dev(s["b_head"]))
+    ref = oracle.sru(s["emb"], s["w_cat"], s["b_f"], s["b_r"], s["w_head"], s["b_head"])
+    # workspace contents must not matter
+    import ctypes
+    need = moe.lib().sru_predict_workspace_bytes(ctypes.byref(w.c), B, L, moe.MOE_BF16)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    pred, logits = moe.sru_predict(to_dev(s["emb"]), w, want_logits=True, ws=ws)
+    lg, want = to_host(logits), ref["logits"].reshape(B * L, -1)
+    # states are stored in bf16 between layers on both sides; the bound of the predictor tests
+    assert np.abs(lg - want).max() <= 5e-3 * np.abs(want).max()
+    assert (to_host(pred) == lg.argmax(axis=1)).all()
