@@ -12,7 +12,10 @@ int route_launch(const void *x, const void *w_router, int w_layout, const float 
 int pack_matrix_launch(const void *in, int K, int N, void *out, hipStream_t st, const char *who);
 // attention.hip: z = h + sparsemax-attention context over each of the B sequences of L states (bf16, n features)
 size_t sru_attention_ws_bytes(int B, int L, int n);   // packed image of the states
-int sru_attention_launch(const void *h, int B, int L, int n, void *z, void *ht_ws, hipStream_t st, const char *who);
+// fragments: h is the fragment image of the states (sru.hip) and ht_ws already holds their packed image
+bool sru_attention_takes_fragments(int L);
+int sru_attention_launch(const void *h, bool fragments, int B, int L, int n, void *z, void *ht_ws, hipStream_t st,
+                         const char *who);
 // plan.hip: histograms of ids in blocks of plan_partial_block() ids, partial[b][E]
 int plan_partial_block();
 int plan_partial_launch(const int32_t *idx, int T, int E, int32_t *partial, hipStream_t st, const char *who);

@@ -207,7 +207,8 @@ __global__ __launch_bounds__(FUS_THREADS, 1) void sru_layer_fused_kernel(const b
                                                                          int n_h, int kgates,
                                                                          const float *__restrict__ b_f,
                                                                          const float *__restrict__ b_r, int packed_out,
-                                                                         bf16_t *__restrict__ h_out)
+                                                                         bf16_t *__restrict__ h_out,
+                                                                         bf16_t *__restrict__ ht_out)
 {
     constexpr int MAX_L = 256 * NRB, CL = MAX_L / FUS_CHUNKS;
     constexpr int KC = NRB <= 2 ? 64 : 32;             // k per register buffer: a whole line per row, or half of one for room
@@ -458,6 +459,23 @@ __global__ __launch_bounds__(FUS_THREADS, 1) void sru_layer_fused_kernel(const b
             *dst = *reinterpret_cast<const u32x4s_t *>(h_lds + t * FUS_CH);
         }
     }
+    // In front of the attention, also the packed image of the states as a (positions x channels) matrix (piece: 8 consecutive
+    // positions of one channel, positions past the sequence zero).
+    if (ht_out) {
+        const int n_groups = (L + 15) / 16 * 2;
+        u32x4s_t *ht = reinterpret_cast<u32x4s_t *>(ht_out) + (size_t)b * (n_h >> 5) * n_groups * 32;
+        const int f = cb * FUS_CH + ch;
+        for (int gr = q; gr < n_groups; gr += FUS_CHUNKS) {
+            u32x4s_t v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int t = gr * 8 + 2 * i;
+                const uint32_t lo = t < L ? h_lds[t * FUS_CH + ch] : 0, hi = t + 1 < L ? h_lds[(t + 1) * FUS_CH + ch] : 0;
+                v[i] = lo | (hi << 16);
+            }
+            ht[((size_t)(f >> 5) * n_groups + gr) * 32 + (f & 31)] = v;
+        }
+    }
 }
 
 // bytes of the fragment image of B sequences of L states of n channels (at most half of B*L*4*n binary32 values if L >= 8)
@@ -563,10 +581,12 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
         }
         bf16_t *out = hbuf[l & 1];
         if (L <= FUS_MAX_L) {
-            // The whole layer in one kernel.  Every layer but the last hands its states on as a fragment image; the two images
+            // The whole layer in one kernel.  Every layer but the last hands its states on as a fragment image (the last does so to the
+            // attention); the two images
             // live in the room that the two-kernel form has for its projections, which holds them from 8 positions on (blocks of
             // 32 positions, padded).
-            const bool pin = packed, pout = l + 1 < w->n_layers && L >= 8;
+            const bool last = l + 1 == w->n_layers;
+            const bool pin = packed, pout = L >= 8 && (!last || (w->attention && sru_attention_takes_fragments(L)));
             if (pout) out = (bf16_t *)(base + lay.u + (l & 1) * fus_image_bytes(B, L, n_h));
             packed = pout;
             // weights through LDS where they fit beside what else is there (K / 16 fragments of 1 KB; the row-major kernel of short
@@ -577,7 +597,8 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
             auto fused = L <= 256 ? MOE_FUS(1) : L <= 512 ? MOE_FUS(2) : MOE_FUS(4);
 #undef MOE_FUS
             hipLaunchKernelGGL(fused, dim3((n_h / FUS_CH) * B), dim3(FUS_THREADS), 0, st, cur, (const bf16_t *)wl, L, nin, n_h, k,
-                               w->b_f ? w->b_f[l] : nullptr, w->b_r ? w->b_r[l] : nullptr, pout ? 1 : 0, out);
+                               w->b_f ? w->b_f[l] : nullptr, w->b_r ? w->b_r[l] : nullptr, pout ? 1 : 0, out,
+                               last && pout ? (bf16_t *)(base + lay.ht) : nullptr);
             MOE_CHECK_LAUNCH("sru_predict/layer");
             cur = out;
             nin = n_h;
@@ -597,7 +618,7 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
     }
     if (w->attention) {
         bf16_t *zbuf = hbuf[w->n_layers & 1];      // the buffer the last layer did not write
-        rc = sru_attention_launch(cur, B, L, n_h, zbuf, base + lay.ht, st, "sru_predict/attention");
+        rc = sru_attention_launch(cur, packed, B, L, n_h, zbuf, base + lay.ht, st, "sru_predict/attention");
         if (rc != MOE_OK) return rc;
         cur = zbuf;
     }

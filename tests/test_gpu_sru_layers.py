@@ -38,3 +38,26 @@ def test_sru_layer_variants(B, L, n_in, n_h, layers):
     # states are stored in bf16 between layers on both sides; the bound of the predictor tests
     assert np.abs(lg - want).max() <= 5e-3 * np.abs(want).max()
     assert (to_host(pred) == lg.argmax(axis=1)).all()
+
+
+@pytest.mark.parametrize("B,L,n_h,layers", [
+    (2, 7, 128, 2),               # row-major states
+    (3, 8, 256, 1),               # the first layer writes the images itself; one part-filled block
+    (2, 65, 128, 2),              # a second score per lane, positions in the last group of 16
+    (1, 257, 256, 2),             # eight scores per lane
+    (8, 513, 128, 1),             # sixteen, the second half of the packed states
+    (1, 1000, 256, 2),
+])
+def test_attention_variants(B, L, n_h, layers):
+    import ctypes
+    import paper_2605_11537_amd as moe
+    s = synth.sru_inputs(B, L, 128, n_h, layers, 128, synth.BF16, 5000 + L, bias_std=0.1)
+    w = moe.SruWeights([to_dev(a) for a in s["w_cat"]], [to_dev(a) for a in s["b_f"]], [to_dev(a) for a in s["b_r"]],
+                       to_dev(s["w_head"]), to_dev(s["b_head"]), attention=True)
+    ref = oracle.sru_attention(s["emb"], s["w_cat"], s["b_f"], s["b_r"], s["w_head"], s["b_head"])
+    need = moe.lib().sru_predict_workspace_bytes(ctypes.byref(w.c), B, L, moe.MOE_BF16)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")     # whatever the images' padding holds: NaN here
+    pred, logits = moe.sru_predict(to_dev(s["emb"]), w, want_logits=True, ws=ws)
+    lg, want = to_host(logits), ref["logits"].reshape(B * L, -1)
+    assert np.abs(lg - want).max() <= 5e-3 * np.abs(want).max()          # the bound of the predictor tests
+    assert (to_host(pred) == lg.argmax(axis=1)).all()
