@@ -81,16 +81,6 @@ __device__ __forceinline__ void gemm_tile_bf16(const bf16_t *__restrict__ A, int
     const u32x4v_t *b_base = reinterpret_cast<const u32x4v_t *>(Bp) + (size_t)((n0 >> 5) + w * NB) * KG * 32;
 
     const bf16_t *a_src[A_PER_THREAD];   // this thread's rows stay the same for every k chunk
-#pragma unroll
-    for (int i = 0; i < A_PER_THREAD; ++i) {
-        int r = a_row + i * ROW_STEP;
-        r = r < nrows ? r : nrows - 1;
-        if (row_idx) {
-            r = row_idx[r];
-            r = (r >= 0 && r < n_src_rows) ? r : 0;
-        }
-        a_src[i] = A + (size_t)r * lda + a_col * 8;
-    }
     auto load_a = [&](int kc, int set) {
 #pragma unroll
         for (int i = 0; i < A_PER_THREAD; ++i) a_reg[set][i] = *reinterpret_cast<const u32x4v_t *>(a_src[i] + kc * BK);
@@ -152,7 +142,32 @@ __device__ __forceinline__ void gemm_tile_bf16(const bf16_t *__restrict__ A, int
     using even = std::integral_constant<int, 0>;
     using odd = std::integral_constant<int, 1>;
 
-    request(0, 0);
+    // The first chunk's weights are on their way before the row numbers they do not depend on have arrived.  From the first
+    // chunk's tokens on the order is the loop's.
+    int rows[A_PER_THREAD];
+#pragma unroll
+    for (int i = 0; i < A_PER_THREAD; ++i) {
+        const int r = a_row + i * ROW_STEP;
+        rows[i] = r < nrows ? r : nrows - 1;
+    }
+    if (row_idx) {
+#pragma unroll
+        for (int i = 0; i < A_PER_THREAD; ++i) rows[i] = row_idx[rows[i]];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) load_b(0, 0, ks);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < A_PER_THREAD; ++i) rows[i] = (rows[i] >= 0 && rows[i] < n_src_rows) ? rows[i] : 0;
+    } else {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) load_b(0, 0, ks);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < A_PER_THREAD; ++i) a_src[i] = A + (size_t)rows[i] * lda + a_col * 8;
+    load_a(0, 0);
+    __builtin_amdgcn_sched_barrier(0);
     request(nk > 1 ? 1 : 0, 1);
     store_a(0, 0);
     __syncthreads();
