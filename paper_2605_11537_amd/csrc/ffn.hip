@@ -18,6 +18,7 @@
 #include "gemm_bf16.h"
 #include "gemm_dense_bf16.h"
 #include "ffn_f32.h"
+#include "ffn_few_rows.h"
 
 namespace moe {
 
@@ -397,7 +398,11 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
         }
         if (dense) {
             // the dense kernel took every row
-        } else if (tall)
+        } else if (listless && ffn_few_rows(max_rows, max_slots, d, F))
+            hipLaunchKernelGGL(ffn_few_rows_bf16_kernel<true>, dim3(few_rows_grid(max_rows, max_slots, schedule, F)),
+                               dim3(SHARE_THREADS), 0, st, (const bf16_t *)x_perm, (const bf16_t *)w1, row_index, n_x_rows, d, F,
+                               E, slot_offset, slot_expert, n_slots, max_slots, schedule, max_rows, (bf16_t *)h);
+        else if (tall)
             hipLaunchKernelGGL((ffn_gemm_bf16_kernel<true, true>), dim3(g1), dim3(GEMM_THREADS), 0, st,
                                (const bf16_t *)x_perm, row_index, n_x_rows, (const bf16_t *)w1, d, F, E, list,
                                n_items, slot_offset, slot_expert, n_slots, max_slots, schedule, max_rows,
@@ -416,7 +421,12 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
             MOE_CHECK_LAUNCH("moe_expert_ffn/dense gemm2");
         }
         if (dense) {
-        } else if (tall)
+        } else if (listless && ffn_few_rows(max_rows, max_slots, F, d))
+            hipLaunchKernelGGL(ffn_few_rows_bf16_kernel<false>, dim3(few_rows_grid(max_rows, max_slots, schedule, d)),
+                               dim3(SHARE_THREADS), 0, st, (const bf16_t *)h, (const bf16_t *)w2, (const int32_t *)nullptr,
+                               max_rows, F, d, E, slot_offset, slot_expert, n_slots, max_slots, schedule, max_rows,
+                               (bf16_t *)y_perm);
+        else if (tall)
             hipLaunchKernelGGL((ffn_gemm_bf16_kernel<false, true>), dim3(g2), dim3(GEMM_THREADS), 0, st,
                                (const bf16_t *)h, (const int32_t *)nullptr, max_rows, (const bf16_t *)w2, F, d, E,
                                list, n_items, slot_offset, slot_expert, n_slots, max_slots, schedule, max_rows,
@@ -434,12 +444,12 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
         const int bm = (long long)max_rows >= 128LL * E ? 64 : 32;
         auto gemm1 = bm == 64 ? ffn_gemm_f32_kernel<true, 64> : ffn_gemm_f32_kernel<true, 32>;
         auto gemm2 = bm == 64 ? ffn_gemm_f32_kernel<false, 64> : ffn_gemm_f32_kernel<false, 32>;
-        hipLaunchKernelGGL(gemm1, dim3(f32_grid(bm, max_rows, max_slots, schedule, F)), dim3(F32_THREADS), 0, st,
+        hipLaunchKernelGGL(gemm1, dim3(share_grid(bm, F32_BN, max_rows, max_slots, schedule, F)), dim3(F32_THREADS), 0, st,
                            (const float *)x_perm, (const float *)w1, row_index, n_x_rows, d, F, E, slot_offset, slot_expert,
                            n_slots, max_slots, schedule, max_rows, (float *)h);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm1");
         if (ev[1]) (void)hipEventRecord(ev[1], st);
-        hipLaunchKernelGGL(gemm2, dim3(f32_grid(bm, max_rows, max_slots, schedule, d)), dim3(F32_THREADS), 0, st,
+        hipLaunchKernelGGL(gemm2, dim3(share_grid(bm, F32_BN, max_rows, max_slots, schedule, d)), dim3(F32_THREADS), 0, st,
                            (const float *)h, (const float *)w2, (const int32_t *)nullptr, max_rows, F, d, E, slot_offset,
                            slot_expert, n_slots, max_slots, schedule, max_rows, (float *)y_perm);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm2");

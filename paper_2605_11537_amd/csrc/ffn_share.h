@@ -1,0 +1,174 @@
+// How a grouped product deals its (expert, row tile, column tile) units to workgroups without a list kernel.
+#pragma once
+#include "common.h"
+
+namespace moe {
+
+constexpr int SHARE_THREADS = 256;
+constexpr int TILE_COST_TILE = 3, TILE_COST_BLOCK = 2;
+
+// Rows of one expert (a tile of them, or in the experts schedule all) x one column tile.
+struct TileItem {
+    int expert, row_begin, row_end, column, reuse;
+};
+
+// Relative cost of a row tile: its 16-row blocks, and what every tile pays for its weights.
+__device__ __forceinline__ int tile_cost(int rows) { return TILE_COST_TILE + TILE_COST_BLOCK * ((rows + 15) >> 4); }
+
+// Which (expert, row tile, column tile) a workgroup works on, found from the slot tables by the whole workgroup: each
+// thread counts the tiles of its slots, a scan gives everybody's place, and the owner of the tile wanted writes it out.  (A list
+// built by a kernel of its own costs a launch of 4-5 us in front of the first product.)
+// The slots of an expert are neighbours and so are their rows: tiles are cut over all rows of the expert (the results are the
+// same, and replicas leave no part-filled tiles behind).  Order: experts as in the tables, their row tiles, the column tiles of
+// a row tile side by side.  The order is cut into 8 ranges of equal COST, one per XCD; ranges of equal length left the XCDs that
+// drew the full tiles of the hot experts with 1.5 times the work of the others.  Each XCD's workgroups with work come first in
+// the grid: a CU moves about 55 GB/s, so two tiles on one CU take twice as long as on two, and the launch order is what spreads them.
+template <int BM>
+struct TileShare {
+    // this thread's slots and the tiles and cost before them
+    int P, E, schedule, n_nt, p0, p1, own_rows, count, count_base;
+    int first, end;                               // units of this workgroup's XCD
+
+    // rows of the expert whose first slot p is, 0 for its other slots
+    __device__ __forceinline__ int rows_of(const int32_t *__restrict__ slot_offset, const int32_t *__restrict__ slot_expert,
+                                           int p) const
+    {
+        const int e = slot_expert[p];
+        if (e < 0 || e >= E) return 0;            // never index weights with a bad id
+        if (p > 0 && slot_expert[p - 1] == e) return 0;
+        int last = p;
+        while (last + 1 < P && slot_expert[last + 1] == e) ++last;
+        const int n = slot_offset[last + 1] - slot_offset[p];
+        return n > 0 ? n : 0;
+    }
+    // the experts schedule makes one tile of all rows (they queue), the slot schedule tiles of BM rows
+    __device__ __forceinline__ int tiles_of(int n) const
+    {
+        return schedule == MOE_SCHEDULE_EXPERTS ? (n > 0 ? 1 : 0) : (n + BM - 1) / BM;
+    }
+    __device__ __forceinline__ int full_cost() const
+    {
+        return schedule == MOE_SCHEDULE_EXPERTS ? TILE_COST_TILE : tile_cost(BM);
+    }
+    __device__ __forceinline__ int cost_of(int n, int tiles) const
+    {
+        if (tiles == 0) return 0;
+        return schedule == MOE_SCHEDULE_EXPERTS ? TILE_COST_TILE
+                                                : (tiles - 1) * tile_cost(BM) + tile_cost(n - (tiles - 1) * BM);
+    }
+    __device__ __forceinline__ int rows_at(const int32_t *__restrict__ slot_offset, const int32_t *__restrict__ slot_expert,
+                                           int p) const
+    {
+        return p1 - p0 == 1 ? own_rows : rows_of(slot_offset, slot_expert, p);
+    }
+
+    __device__ __forceinline__ void find(const int32_t *__restrict__ slot_offset, const int32_t *__restrict__ slot_expert,
+                                         const int32_t *__restrict__ n_slots_p, int max_slots)
+    {
+        constexpr int WAVES = SHARE_THREADS / WAVE;
+        __shared__ int count_sums[WAVES], cost_sums[WAVES];
+        __shared__ int edge_unit[2];              // first unit of this share and of the next one
+        const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+        P = n_slots_p[0];
+        if (P > max_slots) P = max_slots;
+        const int per = (P + SHARE_THREADS - 1) / SHARE_THREADS;
+        p0 = tid * per < P ? tid * per : P;
+        p1 = p0 + per < P ? p0 + per : P;
+        own_rows = p1 - p0 == 1 ? rows_of(slot_offset, slot_expert, p0) : 0;
+        int cost = 0;
+        count = 0;
+        for (int p = p0; p < p1; ++p) {
+            const int n = rows_at(slot_offset, slot_expert, p), t = tiles_of(n);
+            count += t;
+            cost += cost_of(n, t);
+        }
+        int count_inc = count, cost_inc = cost;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int a = __shfl_up(count_inc, o, 64), b = __shfl_up(cost_inc, o, 64);
+            if (lane >= o) {
+                count_inc += a;
+                cost_inc += b;
+            }
+        }
+        if (lane == 63) {
+            count_sums[w] = count_inc;
+            cost_sums[w] = cost_inc;
+        }
+        __syncthreads();
+        int cost_base = 0, n_items = 0, cost_total = 0;
+        count_base = 0;
+#pragma unroll
+        for (int i = 0; i < WAVES; ++i) {
+            count_base += i < w ? count_sums[i] : 0;
+            cost_base += i < w ? cost_sums[i] : 0;
+            n_items += count_sums[i];
+            cost_total += cost_sums[i];
+        }
+        count_base += count_inc - count;
+        cost_base += cost_inc - cost;
+        // a place on the cost axis, where every row tile stands n_nt times; a range takes the units that start inside it
+        const long long axis = (long long)cost_total * n_nt, lo = (long long)cost_base * n_nt, hi = lo + (long long)cost * n_nt;
+        const int xcd = blockIdx.x & 7;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const long long edge = axis * (xcd + q) / 8;
+            if (tid == 0 && edge >= axis) edge_unit[q] = n_items * n_nt;
+            if (edge < axis && edge >= lo && edge < hi) {
+                int before = count_base;
+                long long at = lo;
+                for (int p = p0; p < p1; ++p) {
+                    const int n = rows_at(slot_offset, slot_expert, p), t = tiles_of(n), c = cost_of(n, t);
+                    if (edge < at + (long long)c * n_nt) {
+                        const int in = (int)(edge - at), full = full_cost();
+                        const int tile = in / (full * n_nt) < t - 1 ? in / (full * n_nt) : t - 1;
+                        const int own = tile < t - 1 ? full : c - (t - 1) * full;
+                        edge_unit[q] = (before + tile) * n_nt + (in - tile * full * n_nt + own - 1) / own;
+                        break;
+                    }
+                    before += t;
+                    at += (long long)c * n_nt;
+                }
+            }
+        }
+        __syncthreads();
+        first = edge_unit[0];
+        end = edge_unit[1];
+    }
+
+    // every thread calls it; the thread that owns the unit's expert writes it to *out (LDS)
+    __device__ __forceinline__ void write_item(const int32_t *__restrict__ slot_offset, const int32_t *__restrict__ slot_expert,
+                                               int unit, TileItem *out) const
+    {
+        if (unit < count_base * n_nt || unit >= (count_base + count) * n_nt) return;
+        int before = count_base;
+        for (int p = p0; p < p1; ++p) {
+            const int n = rows_at(slot_offset, slot_expert, p), t = tiles_of(n);
+            if (unit < (before + t) * n_nt) {
+                const int in = unit - before * n_nt, tile = in / n_nt, col = in - tile * n_nt, r0 = slot_offset[p];
+                out->expert = slot_expert[p];
+                out->column = col;
+                out->row_begin = r0 + tile * BM;
+                out->row_end = tile + 1 < t ? r0 + (tile + 1) * BM : r0 + n;
+                out->reuse = n > BM;
+                break;
+            }
+            before += t;
+        }
+    }
+};
+
+// Workgroups enough for the XCD range with the most tiles: a range is an eighth of the cost, and no tile costs less than
+// one of a single block.
+static inline int share_grid(int bm, int bn, int max_rows, int max_slots, int schedule, int N)
+{
+    long long cost = (long long)TILE_COST_TILE * max_slots, least = TILE_COST_TILE;
+    if (schedule == MOE_SCHEDULE_SLOTS) {
+        cost = TILE_COST_TILE * (max_slots + (long long)max_rows / bm) + TILE_COST_BLOCK * (max_slots + (long long)max_rows / 16);
+        least = TILE_COST_TILE + TILE_COST_BLOCK;
+    }
+    const int n_nt = N / bn;
+    return (int)(8 * ((cost * n_nt + 8 * least - 1) / (8 * least) + 1));
+}
+
+}  // namespace moe
