@@ -197,6 +197,19 @@ __device__ __forceinline__ size_t packed_piece(int seq, int n_blocks, int n, int
     return (((size_t)seq * n_blocks + (t >> 5)) * (n >> 4) + (g >> 1)) * 64 + (g & 1) * 32 + (t & 31);
 }
 
+// Row-major embeddings [B*L, K] -> fragment image (positions past a sequence repeat its last).  32 positions x 64 channels per
+// workgroup: whole lines in, 4 KB runs out.
+__global__ __launch_bounds__(256) void sru_pack_input_kernel(const uint4 *__restrict__ x, int L, int K,
+                                                             uint4 *__restrict__ image)
+{
+    __shared__ uint4 buf[256];
+    const int tid = threadIdx.x, r = tid >> 3, g = tid & 7, blk = blockIdx.x, n_blocks = gridDim.x, b = blockIdx.z;
+    const int t = blk * 32 + r < L ? blk * 32 + r : L - 1;
+    buf[(g >> 1) * 64 + (g & 1) * 32 + r] = x[((size_t)b * L + t) * (K >> 3) + blockIdx.y * 8 + g];
+    __syncthreads();
+    image[((size_t)b * n_blocks + blk) * (K >> 4) * 64 + blockIdx.y * 256 + tid] = buf[tid];
+}
+
 // NRB: 32-row blocks per wavefront, L <= 256 * NRB.  PIN: X is a fragment image (else row-major); packed_out: so is h_out.
 // WF > 0: the weight fragments (K / 16 <= 8 * WF of them) are fetched once per workgroup, WF per wavefront, and read from LDS;
 // loaded by every wavefront for itself they are a third of what the CU's load path carries (45 bytes per clock, the bound of the
@@ -570,6 +583,19 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
     const bf16_t *cur = (const bf16_t *)emb;
     int nin = w->n_in;
     bool packed = false;                       // cur is a fragment image
+    // The longest sequences of wide embeddings have them packed once, where the row-major kernel turns them into fragments in each
+    // of the n_hidden / 8 workgroups of a sequence.  The image lies where the second layer's states go afterwards, behind the first's,
+    // if the room for the projections holds it.  5 x 777, 768 wide: first layer 31.6 -> 24.7 us plus 4.5 us for the image, 48 -> 46
+    // us with the second layer and the head; 8 x 512: 19.5 -> 16.3 plus 4.1 us, so not up to 512 positions.
+    if (L > 512 && L <= FUS_MAX_L && nin >= 512 &&
+        fus_image_bytes(B, L, n_h) + fus_image_bytes(B, L, nin) <= (size_t)T * 4 * n_h * sizeof(float)) {
+        bf16_t *image = (bf16_t *)(base + lay.u + fus_image_bytes(B, L, n_h));
+        hipLaunchKernelGGL(sru_pack_input_kernel, dim3(ceil_div(L, 32), nin / 64, B), dim3(256), 0, st, (const uint4 *)cur, L, nin,
+                           (uint4 *)image);
+        MOE_CHECK_LAUNCH("sru_predict/pack_input");
+        cur = image;
+        packed = true;
+    }
     for (int l = 0; l < w->n_layers; ++l) {
         int k = nin == n_h ? 3 : 4;
         int ncol = k * n_h;
@@ -592,7 +618,9 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
             // weights through LDS where they fit beside what else is there (K / 16 fragments of 1 KB; the row-major kernel of short
             // sequences keeps its LDS small, two to four of its workgroups share a CU)
 #define MOE_FUS(N)                                                                                                     \
-    (pin ? (nin <= 256 ? sru_layer_fused_kernel<N, true, 2> : sru_layer_fused_kernel<N, true, 0>)                      \
+    (pin ? (nin <= 256            ? sru_layer_fused_kernel<N, true, 2>                                                 \
+            : N > 2 && nin <= 768 ? sru_layer_fused_kernel<N, true, (N > 2 ? 6 : 2)>                                   \
+                                  : sru_layer_fused_kernel<N, true, 0>)                                                \
          : (N > 1 && nin <= 768 ? sru_layer_fused_kernel<N, false, (N > 1 ? 6 : 0)> : sru_layer_fused_kernel<N, false, 0>))
             auto fused = L <= 256 ? MOE_FUS(1) : L <= 512 ? MOE_FUS(2) : MOE_FUS(4);
 #undef MOE_FUS

@@ -19,7 +19,9 @@ pytestmark = pytest.mark.gpu
     (2, 256, 64, 128, 2),         # the last length of one row block per wavefront
     (8, 257, 320, 128, 2),        # two row blocks, whole sequences per XCD
     (1, 512, 832, 256, 2),        # first layer too wide for its weights in LDS
-    (2, 513, 768, 128, 2),        # four row blocks
+    (2, 513, 768, 128, 2),        # four row blocks; embeddings too wide beside the states for an image of their own
+    (2, 777, 768, 256, 3),        # embeddings packed first, their image overwritten by the second layer
+    (1, 1024, 832, 256, 1),       # the same without room for the weights in LDS, one layer
     (1, 1024, 128, 384, 3),       # the longest; later layers too wide for their weights in LDS
     (1, 1025, 128, 128, 2),       # the two-kernel form
 ])
