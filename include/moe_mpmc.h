@@ -255,8 +255,8 @@ int moe_pack_weights(const void *w, int E, int K, int N, int dtype, void *w_pack
  *   h = relu(x_perm[row] W1[e])  (stored in dtype),   y_perm[row] = h W2[e]  (stored in dtype)
  * W1 [E,d,F], W2 [E,F,d].  MOE_F32 takes MOE_LAYOUT_PLAIN; MOE_BF16 takes MOE_LAYOUT_PACKED
  * (each of W1, W2 packed with moe_pack_weights, K = d resp. F) and needs d % 128 == 0,
- * F % 128 == 0.  schedule: MOE_SCHEDULE_SLOTS gives every slot its own row tiles, so the
- * replicas of a hot expert run side by side; MOE_SCHEDULE_EXPERTS makes one work item per
+ * F % 128 == 0.  schedule: MOE_SCHEDULE_SLOTS gives every slot its own row tiles (some kernels: cuts
+ * the rows of an expert's neighbouring slots into tiles together), so the replicas of a hot expert run side by side; MOE_SCHEDULE_EXPERTS makes one work item per
  * (expert, column tile) walk all rows of that expert one tile after another (tokens queue on
  * the one physical expert).  Both produce the same y_perm.  max_rows bounds the rows
  * (normally T), max_slots the slot tables, E the expert count of W1/W2 (slots naming an
