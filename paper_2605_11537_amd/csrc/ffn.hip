@@ -152,8 +152,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void ffn_dense_bf16_kernel(
 }
 
 // ------------------------------------------------------------------ bf16 grouped GEMM
-// Two tile heights.  Up to 64 rows: 2 row blocks per wavefront, k chunks of 128 -- the
-// weight-streaming shape.  65..128 rows (TALL builds only): 4 row blocks per wavefront, so a weight
+// Three tile heights.  Up to 32 and up to 64 rows: 1 or 2 row blocks per wavefront, k chunks of 128 -- the
+// weight-streaming shapes.  65..128 rows (TALL builds only): 4 row blocks per wavefront, k chunks of 64, so a weight
 // byte fetched from L2/HBM feeds twice the rows.  The build without the tall tile walks a work item
 // 64 rows at a time.  (Three or four workgroups per CU instead of two, tried with a k chunk of 64 to
 // fit the registers, changed the HBM-bound launches by under 1%: two it stays.)
