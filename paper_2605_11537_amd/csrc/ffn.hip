@@ -488,6 +488,9 @@ extern "C" int moe_expert_ffn_timed(const void *x, int n_x_rows, const int32_t *
 {
     MOE_REQUIRE(n_x_rows >= 0 && (row_index || n_x_rows == max_rows), MOE_ERR_INVALID_ARG,
                 "moe_expert_ffn_timed: n_x_rows=%d must equal max_rows=%d without row_index", n_x_rows, max_rows);
+    // the kernels read row 0 in place of a bad index, so there has to be one
+    MOE_REQUIRE(max_rows == 0 || n_x_rows > 0, MOE_ERR_INVALID_ARG,
+                "moe_expert_ffn_timed: max_rows=%d rows cannot be gathered from n_x_rows=0", max_rows);
     void *const evs[3] = {ev_before, ev_between, ev_after};
     return expert_ffn_checked(x, n_x_rows, row_index, w1, w2, weight_layout, slot_offset, slot_expert, n_slots,
                               max_rows, max_slots, E, d, F, dtype, schedule, y_perm, ws, ws_bytes, stream, evs);

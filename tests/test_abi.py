@@ -147,6 +147,22 @@ def test_new_entry_points_reject_bad_arguments_on_the_host():
     assert L.moe_build_id() is not None
 
 
+def test_timed_ffn_refuses_rows_of_an_empty_matrix():
+    """A gather reads row 0 where an index is out of range: with rows to compute there has to be one, as for the untimed call."""
+    L = moe.lib()
+    buf = (C.c_char * 4096)()
+    p = C.cast(buf, C.c_void_p)
+    ev = [None] * 4
+    for dtype, layout, d, F in ((0, 0, 64, 256), (1, 1, 128, 256)):
+        tail = (layout, p, p, p, 12, 8, 8, d, F, dtype, 0, p, p, 1 << 30)
+        assert L.moe_expert_ffn_timed(p, 0, p, p, p, *tail, *ev) == -1
+        assert b"n_x_rows=0" in L.moe_last_error()
+        assert L.moe_expert_ffn_rows(p, 0, p, p, p, *tail, None) == -1
+        empty = (layout, p, p, p, 0, 8, 8, d, F, dtype, 0, p, p, 1 << 30)
+        assert L.moe_expert_ffn_timed(None, 0, p, p, p, *empty, *ev) == 0          # an empty batch stays valid
+        assert L.moe_expert_ffn_timed(None, 0, None, p, p, *empty, *ev) == 0
+
+
 def test_a_library_built_from_other_sources_is_refused(monkeypatch):
     """binding.lib() compares the source hash compiled into the library with the sources beside it."""
     from paper_2605_11537_amd import binding, build
