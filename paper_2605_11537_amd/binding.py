@@ -124,11 +124,17 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# a function of torch that its documentation does not name: where a version lacks it, the documented call serves
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
     """The current stream of the current device as a raw handle.  torch.cuda.current_stream() builds a Stream object
     around the same handle and takes 7 us for it, more than the rest of a call's marshalling: a layer of four calls
     was issued in 46-48 us, 29-31 us without it."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _i32(n, dev):

@@ -178,6 +178,24 @@ def test_a_library_built_from_other_sources_is_refused(monkeypatch):
     assert binding.lib() is not None
 
 
+@pytest.mark.parametrize("known", [True, False])
+def test_current_stream_handle(known):
+    """The raw handle comes from torch's own function for it, or from the Stream object where a torch version has none."""
+    import subprocess
+    import sys
+    code = f"""
+import types, torch
+if {known}: torch._C._cuda_getCurrentRawStream = lambda device: 100 + device
+elif hasattr(torch._C, "_cuda_getCurrentRawStream"): del torch._C._cuda_getCurrentRawStream
+torch.cuda.current_device = lambda: 3
+torch.cuda.current_stream = lambda *a: types.SimpleNamespace(cuda_stream=207)
+from paper_2605_11537_amd import binding
+assert binding._stream() == (103 if {known} else 207)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-1000:]
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU per box: the bench says so and exits before touching any device."""
     import subprocess
