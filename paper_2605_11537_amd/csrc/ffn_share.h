@@ -158,17 +158,20 @@ struct TileShare {
     }
 };
 
-// Workgroups enough for the XCD range with the most tiles: a range is an eighth of the cost, and no tile costs less than
-// one of a single block.
+// Workgroups enough for the XCD range with the most units: a range is an eighth of the cost, every expert has one cheap tile at
+// most (its last, of one block or more), all others are full.  (With every unit counted as the cheapest, grids of long batches
+// were twice as large, and went past the launch limit of 2^32 threads at half the batch.)
 static inline int share_grid(int bm, int bn, int max_rows, int max_slots, int schedule, int N)
 {
-    long long cost = (long long)TILE_COST_TILE * max_slots, least = TILE_COST_TILE;
+    long long cost = (long long)TILE_COST_TILE * max_slots, least = TILE_COST_TILE, full = TILE_COST_TILE;
     if (schedule == MOE_SCHEDULE_SLOTS) {
         cost = TILE_COST_TILE * (max_slots + (long long)max_rows / bm) + TILE_COST_BLOCK * (max_slots + (long long)max_rows / 16);
         least = TILE_COST_TILE + TILE_COST_BLOCK;
+        full = TILE_COST_TILE + TILE_COST_BLOCK * (bm / 16);
     }
-    const int n_nt = N / bn;
-    return (int)(8 * ((cost * n_nt + 8 * least - 1) / (8 * least) + 1));
+    const long long n_nt = N / bn, range = (cost * n_nt + 7) / 8;
+    const long long last = range / least < max_slots * n_nt ? range / least : max_slots * n_nt;
+    return (int)(8 * (last + (range - last * least) / full + 2));
 }
 
 }  // namespace moe

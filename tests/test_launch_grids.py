@@ -1,0 +1,88 @@
+"""Launch sizes that the host computes for the worst case: enough workgroups for any slot tables, and within the launch limit
+of 2^32 threads for every batch that fits the card.  The host functions are compiled from the library's headers; the deal of
+tiles to the eight XCD ranges is done again in Python."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SLOTS, EXPERTS = 0, 1
+
+MAIN = """
+#include "ffn_share.h"
+#include <stdio.h>
+int main()
+{
+    int a[6];
+    while (scanf("%d %d %d %d %d %d", a, a + 1, a + 2, a + 3, a + 4, a + 5) == 6)
+        printf("%d\\n", moe::share_grid(a[0], a[1], a[2], a[3], a[4], a[5]));
+}
+"""
+
+
+def _compiled(tmp_path_factory, name, text):
+    d = tmp_path_factory.mktemp(name)
+    src, exe = str(d / "main.cpp"), str(d / "main")
+    open(src, "w").write(text)
+    subprocess.check_call([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip", "--offload-host-only", "-O1",
+                           "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_11537_amd", "csrc"), src, "-o", exe])
+
+    def ask(rows):
+        text = "\n".join(" ".join(str(v) for v in r) for r in rows)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+        return [[int(v) for v in line.split()] for line in out.splitlines()]
+    return ask
+
+
+@pytest.fixture(scope="module")
+def share_grid(tmp_path_factory):
+    return _compiled(tmp_path_factory, "share", MAIN)
+
+
+def _most_units(rows_of_expert, bm, n_nt, schedule):
+    """The most units one of the eight ranges of equal cost holds."""
+    cost = []
+    for n in rows_of_expert:
+        if n <= 0:
+            continue
+        if schedule == EXPERTS:
+            cost.append(3)
+            continue
+        left = n
+        while left > 0:
+            cost.append(3 + 2 * -(-min(left, bm) // 16))
+            left -= bm
+    starts = np.concatenate([[0], np.cumsum(np.repeat(np.array(cost, np.int64), n_nt))])
+    edges = starts[-1] * np.arange(9) // 8
+    return int(np.diff(np.searchsorted(starts[:-1], edges)).max()) if len(cost) else 0
+
+
+def test_grid_holds_every_range(share_grid):
+    rng = np.random.default_rng(5)
+    asked, want = [], []
+    for _ in range(3000):
+        bm, n_nt, schedule = int(rng.choice([32, 64])), int(rng.integers(1, 9)), int(rng.integers(0, 2))
+        S = int(rng.integers(1, 60))
+        kind = rng.integers(0, 4)
+        rows = (rng.integers(0, 3, S) if kind == 0 else rng.integers(0, 130, S) if kind == 1
+                else (rng.pareto(1.0, S) * 20).astype(int) % 3000 if kind == 2 else np.eye(S, dtype=int)[0] * 2000)
+        expert = np.sort(rng.integers(0, S, S))                      # some experts own several slots
+        per_expert = np.bincount(expert, weights=rows, minlength=S).astype(int)
+        asked.append([bm, 64, max(1, int(rows.sum())), S, schedule, 64 * n_nt])
+        want.append(_most_units(per_expert, bm, n_nt, schedule))
+    for a, w, (got,) in zip(asked, want, share_grid(asked)):
+        assert got % 8 == 0 and got // 8 >= w, (a, w, got)
+
+
+def test_long_batches_fit_a_launch(share_grid):
+    """A row tile of 64 rows needs one workgroup per column tile; up to the slots' own share no batch gets many more, so that the
+    launch limit is reached where the hidden rows alone fill the card (256 GB at T * N = 6.4e10)."""
+    asked = [[64, 64, T, S, schedule, N] for T in (10 ** 5, 4 * 10 ** 6, 10 ** 7, 1.5e7, 3 * 10 ** 7)
+             for S in (8, 256, 4096) for schedule in (SLOTS, EXPERTS) for N in (64, 1024, 2048, 4096) if T * N <= 6.2e10]
+    asked = [[int(v) for v in a] for a in asked]
+    for a, (got,) in zip(asked, share_grid(asked)):
+        T, S, N = a[2], a[3], a[5]
+        assert 0 < got <= (T // 64 + 8 * S + 8) * (N // 64) + 64, (a, got)
+        assert got * 256 < 2 ** 32, (a, got)
