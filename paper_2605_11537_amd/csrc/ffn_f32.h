@@ -96,6 +96,7 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
     share.E = E;
     share.schedule = schedule;
     share.n_nt = N / F32_BN;
+    share.max_rows = max_rows;
     share.find(slot_offset, slot_expert, n_slots_p, max_slots);
     const int tid = threadIdx.x, w = tid >> 6, c = tid & 15;
     const int unit = share.first + (int)(blockIdx.x >> 3);

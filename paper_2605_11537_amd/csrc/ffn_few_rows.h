@@ -29,7 +29,7 @@ struct FewItem {
 __device__ __forceinline__ bool few_rows_find(const int32_t *__restrict__ slot_offset,
                                               const int32_t *__restrict__ slot_expert,
                                               const int32_t *__restrict__ n_slots_p, int max_slots, int schedule, int E,
-                                              int n_nt, FewItem &it)
+                                              int n_nt, int max_rows, FewItem &it)
 {
     __shared__ int wave_sums[SHARE_THREADS / WAVE];
     __shared__ FewItem found;
@@ -49,7 +49,7 @@ __device__ __forceinline__ bool few_rows_find(const int32_t *__restrict__ slot_o
     int tiles[FEW_PER], count = 0;
 #pragma unroll
     for (int i = 0; i < FEW_PER; ++i) {
-        const int p = p0 + i, n = off[i + 1] - off[i];
+        const int p = p0 + i, n = (off[i + 1] < max_rows ? off[i + 1] : max_rows) - off[i];     // the grid is sized for max_rows
         const bool in = i < per && p < P && p < max_slots && e[i + 1] >= 0 && e[i + 1] < E;    // never index weights with a bad id
         // the experts schedule: one unit per expert, its first slot's, whether or not there are rows
         tiles[i] = !in ? 0 : schedule == MOE_SCHEDULE_EXPERTS ? (e[i] != e[i + 1] ? 1 : 0) : n > 0 ? (n + FEW_BM - 1) / FEW_BM : 0;
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(SHARE_THREADS, 3) void ffn_few_rows_bf16_kernel(
 {
     __shared__ __attribute__((aligned(16))) float part[4][FEW_BM][FEW_BN + 4];
     FewItem it;
-    if (!few_rows_find(slot_offset, slot_expert, n_slots_p, max_slots, schedule, E, N / FEW_BN, it)) return;
+    if (!few_rows_find(slot_offset, slot_expert, n_slots_p, max_slots, schedule, E, N / FEW_BN, max_rows, it)) return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const bf16_t *strip = Wp + (size_t)it.expert * K * N + (size_t)it.column * FEW_BN * K;
     const int row_end = it.row_end < max_rows ? it.row_end : max_rows;

@@ -26,10 +26,11 @@ __device__ __forceinline__ int tile_cost(int rows) { return TILE_COST_TILE + TIL
 template <int BM>
 struct TileShare {
     // this thread's slots and the tiles and cost before them
-    int P, E, schedule, n_nt, p0, p1, own_rows, count, count_base;
+    int P, E, schedule, n_nt, max_rows, p0, p1, own_rows, count, count_base;
     int first, end;                               // units of this workgroup's XCD
 
-    // rows of the expert whose first slot p is, 0 for its other slots
+    // rows of the expert whose first slot p is, 0 for its other slots; tables that go on past max_rows end there (the grid is
+    // sized for max_rows: units of the rows past it would push others out)
     __device__ __forceinline__ int rows_of(const int32_t *__restrict__ slot_offset, const int32_t *__restrict__ slot_expert,
                                            int p) const
     {
@@ -38,7 +39,7 @@ struct TileShare {
         if (p > 0 && slot_expert[p - 1] == e) return 0;
         int last = p;
         while (last + 1 < P && slot_expert[last + 1] == e) ++last;
-        const int n = slot_offset[last + 1] - slot_offset[p];
+        const int end = slot_offset[last + 1], n = (end < max_rows ? end : max_rows) - slot_offset[p];
         return n > 0 ? n : 0;
     }
     // the experts schedule makes one tile of all rows (they queue), the slot schedule tiles of BM rows
