@@ -181,6 +181,10 @@ __global__ __launch_bounds__(SRU_CHUNKS * SRU_CHANNELS) void sru_scan_kernel(
 // embeddings) goes through a wavefront-private LDS transposition, which costs as much LDS time per k as the loads take.  All loads are unconditional (rows past the sequence repeat its last
 // row, columns past the gates repeat the first's; neither is used), so that the waits of the chunk pipeline are counts:
 // with conditional ones every chunk waited for the chunk just requested.
+// Up to 256 positions a workgroup is small enough for two on a CU (128 registers, 37 KB), runs as many recurrence steps as it
+// has, and only the wavefronts that have rows load any: with one per CU, four steps and all eight wavefronts loading, 64 sequences of
+// 7, 256 -> 256, took 45.7 us with the head where the kernel before took 38.6, now 18; 16 x 16: 15.5, 13.8, now 9.1; 1 x 1: 10.2, 9.2,
+// now 7.6.
 // Measured per layer at 8 x 512, 256 -> 256: 12.4 -> 9.0 us; 5 x 777, 768 -> 256 and 256 -> 256, both layers: 46 us in two
 // launches against 53 us in four (projection and scan kernels, which now serve L > 1024 only).
 constexpr int FUS_CH = 8;              // channels per workgroup
@@ -215,7 +219,7 @@ __global__ __launch_bounds__(256) void sru_pack_input_kernel(const uint4 *__rest
 // loaded by every wavefront for itself they are a third of what the CU's load path carries (45 bytes per clock, the bound of the
 // product here).
 template <int NRB, bool PIN, int WF>
-__global__ __launch_bounds__(FUS_THREADS, 1) void sru_layer_fused_kernel(const bf16_t *__restrict__ X,
+__global__ __launch_bounds__(FUS_THREADS, NRB == 1 ? 4 : 1) void sru_layer_fused_kernel(const bf16_t *__restrict__ X,
                                                                          const bf16_t *__restrict__ Wp, int L, int K,
                                                                          int n_h, int kgates,
                                                                          const float *__restrict__ b_f,
@@ -223,7 +227,7 @@ __global__ __launch_bounds__(FUS_THREADS, 1) void sru_layer_fused_kernel(const b
                                                                          bf16_t *__restrict__ h_out,
                                                                          bf16_t *__restrict__ ht_out)
 {
-    constexpr int MAX_L = 256 * NRB, CL = MAX_L / FUS_CHUNKS;
+    constexpr int MAX_L = 256 * NRB;
     constexpr int KC = NRB <= 2 ? 64 : 32;             // k per register buffer: a whole line per row, or half of one for room
     constexpr int LDA = KC + 8;
     constexpr int SB = NRB < 2 ? NRB : 2;              // row blocks a wavefront stages at a time
@@ -301,7 +305,8 @@ __global__ __launch_bounds__(FUS_THREADS, 1) void sru_layer_fused_kernel(const b
         f32x16_t acc[NRB][1];
         zero_acc<NRB, 1>(acc);
         constexpr int KS = KC / 16;
-        constexpr int D = 3;                           // chunks in flight
+        // chunks in flight; short row-major sequences: two, which leaves room for a second workgroup per CU (see the launch bounds)
+        constexpr int D = NRB == 1 && !PIN ? 2 : 3;
         constexpr int AR = PIN ? KS : NSB;             // 16-byte pieces per lane, row block and chunk (the same number)
         u32x4s_t ga[D][NRB][AR], fb[WF ? 1 : D][KS], wf[WF ? WF : 1];
         const int nkc = K / KC;
@@ -364,15 +369,21 @@ __global__ __launch_bounds__(FUS_THREADS, 1) void sru_layer_fused_kernel(const b
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+        // A wavefront whose first row block lies past the sequence multiplies nothing: eight of them loaded the same rows at 7 positions.
+        // (Where weights are shared the loads stay unconditional, the wait for the weights is a count over them.)
+        const bool rows = WF > 0 || w * 32 < L;
+        if (rows) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) load(d, d);
+            for (int d = 0; d < D; ++d) load(d, d);
+        }
         if constexpr (WF > 0) {
 #pragma unroll
             for (int i = 0; i < WF; ++i) w_lds[(w + FUS_WAVES * i) * 64 + lane] = wf[i];
             __syncthreads();
         }
+        const int n_chunks = rows ? nkc : 0;
         int kc = 0;
-        for (; kc + D < nkc; kc += D) {
+        for (; kc + D < n_chunks; kc += D) {
 #pragma unroll
             for (int d = 0; d < D; ++d) {
                 compute(kc + d, d);
@@ -381,7 +392,7 @@ __global__ __launch_bounds__(FUS_THREADS, 1) void sru_layer_fused_kernel(const b
         }
 #pragma unroll
         for (int d = 0; d < D; ++d)
-            if (kc + d < nkc) compute(kc + d, d);      // uniform
+            if (kc + d < n_chunks) compute(kc + d, d); // uniform
         __syncthreads();           // the staging pieces alias the tile written next
         if (r < kgates * FUS_CH) {
 #pragma unroll
@@ -408,60 +419,69 @@ __global__ __launch_bounds__(FUS_THREADS, 1) void sru_layer_fused_kernel(const b
 
     // ---- recurrence: chunk q holds positions q*cl .. ; past the end of the sequence a step is the identity
     const int cl = (L + FUS_CHUNKS - 1) / FUS_CHUNKS, t0 = q * cl;
-    float f[CL], g[CL], r[CL], hw[CL];
-#pragma unroll
-    for (int i = 0; i < CL; ++i) {
-        const int t = t0 + i;
-        const float *ut = u_lds + (t < MAX_L ? t : MAX_L - 1) * FUS_LDU + ch;
-        g[i] = ut[0];
-        f[i] = ut[FUS_CH];
-        r[i] = ut[2 * FUS_CH];
-        hw[i] = ut[3 * FUS_CH];
-    }
-    float a = 1.f, c = 0.f;
-#pragma unroll
-    for (int i = 0; i < CL; ++i) {
-        const bool in = i < cl && t0 + i < L;
-        f[i] = in ? sigmoidf_(f[i] + bf) : 1.f;
-        g[i] = in ? (1.f - f[i]) * g[i] : 0.f;
-        r[i] = sigmoidf_(r[i] + br);
-        a *= f[i];
-        c = f[i] * c + g[i];
-    }
-    // Inclusive scan of the chunk maps c -> a c + b.  A wavefront holds 8 neighbouring chunks x 8 channels: three
-    // doubling steps over lanes 8, 16, 32 apart; then the eight wavefronts' totals, composed by every thread for itself.
-#pragma unroll
-    for (int o = FUS_CH; o < 64; o <<= 1) {
-        const float qa = __shfl_up(a, o, 64), qb = __shfl_up(c, o, 64);
-        if (lane >= o) {
-            c = a * qb + c;                                // (this) after (earlier)
-            a = a * qa;
-        }
-    }
-    if (lane >= 64 - FUS_CH) {
-        wave_a[w][ch] = a;
-        wave_b[w][ch] = c;
-    }
-    // the map of the chunks before this one, inside the wavefront
-    float pa = __shfl_up(a, FUS_CH, 64), pb = __shfl_up(c, FUS_CH, 64);
-    if (lane < FUS_CH) {
-        pa = 1.f;
-        pb = 0.f;
-    }
-    __syncthreads();               // also: every projection has been read, the tile is free for the output rows
-    float cin = 0.f;
-#pragma unroll
-    for (int i = 0; i < FUS_WAVES - 1; ++i)
-        if (i < w) cin = wave_a[i][ch] * cin + wave_b[i][ch];
-    c = pa * cin + pb;
-
-    // h of 8 channels makes a 16-byte piece per position: through LDS, one store per row instead of eight of 2 bytes
     bf16_t *h_lds = reinterpret_cast<bf16_t *>(u_lds);
+    auto recurrence = [&](auto STEPS) {                // of up to STEPS positions per chunk
+        constexpr int CL = decltype(STEPS)::value;
+        float f[CL], g[CL], r[CL], hw[CL];
 #pragma unroll
-    for (int i = 0; i < CL; ++i) {
-        c = f[i] * c + g[i];
-        if (i < cl && t0 + i < L) h_lds[(t0 + i) * FUS_CH + ch] = f32_to_bf16(r[i] * tanhf_(c) + (1.f - r[i]) * hw[i]);
-    }
+        for (int i = 0; i < CL; ++i) {
+            const int t = t0 + i;
+            const float *ut = u_lds + (t < MAX_L ? t : MAX_L - 1) * FUS_LDU + ch;
+            g[i] = ut[0];
+            f[i] = ut[FUS_CH];
+            r[i] = ut[2 * FUS_CH];
+            hw[i] = ut[3 * FUS_CH];
+        }
+        float a = 1.f, c = 0.f;
+#pragma unroll
+        for (int i = 0; i < CL; ++i) {
+            const bool in = i < cl && t0 + i < L;
+            f[i] = in ? sigmoidf_(f[i] + bf) : 1.f;
+            g[i] = in ? (1.f - f[i]) * g[i] : 0.f;
+            r[i] = sigmoidf_(r[i] + br);
+            a *= f[i];
+            c = f[i] * c + g[i];
+        }
+        // Inclusive scan of the chunk maps c -> a c + b.  A wavefront holds 8 neighbouring chunks x 8 channels: three
+        // doubling steps over lanes 8, 16, 32 apart; then the eight wavefronts' totals, composed by every thread for itself.
+#pragma unroll
+        for (int o = FUS_CH; o < 64; o <<= 1) {
+            const float qa = __shfl_up(a, o, 64), qb = __shfl_up(c, o, 64);
+            if (lane >= o) {
+                c = a * qb + c;                                // (this) after (earlier)
+                a = a * qa;
+            }
+        }
+        if (lane >= 64 - FUS_CH) {
+            wave_a[w][ch] = a;
+            wave_b[w][ch] = c;
+        }
+        // the map of the chunks before this one, inside the wavefront
+        float pa = __shfl_up(a, FUS_CH, 64), pb = __shfl_up(c, FUS_CH, 64);
+        if (lane < FUS_CH) {
+            pa = 1.f;
+            pb = 0.f;
+        }
+        __syncthreads();               // also: every projection has been read, the tile is free for the output rows
+        float cin = 0.f;
+#pragma unroll
+        for (int i = 0; i < FUS_WAVES - 1; ++i)
+            if (i < w) cin = wave_a[i][ch] * cin + wave_b[i][ch];
+        c = pa * cin + pb;
+
+        // h of 8 channels makes a 16-byte piece per position: through LDS, one store per row instead of eight of 2 bytes
+#pragma unroll
+        for (int i = 0; i < CL; ++i) {
+            c = f[i] * c + g[i];
+            if (i < cl && t0 + i < L) h_lds[(t0 + i) * FUS_CH + ch] = f32_to_bf16(r[i] * tanhf_(c) + (1.f - r[i]) * hw[i]);
+        }
+    };
+    // short sequences: the steps they have
+    using std::integral_constant;
+    if (NRB > 1) recurrence(integral_constant<int, MAX_L / FUS_CHUNKS>{});
+    else if (cl == 1) recurrence(integral_constant<int, 1>{});
+    else if (cl == 2) recurrence(integral_constant<int, 2>{});
+    else recurrence(integral_constant<int, 4>{});
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < HROWS; ++i) {
@@ -621,7 +641,9 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
     (pin ? (nin <= 256            ? sru_layer_fused_kernel<N, true, 2>                                                 \
             : N > 2 && nin <= 768 ? sru_layer_fused_kernel<N, true, (N > 2 ? 6 : 2)>                                   \
                                   : sru_layer_fused_kernel<N, true, 0>)                                                \
-         : (N > 1 && nin <= 768 ? sru_layer_fused_kernel<N, false, (N > 1 ? 6 : 0)> : sru_layer_fused_kernel<N, false, 0>))
+         : (N > 1 && nin <= 256   ? sru_layer_fused_kernel<N, false, (N > 1 ? 2 : 0)>                                  \
+            : N > 1 && nin <= 768 ? sru_layer_fused_kernel<N, false, (N > 1 ? 6 : 0)>                                  \
+                                  : sru_layer_fused_kernel<N, false, 0>))
             auto fused = L <= 256 ? MOE_FUS(1) : L <= 512 ? MOE_FUS(2) : MOE_FUS(4);
 #undef MOE_FUS
             hipLaunchKernelGGL(fused, dim3((n_h / FUS_CH) * B), dim3(FUS_THREADS), 0, st, cur, (const bf16_t *)wl, L, nin, n_h, k,

@@ -14,6 +14,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("B,L,n_in,n_h,layers", [
     (2, 7, 128, 128, 3),          # too short for the fragment images
+    (3, 32, 64, 128, 2),          # seven wavefronts without rows, one chunk of k, one recurrence step
+    (2, 64, 128, 128, 2),         # one step, two chunks
+    (2, 65, 192, 128, 2),         # two steps, three chunks
+    (1, 128, 320, 128, 2),        # two steps, four wavefronts with rows
+    (2, 129, 256, 128, 2),        # three steps
+    (1, 300, 64, 128, 2),         # two row blocks per wavefront, few weights
     (3, 8, 128, 256, 3),          # the shortest with them
     (1, 33, 256, 256, 2),         # one position in the last block; highway input from row-major and from fragments
     (2, 256, 64, 128, 2),         # the last length of one row block per wavefront
