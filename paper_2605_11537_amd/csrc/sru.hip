@@ -10,9 +10,10 @@
 // composed by a scan, and each thread then re-runs its chunk from its true carry-in and writes h_t.
 // For sequences of up to 1024 positions steps (2) and (3) are one kernel per layer with the projections
 // kept in LDS (sru_layer_fused_kernel below); the two-kernel form (sru_proj_kernel, sru_scan_kernel)
-// serves longer sequences.  The head is a router-shaped product + argmax and reuses the router's kernel.
+// serves longer sequences, and those of over 512 positions where it is the faster one (sru_forms.h).  The head is a router-shaped product + argmax and reuses the router's kernel.
 #include "gemm_bf16.h"
 #include "route.h"
+#include "sru_forms.h"
 
 namespace moe {
 
@@ -60,6 +61,13 @@ __device__ __forceinline__ float tanhf_(float v)
     return copysignf(t, v);
 }
 
+// 16-byte piece of position t, channels 8g .. 8g+7, in the fragment image of a sequence's states (n channels, blocks of 32
+// positions; fragment (block, 16 channels) = 64 lanes x 16 bytes, the lane order of the matrix instruction's operand)
+__device__ __forceinline__ size_t packed_piece(int seq, int n_blocks, int n, int t, int g)
+{
+    return (((size_t)seq * n_blocks + (t >> 5)) * (n >> 4) + (g >> 1)) * 64 + (g & 1) * 32 + (t & 31);
+}
+
 // grid (n_h/16, B); block = 16 channels x 64 time chunks.  Phase 1: every thread composes its
 // chunk into (A, B) with c_out = A*c_in + B.  Phase 2: one wavefront per channel composes the 64
 // chunk maps by a scan.  Phase 3: every thread re-runs its chunk from its true carry-in and writes h_t.
@@ -70,7 +78,7 @@ __device__ __forceinline__ float tanhf_(float v)
 template <int CL>
 __global__ __launch_bounds__(SRU_CHUNKS * SRU_CHANNELS) void sru_scan_kernel(
     const float *__restrict__ U, const bf16_t *__restrict__ x_in, int L, int n_h, int k,
-    const float *__restrict__ b_f, const float *__restrict__ b_r, bf16_t *__restrict__ h_out)
+    const float *__restrict__ b_f, const float *__restrict__ b_r, int packed_out, bf16_t *__restrict__ h_out)
 {
     __shared__ float carry_a[SRU_CHUNKS][SRU_CHANNELS], carry_b[SRU_CHUNKS][SRU_CHANNELS];
     const int ch = threadIdx.x & (SRU_CHANNELS - 1), q = threadIdx.x / SRU_CHANNELS;
@@ -82,7 +90,10 @@ __global__ __launch_bounds__(SRU_CHUNKS * SRU_CHANNELS) void sru_scan_kernel(
     const float bf = b_f ? b_f[j] : 0.f, br = b_r ? b_r[j] : 0.f;
     const float *u = U + (size_t)b * L * ncol + j;
     const bf16_t *xi = x_in + (size_t)b * L * n_h + j;   // only read when k == 3 (n_in == n_h)
-    bf16_t *ho = h_out + (size_t)b * L * n_h + j;
+    // row-major states, or (up to 1024 positions) the fragment image that the one-kernel layer reads (packed_piece: channel j is element j % 8 of its piece)
+    const bool image = CL > 0 && packed_out;
+    bf16_t *ho = image ? h_out + packed_piece(b, (L + 31) >> 5, n_h, 0, j >> 3) * 8 + (j & 7) : h_out + (size_t)b * L * n_h + j;
+    auto place = [&](int t) { return image ? (size_t)(t >> 5) * n_h * 32 + (t & 31) * 8 : (size_t)t * n_h; };
 
     constexpr int NR = CL > 0 ? CL : 1;
     float ux[NR], uf[NR], ur[NR], uh[NR];
@@ -152,7 +163,7 @@ __global__ __launch_bounds__(SRU_CHUNKS * SRU_CHANNELS) void sru_scan_kernel(
                 const float f = uf[i];
                 const float r = sigmoidf_(ur[i] + br);
                 c = f * c + (1.f - f) * ux[i];
-                ho[(size_t)(t0 + i) * n_h] = f32_to_bf16(r * tanhf_(c) + (1.f - r) * uh[i]);
+                ho[place(t0 + i)] = f32_to_bf16(r * tanhf_(c) + (1.f - r) * uh[i]);
             }
         return;
     }
@@ -163,7 +174,7 @@ __global__ __launch_bounds__(SRU_CHUNKS * SRU_CHANNELS) void sru_scan_kernel(
         float r = sigmoidf_(ut[2 * n_h] + br);
         c = f * c + (1.f - f) * ut[0];
         float hw = k == 4 ? ut[3 * n_h] : bf16_to_f32(xi[(size_t)t * n_h]);
-        ho[(size_t)t * n_h] = f32_to_bf16(r * tanhf_(c) + (1.f - r) * hw);
+        ho[place(t)] = f32_to_bf16(r * tanhf_(c) + (1.f - r) * hw);
     }
 }
 
@@ -186,20 +197,11 @@ __global__ __launch_bounds__(SRU_CHUNKS * SRU_CHANNELS) void sru_scan_kernel(
 // 7, 256 -> 256, took 45.7 us with the head where the kernel before took 38.6, now 18; 16 x 16: 15.5, 13.8, now 9.1; 1 x 1: 10.2, 9.2,
 // now 7.6.
 // Measured per layer at 8 x 512, 256 -> 256: 12.4 -> 9.0 us; 5 x 777, 768 -> 256 and 256 -> 256, both layers: 46 us in two
-// launches against 53 us in four (projection and scan kernels, which now serve L > 1024 only).
-constexpr int FUS_CH = 8;              // channels per workgroup
+// launches against 53 us in four (projection and scan kernels).
 constexpr int FUS_THREADS = 512;       // 8 wavefronts: 2 per SIMD, so one's loads fly under the other's work
 constexpr int FUS_WAVES = FUS_THREADS / 64;
 constexpr int FUS_CHUNKS = FUS_THREADS / FUS_CH;   // 64 time chunks per sequence
-constexpr int FUS_MAX_L = 1024;
 constexpr int FUS_LDU = 33;            // row stride of the LDS tile, binary32 elements
-
-// 16-byte piece of position t, channels 8g .. 8g+7, in the fragment image of a sequence's states (n channels, blocks of 32
-// positions; fragment (block, 16 channels) = 64 lanes x 16 bytes, the lane order of the matrix instruction's operand)
-__device__ __forceinline__ size_t packed_piece(int seq, int n_blocks, int n, int t, int g)
-{
-    return (((size_t)seq * n_blocks + (t >> 5)) * (n >> 4) + (g >> 1)) * 64 + (g & 1) * 32 + (t & 31);
-}
 
 // Row-major embeddings [B*L, K] -> fragment image (positions past a sequence repeat its last).  32 positions x 64 channels per
 // workgroup: whole lines in, 4 KB runs out.
@@ -511,9 +513,6 @@ __global__ __launch_bounds__(FUS_THREADS, NRB == 1 ? 4 : 1) void sru_layer_fused
     }
 }
 
-// bytes of the fragment image of B sequences of L states of n channels (at most half of B*L*4*n binary32 values if L >= 8)
-static inline size_t fus_image_bytes(int B, int L, int n) { return (size_t)B * align_up((size_t)L, 32) * n * 2; }
-
 struct SruWs {
     size_t u, h0, h1, wp, rws, prob, ht, total;
 };
@@ -603,12 +602,11 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
     const bf16_t *cur = (const bf16_t *)emb;
     int nin = w->n_in;
     bool packed = false;                       // cur is a fragment image
-    // The longest sequences of wide embeddings have them packed once, where the row-major kernel turns them into fragments in each
-    // of the n_hidden / 8 workgroups of a sequence.  The image lies where the second layer's states go afterwards, behind the first's,
-    // if the room for the projections holds it.  5 x 777, 768 wide: first layer 31.6 -> 24.7 us plus 4.5 us for the image, 48 -> 46
-    // us with the second layer and the head; 8 x 512: 19.5 -> 16.3 plus 4.1 us, so not up to 512 positions.
-    if (L > 512 && L <= FUS_MAX_L && nin >= 512 &&
-        fus_image_bytes(B, L, n_h) + fus_image_bytes(B, L, nin) <= (size_t)T * 4 * n_h * sizeof(float)) {
+    bool packed_in_h = false;                  // which lies in the two state buffers
+    // the attention reads fragments from a one-kernel layer, which also writes the image of its weighted sums
+    const bool first_two = !(w->attention && w->n_layers == 1) && sru_two_kernels(B, L, nin, n_h, false);
+    const bool later_two = !w->attention && sru_two_kernels(B, L, n_h, n_h, true);
+    if (!first_two && fus_packs_input(B, L, nin, n_h)) {
         bf16_t *image = (bf16_t *)(base + lay.u + fus_image_bytes(B, L, n_h));
         hipLaunchKernelGGL(sru_pack_input_kernel, dim3(ceil_div(L, 32), nin / 64, B), dim3(256), 0, st, (const uint4 *)cur, L, nin,
                            (uint4 *)image);
@@ -625,16 +623,19 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
             if (rc != MOE_OK) return rc;
             wl = wp;
         }
-        bf16_t *out = hbuf[l & 1];
-        if (L <= FUS_MAX_L) {
-            // The whole layer in one kernel.  Every layer but the last hands its states on as a fragment image (the last does so to the
-            // attention); the two images
-            // live in the room that the two-kernel form has for its projections, which holds them from 8 positions on (blocks of
-            // 32 positions, padded).
-            const bool last = l + 1 == w->n_layers;
-            const bool pin = packed, pout = L >= 8 && (!last || (w->attention && sru_attention_takes_fragments(L)));
-            if (pout) out = (bf16_t *)(base + lay.u + (l & 1) * fus_image_bytes(B, L, n_h));
-            packed = pout;
+        // Every one-kernel layer but the last hands its states on as a fragment image (the last does so to the attention), if they are
+        // read by such a layer; so does the scan of the first layer.  The images live in the room that the two-kernel form has for
+        // its projections, which holds two of them from 8 positions on (blocks of 32 positions, padded).  The scan's lies in the two
+        // state buffers, since it reads the projections as it writes; the layer after it then has its states where the images go.
+        const bool last = l + 1 == w->n_layers, two = l == 0 ? first_two : later_two;
+        const bool pin = packed;
+        const bool pout = L <= FUS_MAX_L && L >= 8 &&
+                          (last ? w->attention && sru_attention_takes_fragments(L) : !later_two);
+        bf16_t *const image = (bf16_t *)(base + lay.u + (l & 1) * fus_image_bytes(B, L, n_h));
+        bf16_t *const out = two ? hbuf[pout ? 0 : l & 1] : pout || packed_in_h ? image : hbuf[l & 1];
+        packed = pout;
+        packed_in_h = two && pout;
+        if (!two) {
             // weights through LDS where they fit beside what else is there (K / 16 fragments of 1 KB; the row-major kernel of short
             // sequences keeps its LDS small, two to four of its workgroups share a CU)
 #define MOE_FUS(N)                                                                                                     \
@@ -657,11 +658,10 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
         hipLaunchKernelGGL(sru_proj_kernel, dim3(ceil_div(T, 64) * (ncol / 128)), dim3(GEMM_THREADS), 0, st, cur,
                            (const bf16_t *)wl, T, nin, ncol, U);
         MOE_CHECK_LAUNCH("sru_predict/proj");
-        const int chunk_len = ceil_div(L, SRU_CHUNKS);
-        auto scan = chunk_len <= 8 ? sru_scan_kernel<8> : chunk_len <= 16 ? sru_scan_kernel<16> : sru_scan_kernel<0>;
+        auto scan = L <= 16 * SRU_CHUNKS ? sru_scan_kernel<16> : sru_scan_kernel<0>;
         hipLaunchKernelGGL(scan, dim3(n_h / SRU_CHANNELS, B), dim3(SRU_CHUNKS * SRU_CHANNELS), 0, st, U, cur, L,
                            n_h, k,
-                           w->b_f ? w->b_f[l] : nullptr, w->b_r ? w->b_r[l] : nullptr, out);
+                           w->b_f ? w->b_f[l] : nullptr, w->b_r ? w->b_r[l] : nullptr, pout ? 1 : 0, out);
         MOE_CHECK_LAUNCH("sru_predict/scan");
         cur = out;
         nin = n_h;

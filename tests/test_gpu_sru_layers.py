@@ -30,6 +30,10 @@ pytestmark = pytest.mark.gpu
     (1, 1024, 832, 256, 1),       # the same without room for the weights in LDS, one layer
     (1, 1024, 128, 384, 3),       # the longest; later layers too wide for their weights in LDS
     (1, 1025, 128, 128, 2),       # the two-kernel form
+    (1, 600, 1024, 256, 2),       # the two-kernel form in front of one kernel: its states as fragments, the last layer's row-major
+    (2, 513, 1024, 128, 3),       # the same with a layer in between
+    (3, 520, 64, 1024, 2),        # one kernel in front of the two-kernel form
+    (1, 513, 2048, 128, 1),       # the two-kernel form alone, under 1024 positions
 ])
 def test_sru_layer_variants(B, L, n_in, n_h, layers):
     import paper_2605_11537_amd as moe
@@ -48,18 +52,20 @@ def test_sru_layer_variants(B, L, n_in, n_h, layers):
     assert (to_host(pred) == lg.argmax(axis=1)).all()
 
 
-@pytest.mark.parametrize("B,L,n_h,layers", [
-    (2, 7, 128, 2),               # row-major states
-    (3, 8, 256, 1),               # the first layer writes the images itself; one part-filled block
-    (2, 65, 128, 2),              # a second score per lane, positions in the last group of 16
-    (1, 257, 256, 2),             # eight scores per lane
-    (8, 513, 128, 1),             # sixteen, the second half of the packed states
-    (1, 1000, 256, 2),
+@pytest.mark.parametrize("B,L,n_in,n_h,layers", [
+    (2, 7, 128, 128, 2),               # row-major states
+    (3, 8, 128, 256, 1),               # the first layer writes the images itself; one part-filled block
+    (2, 65, 128, 128, 2),              # a second score per lane, positions in the last group of 16
+    (1, 257, 128, 256, 2),             # eight scores per lane
+    (8, 513, 128, 128, 1),             # sixteen, the second half of the packed states
+    (1, 1000, 128, 256, 2),
+    (1, 600, 1024, 256, 2),       # after a first layer in two kernels
+    (1, 600, 2048, 128, 1),       # whose form does not go in front of the attention
 ])
-def test_attention_variants(B, L, n_h, layers):
+def test_attention_variants(B, L, n_in, n_h, layers):
     import ctypes
     import paper_2605_11537_amd as moe
-    s = synth.sru_inputs(B, L, 128, n_h, layers, 128, synth.BF16, 5000 + L, bias_std=0.1)
+    s = synth.sru_inputs(B, L, n_in, n_h, layers, 128, synth.BF16, 5000 + L, bias_std=0.1)
     w = moe.SruWeights([to_dev(a) for a in s["w_cat"]], [to_dev(a) for a in s["b_f"]], [to_dev(a) for a in s["b_r"]],
                        to_dev(s["w_head"]), to_dev(s["b_head"]), attention=True)
     ref = oracle.sru_attention(s["emb"], s["w_cat"], s["b_f"], s["b_r"], s["w_head"], s["b_head"])
