@@ -44,16 +44,20 @@ __global__ __launch_bounds__(GEMM_THREADS) void sru_proj_kernel(const bf16_t *__
         }
 }
 
-// 1 / x for 1 <= x < 2^120: the hardware reciprocal and one Newton step (the full division is ten instructions, and the gates
+// 1 / x for finite x >= 1: the hardware reciprocal and one Newton step (the full division is ten instructions, and the gates
 // are most of what a layer's recurrence issues)
 __device__ __forceinline__ float recip_(float x)
 {
     const float r = __builtin_amdgcn_rcpf(x);
     return fmaf(r, fmaf(-x, r, 1.f), r);
 }
-// binary32 with the hardware exponential: a few ulp, far inside the bf16 rounding of h.  Below -80 the exponential is held where the
-// reciprocal is finite (sigmoid 1e-35); the comparison leaves a NaN a NaN.
-__device__ __forceinline__ float sigmoidf_(float v) { return recip_(1.f + __expf(v < -80.f ? 80.f : -v)); }
+// binary32 with the hardware exponential: a few ulp, far inside the bf16 rounding of h, down to the smallest normal number.  An
+// infinite denominator is held at the largest finite one (sigmoid 0 or below 2^-126); the comparison leaves a NaN a NaN.
+__device__ __forceinline__ float sigmoidf_(float v)
+{
+    const float x = 1.f + __expf(-v);
+    return recip_(x > 3.402823466e38f ? 3.402823466e38f : x);
+}
 __device__ __forceinline__ float tanhf_(float v)
 {
     float a = fminf(fabsf(v), 15.f);

@@ -52,6 +52,29 @@ def test_sru_layer_variants(B, L, n_in, n_h, layers):
     assert (to_host(pred) == lg.argmax(axis=1)).all()
 
 
+@pytest.mark.parametrize("L", [40, 1030])                 # one kernel, two kernels
+@pytest.mark.parametrize("bias", [-1.0, -50.0, -79.0, -82.0, -86.0, -200.0])
+def test_sru_nearly_closed_gate(L, bias):
+    """A state that is the reset gate alone (x' large, forget gate and highway closed): sigmoid(bias) in bf16, also where it is tiny."""
+    import paper_2605_11537_amd as moe
+    n_in, n_h, n_out = 64, 128, 8
+    dev = dict(dtype=torch.bfloat16, device="cuda")
+    w_cat = torch.zeros(n_in, 4 * n_h, **dev)
+    w_cat[:, :n_h] = 1.0                                    # x' = 64: tanh(c) = 1
+    shift = 2.0 ** round(min(-bias / np.log(2.0), 120.0))
+    b_f = torch.full((n_h,), -300.0, device="cuda")
+    b_r = torch.full((n_h,), bias, device="cuda")
+    w = moe.SruWeights([w_cat], [b_f], [b_r], torch.full((n_h, n_out), shift, **dev))
+    _, logits = moe.sru_predict(torch.ones(2, L, n_in, **dev), w, want_logits=True)
+    lg = to_host(logits).astype(np.float64)
+    if bias < -88.0:                                        # below every normal number
+        assert (lg >= 0).all() and (lg <= n_h * 2.0 ** -126 * shift).all()
+        return
+    want = n_h * shift / (1.0 + np.exp(-bias))
+    # half an ulp of the stored state, a few of the hardware's exponential (whose argument is rounded to 2^-24 of itself)
+    assert (np.abs(lg / want - 1) <= 2.0 ** -8 + abs(bias) * 2.0 ** -23).all()
+
+
 @pytest.mark.parametrize("B,L,n_in,n_h,layers", [
     (2, 7, 128, 128, 2),               # row-major states
     (3, 8, 128, 256, 1),               # the first layer writes the images itself; one part-filled block
