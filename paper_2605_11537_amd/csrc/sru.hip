@@ -311,8 +311,10 @@ __global__ __launch_bounds__(FUS_THREADS, NRB == 1 ? 4 : 1) void sru_layer_fused
         f32x16_t acc[NRB][1];
         zero_acc<NRB, 1>(acc);
         constexpr int KS = KC / 16;
-        // chunks in flight; short row-major sequences: two, which leaves room for a second workgroup per CU (see the launch bounds)
-        constexpr int D = NRB == 1 && !PIN ? 2 : 3;
+        // Chunks in flight, of which D - 1 are asked for past the end.  Short row-major sequences: two, which leaves room for a second
+        // workgroup per CU (see the launch bounds).  Narrow first layers have 1 .. 8 chunks, and the other wavefront's loads to hide
+        // behind: 2 x 300, 64 -> 128, with the head, three, two, one chunk: 10.8, 10.5, 9.9 us; 16 x 1024, 256 -> 256: 46.1, 44.3, 43.5.
+        constexpr int D = PIN ? 3 : WF == 2 ? 1 : NRB == 1 ? 2 : 3;
         constexpr int AR = PIN ? KS : NSB;             // 16-byte pieces per lane, row block and chunk (the same number)
         u32x4s_t ga[D][NRB][AR], fb[WF ? 1 : D][KS], wf[WF ? WF : 1];
         const int nkc = K / KC;
