@@ -285,13 +285,16 @@ static void route_direct_launch_vec(const void *x, const void *w, const float *b
 }
 
 // Columns per lane: the fewest that cover E in one group, but never so many that a lane's load of VEC columns would
-// not be aligned in every row (a row is E elements, so VEC has to divide E).
+// not be aligned in every row (a row is E elements, so VEC has to divide E) or from the matrix' address on (the predictor's head
+// is taken at any).
 template <bool BF16>
 static void route_direct_launch(const void *x, const void *w, const float *bias, int T, int d, int E, int top_k,
                                 int renormalize, int32_t *idx, float *prob, float *logits_opt, hipStream_t st)
 {
     int vec = 1;
-    while (vec < 8 && 32 * vec < E && E % (2 * vec) == 0) vec *= 2;
+    constexpr int PIECE = BF16 ? 8 : 4;                          // elements of the widest load
+    const size_t at = reinterpret_cast<uintptr_t>(w) / (16 / PIECE);
+    while (vec < 8 && 32 * vec < E && E % (2 * vec) == 0 && at % (2 * vec < PIECE ? 2 * vec : PIECE) == 0) vec *= 2;
 #define MOE_RD(V) \
     case V: route_direct_launch_vec<BF16, V>(x, w, bias, T, d, E, top_k, renormalize, idx, prob, logits_opt, st); break
     switch (vec) {

@@ -75,6 +75,27 @@ def test_sru_nearly_closed_gate(L, bias):
     assert (np.abs(lg / want - 1) <= 2.0 ** -8 + abs(bias) * 2.0 ** -23).all()
 
 
+@pytest.mark.parametrize("n_out,shift", [(64, 1), (104, 1), (104, 2), (512, 1), (512, 4), (1024, 3)])
+def test_sru_head_at_any_address(n_out, shift):
+    """A plain head matrix that starts in the middle of a 16-byte piece: columns are loaded as far as it is aligned."""
+    import paper_2605_11537_amd as moe
+    B, L, n_in, n_h = 2, 33, 64, 128
+    s = synth.sru_inputs(B, L, n_in, n_h, 1, n_out, synth.BF16, 61 + n_out, bias_std=0.2)
+    head = to_dev(s["w_head"])
+    moved = torch.zeros(head.numel() + shift, dtype=head.dtype, device="cuda")[shift:].view(n_h, n_out)
+    moved.copy_(head)
+    assert moved.data_ptr() % 16 == 2 * shift and moved.is_contiguous()
+    lg = []
+    for w_head in (head, moved):
+        w = moe.SruWeights([to_dev(a) for a in s["w_cat"]], [to_dev(a) for a in s["b_f"]], [to_dev(a) for a in s["b_r"]], w_head,
+                           to_dev(s["b_head"]))
+        pred, logits = moe.sru_predict(to_dev(s["emb"]), w, want_logits=True)
+        lg.append(to_host(logits).astype(np.float64))
+        assert (to_host(pred) == lg[-1].argmax(axis=1)).all()
+    # the same products of bf16 values, summed in binary32 in another order
+    assert np.abs(lg[0] - lg[1]).max() <= (n_h + 2) * 2.0 ** -22 * np.abs(lg[0]).max()
+
+
 @pytest.mark.parametrize("B,L,n_in,n_h,layers", [
     (2, 7, 128, 128, 2),               # row-major states
     (3, 8, 128, 256, 1),               # the first layer writes the images itself; one part-filled block
