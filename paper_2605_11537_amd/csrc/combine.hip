@@ -1,15 +1,15 @@
 // moe_combine: scale expert outputs by the gate probability and scatter them back to token
 // order; tokens over capacity are copied through bit for bit.  HBM-bound: every 16-byte
 // piece of x, y_perm and out is touched once.
-#include "common.h"
+#include "row_groups.h"
 
 namespace moe {
 
-constexpr int CMB_THREADS = 256;
+constexpr int CMB_THREADS = ROW_THREADS;
 
 typedef unsigned cmb_u32x4_t __attribute__((ext_vector_type(4)));
 constexpr int CMB_LANES = 32;                            // lanes per token row
-constexpr int CMB_WG_ROWS = CMB_THREADS / CMB_LANES;
+constexpr int CMB_LG_LANES = 5;
 constexpr int CMB_PIECES = 3;                            // 16-byte pieces per lane and trip
 
 // 32 lanes per row: the row index is a shift (a 64-bit division per piece was as long as the piece's other work), inv and
@@ -26,8 +26,9 @@ __global__ __launch_bounds__(CMB_THREADS) void combine_kernel(const cmb_u32x4_t 
                                                               const float *__restrict__ prob, int T, int vec_per_row,
                                                               cmb_u32x4_t *__restrict__ out)
 {
-    const int s = blockIdx.x * CMB_WG_ROWS + threadIdx.x / CMB_LANES, lane = threadIdx.x % CMB_LANES;
-    if (s >= T) return;
+    const unsigned wg = blockIdx.y * gridDim.x + blockIdx.x, s = wg * (CMB_THREADS / CMB_LANES) + threadIdx.x / CMB_LANES;
+    const int lane = threadIdx.x % CMB_LANES;
+    if (s >= (unsigned)T) return;
     const int pos = inv[s];
     const float p = prob[s];
     const cmb_u32x4_t *xr = x + (size_t)s * vec_per_row;
@@ -74,8 +75,9 @@ __global__ __launch_bounds__(CMB_THREADS) void combine_topk_kernel(const cmb_u32
                                                                    int vec_per_row, cmb_u32x4_t *__restrict__ out)
 {
     constexpr int V = BF16 ? 8 : 4;                      // values per piece
-    const int s = blockIdx.x * (CMB_THREADS / CMB_LANES) + threadIdx.x / CMB_LANES, lane = threadIdx.x % CMB_LANES;
-    if (s >= T) return;
+    const unsigned wg = blockIdx.y * gridDim.x + blockIdx.x, s = wg * (CMB_THREADS / CMB_LANES) + threadIdx.x / CMB_LANES;
+    const int lane = threadIdx.x % CMB_LANES;
+    if (s >= (unsigned)T) return;
     int pos[MOE_MAX_TOPK];
     float p[MOE_MAX_TOPK];
     bool any = false;
@@ -149,14 +151,14 @@ extern "C" int moe_combine(const void *y_perm, const void *x, const int32_t *inv
     MOE_REQUIRE(aligned16(y_perm) && aligned16(x) && aligned16(out), MOE_ERR_INVALID_ARG,
                 "moe_combine: tensor misaligned");
     int vec_per_row = (int)((size_t)d * esz / 16);
-    const int grid = ceil_div(T, CMB_WG_ROWS);
+    const dim3 grid = rows_grid(T, CMB_LG_LANES);
     hipStream_t st = (hipStream_t)stream;
     const bool big = (size_t)T * vec_per_row * 16 >= CMB_STREAM_BYTES;
 #define MOE_CMB(B, R) (big ? combine_kernel<B, R, true> : combine_kernel<B, R, false>)
     auto kern = dtype == MOE_BF16 ? (residual ? MOE_CMB(true, true) : MOE_CMB(true, false))
                                   : (residual ? MOE_CMB(false, true) : MOE_CMB(false, false));
 #undef MOE_CMB
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(CMB_THREADS), 0, st, (const cmb_u32x4_t *)y_perm, (const cmb_u32x4_t *)x,
+    hipLaunchKernelGGL(kern, grid, dim3(CMB_THREADS), 0, st, (const cmb_u32x4_t *)y_perm, (const cmb_u32x4_t *)x,
                        inv, expert_prob, T, vec_per_row, (cmb_u32x4_t *)out);
     MOE_CHECK_LAUNCH("moe_combine");
     return MOE_OK;
@@ -179,11 +181,11 @@ extern "C" int moe_combine_topk(const void *y_perm, const void *x, const int32_t
     MOE_REQUIRE(aligned16(y_perm) && aligned16(x) && aligned16(out), MOE_ERR_INVALID_ARG,
                 "moe_combine_topk: tensor misaligned");
     int vec_per_row = (int)((size_t)d * esz / 16);
-    const int grid = ceil_div(T, CMB_THREADS / CMB_LANES);
+    const dim3 grid = rows_grid(T, CMB_LG_LANES);
     hipStream_t st = (hipStream_t)stream;
     auto kern = dtype == MOE_BF16 ? (residual ? combine_topk_kernel<true, true> : combine_topk_kernel<true, false>)
                                   : (residual ? combine_topk_kernel<false, true> : combine_topk_kernel<false, false>);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(CMB_THREADS), 0, st, (const cmb_u32x4_t *)y_perm, (const cmb_u32x4_t *)x, inv,
+    hipLaunchKernelGGL(kern, grid, dim3(CMB_THREADS), 0, st, (const cmb_u32x4_t *)y_perm, (const cmb_u32x4_t *)x, inv,
                        expert_weight, T, k, vec_per_row, (cmb_u32x4_t *)out);
     MOE_CHECK_LAUNCH("moe_combine_topk");
     return MOE_OK;

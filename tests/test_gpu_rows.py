@@ -57,3 +57,20 @@ def test_rows_topk(T, d, dtype, k, residual):
     assert torch.equal(out[none], x[none])
     ulp = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -23
     assert ((out.double() - acc).abs() <= ulp * acc.abs() + (k + 1) * 2.0 ** -23 * mag)[~none].all()
+
+
+def test_rows_past_one_grid_dimension():
+    """More rows than 2^32 threads hold at 32 per row: short rows, some dropped."""
+    import paper_2605_11537_amd as moe
+    T, d, n_y = (1 << 27) + 5, 8, 1000
+    x = torch.arange(T, device="cuda", dtype=torch.int32).remainder_(251).to(torch.bfloat16)[:, None].expand(T, d).contiguous()
+    y = torch.arange(n_y * d, device="cuda", dtype=torch.float32).remainder_(127).to(torch.bfloat16).view(n_y, d)
+    inv = torch.arange(T, device="cuda", dtype=torch.int32).remainder_(n_y + 1).sub_(1)
+    one = torch.ones(T, device="cuda")
+    ref = torch.cat([torch.zeros(1, d, dtype=torch.bfloat16, device="cuda"), y])
+    for k, out in ((1, moe.moe_combine(y, x, inv, one)),
+                   (2, moe.moe_combine_topk(y, x, torch.stack([inv, torch.full_like(inv, -1)]), torch.stack([one, one])))):
+        for lo in (0, T // 2, T - 100000):
+            i = inv[lo:lo + 100000].long()
+            want = torch.where((i < 0)[:, None], x[lo:lo + 100000], ref[i + 1])
+            assert torch.equal(out[lo:lo + 100000], want), (k, lo)

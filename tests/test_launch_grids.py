@@ -114,3 +114,27 @@ def test_sru_forms(tmp_path_factory):
     for B, L, K, n_h in [(16, 1024, 768, 256), (2, 513, 768, 128), (2, 513, 512, 128), (1, 1024, 1792, 256), (1, 1024, 1856, 256)]:
         (_, packs), = ask([(B, L, K, n_h, 0)])
         assert packs == (2 * B * (-(-L // 32) * 32) * (K + n_h) <= 16 * B * L * n_h)
+
+
+ROWS = """
+#include "row_groups.h"
+#include <stdio.h>
+int main()
+{
+    int a[2];
+    while (scanf("%d %d", a, a + 1) == 2) {
+        const dim3 g = moe::rows_grid(a[0], a[1]);
+        printf("%u %u\\n", g.x, g.y);
+    }
+}
+"""
+
+
+def test_rows_grid(tmp_path_factory):
+    """The grid of the combine kernels stays within the limit per dimension and reaches the last row."""
+    ask = _compiled(tmp_path_factory, "rows_grid", ROWS)
+    asked = [[T, lg] for T in (1, 7, 64, 65536, 2 ** 22 + 1, 2 ** 27 - 1, 2 ** 27 + 5, 2 ** 31 - 1) for lg in (0, 3, 5, 8)]
+    for (T, lg), (gx, gy) in zip(asked, ask(asked)):
+        threads = gx * gy * 256
+        assert gx * 256 < 2 ** 32 and gy < 2 ** 16 and gx * gy * (256 >> lg) < 2 ** 32
+        assert T << lg <= threads < (T << lg) + (gx + 1) * 256 + 256
