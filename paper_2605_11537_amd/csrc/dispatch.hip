@@ -265,7 +265,8 @@ __global__ __launch_bounds__(DSP_THREADS) void dispatch_permute_kernel(
 // x_perm[pos] = x[perm[pos]] for pos < K (K is not read: the permutation ends in -1 entries).  32 lanes per row, 8 rows per workgroup, 16-byte
 // pieces: the scattered row reads and the contiguous writes are both whole lines, the row
 // index is read once per row, and a lane's three loads of a trip are independent.
-// STREAM: an output far beyond what the L2s hold is written past them.  Measured, 65536 x 768 bf16: 47 -> 37 us (30 us alone, 6.7 TB/s) on top of
+// STREAM: an output far beyond what the L2s hold is written past them (combine.hip: where the line lies, and what it costs a reader
+// that follows at once).  Measured, 65536 x 768 bf16: 47 -> 37 us (30 us alone, 6.7 TB/s) on top of
 // the tables; 16384 tokens 16 -> 8.6 us (a trip of four pieces that rows of 96 never fill took the leftover path before).
 constexpr int GATHER_ROWS = DSP_THREADS / 32;
 constexpr size_t GATHER_STREAM_BYTES = (size_t)64 << 20;

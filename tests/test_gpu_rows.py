@@ -20,6 +20,8 @@ def _case(T, d, dtype, k, seed):
 @pytest.mark.parametrize("residual", [0, 1])
 @pytest.mark.parametrize("T,d,dtype", [
     (1, 8, torch.bfloat16), (17, 768, torch.bfloat16), (33, 776, torch.bfloat16), (100, 248, torch.float32),
+    (1000, 8, torch.bfloat16), (333, 24, torch.bfloat16), (2500, 72, torch.bfloat16), (130, 132, torch.float32),   # 1, 3, 9, 33 pieces
+    (2049, 264, torch.bfloat16), (2049, 4096, torch.bfloat16), (7, 8200, torch.bfloat16),    # more rows: 32 lanes; 256 lanes
     (43688, 768, torch.bfloat16), (43691, 768, torch.bfloat16),      # 64 MiB are 43690.7 such rows
 ])
 def test_rows(T, d, dtype, residual):
@@ -43,7 +45,10 @@ def test_rows(T, d, dtype, residual):
 
 
 @pytest.mark.parametrize("residual", [0, 1])
-@pytest.mark.parametrize("T,d,dtype,k", [(17, 776, torch.bfloat16, 3), (9, 8, torch.bfloat16, 8), (50, 392, torch.float32, 2)])
+@pytest.mark.parametrize("T,d,dtype,k", [
+    (17, 776, torch.bfloat16, 3), (9, 8, torch.bfloat16, 8), (50, 392, torch.float32, 2), (777, 40, torch.bfloat16, 2),
+    (2049, 264, torch.bfloat16, 2), (4097, 264, torch.bfloat16, 3), (3, 4104, torch.bfloat16, 2),
+])
 def test_rows_topk(T, d, dtype, k, residual):
     import paper_2605_11537_amd as moe
     x, y, inv, p = _case(T, d, dtype, k, T * k)

@@ -138,3 +138,35 @@ def test_rows_grid(tmp_path_factory):
         threads = gx * gy * 256
         assert gx * 256 < 2 ** 32 and gy < 2 ** 16 and gx * gy * (256 >> lg) < 2 ** 32
         assert T << lg <= threads < (T << lg) + (gx + 1) * 256 + 256
+
+
+LANES = """
+#include "row_groups.h"
+#include <stdio.h>
+int main()
+{
+    int a[3];
+    while (scanf("%d %d %d", a, a + 1, a + 2) == 3) {
+        const int lg = a[2] ? moe::combine_topk_lanes(a[0], a[1]) : moe::combine_lanes(a[0], a[1]);
+        const dim3 g = moe::rows_grid(a[0], lg < 0 ? 5 : lg);
+        printf("%d %u %u\\n", lg, g.x, g.y);
+    }
+}
+"""
+
+
+def test_row_groups(tmp_path_factory):
+    """Lanes per row of the combine kernels: none idle on short rows, and a grid within the limit that reaches the last row."""
+    ask = _compiled(tmp_path_factory, "lanes", LANES)
+    asked = [[T, vec, topk] for T in (1, 7, 64, 2048, 2049, 4097, 65536, 2 ** 22 + 1, 2 ** 27 + 5, 2 ** 31 - 1)
+             for vec in (1, 2, 3, 8, 9, 31, 32, 33, 96, 97, 255, 256, 512, 1025) for topk in (0, 1)]
+    for (T, vec, topk), (lg, gx, gy) in zip(asked, ask(asked)):
+        if T * vec * 16 > 2 ** 39:                       # past any card
+            continue
+        lanes = 1 << (5 if lg < 0 else lg)
+        if vec <= 32:
+            assert lg >= 0 and vec <= lanes < 2 * vec, (T, vec, lg)
+        assert lanes <= 1024 and (lanes <= 256 or T <= 2048 or vec >= 256)
+        assert gx * 256 < 2 ** 32 and gy < 2 ** 16
+        threads = gx * gy * 256
+        assert T * lanes <= threads < T * lanes + (gx + 1) * 256 + 256 and gx * gy * max(1, 256 // lanes) < 2 ** 32
