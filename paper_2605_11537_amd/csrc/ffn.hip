@@ -390,6 +390,7 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
         size_t gi = align_up((size_t)ceil_div(grid_items, FFN_GROUP), 8) * FFN_GROUP;
         int g1 = (int)(gi * (F / FFN_BN));
         int g2 = (int)(gi * (d / FFN_BN));
+        const bool by_slots = schedule == MOE_SCHEDULE_SLOTS;
         if (dense) {
             hipLaunchKernelGGL(ffn_dense_bf16_kernel<true>, dim3(n_cu), dim3(GEMM_THREADS), 0, st,
                                (const bf16_t *)x_perm, row_index, n_x_rows, (const bf16_t *)w1, d, F, dtiles,
@@ -399,9 +400,10 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
         if (dense) {
             // the dense kernel took every row
         } else if (listless && ffn_few_rows(max_rows, max_slots, d, F))
-            hipLaunchKernelGGL(ffn_few_rows_bf16_kernel<true>, dim3(few_rows_grid(max_rows, max_slots, schedule, F)),
-                               dim3(SHARE_THREADS), 0, st, (const bf16_t *)x_perm, (const bf16_t *)w1, row_index, n_x_rows, d, F,
-                               E, slot_offset, slot_expert, n_slots, max_slots, schedule, max_rows, (bf16_t *)h);
+            hipLaunchKernelGGL((by_slots ? ffn_few_rows_bf16_kernel<true, false> : ffn_few_rows_bf16_kernel<true, true>),
+                               dim3(few_rows_grid(max_rows, max_slots, schedule, F)), dim3(SHARE_THREADS), 0, st,
+                               (const bf16_t *)x_perm, (const bf16_t *)w1, row_index, n_x_rows, d, F, E, slot_offset, slot_expert,
+                               n_slots, max_slots, max_rows, (bf16_t *)h);
         else if (tall)
             hipLaunchKernelGGL((ffn_gemm_bf16_kernel<true, true>), dim3(g1), dim3(GEMM_THREADS), 0, st,
                                (const bf16_t *)x_perm, row_index, n_x_rows, (const bf16_t *)w1, d, F, E, list,
@@ -422,10 +424,10 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
         }
         if (dense) {
         } else if (listless && ffn_few_rows(max_rows, max_slots, F, d))
-            hipLaunchKernelGGL(ffn_few_rows_bf16_kernel<false>, dim3(few_rows_grid(max_rows, max_slots, schedule, d)),
-                               dim3(SHARE_THREADS), 0, st, (const bf16_t *)h, (const bf16_t *)w2, (const int32_t *)nullptr,
-                               max_rows, F, d, E, slot_offset, slot_expert, n_slots, max_slots, schedule, max_rows,
-                               (bf16_t *)y_perm);
+            hipLaunchKernelGGL((by_slots ? ffn_few_rows_bf16_kernel<false, false> : ffn_few_rows_bf16_kernel<false, true>),
+                               dim3(few_rows_grid(max_rows, max_slots, schedule, d)), dim3(SHARE_THREADS), 0, st, (const bf16_t *)h,
+                               (const bf16_t *)w2, (const int32_t *)nullptr, max_rows, F, d, E, slot_offset, slot_expert, n_slots,
+                               max_slots, max_rows, (bf16_t *)y_perm);
         else if (tall)
             hipLaunchKernelGGL((ffn_gemm_bf16_kernel<false, true>), dim3(g2), dim3(GEMM_THREADS), 0, st,
                                (const bf16_t *)h, (const int32_t *)nullptr, max_rows, (const bf16_t *)w2, F, d, E,

@@ -51,3 +51,10 @@ def check_ids_margin(got, ref_idx, ref_idx2, ref_margin, tau, what=""):
         f"{what}: {int((diff & clear).sum())} ids differ where the top-2 gap exceeds {tau:g}"
     assert (got[diff] == ref_idx2[diff]).all(), f"{what}: a near-tie resolved to a third id"
     return int(diff.sum())
+
+
+def few_rows(max_rows, max_slots, K, N):
+    """Whether a bf16 expert product of depth K and N columns runs on the kernel for few rows (the library's rule)."""
+    if max_rows > 64 * max_slots or max_slots > 1024:
+        return False
+    return 2 * max_rows <= max_slots or (K >= 1024 and min(max_rows, max_slots) * (N // 128) <= 128 and max_rows <= 32 * max_slots)

@@ -7,6 +7,8 @@ import subprocess
 import numpy as np
 import pytest
 
+from gpu_util import few_rows
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SLOTS, EXPERTS = 0, 1
 
@@ -170,3 +172,27 @@ def test_row_groups(tmp_path_factory):
         assert gx * 256 < 2 ** 32 and gy < 2 ** 16
         threads = gx * gy * 256
         assert T * lanes <= threads < T * lanes + (gx + 1) * 256 + 256 and gx * gy * max(1, 256 // lanes) < 2 ** 32
+
+
+FEW = """
+#include "ffn_few_rows.h"
+#include <stdio.h>
+int main()
+{
+    int a[5];
+    while (scanf("%d %d %d %d %d", a, a + 1, a + 2, a + 3, a + 4) == 5)
+        printf("%d %d\\n", moe::ffn_few_rows(a[0], a[1], a[2], a[3]), moe::few_rows_grid(a[0], a[1], a[4], a[3]));
+}
+"""
+
+
+def test_few_rows(tmp_path_factory):
+    """Which products the kernel for few rows takes, and how many workgroups look for work: never more than are resident, nor, with one
+    unit per expert that has rows, more than that many experts have column tiles."""
+    ask = _compiled(tmp_path_factory, "few", FEW)
+    asked = [[rows, slots, K, N, schedule] for rows in (1, 8, 37, 72, 73, 144, 500, 2048, 32768) for slots in (1, 8, 36, 144, 288, 1024)
+             for K in (128, 768, 1024, 3072) for N in (128, 256, 3072) for schedule in (SLOTS, EXPERTS) if rows <= 64 * slots]
+    for (rows, slots, K, N, schedule), (takes, grid) in zip(asked, ask(asked)):
+        assert takes == few_rows(rows, slots, K, N)
+        units = (min(rows, slots) + (rows // 32 if schedule == SLOTS else 0)) * (N // 32)
+        assert grid == min(-(-units // 8) * 8, 256 * (3 if schedule == SLOTS else 2))
