@@ -440,18 +440,22 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
                                (bf16_t *)y_perm);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm2");
     } else {
-        // Tile height.  64 rows load a third less per multiply-add, 32 rows leave no CU with twice the tiles of another: few
-        // rows per expert make few tiles, and from 128 on average on there are enough of them (8 experts x 512 rows, 768 x 3072:
-        // 215, 279 us against 248, 318 with 32 rows; 40 slots of 10 .. 59 rows, 512 x 2048: 80, 114 against 66, 75).
-        const int bm = (long long)max_rows >= 128LL * E ? 64 : 32;
-        auto gemm1 = bm == 64 ? ffn_gemm_f32_kernel<true, 64> : ffn_gemm_f32_kernel<true, 32>;
-        auto gemm2 = bm == 64 ? ffn_gemm_f32_kernel<false, 64> : ffn_gemm_f32_kernel<false, 32>;
-        hipLaunchKernelGGL(gemm1, dim3(share_grid(bm, F32_BN, max_rows, max_slots, schedule, F)), dim3(F32_THREADS), 0, st,
+        // tile height of a product of depth K (0: 32 rows and a short k); the results are the same
+        auto height = [&](int K) { return f32_depth(K) == 1 ? 0 : f32_rows(max_rows, E); };
+        const int bm1 = height(d), bm2 = height(F);
+#define MOE_F32(RELU, BM, K)                                                                                        \
+    (BM == 0          ? ffn_gemm_f32_kernel<RELU, 32, 1, true>                                                      \
+     : f32_several(K) ? (BM == 64 ? ffn_gemm_f32_kernel<RELU, 64, 4, true> : ffn_gemm_f32_kernel<RELU, 32, 4, true>) \
+                      : (BM == 64 ? ffn_gemm_f32_kernel<RELU, 64, 4, false> : ffn_gemm_f32_kernel<RELU, 32, 4, false>))
+        auto gemm1 = MOE_F32(true, bm1, d);
+        auto gemm2 = MOE_F32(false, bm2, F);
+#undef MOE_F32
+        hipLaunchKernelGGL(gemm1, dim3(f32_grid(bm1, max_rows, max_slots, schedule, d, F)), dim3(F32_THREADS), 0, st,
                            (const float *)x_perm, (const float *)w1, row_index, n_x_rows, d, F, E, slot_offset, slot_expert,
                            n_slots, max_slots, schedule, max_rows, (float *)h);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm1");
         if (ev[1]) (void)hipEventRecord(ev[1], st);
-        hipLaunchKernelGGL(gemm2, dim3(share_grid(bm, F32_BN, max_rows, max_slots, schedule, d)), dim3(F32_THREADS), 0, st,
+        hipLaunchKernelGGL(gemm2, dim3(f32_grid(bm2, max_rows, max_slots, schedule, F, d)), dim3(F32_THREADS), 0, st,
                            (const float *)h, (const float *)w2, (const int32_t *)nullptr, max_rows, F, d, E, slot_offset,
                            slot_expert, n_slots, max_slots, schedule, max_rows, (float *)y_perm);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm2");

@@ -39,7 +39,9 @@ struct TileShare {
         if (p > 0 && slot_expert[p - 1] == e) return 0;
         int last = p;
         while (last + 1 < P && slot_expert[last + 1] == e) ++last;
-        const int end = slot_offset[last + 1], n = (end < max_rows ? end : max_rows) - slot_offset[p];
+        const int r0 = slot_offset[p], left = max_rows - r0;
+        int n = slot_offset[last + 1] - r0;
+        if (n > left) n = left;
         return n > 0 ? n : 0;
     }
     // the experts schedule makes one tile of all rows (they queue), the slot schedule tiles of BM rows

@@ -1,5 +1,6 @@
-"""The binary32 expert products: slots around the 16-row blocks and the 64-row tiles, one to many steps of k, more
-slots than a workgroup has threads, both schedules, with and without the gather."""
+"""The binary32 expert products: slots around the 16-row blocks and the tiles of 32 and 64 rows, every number of blocks in the last
+tile, one to many steps of k, units dealt one by one and several to a workgroup, more slots than a workgroup has threads, both
+schedules, with and without the gather."""
 import numpy as np
 import pytest
 import torch
@@ -12,18 +13,24 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("schedule", [0, 1])
-@pytest.mark.parametrize("d,F,E,rows,gather", [
-    (64, 64, 3, [1, 0, 16, 17], False),                              # one step of k per wavefront
-    (64, 320, 4, [15, 48, 49, 64, 65, 31, 33, 0, 130], True),        # every block count; a second and third tile
-    (448, 192, 2, [200, 3], True),                                   # an odd number of steps
-    (64, 128, 40, [(7 * i) % 23 for i in range(600)], False),        # three slots per thread
-    (128, 64, 3, [130, 64, 65, 0, 47, 16, 200], True),               # over 128 rows per expert: tiles of 64 rows
+@pytest.mark.parametrize("d,F,E,rows,se,gather", [
+    (64, 64, 3, [1, 0, 16, 17], None, False),                              # one step of k per wavefront
+    (64, 320, 4, [15, 48, 49, 64, 65, 31, 33, 0, 130], None, True),        # tiles of 32 rows: one and two blocks; five steps
+    (448, 192, 2, [200, 3], None, True),                                   # seven steps, three steps
+    (64, 128, 40, [(7 * i) % 23 for i in range(600)], None, False),        # three slots per thread
+    (64, 512, 40, [(7 * i) % 23 for i in range(600)], None, False),        # more units than workgroups of a short k
+    # 128 rows per expert and more: tiles of 64 rows, whose last ones have 2, 3, 4 and 1 blocks; one slot or several per expert
+    (320, 448, 3, [96, 112, 250], [0, 1, 2], True),
+    (256, 320, 4, [50, 46, 0, 112, 100, 150, 129], [0, 0, 0, 1, 2, 2, 3], True),    # k = 256: several units per workgroup allowed
+    (256, 3072, 8, [190] * 8, list(range(8)), False),                      # and more than there are workgroups
+    (256, 64, 5, [20, 40, 33, 64, 1], None, True),                         # k = 256 with tiles of 32 rows
 ])
-def test_ffn_f32_tiles(d, F, E, rows, gather, schedule):
+def test_ffn_f32_tiles(d, F, E, rows, se, gather, schedule):
     import paper_2605_11537_amd as moe
     rng = np.random.default_rng(d + F)
     so = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
-    se = np.sort(rng.integers(0, E, len(rows))).astype(np.int32)     # slots of one expert are neighbours
+    # slots of one expert are neighbours
+    se = np.array(se, np.int32) if se else np.sort(rng.integers(0, E, len(rows))).astype(np.int32)
     n, T = int(so[-1]), int(so[-1]) + 5
     x = synth.normal_tensor((T, d), 1.0, [1, d, F], synth.F32)
     w1 = synth.normal_tensor((E, d, F), 0.1, [2, d, F], synth.F32)

@@ -196,3 +196,26 @@ def test_few_rows(tmp_path_factory):
         assert takes == few_rows(rows, slots, K, N)
         units = (min(rows, slots) + (rows // 32 if schedule == SLOTS else 0)) * (N // 32)
         assert grid == min(-(-units // 8) * 8, 256 * (3 if schedule == SLOTS else 2))
+
+
+F32 = """
+#include "ffn_f32.h"
+#include <stdio.h>
+int main()
+{
+    int a[7];
+    while (scanf("%d %d %d %d %d %d %d", a, a + 1, a + 2, a + 3, a + 4, a + 5, a + 6) == 7)
+        printf("%d %d %d\\n", moe::f32_depth(a[4]), moe::f32_rows(a[1], a[6]), moe::f32_grid(a[0], a[1], a[2], a[3], a[4], a[5]));
+}
+"""
+
+
+def test_f32_grid(share_grid, tmp_path_factory):
+    """binary32 products: a workgroup per unit from k = 320 on, at most a few per compute unit below."""
+    ask = _compiled(tmp_path_factory, "f32", F32)
+    asked = [[bm, rows, slots, schedule, K, N, E] for bm in (0, 32, 64) for rows in (1, 100, 16384) for slots in (1, 40, 600)
+             for schedule in (SLOTS, EXPERTS) for K in (64, 192, 256, 320, 2048) for N in (64, 2048) for E in (8, 128)]
+    each = share_grid([[a[0] or 32, 64, a[1], a[2], a[3], a[5]] for a in asked])
+    for (bm, rows, slots, schedule, K, N, E), (all_,), (depth, height, grid) in zip(asked, each, ask(asked)):
+        assert depth == (1 if K < 256 else 4) and height == (64 if rows >= 128 * E else 32)
+        assert grid == (all_ if K > 256 else min(all_, 256 * {0: 4, 32: 6, 64: 4}[bm])) and grid % 8 == 0
