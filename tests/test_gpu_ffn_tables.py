@@ -1,5 +1,6 @@
-"""The expert products on slot tables that do not match the batch: rows past max_rows, which the kernels leave alone.  Every row
-before it is computed."""
+"""The expert products on slot tables and row numbers that are not what they should be, on every kernel that takes them: rows past
+max_rows, entries past n_slots, ids that are no expert's, row numbers out of range.  Those rows are left alone (or, for the last, get
+some value), everything else is computed."""
 import numpy as np
 import pytest
 import torch
@@ -38,3 +39,75 @@ def test_rows_past_the_batch(dtype, max_rows, rows, schedule):
         assert np.abs(got - ref).max() <= 1e-4 * np.abs(ref).max()
     else:                                       # half an ulp of the stored y, and of every stored h carried through W2
         assert (np.abs(got - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-3 * np.abs(ref).max()).all()
+
+
+# rows per slot and the shape that takes each kernel: binary32 (both tile heights, short and long k), bf16 for few rows, 128 columns, 256 x 256
+KERNELS = [
+    pytest.param(synth.F32, 64, 320, 1, 0, id="f32-short"),
+    pytest.param(synth.F32, 320, 448, 12, 0, id="f32-64rows"),
+    pytest.param(synth.BF16, 128, 256, 1, 200, id="few-rows"),
+    pytest.param(synth.BF16, 128, 256, 4, 0, id="128-columns"),
+    pytest.param(synth.BF16, 256, 512, 100, 0, id="256x256"),
+]
+
+
+def _run(dtype, d, F, E, rows, se, used, schedule, index=None, n_src=None):
+    """-> (y, oracle's y for the rows of each slot under its own id) with y preset to 7."""
+    import paper_2605_11537_amd as moe
+    so = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    T = int(so[-1])
+    x = synth.normal_tensor((n_src or T, d), 1.0, [94, d, T], dtype)
+    w1 = synth.normal_tensor((E, d, F), 0.05, [95, d, F], dtype)
+    w2 = synth.normal_tensor((E, F, d), 0.05, [96, d, F], dtype)
+    good = (se >= 0) & (se < E)
+    src = x if index is None else np.ascontiguousarray(x[np.clip(index, 0, len(x) - 1)])
+    ref = f64(oracle.ffn(src, w1, w2, so, np.where(good, se, 0).astype(np.int32), len(rows)))
+    pack = (lambda w: w) if dtype == synth.F32 else moe.moe_pack_weights
+    t = torch.float32 if dtype == synth.F32 else torch.bfloat16
+    y = torch.full((T, d), 7.0, dtype=t, device="cuda")
+    n_slots = torch.tensor([used], dtype=torch.int32, device="cuda")
+    if index is None:
+        moe.moe_expert_ffn(to_dev(x), pack(to_dev(w1)), pack(to_dev(w2)), to_dev(so), to_dev(se), n_slots, E, F,
+                           schedule=schedule, out=y)
+    else:
+        moe.moe_expert_ffn_rows(to_dev(x), to_dev(index), T, pack(to_dev(w1)), pack(to_dev(w2)), to_dev(so), to_dev(se), n_slots,
+                                E, F, schedule=schedule, out=y)
+    return f64(to_host(y)), ref, np.repeat(np.arange(len(rows)), rows)
+
+
+def _close(got, ref, dtype):
+    if dtype == synth.F32:                      # d and F roundings of binary32 sums, far inside
+        return np.abs(got - ref).max() <= 1e-4 * np.abs(ref).max()
+    return (np.abs(got - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-3 * np.abs(ref).max()).all()
+
+
+@pytest.mark.parametrize("schedule", [0, 1])
+@pytest.mark.parametrize("dtype,d,F,scale,empty", KERNELS)
+def test_slots_that_are_none(dtype, d, F, scale, empty, schedule):
+    E = 6
+    rows = [5, 3, 4, 0, 33, 6, 2, 9, 4]
+    se = [0, E, 0, 2, 2, -1, 4, 4, 5]           # ids that are no expert's, one between two slots of an expert
+    used = 7                                    # the second slot of expert 4 and expert 5's are not slots
+    rows, se = [r * scale for r in rows] + [0] * empty, np.array(se + [5] * empty, np.int32)
+    got, ref, slot = _run(dtype, d, F, E, rows, se, used, schedule)
+    on = (slot < used) & (se[slot] >= 0) & (se[slot] < E)
+    assert (got[~on] == 7.0).all()
+    assert _close(got[on], ref[on], dtype)
+
+
+@pytest.mark.parametrize("schedule", [0, 1])
+@pytest.mark.parametrize("dtype,d,F,scale,empty", KERNELS)
+def test_row_numbers_out_of_range(dtype, d, F, scale, empty, schedule):
+    E = 4
+    rows = [r * scale for r in (7, 40, 1, 18)] + [0] * empty
+    se = np.array([0, 1, 2, 3] + [3] * empty, np.int32)
+    T = sum(rows)
+    n_src = T // 2 + 1
+    rng = np.random.default_rng(T)
+    index = rng.integers(0, n_src, T).astype(np.int32)
+    bad = rng.random(T) < 0.2
+    bad[0] = bad[-1] = True
+    index[bad] = rng.choice([-1, -2 ** 31, n_src, 2 ** 31 - 1], bad.sum())
+    got, ref, _ = _run(dtype, d, F, E, rows, se, len(rows), schedule, index, n_src)
+    assert np.isfinite(got).all()
+    assert _close(got[~bad], ref[~bad], dtype)

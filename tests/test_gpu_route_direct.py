@@ -72,4 +72,13 @@ def test_route_direct_specials(dtype):
     rows = [r for r in range(T) if r != 7]
     assert not torch.isnan(lg[rows]).any() and (lg[rows][:, 2] == float("-inf")).all()
     assert (idx.cpu()[rows] != 2).all() and (prob.cpu()[rows] > 0).all()
-    print("subnormal times 2^20:", float(lg[9, 11]), "exact", 2.0 ** -110, flush=True)
+    # subnormal operands count (2^-130 times 2^20), and stay where they are: the matrix row they meet is zero elsewhere
+    assert lg[9, 11] == 2.0 ** -110
+    others = [c for c in range(E) if c not in (2, 11)]
+    assert (lg[9][others] == 0).all()
+    # the other rows: sums of d products in binary32, in any order
+    plain = [r for r in range(T) if r not in (7, 9)]
+    cols = [c for c in range(E) if c != 2]
+    xs, ws = x.to(t).double()[plain], w.to(t).double()[:, cols]
+    bound = (d + 2) * 2.0 ** -24 * (xs.abs() @ ws.abs())
+    assert ((lg[plain][:, cols].double() - xs @ ws).abs() <= bound).all()
