@@ -2,16 +2,17 @@
 // moe_pack_weights: one-time re-layout of static expert weights for the matrix-core kernels.
 //
 //   worklist  one workgroup turns the device-side slot tables into a list of row tiles
-//             (expert, first row, end row); a slot of more than 64 rows gives several tiles,
+//             (expert, first row, end row); a slot of more than 128 rows gives several tiles,
 //             so the replicas of a hot expert and the tiles inside a replica all run side by
 //             side.  In the "experts" schedule there is one item per logical expert instead
-//             and the kernel walks its rows 64 at a time.
+//             and the kernel walks its rows 128 at a time.
 //   gemm1     h = relu(x_perm * W1[e])   per (row tile, 128-column tile)
 //   gemm2     y_perm = h * W2[e]
 // At large batch the list cuts every slot into pieces of 256 rows instead and both products run on
 // the persistent 256 x 256 tile kernel (gemm_dense_bf16.h); the 128-column kernel is then not launched.
 // At small batch with short slots the 128-column kernel reads the slot tables itself (no list kernel), and so
-// does the binary32 kernel (ffn_f32.h) at any batch.
+// do the binary32 kernel (ffn_f32.h) at any batch and the kernel for few rows (ffn_few_rows.h), which takes
+// either product of a small batch where most of the 128-column kernel's grid would have nothing to do.
 // Grids are sized for the worst case on the host (rows and slots are only known on the
 // device); workgroups beyond the list exit at once.  Workgroup ids are remapped so that the
 // column tiles of one row tile, which share the token rows, run on one XCD.
@@ -22,8 +23,8 @@
 
 namespace moe {
 
-constexpr int FFN_BM = 64;    // rows per tile (short tile of the bf16 path)
-constexpr int FFN_BM_TALL = 128;  // bf16 path: a slot is cut into tiles of up to 128 rows
+constexpr int FFN_BM_SHORT = 64;  // rows a tile with k chunks of FFN_BK holds
+constexpr int FFN_BM = 128;   // rows per tile: a slot is cut into tiles of up to 128 rows
 constexpr int FFN_BN = 128;   // columns per workgroup (bf16 path)
 constexpr int FFN_BK = 128;   // k chunk of the bf16 path, tiles of up to 64 rows
 constexpr int FFN_BK_TALL = 64;   // k chunk for tiles of 65..128 rows
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const bf16_t *__restr
 __global__ __launch_bounds__(1024) void ffn_worklist_kernel(const int32_t *__restrict__ slot_offset,
                                                             const int32_t *__restrict__ slot_expert,
                                                             const int32_t *__restrict__ n_slots_p, int max_slots,
-                                                            int max_items, int schedule, int tile_rows, int E,
+                                                            int max_items, int schedule, int E,
                                                             int dense, int max_dense, WorkItem *__restrict__ items,
                                                             DenseTile *__restrict__ dtiles,
                                                             int32_t *__restrict__ n_items)
@@ -83,14 +84,14 @@ __global__ __launch_bounds__(1024) void ffn_worklist_kernel(const int32_t *__res
                 const int n = r1 > r0 ? r1 - r0 : 0;
                 if (dense) nd = (n + DENSE_BM - 1) / DENSE_BM;
                 const int covered = nd * DENSE_BM < n ? nd * DENSE_BM : n;
-                cnt = (n - covered + tile_rows - 1) / tile_rows;
+                cnt = (n - covered + FFN_BM - 1) / FFN_BM;
                 reuse = cnt + nd > 1 || (p > 0 && slot_expert[p - 1] == e) || (p + 1 < P && slot_expert[p + 1] == e);
             } else if (p == 0 || slot_expert[p - 1] != e) {
                 int q = p + 1;
                 while (q < P && slot_expert[q] == e) ++q;
                 r1 = slot_offset[q];
                 cnt = r1 > r0 ? 1 : 0;
-                reuse = r1 - r0 > tile_rows;
+                reuse = r1 - r0 > FFN_BM;
             }
             if (e < 0 || e >= E) cnt = nd = 0;   // never index weights with a bad id
             // experts that own at least one tile (slots of an expert are adjacent)
@@ -116,8 +117,8 @@ __global__ __launch_bounds__(1024) void ffn_worklist_kernel(const int32_t *__res
                 it.expert = e;
                 it.reuse = reuse;
                 if (schedule == MOE_SCHEDULE_SLOTS) {
-                    it.row_begin = r0 + covered + i * tile_rows;
-                    it.row_end = it.row_begin + tile_rows < r1 ? it.row_begin + tile_rows : r1;
+                    it.row_begin = r0 + covered + i * FFN_BM;
+                    it.row_end = it.row_begin + FFN_BM < r1 ? it.row_begin + FFN_BM : r1;
                 } else {
                     it.row_begin = r0;
                     it.row_end = r1;
@@ -152,12 +153,11 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void ffn_dense_bf16_kernel(
 }
 
 // ------------------------------------------------------------------ bf16 grouped GEMM
-// Three tile heights.  Up to 32 and up to 64 rows: 1 or 2 row blocks per wavefront, k chunks of 128 -- the
-// weight-streaming shapes.  65..128 rows (TALL builds only): 4 row blocks per wavefront, k chunks of 64, so a weight
-// byte fetched from L2/HBM feeds twice the rows.  The build without the tall tile walks a work item
-// 64 rows at a time.  (Three or four workgroups per CU instead of two, tried with a k chunk of 64 to
+// Three tile heights, chosen per tile.  Up to 32 and up to 64 rows: 1 or 2 row blocks per wavefront, k chunks of 128 -- the
+// weight-streaming shapes.  65..128 rows: 4 row blocks per wavefront, k chunks of 64, so a weight
+// byte fetched from L2/HBM feeds twice the rows.  (Three or four workgroups per CU instead of two, tried with a k chunk of 64 to
 // fit the registers, changed the HBM-bound launches by under 1%: two it stays.)
-template <bool RELU, bool TALL>
+template <bool RELU>
 __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
     const bf16_t *__restrict__ A, const int32_t *__restrict__ row_index, int n_src_rows,
     const bf16_t *__restrict__ Wp, int K, int N, int E, const WorkItem *__restrict__ items,
@@ -165,10 +165,10 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
     const int32_t *__restrict__ slot_expert, const int32_t *__restrict__ n_slots_p, int max_slots, int schedule,
     int max_rows, bf16_t *__restrict__ C)
 {
-    constexpr int TM = TALL ? FFN_BM_TALL : FFN_BM;          // rows per pass over a work item
+    constexpr int TM = FFN_BM;                               // rows per pass over a work item
     constexpr int MBT = TM / 32;
     constexpr int LDC = FFN_BN + 8;
-    constexpr int S0 = gemm_lds_elems<2, FFN_BK>(), S1 = TALL ? gemm_lds_elems<4, FFN_BK_TALL>() : 0, S2 = TM * LDC;
+    constexpr int S0 = gemm_lds_elems<2, FFN_BK>(), S1 = gemm_lds_elems<4, FFN_BK_TALL>(), S2 = TM * LDC;
     __shared__ __attribute__((aligned(16))) bf16_t lds[(S0 > S1 ? S0 : S1) > S2 ? (S0 > S1 ? S0 : S1) : S2];
     const int n_nt = N / FFN_BN;
     int item, nt;
@@ -211,14 +211,16 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
         zero_acc<MBT, 1>(acc);
         // the fewest 32-row blocks that hold the rows: a block less is a matrix instruction, an LDS read and the
         // token loads of 32 rows less per step
-#define MOE_TILE(MB_, BK_, NT_)                                                                                            gemm_tile_bf16<MB_, 1, BK_, NT_>(a0, K, nrows, Bp, nt * FFN_BN, K, lds,                                                                                 reinterpret_cast<f32x16_t(&)[MB_][1]>(acc), ri, n_src_rows)
+#define MOE_TILE(MB_, BK_, NT_)                                                              \
+    gemm_tile_bf16<MB_, 1, BK_, NT_>(a0, K, nrows, Bp, nt * FFN_BN, K, lds,                  \
+                                     reinterpret_cast<f32x16_t(&)[MB_][1]>(acc), ri, n_src_rows)
         if (nrows <= 32) {
             if (it.reuse) MOE_TILE(1, FFN_BK, false);
             else MOE_TILE(1, FFN_BK, true);
-        } else if (!TALL || nrows <= FFN_BM) {
+        } else if (nrows <= FFN_BM_SHORT) {
             if (it.reuse) MOE_TILE(2, FFN_BK, false);
             else MOE_TILE(2, FFN_BK, true);
-        } else if constexpr (TALL) {
+        } else {
             if (it.reuse) MOE_TILE(4, FFN_BK_TALL, false);
             else MOE_TILE(4, FFN_BK_TALL, true);
         }
@@ -250,7 +252,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
     }
 }
 
-static inline int ffn_max_items(int max_rows, int max_slots) { return max_slots + max_rows / FFN_BM + 1; }
+static inline int ffn_max_items(int max_rows, int max_slots) { return max_slots + max_rows / FFN_BM_SHORT + 1; }
 // every dense tile but the last of a slot has 256 rows
 static inline int ffn_max_dense(int max_rows, int max_slots) { return max_rows / DENSE_BM + max_slots + 1; }
 
@@ -354,8 +356,6 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     // Without the dense kernel (small batches, short slots on average, shapes outside its tiling, the
     // experts schedule) the 128-column kernel cuts work items 128 rows high and picks the tile height per
     // item; with it, the 128-column kernel is not launched at all.
-    const bool tall = dtype == MOE_BF16 && !dense;
-    const int tile_rows = tall ? FFN_BM_TALL : FFN_BM;
     // Slots that hold 64 rows on average at most are one tile each, give or take: the 128-column kernel
     // then reads the slot tables itself and the list kernel (a launch of ~5 us in front of the first
     // product) is skipped.  Long slots without the dense kernel keep the list: it cuts them into tiles
@@ -363,7 +363,7 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     const bool listless = dtype == MOE_F32 || (!dense && (long long)max_rows <= 64LL * max_slots);
     if (!listless) {
         hipLaunchKernelGGL(ffn_worklist_kernel, dim3(1), dim3(1024), 0, st, slot_offset, slot_expert, n_slots,
-                           max_slots, max_items, schedule, tile_rows, E, dense ? 1 : 0, max_dense, items, dtiles,
+                           max_slots, max_items, schedule, E, dense ? 1 : 0, max_dense, items, dtiles,
                            n_items);
         MOE_CHECK_LAUNCH("moe_expert_ffn/worklist");
     }
@@ -371,7 +371,7 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     // upper bounds of the 128-column kernel's list: with the dense kernel on, a slot leaves it one piece at most
     int grid_items = schedule != MOE_SCHEDULE_SLOTS ? (max_slots < max_items ? max_slots : max_items)
                      : (dense || listless)          ? max_slots
-                                                    : max_slots + max_rows / tile_rows + 1;
+                                                    : max_slots + max_rows / FFN_BM + 1;
     // measurement only (moe_expert_ffn_timed): events recorded before, between and after the two products
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
     if (timing_events)
@@ -404,16 +404,10 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
                                dim3(few_rows_grid(max_rows, max_slots, schedule, F)), dim3(SHARE_THREADS), 0, st,
                                (const bf16_t *)x_perm, (const bf16_t *)w1, row_index, n_x_rows, d, F, E, slot_offset, slot_expert,
                                n_slots, max_slots, max_rows, (bf16_t *)h);
-        else if (tall)
-            hipLaunchKernelGGL((ffn_gemm_bf16_kernel<true, true>), dim3(g1), dim3(GEMM_THREADS), 0, st,
-                               (const bf16_t *)x_perm, row_index, n_x_rows, (const bf16_t *)w1, d, F, E, list,
-                               n_items, slot_offset, slot_expert, n_slots, max_slots, schedule, max_rows,
-                               (bf16_t *)h);
         else
-            hipLaunchKernelGGL((ffn_gemm_bf16_kernel<true, false>), dim3(g1), dim3(GEMM_THREADS), 0,
-                               st, (const bf16_t *)x_perm, row_index, n_x_rows, (const bf16_t *)w1, d, F, E, list,
-                               n_items, slot_offset, slot_expert, n_slots, max_slots, schedule, max_rows,
-                               (bf16_t *)h);
+            hipLaunchKernelGGL(ffn_gemm_bf16_kernel<true>, dim3(g1), dim3(GEMM_THREADS), 0, st, (const bf16_t *)x_perm, row_index,
+                               n_x_rows, (const bf16_t *)w1, d, F, E, list, n_items, slot_offset, slot_expert, n_slots,
+                               max_slots, schedule, max_rows, (bf16_t *)h);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm1");
         if (ev[1]) (void)hipEventRecord(ev[1], st);
         if (dense) {
@@ -428,16 +422,10 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
                                dim3(few_rows_grid(max_rows, max_slots, schedule, d)), dim3(SHARE_THREADS), 0, st, (const bf16_t *)h,
                                (const bf16_t *)w2, (const int32_t *)nullptr, max_rows, F, d, E, slot_offset, slot_expert, n_slots,
                                max_slots, max_rows, (bf16_t *)y_perm);
-        else if (tall)
-            hipLaunchKernelGGL((ffn_gemm_bf16_kernel<false, true>), dim3(g2), dim3(GEMM_THREADS), 0, st,
-                               (const bf16_t *)h, (const int32_t *)nullptr, max_rows, (const bf16_t *)w2, F, d, E,
-                               list, n_items, slot_offset, slot_expert, n_slots, max_slots, schedule, max_rows,
-                               (bf16_t *)y_perm);
         else
-            hipLaunchKernelGGL((ffn_gemm_bf16_kernel<false, false>), dim3(g2), dim3(GEMM_THREADS), 0,
-                               st, (const bf16_t *)h, (const int32_t *)nullptr, max_rows, (const bf16_t *)w2, F, d, E,
-                               list, n_items, slot_offset, slot_expert, n_slots, max_slots, schedule, max_rows,
-                               (bf16_t *)y_perm);
+            hipLaunchKernelGGL(ffn_gemm_bf16_kernel<false>, dim3(g2), dim3(GEMM_THREADS), 0, st, (const bf16_t *)h,
+                               (const int32_t *)nullptr, max_rows, (const bf16_t *)w2, F, d, E, list, n_items, slot_offset,
+                               slot_expert, n_slots, max_slots, schedule, max_rows, (bf16_t *)y_perm);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm2");
     } else {
         // tile height of a product of depth K (0: 32 rows and a short k); the results are the same

@@ -58,6 +58,8 @@ __device__ __forceinline__ float sigmoidf_(float v)
     const float x = 1.f + __expf(-v);
     return recip_(x > 3.402823466e38f ? 3.402823466e38f : x);
 }
+// The same exponential and reciprocal: an absolute error of about 1e-7.  1 - 2 / (1 + e^2a) cancels for small |v| (relative error 1.4e-3 at
+// 1e-5, 5e-2 at 1e-6), which the bf16 rounding of h only covers beside a highway or other states of ordinary size.
 __device__ __forceinline__ float tanhf_(float v)
 {
     float a = fminf(fabsf(v), 15.f);
