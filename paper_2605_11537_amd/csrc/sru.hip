@@ -612,8 +612,9 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
     bool packed = false;                       // cur is a fragment image
     bool packed_in_h = false;                  // which lies in the two state buffers
     // the attention reads fragments from a one-kernel layer, which also writes the image of its weighted sums
-    const bool first_two = !(w->attention && w->n_layers == 1) && sru_two_kernels(B, L, nin, n_h, false);
-    const bool later_two = !w->attention && sru_two_kernels(B, L, n_h, n_h, true);
+    const bool later_two = !w->attention && sru_two_kernels(B, L, n_h, n_h, true, false);
+    const bool first_two = !(w->attention && w->n_layers == 1) &&
+                           sru_two_kernels(B, L, nin, n_h, false, w->n_layers > 1 && !later_two);
     if (!first_two && fus_packs_input(B, L, nin, n_h)) {
         bf16_t *image = (bf16_t *)(base + lay.u + fus_image_bytes(B, L, n_h));
         hipLaunchKernelGGL(sru_pack_input_kernel, dim3(ceil_div(L, 32), nin / 64, B), dim3(256), 0, st, (const uint4 *)cur, L, nin,

@@ -28,13 +28,15 @@ static inline bool fus_packs_input(int B, int L, int K, int n_h)
 // sequences of 513 .. 1024 positions, 64 .. 2048 -> 128 .. 1024 channels, with mean errors of 6 and 8 %; taking the form they
 // choose costs 0.4 % on average against always knowing.  Two against one kernel: 1 x 1024, 1024 -> 256: 25 and 35 us;
 // 5 x 777, 1024 -> 1024: 68 and 94; 8 x 1024, 256 -> 256: 29 and 15; 16 x 1024, 768 -> 256: 73 and 60.
-// from_fragments: the one-kernel form would read its states as the layer before leaves them.
-static inline bool sru_two_kernels(int B, int L, int K, int n_h, bool from_fragments)
+// from_fragments: the one-kernel form would read its states as the layer before leaves them.  hands_on: the next layer is one kernel; the
+// scan's states reach it 0.5 us (1 x 1024, 128 channels) to 3.5 us (5 x 777, 256 channels) later than those of a kernel of its own kind.
+static inline bool sru_two_kernels(int B, int L, int K, int n_h, bool from_fragments, bool hands_on)
 {
     if (L <= 512) return false;
     if (L > FUS_MAX_L) return true;
     const double k = K / 1e3, l = L / 1e3, x = (double)B * L * n_h * (K == n_h ? 3 : 4) / 1e6;
-    const double two = 10.5 + 7.7 * l + 1.5 * k * l + (1.37 + 1.74 * k) * x + (x > 10 ? 1.2 * (x - 10) : 0);
+    const double two = 10.5 + 7.7 * l + 1.5 * k * l + (1.37 + 1.74 * k) * x + (x > 10 ? 1.2 * (x - 10) : 0) +
+                       (!hands_on ? 0 : x < 3 ? 0.5 + 0.8 * x : 3);
     const bool packs = !from_fragments && fus_packs_input(B, L, K, n_h);
     const double wgs = (double)B * (n_h / FUS_CH);
     const int rounds = (int)((wgs + 255) / 256);

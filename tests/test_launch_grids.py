@@ -95,26 +95,27 @@ FORMS = """
 #include <stdio.h>
 int main()
 {
-    int a[5];
-    while (scanf("%d %d %d %d %d", a, a + 1, a + 2, a + 3, a + 4) == 5)
-        printf("%d %d\\n", moe::sru_two_kernels(a[0], a[1], a[2], a[3], a[4]), moe::fus_packs_input(a[0], a[1], a[2], a[3]));
+    int a[6];
+    while (scanf("%d %d %d %d %d %d", a, a + 1, a + 2, a + 3, a + 4, a + 5) == 6)
+        printf("%d %d\\n", moe::sru_two_kernels(a[0], a[1], a[2], a[3], a[4], a[5]), moe::fus_packs_input(a[0], a[1], a[2], a[3]));
 }
 """
 
 
 def test_sru_forms(tmp_path_factory):
     """The form an SRU layer takes, where the two differ by 20 % and more in measurements (sequences, positions, widths, input as
-    fragments), and the forms that are the only ones."""
+    fragments, one kernel behind), and the forms that are the only ones."""
     ask = _compiled(tmp_path_factory, "forms", FORMS)
-    one = [(5, 512, 2048, 1024, 0), (64, 7, 768, 256, 0), (8, 1024, 256, 256, 1), (8, 1024, 256, 256, 0), (16, 1024, 128, 128, 1),
-           (1, 1024, 256, 256, 1), (32, 1024, 512, 512, 1), (16, 1024, 768, 256, 0)]
-    two = [(1, 1025, 64, 128, 0), (16, 4096, 256, 256, 1), (1, 600, 1024, 256, 0), (5, 777, 1024, 1024, 1), (1, 600, 2048, 256, 0),
-           (5, 777, 2048, 256, 0), (5, 777, 768, 128, 0), (1, 1024, 1024, 1024, 0)]
+    one = [(5, 512, 2048, 1024, 0, 0), (64, 7, 768, 256, 0, 1), (8, 1024, 256, 256, 1, 0), (8, 1024, 256, 256, 0, 1),
+           (16, 1024, 128, 128, 1, 1), (1, 1024, 256, 256, 1, 0), (32, 1024, 512, 512, 1, 0), (16, 1024, 768, 256, 0, 1),
+           (5, 777, 768, 256, 0, 1)]
+    two = [(1, 1025, 64, 128, 0, 0), (16, 4096, 256, 256, 1, 0), (1, 600, 1024, 256, 0, 1), (5, 777, 1024, 1024, 1, 0),
+           (1, 600, 2048, 256, 0, 1), (5, 777, 2048, 256, 0, 1), (5, 777, 768, 128, 0, 1), (1, 1024, 1024, 1024, 0, 0)]
     assert [r[0] for r in ask(one)] == [0] * len(one)
     assert [r[0] for r in ask(two)] == [1] * len(two)
     # an image of the embeddings only beside the states' in the room of the projections (16 bytes per state and channel)
     for B, L, K, n_h in [(16, 1024, 768, 256), (2, 513, 768, 128), (2, 513, 512, 128), (1, 1024, 1792, 256), (1, 1024, 1856, 256)]:
-        (_, packs), = ask([(B, L, K, n_h, 0)])
+        (_, packs), = ask([(B, L, K, n_h, 0, 0)])
         assert packs == (2 * B * (-(-L // 32) * 32) * (K + n_h) <= 16 * B * L * n_h)
 
 
