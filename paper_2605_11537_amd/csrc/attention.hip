@@ -22,7 +22,7 @@
 //      as the other operand, rounded to bf16 (relative error 2^-9 per weight, the size of the bf16
 //      rounding of z itself).  On the vector units the same sum is 16384 multiply-adds per lane and took
 //      three times as long as everything else in the kernel.
-// Measured, 8 x 512, 256 features: 13 us, against 23 us and 4 us for the image in a kernel of its own.
+// Measured, 8 x 512, 256 features: 12.3 us at best, 13 in the predictor, against 23 us and 4 us for the image in a kernel of its own.
 #include "gemm_bf16.h"
 #include "route.h"
 

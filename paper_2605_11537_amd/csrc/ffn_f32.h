@@ -8,8 +8,9 @@
 //            column c of instruction strip s, so the 64 columns of the tile are 4 strips and every load is a 256-byte run
 // 16-row blocks keep the padding of short slots small; blocks a tile does not have are not compiled into its body.
 //
-// Bound: what a CU can load, about 55 GB/s (23 bytes per clock) beside the matrix instructions: a 32 x 64 tile loads 24 KB per
-// 16 k where its matrix instructions take 1024 clocks.  Measured (first, second product; the vector-unit tile before, 64 x 64 with
+// Bound: load time and matrix time add up.  A 32 x 64 tile loads 24 KB per 16 k, where its matrix instructions take 1024 clocks; with
+// either left out 8 experts x 512 rows, 768 x 3072, take 128 and 161 us, with both 305.  Together the loads come in at about 55 GB/s per CU (a
+// CU takes 135 GB/s of plain loads from its L2).  Measured (first, second product; the vector-unit tile before, 64 x 64 with
 // both operands in LDS and one workgroup's whole k in one chain, in brackets): 32 experts x 32 rows, 512 x 2048: 43, 32 us (62, 102);
 // 40 slots of 10 .. 59 rows: 66, 75 us (83, 140); 8 experts x 512 rows, 768 x 3072: 215, 279 us (249, 287).
 #pragma once

@@ -1,5 +1,5 @@
 // bf16 grouped product for batches that leave most of the chip idle in the 128-column kernel: a decode step has rows for a
-// few experts only, and 22 experts x 6 column tiles are 132 workgroups that each pull 786 KB, where a CU pulls about 55 GB/s.
+// few experts only, and 22 experts x 6 column tiles are 132 workgroups that each pull 786 KB, where a CU pulls about 55 GB/s from memory.
 //
 // Up to 32 rows of one expert x 32 columns per workgroup, the four wavefronts split k: four times as many workgroups, and
 // no LDS and no barrier in the k loop.  Each wavefront streams its quarter of one 32-column strip of the packed image (1 KB of

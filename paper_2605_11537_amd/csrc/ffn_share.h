@@ -22,7 +22,7 @@ __device__ __forceinline__ int tile_cost(int rows) { return TILE_COST_TILE + TIL
 // same, and replicas leave no part-filled tiles behind).  Order: experts as in the tables, their row tiles, the column tiles of
 // a row tile side by side.  The order is cut into 8 ranges of equal COST, one per XCD; ranges of equal length left the XCDs that
 // drew the full tiles of the hot experts with 1.5 times the work of the others.  Each XCD's workgroups with work come first in
-// the grid: a CU moves about 55 GB/s, so two tiles on one CU take twice as long as on two, and the launch order is what spreads them.
+// the grid: two tiles on one CU take twice as long as on two, and the launch order is what spreads them.
 template <int BM>
 struct TileShare {
     // this thread's slots and the tiles and cost before them
