@@ -243,15 +243,18 @@ __global__ __launch_bounds__(SHARE_THREADS, EXPERTS ? 2 : 3) void ffn_few_rows_b
     }
 }
 
-// Where this kernel is the faster one (first / second product in us against the 128-column kernel):
-//  - at most half of the slots can have a row: most of the 128-column kernel's grid is slots without rows (37 rows in 144 slots, 768 x
-//    3072: 26.8 / 24.0 against 36.0 / 36.3; with rows in every slot, 36 in 36: 35 / 30 against 28 / 27);
+// Where this kernel is the faster one:
+//  - at most half of the slots can have a row: most of the 128-column kernel's grid is slots without rows.  Both products against that
+//    kernel, rows dealt evenly (by Zipf's law), us: 36 rows in 144 slots, 768 x 3072: 53, 72 (44, 70), 72 rows 91, 100 (62, 93), 144
+//    rows 138, 151 (96, 115); 256 x 1024, 72 rows 17, 22 (15, 21), 216 rows 28.6, 28.2 (20, 23); 300 rows in 600 slots, 256 x 1024:
+//    51.6, 50.9 (30.7, 31.8).  So the line could lie at twice as many rows for wide matrices; at half it loses nothing.  Matrices of
+//    under 131072 elements are latency alone: 128 x 256, 18 rows in 36 slots 7.6, 7.2, 144 in 288 9.5, 8.4.
 //  - a long k and tiles for half of the CUs at most, slots of 32 rows at most on average (9 slots of 8 rows, k = 3072: 12.6 against 20.4, of
 //    30 rows: 15.9 against 21.6; 8 slots of 20 rows, k = 1024: 8.5 against 9.8, k = 256: 7.6 against 6.9; 216 tiles: 14.8 against 11.4).
 static inline bool ffn_few_rows(int max_rows, int max_slots, int K, int N)
 {
     if (max_slots > FEW_PER * SHARE_THREADS) return false;
-    if (2LL * max_rows <= max_slots) return true;
+    if (2LL * max_rows <= max_slots && (long long)K * N >= 131072) return true;
     const long long active = max_rows < max_slots ? max_rows : max_slots;
     return K >= 1024 && active * (N / 128) <= 128 && (long long)max_rows <= 32LL * max_slots;
 }

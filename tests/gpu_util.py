@@ -57,4 +57,6 @@ def few_rows(max_rows, max_slots, K, N):
     """Whether a bf16 expert product of depth K and N columns runs on the kernel for few rows (the library's rule)."""
     if max_rows > 64 * max_slots or max_slots > 1024:
         return False
-    return 2 * max_rows <= max_slots or (K >= 1024 and min(max_rows, max_slots) * (N // 128) <= 128 and max_rows <= 32 * max_slots)
+    if 2 * max_rows <= max_slots and K * N >= 131072:
+        return True
+    return K >= 1024 and min(max_rows, max_slots) * (N // 128) <= 128 and max_rows <= 32 * max_slots

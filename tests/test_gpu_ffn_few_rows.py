@@ -19,12 +19,13 @@ def _spread(n_slots, rows):
 
 
 @pytest.mark.parametrize("d,F,E,rows,products", [
-    (128, 256, 20, _spread(150, [1, 2, 33, 32, 3]), (True, True)),            # two and four steps of k per wavefront
+    (128, 1024, 20, _spread(150, [1, 2, 33, 32, 3]), (True, True)),           # two steps of k per wavefront; 16
     (384, 640, 9, _spread(150, [31, 7]), (True, True)),                       # six and ten: half a burst past the end
-    (128, 256, 30, _spread(400, [40, 65, 1, 90]), (True, True)),              # two slots per thread; passes of 2, 3, 1 and 3 blocks
-    (128, 128, 50, _spread(700, [5, 40, 1, 1, 1]), (True, True)),             # three slots per thread
-    (128, 256, 40, _spread(1024, [130, 1, 200, 64, 100]), (True, True)),      # four; a second pass of 2 and of 72 rows
-    (128, 256, 40, _spread(1025, [130, 1, 200, 64, 100]), (False, False)),    # one slot too many: the 128-column kernel
+    (128, 896, 9, _spread(150, [31, 7]), (False, False)),                     # matrices too small for it
+    (128, 1024, 30, _spread(400, [40, 65, 1, 90]), (True, True)),             # two slots per thread; passes of 2, 3, 1 and 3 blocks
+    (256, 512, 50, _spread(700, [5, 40, 1, 1, 1]), (True, True)),             # three slots per thread
+    (128, 1024, 40, _spread(1024, [130, 1, 200, 64, 100]), (True, True)),     # four; a second pass of 2 and of 72 rows
+    (128, 1024, 40, _spread(1025, [130, 1, 200, 64, 100]), (False, False)),   # one slot too many: the 128-column kernel
     (256, 1152, 4, [7, 0, 31, 33, 20], (False, True)),                        # few slots: the second product only, 18 steps
     (256, 1408, 3, [20, 40, 1], (False, True)),                               # 22 steps: half a burst after a round
     (128, 3072, 4, [20, 40, 1, 60], (False, True)),                           # 48 steps: four rounds

@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
 ])
 def test_rows_past_the_batch(dtype, max_rows, rows, schedule):
     import paper_2605_11537_amd as moe
-    d, F, S = 128, 256, len(rows)
+    d, F, S = 128, 1024, len(rows)
     E = S
     so = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
     se = np.arange(S, dtype=np.int32)
@@ -45,7 +45,7 @@ def test_rows_past_the_batch(dtype, max_rows, rows, schedule):
 KERNELS = [
     pytest.param(synth.F32, 64, 320, 1, 0, id="f32-short"),
     pytest.param(synth.F32, 320, 448, 12, 0, id="f32-64rows"),
-    pytest.param(synth.BF16, 128, 256, 1, 200, id="few-rows"),
+    pytest.param(synth.BF16, 128, 1024, 1, 200, id="few-rows"),
     pytest.param(synth.BF16, 128, 256, 4, 0, id="128-columns"),
     pytest.param(synth.BF16, 256, 512, 100, 0, id="256x256"),
 ]
