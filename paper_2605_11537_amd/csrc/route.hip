@@ -13,7 +13,8 @@
 
 namespace moe {
 
-constexpr int RT_BK = 128;
+constexpr int RT_DEPTH = 128;   // d is a multiple of this
+constexpr int RT_BK = 64;       // k chunk
 
 __device__ __forceinline__ void argmax_merge(float &v, int &i, float ov, int oi)
 {
@@ -41,8 +42,15 @@ __global__ __launch_bounds__(256) void pack_matrix_kernel(const bf16_t *__restri
 // MB row blocks of 32 tokens per workgroup: 1 for small batches (many small workgroups hide the
 // k-loop latency), 2 above 8192 tokens (every workgroup reads the whole packed router matrix from L2, so
 // taller tiles cut that traffic; the 256-expert shapes go to route_resident_kernel from 16384 tokens on).
-template <int NB, int MB>
-__global__ __launch_bounds__(GEMM_THREADS) void route_mfma_kernel(const bf16_t *__restrict__ x,
+//
+// BK: the product holds two chunks of both operands in registers, so the chunk decides how many wavefronts a SIMD takes:
+// with 64 k two and more for every tile, with 128 k one for 256 experts and half as many for MB = 2.  The small workgroups
+// of MB = 1 with 128 experts have registers left and their number is what the batch gives, so there the deeper chunk is the
+// better one, unless d is one chunk (the product would request it twice).  Measured, chunks of 128 -> 64 (us):
+//   256 experts  65536 x 384: 46.1 -> 29.1    30000 x 1024: 38.7 -> 28.5    64 x 2048: 19.9 -> 18.9
+//   128 experts  65536 x 768: 29.0 -> 25.4    4096 x 128: 6.26 -> 6.14, but 4096 x 384: 6.94 -> 7.09, x 2048: 13.6 -> 14.8
+template <int NB, int MB, int BK>
+__global__ __launch_bounds__(GEMM_THREADS, 2) void route_mfma_kernel(const bf16_t *__restrict__ x,
                                                                   const bf16_t *__restrict__ wr_packed,
                                                                   const float *__restrict__ bias, int T, int d,
                                                                   int top_k, int renormalize,
@@ -52,7 +60,6 @@ __global__ __launch_bounds__(GEMM_THREADS) void route_mfma_kernel(const bf16_t *
     constexpr int E = NB * 128;
     constexpr int LDL = E + 8;                    // 8 threads per row, 4 rows per half wavefront: bank 8 r + sub
     constexpr int RT_BM = MB * 32;
-    constexpr int BK = RT_BK;
     constexpr int STAGE_BYTES = gemm_lds_elems<MB, BK>() * 2, TILE_BYTES = 32 * LDL * 4;
     // the logits tile reuses the A staging buffers, which are free once the product is done
     __shared__ __attribute__((aligned(16))) char smem[STAGE_BYTES > TILE_BYTES ? STAGE_BYTES : TILE_BYTES];
@@ -160,7 +167,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void route_mfma_kernel(const bf16_t *
 
 static inline bool route_uses_mfma(int d, int E, int dtype)
 {
-    return dtype == MOE_BF16 && (E == 128 || E == 256) && d % RT_BK == 0;
+    return dtype == MOE_BF16 && (E == 128 || E == 256) && d % RT_DEPTH == 0;
 }
 
 int pack_matrix_launch(const void *in, int K, int N, void *out, hipStream_t st, const char *who)
@@ -216,15 +223,16 @@ int route_launch(const void *x, const void *w_router, int w_layout, const float 
         }
         const int mbk = T <= 8192 ? 1 : 2;
         int grid = ceil_div(T, 32 * mbk);
-#define MOE_ROUTE_LAUNCH(NB_, MB_)                                                                            \
-    hipLaunchKernelGGL((route_mfma_kernel<NB_, MB_>), dim3(grid), dim3(GEMM_THREADS), 0, st, (const bf16_t *)x, \
+#define MOE_ROUTE_LAUNCH(NB_, MB_, BK_)                                                                             \
+    hipLaunchKernelGGL((route_mfma_kernel<NB_, MB_, BK_>), dim3(grid), dim3(GEMM_THREADS), 0, st, (const bf16_t *)x, \
                        (const bf16_t *)wp, b_router, T, d, top_k, renormalize, idx, prob, logits_opt)
         if (E == 128) {
-            if (mbk == 1) MOE_ROUTE_LAUNCH(1, 1);
-            else MOE_ROUTE_LAUNCH(1, 2);
+            if (mbk == 2) MOE_ROUTE_LAUNCH(1, 2, RT_BK);
+            else if (d > 2 * RT_BK) MOE_ROUTE_LAUNCH(1, 1, 2 * RT_BK);
+            else MOE_ROUTE_LAUNCH(1, 1, RT_BK);
         } else {
-            if (mbk == 1) MOE_ROUTE_LAUNCH(2, 1);
-            else MOE_ROUTE_LAUNCH(2, 2);
+            if (mbk == 1) MOE_ROUTE_LAUNCH(2, 1, RT_BK);
+            else MOE_ROUTE_LAUNCH(2, 2, RT_BK);
         }
 #undef MOE_ROUTE_LAUNCH
     } else if (dtype == MOE_BF16) {

@@ -51,6 +51,22 @@ def test_route_direct(T, d, E, dtype, k):
     assert np.abs(to_host(prob) / p - 1).max() <= 2e-6 + E * 2.0 ** -24
 
 
+# the packed kernel's tiles: 128 / 256 experts x 32 / 64 tokens (above 8192), k chunks of 64, or of 128 where d has two and more
+@pytest.mark.parametrize("T,d,E,k", [
+    (1, 128, 128, 1),
+    (33, 256, 128, 2),
+    (31, 384, 128, 1),                   # an odd number of deep chunks
+    (8193, 128, 128, 3),
+    (8193, 384, 128, 1),
+    (31, 128, 256, 2),
+    (8192, 640, 256, 1),
+    (8193, 128, 256, 1),                 # one row past the last full tile
+    (16415, 384, 256, 3),
+])
+def test_route_packed_tiles(T, d, E, k):
+    test_route_direct(T, d, E, synth.BF16, k)
+
+
 @pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
 def test_route_direct_specials(dtype):
     """An infinite bias, a token with a NaN and a token of subnormal size: each stays in its own row or column."""
