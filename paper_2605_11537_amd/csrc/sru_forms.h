@@ -24,10 +24,11 @@ static inline bool fus_packs_input(int B, int L, int K, int n_h)
 // Projection and scan in two kernels, or the layer in one?  One kernel up to 512 positions, two above 1024.  Between them one
 // workgroup fills a CU and reads all rows of its sequence, so its time grows with K, in steps of 256 workgroups (rounds, of which
 // share is filled), while the two kernels deal the work out evenly but send the projections through memory (dearer from 10 million
-// on, 40 MB).  The estimates (microseconds; K and L in thousands, x in millions of projections) are fitted to 230 layers of 1 .. 64
-// sequences of 513 .. 1024 positions, 64 .. 2048 -> 128 .. 1024 channels, with mean errors of 6 and 8 %; taking the form they
-// choose costs 0.4 % on average against always knowing.  Two against one kernel: 1 x 1024, 1024 -> 256: 25 and 35 us;
-// 5 x 777, 1024 -> 1024: 68 and 94; 8 x 1024, 256 -> 256: 29 and 15; 16 x 1024, 768 -> 256: 73 and 60.
+// on, 40 MB).  The estimates (microseconds; K and L in thousands, x in millions of projections) are fitted to 300 layers of 1 .. 200
+// sequences of 513 .. 1024 positions, 64 .. 2048 -> 128 .. 1024 channels, with mean errors of at most 12 and 8 %; taking the form they
+// choose costs 0.3 % on average against always knowing.  Two against one kernel: 1 x 1024, 1024 -> 256: 25 and 35 us;
+// 5 x 777, 1024 -> 1024: 68 and 94; 64 x 600, 1024 -> 1024: 640 and 972; 8 x 1024, 256 -> 256: 29 and 15; 16 x 1024, 768 -> 256:
+// 73 and 60; 64 x 1024, 384 -> 384: 303 and 269.
 // from_fragments: the one-kernel form would read its states as the layer before leaves them.  hands_on: the next layer is one kernel; the
 // scan's states reach it 0.5 us (1 x 1024, 128 channels) to 3.5 us (5 x 777, 256 channels) later than those of a kernel of its own kind.
 static inline bool sru_two_kernels(int B, int L, int K, int n_h, bool from_fragments, bool hands_on)
@@ -35,7 +36,7 @@ static inline bool sru_two_kernels(int B, int L, int K, int n_h, bool from_fragm
     if (L <= 512) return false;
     if (L > FUS_MAX_L) return true;
     const double k = K / 1e3, l = L / 1e3, x = (double)B * L * n_h * (K == n_h ? 3 : 4) / 1e6;
-    const double two = 10.5 + 7.7 * l + 1.5 * k * l + (1.37 + 1.74 * k) * x + (x > 10 ? 1.2 * (x - 10) : 0) +
+    const double two = 10.5 + 7.7 * l + 1.5 * k * l + (1.37 + 1.74 * k) * x + (x > 10 ? (2.2 - 0.9 * k) * (x - 10) : 0) +
                        (!hands_on ? 0 : x < 3 ? 0.5 + 0.8 * x : 3);
     const bool packs = !from_fragments && fus_packs_input(B, L, K, n_h);
     const double wgs = (double)B * (n_h / FUS_CH);

@@ -103,14 +103,15 @@ int main()
 
 
 def test_sru_forms(tmp_path_factory):
-    """The form an SRU layer takes, where the two differ by 20 % and more in measurements (sequences, positions, widths, input as
+    """The form an SRU layer takes, where the two differ by 12 % and more in measurements (sequences, positions, widths, input as
     fragments, one kernel behind), and the forms that are the only ones."""
     ask = _compiled(tmp_path_factory, "forms", FORMS)
     one = [(5, 512, 2048, 1024, 0, 0), (64, 7, 768, 256, 0, 1), (8, 1024, 256, 256, 1, 0), (8, 1024, 256, 256, 0, 1),
            (16, 1024, 128, 128, 1, 1), (1, 1024, 256, 256, 1, 0), (32, 1024, 512, 512, 1, 0), (16, 1024, 768, 256, 0, 1),
-           (5, 777, 768, 256, 0, 1)]
+           (5, 777, 768, 256, 0, 1), (64, 1024, 384, 384, 0, 0), (64, 1024, 768, 768, 0, 0), (24, 1024, 768, 768, 0, 0)]
     two = [(1, 1025, 64, 128, 0, 0), (16, 4096, 256, 256, 1, 0), (1, 600, 1024, 256, 0, 1), (5, 777, 1024, 1024, 1, 0),
-           (1, 600, 2048, 256, 0, 1), (5, 777, 2048, 256, 0, 1), (5, 777, 768, 128, 0, 1), (1, 1024, 1024, 1024, 0, 0)]
+           (1, 600, 2048, 256, 0, 1), (5, 777, 2048, 256, 0, 1), (5, 777, 768, 128, 0, 1), (1, 1024, 1024, 1024, 0, 0),
+           (64, 600, 1024, 1024, 0, 0), (64, 600, 2048, 512, 0, 0)]
     assert [r[0] for r in ask(one)] == [0] * len(one)
     assert [r[0] for r in ask(two)] == [1] * len(two)
     # an image of the embeddings only beside the states' in the room of the projections (16 bytes per state and channel)
