@@ -202,7 +202,7 @@ __global__ __launch_bounds__(SRU_CHUNKS * SRU_CHANNELS) void sru_scan_kernel(
 // has, and only the wavefronts that have rows load any: with one per CU, four steps and all eight wavefronts loading, 64 sequences of
 // 7, 256 -> 256, took 45.7 us with the head where the kernel before took 38.6, now 18; 16 x 16: 15.5, 13.8, now 9.1; 1 x 1: 10.2, 9.2,
 // now 7.6.
-// Measured per layer at 8 x 512, 256 -> 256, in a predictor of ten: 12.4 -> 9.0 us (8.0 at best); 5 x 777, 768 -> 256 and 256 -> 256, both layers: 46 us in two
+// Measured per layer at 8 x 512, 256 -> 256, in a predictor of ten: 12.4 -> 9.0 us (8.0 .. 8.3 at best); 5 x 777, 768 -> 256 and 256 -> 256, both layers: 46 us in two
 // launches against 53 us in four (projection and scan kernels).
 constexpr int FUS_THREADS = 512;       // 8 wavefronts: 2 per SIMD, so one's loads fly under the other's work
 constexpr int FUS_WAVES = FUS_THREADS / 64;
