@@ -431,19 +431,29 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
         // tile height of a product of depth K (0: 32 rows and a short k); the results are the same
         auto height = [&](int K) { return f32_depth(K) == 1 ? 0 : f32_rows(max_rows, E); };
         const int bm1 = height(d), bm2 = height(F);
-#define MOE_F32(RELU, BM, K)                                                                                        \
-    (BM == 0          ? ffn_gemm_f32_kernel<RELU, 32, 1, true>                                                      \
-     : f32_several(K) ? (BM == 64 ? ffn_gemm_f32_kernel<RELU, 64, 4, true> : ffn_gemm_f32_kernel<RELU, 32, 4, true>) \
-                      : (BM == 64 ? ffn_gemm_f32_kernel<RELU, 64, 4, false> : ffn_gemm_f32_kernel<RELU, 32, 4, false>))
-        auto gemm1 = MOE_F32(true, bm1, d);
-        auto gemm2 = MOE_F32(false, bm2, F);
-#undef MOE_F32
-        hipLaunchKernelGGL(gemm1, dim3(f32_grid(bm1, max_rows, max_slots, schedule, d, F)), dim3(F32_THREADS), 0, st,
+        auto narrow = [&](int K, int N) { return f32_narrow(max_rows, max_slots, E, schedule, K, N); };
+        const bool narrow1 = narrow(d, F), narrow2 = narrow(F, d);
+#define MOE_F32_BM(RELU, BM, D, SEVERAL) \
+    (BM == 64 ? ffn_gemm_f32_kernel<RELU, 64, F32_BN, D, SEVERAL> : ffn_gemm_f32_kernel<RELU, 32, F32_BN, D, SEVERAL>)
+#define MOE_F32_KERNEL(RELU, BM, NARROW, K)                                                       \
+    (NARROW            ? ffn_gemm_f32_kernel<RELU, 32, F32_NARROW_BN, F32_STAGED, false>          \
+     : BM == 0         ? ffn_gemm_f32_kernel<RELU, 32, F32_BN, 1, true>                           \
+     : f32_staged(K)   ? MOE_F32_BM(RELU, BM, F32_STAGED, false)                                  \
+     : f32_several(K)  ? MOE_F32_BM(RELU, BM, 4, true)                                            \
+                       : MOE_F32_BM(RELU, BM, 4, false))
+        auto gemm1 = MOE_F32_KERNEL(true, bm1, narrow1, d);
+        auto gemm2 = MOE_F32_KERNEL(false, bm2, narrow2, F);
+#undef MOE_F32_KERNEL
+#undef MOE_F32_BM
+        auto grid = [&](int bm, bool few, int K, int N) {
+            return dim3(few ? f32_narrow_grid(max_rows, max_slots, schedule, N) : f32_grid(bm, max_rows, max_slots, schedule, K, N));
+        };
+        hipLaunchKernelGGL(gemm1, grid(bm1, narrow1, d, F), dim3(F32_THREADS), 0, st,
                            (const float *)x_perm, (const float *)w1, row_index, n_x_rows, d, F, E, slot_offset, slot_expert,
                            n_slots, max_slots, schedule, max_rows, (float *)h);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm1");
         if (ev[1]) (void)hipEventRecord(ev[1], st);
-        hipLaunchKernelGGL(gemm2, dim3(f32_grid(bm2, max_rows, max_slots, schedule, F, d)), dim3(F32_THREADS), 0, st,
+        hipLaunchKernelGGL(gemm2, grid(bm2, narrow2, F, d), dim3(F32_THREADS), 0, st,
                            (const float *)h, (const float *)w2, (const int32_t *)nullptr, max_rows, F, d, E, slot_offset,
                            slot_expert, n_slots, max_slots, schedule, max_rows, (float *)y_perm);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm2");

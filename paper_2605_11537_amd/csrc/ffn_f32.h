@@ -1,28 +1,31 @@
 // binary32 grouped product of the expert FFN on the matrix cores: up to 32 or 64 rows of one expert x 64 columns per workgroup.
 //
-// v_mfma_f32_16x16x4_f32 multiplies and accumulates in binary32.  The four wavefronts split k, so the k loop has no LDS and
-// no barrier: every wavefront streams its quarter of the rows and of the weights straight into registers, D steps of 16 k
-// ahead, and the four partial tiles meet in LDS once at the end.
-//   tokens   lane (g, c) of 4 x 16 loads 4 consecutive k (4g .. 4g+3) of row c: one k per instruction
+// v_mfma_f32_16x16x4_f32 multiplies and accumulates in binary32.  The four wavefronts split k, so the k loop has no
+// barrier: every wavefront streams its quarter of the rows and of the weights into registers, 64 k ahead, and the four partial tiles
+// meet in LDS once at the end.
+//   tokens   lane (g, c) of 4 x 16 wants 4 consecutive k (4g .. 4g+3) of row c, one k per instruction: through LDS where k
+//            allows (f32_tile_staged), else straight from memory
 //   weights  row-major as the caller keeps them: the lane loads columns 4c .. 4c+3 of each of its 4 k; column 4c + s is
 //            column c of instruction strip s, so the 64 columns of the tile are 4 strips and every load is a 256-byte run
 // 16-row blocks keep the padding of short slots small; blocks a tile does not have are not compiled into its body.
 //
-// Bound: load time and matrix time add up.  A 32 x 64 tile loads 24 KB per 16 k, where its matrix instructions take 1024 clocks; with
-// either left out 8 experts x 512 rows, 768 x 3072, take 128 and 161 us, with both 305.  Together the loads come in at about 55 GB/s per CU (a
-// CU takes 135 GB/s of plain loads from its L2).  Measured (first, second product; the vector-unit tile before, 64 x 64 with
-// both operands in LDS and one workgroup's whole k in one chain, in brackets): 32 experts x 32 rows, 512 x 2048: 43, 32 us (62, 102);
-// 40 slots of 10 .. 59 rows: 66, 75 us (83, 140); 8 experts x 512 rows, 768 x 3072: 215, 279 us (249, 287).
+// Bound: few rows per expert by the weight stream (32 experts x 32 rows, 512 x 2048: 4.4 TB/s, 4.9 with no matrix work), many by the
+// matrix pipes (8 x 512 rows, 768 x 3072: 100 of 120 TFLOP/s that the loop reaches without loads); between them by what the tiles load
+// twice.  Both products, tokens straight from memory and as now, us (of the gain 1 .. 1.5 us per product are the search of ffn_share.h):
+//   512 x 2048: 32 experts x 32 rows 68, 58; 40 slots of 10 .. 59 rows 111, 92; 8 x 256 rows 107, 94; 16 x 94 rows 112, 91
+//   768 x 3072, 8 x 512 rows: 498, 395       256 x 1024, 8 experts, 300 rows 22.5, 17.0       64 x 256, 8 x 64 rows 12.9, 10.1
 #pragma once
 #include "ffn_share.h"
+#include <type_traits>
 
 namespace moe {
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int F32_THREADS = SHARE_THREADS;
-constexpr int F32_BN = 64;
+constexpr int F32_BN = 64, F32_NARROW_BN = 32;
 constexpr int F32_LD = F32_BN + 4;
+constexpr int F32_STAGED = 2;          // D of the kernel that stages its tokens: two steps of 32 k
 
 // part[w] <- this wavefront's share of k of (16 * MB rows) x 64 columns.  D: steps of 16 k in flight (f32_depth below)
 template <int MB, bool STREAM, int D, int BLOCKS>
@@ -84,57 +87,165 @@ __device__ __forceinline__ void f32_tile(const float *const (&a_row)[BLOCKS], co
                 (f32x4_t){acc[m][0][i], acc[m][1][i], acc[m][2][i], acc[m][3][i]};
 }
 
+// The same share of k with the tokens staged through the wavefront's own piece of LDS (its part of `part`, which is written after the
+// last step): a step is 32 k, a token load takes eight rows' 128 consecutive bytes, and the fragments (lane (g, c): row c, 4 k) are
+// read back from there.  Loaded straight from memory a fragment touches 16 lines per 16 lanes and holds the load path four times as
+// long as its bytes need.  Wavefront w takes the steps w, w + 4, ..: the four of a workgroup read on in neighbouring lines.
+constexpr int F32_LDA = 32 + 4;
+
+//
+// src: the rows this lane loads (tile rows lane / 8 + 8 i), possibly still on their way: the first weights do not wait for them.
+// gathered: they come from an index, a bad one reads row 0.
+template <int MB, int NS, bool STREAM, int D, int ROWS>
+__device__ __forceinline__ void f32_tile_staged(const float *__restrict__ A, const int (&src)[ROWS], bool gathered, int n_src_rows,
+                                                const float *__restrict__ B, int K, int N, float (*__restrict__ part)[16 * NS + 4])
+{
+    typedef float strips_t __attribute__((ext_vector_type(NS)));    // neighbouring columns of a lane, one per strip
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 15, g = lane >> 4;
+    const int steps = K / 128;                                   // per wavefront
+    const unsigned b_lane = (unsigned)(4 * g) * N + NS * c;
+    float *stage = &part[0][0];
+    float *put = stage + (lane >> 3) * F32_LDA + (lane & 7) * 4;
+    const float *get = stage + c * F32_LDA + 4 * g;
+    f32x4_t a[D][2 * MB], acc[MB][NS];
+    strips_t b[D][2][4];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) acc[m][s] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    auto k_of = [&](int step) { return ((step < steps ? step : steps - 1) * 4 + w) * 32; };     // past the end: a harmless re-read
+    auto load_b = [&](int step, int j) {
+        const int k0 = k_of(step);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const strips_t *p = reinterpret_cast<const strips_t *>(B + (size_t)(k0 + 16 * h + i) * N + b_lane);
+                b[j][h][i] = STREAM ? __builtin_nontemporal_load(p) : *p;
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const float *a_row[2 * MB];
+    auto load_a = [&](int step, int j) {
+        const int k0 = k_of(step);
+#pragma unroll
+        for (int i = 0; i < 2 * MB; ++i) a[j][i] = *reinterpret_cast<const f32x4_t *>(a_row[i] + k0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto load = [&](int step, int j) {
+        load_a(step, j);
+        load_b(step, j);
+    };
+    auto multiply = [&](int j) {
+        f32x4_t f[2][MB];
+#pragma unroll
+        for (int i = 0; i < 2 * MB; ++i) *reinterpret_cast<f32x4_t *>(put + i * 8 * F32_LDA) = a[j][i];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // LDS operations of one wavefront execute in order
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int m = 0; m < MB; ++m) f[h][m] = *reinterpret_cast<const f32x4_t *>(get + m * 16 * F32_LDA + 16 * h);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int m = 0; m < MB; ++m)
+#pragma unroll
+                    for (int s = 0; s < NS; ++s)
+                        acc[m][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[h][m][i], b[j][h][i][s], acc[m][s], 0, 0, 0);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+#pragma unroll
+    for (int i = 0; i < 2 * MB; ++i) {
+        const int r = !gathered || (src[i] >= 0 && src[i] < n_src_rows) ? src[i] : 0;
+        a_row[i] = A + (size_t)r * K + (lane & 7) * 4;
+    }
+#pragma unroll
+    for (int j = 0; j < D; ++j) load(j, j);
+    int s = 0;
+    for (; s + D < steps; s += D) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            multiply(j);
+            load(s + D + j, j);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+        if (s + j < steps) multiply(j);                          // uniform
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            strips_t v;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) v[s] = acc[m][s][i];
+            *reinterpret_cast<strips_t *>(&part[m * 16 + 4 * g + i][NS * c]) = v;
+        }
+}
+
 // SEVERAL: units per workgroup (f32_grid); else one, which is up to 5 % faster with nothing kept for the next
-template <bool RELU, int BM, int D, bool SEVERAL>
+template <bool RELU, int BM, int BN, int D, bool SEVERAL>
 __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_kernel(
     const float *__restrict__ A, const float *__restrict__ W, const int32_t *__restrict__ row_index, int n_src_rows, int K,
     int N, int E, const int32_t *__restrict__ slot_offset, const int32_t *__restrict__ slot_expert,
     const int32_t *__restrict__ n_slots_p, int max_slots, int schedule, int max_rows, float *__restrict__ C)
 {
-    __shared__ __attribute__((aligned(16))) float part[4][BM][F32_LD];
+    __shared__ __attribute__((aligned(16))) float part[4][BM][BN + 4];
     __shared__ TileItem found;
     TileShare<BM> share;
     share.E = E;
     share.schedule = schedule;
-    share.n_nt = N / F32_BN;
+    share.n_nt = N / BN;
     share.max_rows = max_rows;
-    share.find(slot_offset, slot_expert, n_slots_p, max_slots);
+    share.find(slot_offset, slot_expert, n_slots_p, max_slots, &found);
     const int tid = threadIdx.x, w = tid >> 6, c = tid & 15;
     for (int unit = share.first + (int)(blockIdx.x >> 3); unit < share.end; unit += (int)(gridDim.x >> 3)) {      // uniform
-        if (tid == 0) found.expert = -1;                             // stays so if the slot tables contradict themselves
-        __syncthreads();
         share.write_item(slot_offset, slot_expert, unit, &found);
         __syncthreads();
         const TileItem it = found;
-        if (it.expert < 0 || it.expert >= E || it.row_begin < 0) {               // uniform; never index with a bad table
-            if (!SEVERAL) break;
-            __syncthreads();                                         // found is read before the next unit's
-            continue;
-        }
+        const bool good = it.expert >= 0 && it.expert < E && it.row_begin >= 0;       // uniform; never index with a bad table
         const int nt = it.column;
-        const float *B = W + (size_t)it.expert * K * N + nt * F32_BN;
-        const int row_end = it.row_end < max_rows ? it.row_end : max_rows;
+        const float *B = W + (size_t)it.expert * K * N + nt * BN;
+        const int row_end = !good ? it.row_begin : it.row_end < max_rows ? it.row_end : max_rows;
         for (int r0 = it.row_begin; r0 < row_end; r0 += BM) {
             const int nrows = row_end - r0 < BM ? row_end - r0 : BM;
-            int src[BM / 16];
+            // the rows this lane loads: row c of every block, or (staged) every eighth row of the tile
+            constexpr int LOADS = D == F32_STAGED ? BM / 8 : BM / 16;
+            const int l_row = D == F32_STAGED ? (tid & 63) >> 3 : c;
+            int src[LOADS];
 #pragma unroll
-            for (int m = 0; m < BM / 16; ++m)                    // rows past the tile repeat its last row
-                src[m] = r0 + (m * 16 + c < nrows ? m * 16 + c : nrows - 1);
+            for (int m = 0; m < LOADS; ++m) {                    // rows past the tile repeat its last row
+                const int r = m * (BM / LOADS) + l_row;
+                src[m] = r0 + (r < nrows ? r : nrows - 1);
+            }
             if (row_index) {
 #pragma unroll
-                for (int m = 0; m < BM / 16; ++m) src[m] = row_index[src[m]];
-#pragma unroll
-                for (int m = 0; m < BM / 16; ++m)                // a bad index reads row 0
-                    src[m] = src[m] >= 0 && src[m] < n_src_rows ? src[m] : 0;
+                for (int m = 0; m < LOADS; ++m) src[m] = row_index[src[m]];
+                __builtin_amdgcn_sched_barrier(0);
             }
-            const float *a_row[BM / 16];
-#pragma unroll
-            for (int m = 0; m < BM / 16; ++m) a_row[m] = A + (size_t)src[m] * K;
             const int blocks = (nrows + 15) >> 4;
-#define MOE_F32_TILE(M)                                               \
-    do {                                                              \
-        if (it.reuse) f32_tile<M, false, D>(a_row, B, K, N, part[w]); \
-        else f32_tile<M, true, D>(a_row, B, K, N, part[w]);           \
+            auto tile = [&](auto BLOCKS, auto STREAM) {
+                constexpr int M = decltype(BLOCKS)::value;
+                constexpr bool S = decltype(STREAM)::value;
+                if constexpr (D == F32_STAGED) {
+                    f32_tile_staged<M, BN / 16, S, D>(A, src, row_index != nullptr, n_src_rows, B, K, N, part[w]);
+                } else {
+                    const float *a_row[LOADS];
+#pragma unroll
+                    for (int m = 0; m < LOADS; ++m)              // a bad index reads row 0
+                        a_row[m] = A + (size_t)(!row_index || (src[m] >= 0 && src[m] < n_src_rows) ? src[m] : 0) * K;
+                    f32_tile<M, S, D>(a_row, B, K, N, part[w]);
+                }
+            };
+            using std::integral_constant;
+#define MOE_F32_TILE(M)                                                        \
+    do {                                                                       \
+        if (it.reuse) tile(integral_constant<int, M>{}, std::false_type{});    \
+        else tile(integral_constant<int, M>{}, std::true_type{});              \
     } while (0)
             if (blocks == 1) MOE_F32_TILE(1);
             else if (BM == 32 || blocks == 2) MOE_F32_TILE(2);
@@ -144,21 +255,25 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
             }
 #undef MOE_F32_TILE
             __syncthreads();
-            for (int r = tid >> 4; r < nrows; r += 16) {
+            const int col = tid % (BN / 4) * 4;
+            for (int r = tid / (BN / 4); r < nrows; r += F32_THREADS / (BN / 4)) {
                 f32x4_t p[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) p[q] = *reinterpret_cast<const f32x4_t *>(&part[q][r][4 * c]);
+                for (int q = 0; q < 4; ++q) p[q] = *reinterpret_cast<const f32x4_t *>(&part[q][r][col]);
                 f32x4_t o;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float v = (p[0][i] + p[1][i]) + (p[2][i] + p[3][i]);
                     o[i] = RELU ? fmaxf(v, 0.f) : v;
                 }
-                *reinterpret_cast<f32x4_t *>(C + (size_t)(r0 + r) * N + nt * F32_BN + 4 * c) = o;
+                *reinterpret_cast<f32x4_t *>(C + (size_t)(r0 + r) * N + nt * BN + col) = o;
             }
             __syncthreads();
         }
         if (!SEVERAL) break;
+        __syncthreads();                                             // found has been read by all
+        if (tid == 0) found.expert = -1;
+        __syncthreads();
     }
 }
 
@@ -170,7 +285,8 @@ static inline int f32_depth(int K) { return K < 256 ? 1 : 4; }
 
 // Tile height of the others.  64 rows load a third less per multiply-add, 32 rows leave no CU with twice the tiles of another: few
 // rows per expert make few tiles, and from 128 on average on there are enough of them (8 experts x 512 rows, 768 x 3072:
-// 215, 279 us against 248, 318 with 32 rows; 40 slots of 10 .. 59 rows, 512 x 2048: 80, 114 against 66, 75).
+// 215, 279 us against 248, 318 with 32 rows; 512 x 2048, both products: 40 slots of 10 .. 59 rows 94 against 91, 1300 rows by Zipf's law over
+// 32 experts 136 against 116).
 static inline int f32_rows(int max_rows, int E) { return (long long)max_rows >= 128LL * E ? 64 : 32; }
 
 // A workgroup per unit, except up to k = 256, where a unit is short beside its search: there twice as many as are resident (two with 64
@@ -182,6 +298,23 @@ static inline int f32_grid(int bm, int max_rows, int max_slots, int schedule, in
     const int all = share_grid(bm ? bm : 32, F32_BN, max_rows, max_slots, schedule, N);
     const int most = 256 * (bm == 0 ? 4 : bm == 64 ? 2 * 2 : 2 * 3);
     return !f32_several(K) || all < most ? all : most;
+}
+
+// Tokens through LDS wherever a wavefront's share of k is whole steps of 32.  At k = 256 there are two of them, and the loads they save
+// are no longer than what the second unit of a workgroup needs (256 -> 1024 -> 256, 32 x 64 rows: 37.2 us without, 39.1 with).
+static inline bool f32_staged(int K) { return !f32_several(K) && K % 128 == 0; }
+
+// 32 columns where 64 would leave at least half of the CUs without a unit: half the work per unit, but every token row is loaded twice as often.
+// Both products, 64 and 32 columns, us: 256 -> 1024 -> 256, 300 rows over 8 experts 21.4 and 17.0; 512 -> 2048 -> 512, 200 over 16
+// 42.6 and 43.8; 512 over 8 48.4 and 56.8.
+static inline bool f32_narrow(int max_rows, int max_slots, int E, int schedule, int K, int N)
+{
+    const long long tiles = max_rows / 32 + (max_slots < E ? max_slots : E);
+    return schedule == MOE_SCHEDULE_SLOTS && K >= 256 && K % 128 == 0 && f32_rows(max_rows, E) == 32 && tiles * (N / F32_BN) <= 128;
+}
+static inline int f32_narrow_grid(int max_rows, int max_slots, int schedule, int N)
+{
+    return share_grid(32, F32_NARROW_BN, max_rows, max_slots, schedule, N);
 }
 
 }  // namespace moe

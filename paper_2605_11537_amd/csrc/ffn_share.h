@@ -23,11 +23,26 @@ __device__ __forceinline__ int tile_cost(int rows) { return TILE_COST_TILE + TIL
 // a row tile side by side.  The order is cut into 8 ranges of equal COST, one per XCD; ranges of equal length left the XCDs that
 // drew the full tiles of the hot experts with 1.5 times the work of the others.  Each XCD's workgroups with work come first in
 // the grid: two tiles on one CU take twice as long as on two, and the launch order is what spreads them.
+// inclusive sums over the wavefront, on the data-parallel-primitive path: rows of 16 by shifts, then the last lane of a row (of the
+// first two) added to the lanes after it
+__device__ __forceinline__ int wave_scan_incl(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
 template <int BM>
 struct TileShare {
     // this thread's slots and the tiles and cost before them
     int P, E, schedule, n_nt, max_rows, p0, p1, own_rows, count, count_base;
     int first, end;                               // units of this workgroup's XCD
+    bool own;                                     // one slot per thread: expert and first row are its own
+    int own_expert, own_row;
 
     // rows of the expert whose first slot p is, 0 for its other slots; tables that go on past max_rows end there (the grid is
     // sized for max_rows: units of the rows past it would push others out)
@@ -66,34 +81,57 @@ struct TileShare {
     }
 
     __device__ __forceinline__ void find(const int32_t *__restrict__ slot_offset, const int32_t *__restrict__ slot_expert,
-                                         const int32_t *__restrict__ n_slots_p, int max_slots)
+                                         const int32_t *__restrict__ n_slots_p, int max_slots, TileItem *out)
     {
         constexpr int WAVES = SHARE_THREADS / WAVE;
         __shared__ int count_sums[WAVES], cost_sums[WAVES];
         __shared__ int edge_unit[2];              // first unit of this share and of the next one
+        __shared__ int off_lds[SHARE_THREADS + 1];
+        __shared__ unsigned long long last_lds[WAVES];
         const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+        own = max_slots <= SHARE_THREADS;             // uniform
         P = n_slots_p[0];
-        if (P > max_slots) P = max_slots;
-        const int per = (P + SHARE_THREADS - 1) / SHARE_THREADS;
-        p0 = tid * per < P ? tid * per : P;
-        p1 = p0 + per < P ? p0 + per : P;
-        own_rows = p1 - p0 == 1 ? rows_of(slot_offset, slot_expert, p0) : 0;
         int cost = 0;
         count = 0;
-        for (int p = p0; p < p1; ++p) {
-            const int n = rows_at(slot_offset, slot_expert, p), t = tiles_of(n);
-            count += t;
-            cost += cost_of(n, t);
-        }
-        int count_inc = count, cost_inc = cost;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int a = __shfl_up(count_inc, o, 64), b = __shfl_up(cost_inc, o, 64);
-            if (lane >= o) {
-                count_inc += a;
-                cost_inc += b;
+        if (own) {
+            // A slot per thread.  Every entry is asked for at once (the tables hold max_slots entries, so none has to wait for n_slots);
+            // where an expert's slots end comes from a bit per slot.  One memory round trip; walking the slots is one per slot.
+            const int q = tid < max_slots ? tid : max_slots - 1;
+            own_expert = slot_expert[q];
+            const int before = slot_expert[q > 0 ? q - 1 : 0], after = slot_expert[q + 1 < max_slots ? q + 1 : q];
+            own_row = slot_offset[q];
+            const int last_row = slot_offset[max_slots];
+            if (P > max_slots) P = max_slots;
+            const unsigned long long ends = __ballot(tid + 1 >= P || own_expert != after);
+            if (lane == 0) last_lds[w] = ends;
+            if (tid < max_slots) off_lds[tid] = own_row;
+            if (tid == 0) off_lds[max_slots] = last_row;
+            __syncthreads();
+            p0 = tid < P ? tid : P;
+            p1 = tid < P ? tid + 1 : P;
+            own_rows = 0;
+            if (tid < P && own_expert >= 0 && own_expert < E && (tid == 0 || before != own_expert)) {
+                unsigned long long m = ends & (~0ull << lane);
+                int word = w;
+                while (m == 0) m = last_lds[++word];  // ends: the bit of slot P - 1 is set
+                const int left = max_rows - own_row, n = off_lds[word * WAVE + __builtin_ctzll(m) + 1] - own_row;
+                own_rows = n < left ? (n > 0 ? n : 0) : (left > 0 ? left : 0);
+            }
+            count = tiles_of(own_rows);
+            cost = cost_of(own_rows, count);
+        } else {
+            if (P > max_slots) P = max_slots;
+            const int per = (P + SHARE_THREADS - 1) / SHARE_THREADS;
+            p0 = tid * per < P ? tid * per : P;
+            p1 = p0 + per < P ? p0 + per : P;
+            own_rows = p1 - p0 == 1 ? rows_of(slot_offset, slot_expert, p0) : 0;
+            for (int p = p0; p < p1; ++p) {
+                const int n = rows_at(slot_offset, slot_expert, p), t = tiles_of(n);
+                count += t;
+                cost += cost_of(n, t);
             }
         }
+        const int count_inc = wave_scan_incl(count), cost_inc = wave_scan_incl(cost);
         if (lane == 63) {
             count_sums[w] = count_inc;
             cost_sums[w] = cost_inc;
@@ -113,11 +151,17 @@ struct TileShare {
         // a place on the cost axis, where every row tile stands n_nt times; a range takes the units that start inside it
         const long long axis = (long long)cost_total * n_nt, lo = (long long)cost_base * n_nt, hi = lo + (long long)cost * n_nt;
         const int xcd = blockIdx.x & 7;
+        if (tid == 0) out->expert = -1;               // stays so if the slot tables contradict themselves
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const long long edge = axis * (xcd + q) / 8;
             if (tid == 0 && edge >= axis) edge_unit[q] = n_items * n_nt;
-            if (edge < axis && edge >= lo && edge < hi) {
+            if (edge < axis && edge >= lo && edge < hi && own) {
+                const int in = (int)(edge - lo), full = full_cost() * n_nt;
+                const int tile = in / full < count - 1 ? in / full : count - 1;
+                const int last = cost - (count - 1) * full_cost(), each = tile < count - 1 ? full_cost() : last;
+                edge_unit[q] = (count_base + tile) * n_nt + (in - tile * full + each - 1) / each;
+            } else if (edge < axis && edge >= lo && edge < hi) {
                 int before = count_base;
                 long long at = lo;
                 for (int p = p0; p < p1; ++p) {
@@ -144,6 +188,15 @@ struct TileShare {
                                                int unit, TileItem *out) const
     {
         if (unit < count_base * n_nt || unit >= (count_base + count) * n_nt) return;
+        if (own) {
+            const int in = unit - count_base * n_nt, tile = in / n_nt;
+            out->expert = own_expert;
+            out->column = in - tile * n_nt;
+            out->row_begin = own_row + tile * BM;
+            out->row_end = tile + 1 < count ? own_row + (tile + 1) * BM : own_row + own_rows;
+            out->reuse = own_rows > BM;
+            return;
+        }
         int before = count_base;
         for (int p = p0; p < p1; ++p) {
             const int n = rows_at(slot_offset, slot_expert, p), t = tiles_of(n);
