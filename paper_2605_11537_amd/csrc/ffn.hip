@@ -10,6 +10,7 @@
 //   gemm2     y_perm = h * W2[e]
 // At large batch the list cuts every slot into pieces of 256 rows instead and both products run on
 // the persistent 256 x 256 tile kernel (gemm_dense_bf16.h); the 128-column kernel is then not launched.
+// Between them, with more than 64 rows per slot but too few tiles of that size, both run on 128-row tiles through LDS (ffn_lds_tile.h).
 // At small batch with short slots the 128-column kernel reads the slot tables itself (no list kernel), and so
 // do the binary32 kernel (ffn_f32.h) at any batch and the kernel for few rows (ffn_few_rows.h), which takes
 // either product of a small batch where most of the 128-column kernel's grid would have nothing to do.
@@ -20,6 +21,7 @@
 #include "gemm_dense_bf16.h"
 #include "ffn_f32.h"
 #include "ffn_few_rows.h"
+#include "ffn_lds_tile.h"
 
 namespace moe {
 
@@ -257,11 +259,22 @@ static inline int ffn_max_items(int max_rows, int max_slots) { return max_slots 
 static inline int ffn_max_dense(int max_rows, int max_slots) { return max_rows / DENSE_BM + max_slots + 1; }
 
 // The 256 x 256 tile pays off when slots are long: it is launched when the rows could fill slots of
-// 64 and more on average, the matrix sizes fit its tiling, and the batch can fill the chip.
+// 64 and more on average, the matrix sizes fit its tiling, and its tiles fill the chip.
 static inline bool ffn_use_dense(int max_rows, int max_slots, int K, int N, int schedule)
 {
     return schedule == MOE_SCHEDULE_SLOTS && N % DENSE_BN == 0 && K % DENSE_BK == 0 && K >= DENSE_MIN_K &&
            (long long)max_rows >= 64LL * max_slots && max_rows >= 4096;
+}
+
+// Tiles of the product with fewer columns that can be expected (a slot has one at least): under five eighths of the CUs the others
+// leave less of the chip idle.  Both products, us, this kernel and the one taken instead: 16384 rows over 16 experts, 768 x 3072 (192 tiles) 198, 229;
+// 16384 over 8, 512 x 2048 (128) 95, 85; 10032 over 16, 768 x 3072 (117) 139, 113; 16384 over 8, 256 x 1024 (64) 47, 34; 8192 over 64, 512 x 2048
+// (128) 84, 78.  At d = 1024 half of the CUs are enough: 8192 rows over 8, 1024 x 4096 (128), dealt by Zipf's law 160, 177, evenly 155, 141.
+static inline bool ffn_dense_fills(int max_rows, int max_slots, int d, int F)
+{
+    const long long ranges = max_rows / DENSE_BM > max_slots ? max_rows / DENSE_BM : max_slots;
+    const int n = d < F ? d : F;
+    return ranges * (n / DENSE_BN) >= (n >= 1024 ? 128 : 160);
 }
 
 }  // namespace moe
@@ -352,7 +365,8 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
 
     // both products must take the dense route or neither: the lists split the rows once
     const bool dense = dtype == MOE_BF16 && ffn_use_dense(max_rows, max_slots, d, F, schedule) &&
-                       ffn_use_dense(max_rows, max_slots, F, d, schedule);
+                       ffn_use_dense(max_rows, max_slots, F, d, schedule) && ffn_dense_fills(max_rows, max_slots, d, F);
+    const bool mid = dtype == MOE_BF16 && !dense && ffn_mid(max_rows, max_slots, E, d, F, schedule);
     // Without the dense kernel (small batches, short slots on average, shapes outside its tiling, the
     // experts schedule) the 128-column kernel cuts work items 128 rows high and picks the tile height per
     // item; with it, the 128-column kernel is not launched at all.
@@ -360,7 +374,7 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     // then reads the slot tables itself and the list kernel (a launch of ~5 us in front of the first
     // product) is skipped.  Long slots without the dense kernel keep the list: it cuts them into tiles
     // that run side by side.
-    const bool listless = dtype == MOE_F32 || (!dense && (long long)max_rows <= 64LL * max_slots);
+    const bool listless = mid || dtype == MOE_F32 || (!dense && (long long)max_rows <= 64LL * max_slots);
     if (!listless) {
         hipLaunchKernelGGL(ffn_worklist_kernel, dim3(1), dim3(1024), 0, st, slot_offset, slot_expert, n_slots,
                            max_slots, max_items, schedule, E, dense ? 1 : 0, max_dense, items, dtiles,
@@ -397,9 +411,17 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
                                n_items + 2, (bf16_t *)h);
             MOE_CHECK_LAUNCH("moe_expert_ffn/dense gemm1");
         }
+        auto mid_launch = [&](auto narrow, auto wide, const void *a, const int32_t *rows, int n_rows, const void *w, int K, int N, void *c) {
+            const int nb = mid_strips(max_rows, max_slots, N);
+            hipLaunchKernelGGL((nb == 4 ? wide : narrow), dim3(share_grid(MID_BM, 64 * nb, max_rows, max_slots, schedule, N)),
+                               dim3(SHARE_THREADS), 0, st, (const bf16_t *)a, (const bf16_t *)w, rows, n_rows, K, N, E, slot_offset,
+                               slot_expert, n_slots, max_slots, max_rows, (bf16_t *)c);
+        };
         if (dense) {
             // the dense kernel took every row
-        } else if (listless && ffn_few_rows(max_rows, max_slots, d, F))
+        } else if (mid)
+            mid_launch(ffn_lds_tile_bf16_kernel<true, 2>, ffn_lds_tile_bf16_kernel<true, 4>, x_perm, row_index, n_x_rows, w1, d, F, h);
+        else if (listless && ffn_few_rows(max_rows, max_slots, d, F))
             hipLaunchKernelGGL((by_slots ? ffn_few_rows_bf16_kernel<true, false> : ffn_few_rows_bf16_kernel<true, true>),
                                dim3(few_rows_grid(max_rows, max_slots, schedule, F)), dim3(SHARE_THREADS), 0, st,
                                (const bf16_t *)x_perm, (const bf16_t *)w1, row_index, n_x_rows, d, F, E, slot_offset, slot_expert,
@@ -417,7 +439,9 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
             MOE_CHECK_LAUNCH("moe_expert_ffn/dense gemm2");
         }
         if (dense) {
-        } else if (listless && ffn_few_rows(max_rows, max_slots, F, d))
+        } else if (mid)
+            mid_launch(ffn_lds_tile_bf16_kernel<false, 2>, ffn_lds_tile_bf16_kernel<false, 4>, h, nullptr, max_rows, w2, F, d, y_perm);
+        else if (listless && ffn_few_rows(max_rows, max_slots, F, d))
             hipLaunchKernelGGL((by_slots ? ffn_few_rows_bf16_kernel<false, false> : ffn_few_rows_bf16_kernel<false, true>),
                                dim3(few_rows_grid(max_rows, max_slots, schedule, d)), dim3(SHARE_THREADS), 0, st, (const bf16_t *)h,
                                (const bf16_t *)w2, (const int32_t *)nullptr, max_rows, F, d, E, slot_offset, slot_expert, n_slots,
