@@ -290,6 +290,31 @@ int moe_expert_ffn(const void *x_perm, const int32_t *row_index, const void *w1,
 int moe_combine(const void *y_perm, const void *x, const int32_t *inv, const float *expert_prob,
                 int T, int d, int dtype, int residual, void *out, void *stream);
 
+/* ---------------------------------------------------------------------------------------
+ * moe_layer_forward -- moe_route, moe_plan_dispatch, moe_expert_ffn (rows gathered through perm) and
+ * moe_combine in turn on one stream; with top_k >= 1 moe_route_topk, moe_plan_dispatch, moe_expert_ffn_rows and
+ * moe_combine_topk.  Every field is the argument of that name of those calls; router_E is the router's E,
+ * max_slots is E + budget, plan_idx = NULL plans from the routed ids.  Each step checks its arguments before it
+ * enqueues anything; on error the steps before the failing one have been enqueued.
+ */
+typedef struct moe_layer_args {
+    const void *x, *w_router;
+    const float *b_router;
+    const void *w1, *w2;
+    const int32_t *plan_idx;
+    int32_t *expert_idx;
+    float *expert_prob;
+    int32_t *plan_counts, *replicas, *slot_base, *slot_expert, *n_slots;
+    int32_t *counts, *kept, *expert_offset, *slot_offset, *perm, *inv, *row_token;
+    void *y_perm, *out;
+    void *route_ws, *front_ws, *ffn_ws;
+    size_t route_ws_bytes, front_ws_bytes, ffn_ws_bytes;
+    int T, n_plan, top_k, renormalize; /* top_k = 0: the top-1 calls */
+    int d, F, router_E, E, budget, slot_capacity, policy;
+    int dtype, router_layout, weight_layout, schedule, residual;
+} moe_layer_args;
+int moe_layer_forward(const moe_layer_args *args, void *stream);
+
 /* =======================================================================================
  * Measurement (not part of the method; used by the benchmark only).
  * moe_expert_ffn_timed: moe_expert_ffn_rows (with row_index NULL: moe_expert_ffn, n_x_rows =

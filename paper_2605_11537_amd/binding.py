@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 
 import torch
 
@@ -30,7 +31,7 @@ EXPORTS = (
     "moe_expert_ffn_workspace_bytes", "moe_expert_ffn", "moe_expert_ffn_timed",
     "moe_combine",
     "moe_route_topk", "moe_dispatch_topk", "moe_expert_ffn_rows", "moe_combine_topk",
-    "moe_plan_dispatch_workspace_bytes", "moe_plan_dispatch",
+    "moe_plan_dispatch_workspace_bytes", "moe_plan_dispatch", "moe_layer_forward",
     "moe_measure_sink_bytes", "moe_measure_stream_read", "moe_measure_mfma_bf16_flops", "moe_measure_mfma_bf16",
 )
 
@@ -100,6 +101,7 @@ def lib():
         _lib.moe_measure_mfma_bf16.argtypes = [I, I, P, P]
         _lib.moe_plan_dispatch_workspace_bytes.argtypes = [I, I, I, I]
         _lib.moe_plan_dispatch.argtypes = [P, I, P, I, I, I, I, I, I] + [P] * 12 + [P, S, P]
+        _lib.moe_layer_forward.argtypes = [C.c_char_p, P]
     return _lib
 
 
@@ -328,6 +330,30 @@ def moe_plan_dispatch(plan_idx, expert_idx, E, budget, slot_capacity, policy=0, 
     return po, do
 
 
+# struct moe_layer_args: 25 pointers, 3 sizes, 16 ints in the machine's own layout
+_layer_args = struct.Struct("@25P3N16i")
+
+
+def _layer_forward(layer, x, w_router, b_router, w1, w2, plan_ids, schedule, residual, out, router_layout, top_k, renormalize):
+    """A whole layer forward as one call of the library (moe_layer_forward): the checks, launches and results of the four calls."""
+    dt = _dt(x)
+    if _dt(w_router) != dt or w_router.shape[0] != layer.d:
+        raise ValueError("w_router must be [d, E] (or its packed image) in the dtype of x")
+    pl, dp = layer.plan_out, layer.disp_out
+    out = layer.out if out is None else out
+    idx, prob = layer.route_out
+    ptrs = [_ptr(t) or 0 for t in (
+        x, w_router, b_router, w1, w2, plan_ids, idx, prob, pl["plan_counts"], pl["replicas"], pl["slot_base"],
+        pl["slot_expert"], pl["n_slots"], dp["counts"], dp["kept"], dp["expert_offset"], dp["slot_offset"], dp["perm"], dp["inv"],
+        dp.get("row_token"), layer.y_perm, out, layer.route_ws, layer.front_ws, layer.ffn_ws)]
+    _check(lib().moe_layer_forward(_layer_args.pack(
+        *ptrs, layer.route_ws.numel(), layer.front_ws.numel(), layer.ffn_ws.numel(), layer.T,
+        0 if plan_ids is None else plan_ids.numel(), top_k, int(bool(renormalize)), layer.d, layer.F, w_router.shape[1], layer.E, layer.R,
+        layer.C, layer.policy, dt, router_layout, LAYOUT_PACKED if dt == MOE_BF16 else LAYOUT_PLAIN, schedule, int(residual)),
+        _stream()))
+    return out
+
+
 # --------------------------------------------------------------------------- measurement
 def measure_ceilings(read_bytes=1 << 30, mfma_iters=4000, repeats=5):
     """Event-timed ceilings of this machine for kernels shaped like the library's (see the header's
@@ -467,6 +493,9 @@ class MoeLayerTopK:
     def forward(self, x, w_router, b_router, w1, w2, plan_ids=None, schedule=SCHEDULE_SLOTS, residual=0,
                 out=None, router_layout=LAYOUT_PLAIN, marks=None, ffn_events=None):
         """marks, ffn_events: as in MoeLayer.forward."""
+        if marks is None and ffn_events is None and x.shape == (self.T, self.d) and (plan_ids is None or plan_ids.numel()):
+            return _layer_forward(self, x, w_router, b_router, w1, w2, plan_ids, schedule, residual, out, router_layout, int(self.k),
+                                  self.renormalize)
         if marks is not None:
             marks[0].record()
         idx, wgt, _ = moe_route_topk(x, w_router, b_router, self.k, self.renormalize, out=self.route_out,
@@ -521,6 +550,9 @@ class MoeLayer:
         marks: five torch.cuda.Event objects recorded before the router and after each of the four
         calls (router, plan + dispatch, expert FFN, combine), for per-call timing.
         ffn_events: three events recorded around the two products of the expert FFN (measurement only)."""
+        if (plan is None and fuse_gather and marks is None and ffn_events is None and x.shape == (self.T, self.d)
+                and (plan_ids is None or plan_ids.numel())):
+            return _layer_forward(self, x, w_router, b_router, w1, w2, plan_ids, schedule, residual, out, router_layout, 0, False)
         if marks is not None:
             marks[0].record()
         idx, prob, _ = moe_route(x, w_router, b_router, out=self.route_out, ws=self.route_ws,
