@@ -99,6 +99,19 @@ __device__ __forceinline__ bool grouped_tile_of(int bid, int n_items, int n_nt, 
     return true;
 }
 
+// inclusive sums over the wavefront, on the data-parallel-primitive path: rows of 16 by shifts, then the last lane of a row (of the
+// first two) added to the lanes after it
+__device__ __forceinline__ int wave_scan_incl(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
 // Exclusive scan of one int per thread over a 1024-thread workgroup.  Returns the prefix and
 // leaves the grand total in *total_out (LDS).  wave_sums is LDS scratch of 16 ints.
 __device__ __forceinline__ int block_scan_excl_1024(int v, int *wave_sums, int *total_out)

@@ -3,12 +3,16 @@
 // Three kernels, no global atomics, so the permutation is the stable one whatever the
 // hardware scheduling:
 //   hist     one workgroup per 1024 tokens: LDS histogram of expert ids -> block_hist[b][e]
-//   permute  one workgroup per 1024 tokens: per expert, prefix over the earlier token blocks,
+//   permute  one workgroup of 1024 threads per 1024 tokens: per expert, total and prefix over the earlier token blocks
+//            (the blocks dealt to 4 .. 16 threads per expert, so that their histograms are one memory round trip),
 //            kept counts, expert offsets (scan over experts), slot offsets (balanced split
 //            per expert); then the rank of every token among the tokens of its expert
 //            = prefix over earlier blocks + prefix over earlier 64-token chunks of the block
 //            (LDS table) + rank inside the chunk (wavefront ballots, one per id bit);
 //            writes inv / perm
+//            Latency is all it is (one round trip for the loads, one for the stores, a dozen steps in LDS between): with 256 threads, whose
+//            histogram sums were four trips and whose ranks four rounds, 65536 ids over 256 experts took 22.8 us with the plan and
+//            16.6 without, hist included; now 15.0 and 10.1.
 //   gather   whole-chip copy of the kept rows, x_perm[pos] = x[perm[pos]], 16-byte accesses
 #include <mutex>
 
@@ -21,49 +25,55 @@ constexpr int DSP_THREADS = 256;
 constexpr int DSP_TOKENS = 1024;  // tokens per workgroup
 constexpr int DSP_CHUNKS = DSP_TOKENS / WAVE;
 
-__global__ __launch_bounds__(DSP_THREADS) void dispatch_hist_kernel(const int32_t *__restrict__ idx, int T,
-                                                                    int E, int32_t *__restrict__ block_hist)
+// lanes of the wavefront with this lane's id (0 for an id that does not count)
+__device__ __forceinline__ unsigned long long same_id_lanes(int e, bool valid, int nbits)
 {
-    __shared__ int hist[MOE_MAX_EXPERTS];
-    for (int e = threadIdx.x; e < E; e += DSP_THREADS) hist[e] = 0;
-    __syncthreads();
-    int base = blockIdx.x * DSP_TOKENS;
-#pragma unroll
-    for (int i = 0; i < DSP_TOKENS / DSP_THREADS; ++i) {
-        int t = base + i * DSP_THREADS + threadIdx.x;
-        if (t < T) {
-            int e = idx[t];
-            if (e >= 0 && e < E) atomicAdd(&hist[e], 1);
-        }
+    unsigned long long mask = __ballot(valid);
+    for (int b = 0; b < nbits; ++b) {
+        const bool bit = (e >> b) & 1;
+        const unsigned long long bal = __ballot(bit);
+        mask &= bit ? bal : ~bal;
     }
-    __syncthreads();
-    for (int e = threadIdx.x; e < E; e += DSP_THREADS) block_hist[(size_t)blockIdx.x * E + e] = hist[e];
+    return valid ? mask : 0ull;
 }
 
-// exclusive scan over E <= 1024 values held 4 per thread (thread t owns experts 4t .. 4t+3)
-__device__ __forceinline__ void block_scan4_256(const int (&v)[4], int (&excl)[4], int *wave_sums, int *total_out)
+// ids that share a wavefront are counted with ballots: a hot expert does not serialise the LDS atomics
+__global__ __launch_bounds__(DSP_TOKENS) void dispatch_hist_kernel(const int32_t *__restrict__ idx, int T, int E, int nbits,
+                                                                   int32_t *__restrict__ block_hist)
+{
+    __shared__ int hist[MOE_MAX_EXPERTS];
+    const int tid = threadIdx.x, t = blockIdx.x * DSP_TOKENS + tid;
+    const int e = t < T ? idx[t] : -1;
+    if (tid < E) hist[tid] = 0;
+    __syncthreads();
+    const unsigned long long mask = same_id_lanes(e, e >= 0 && e < E, nbits);
+    if (mask && (mask & ((1ull << (tid & 63)) - 1ull)) == 0) atomicAdd(&hist[e], __popcll(mask));
+    __syncthreads();
+    if (tid < E) block_hist[(size_t)blockIdx.x * E + tid] = hist[tid];
+}
+
+// Exclusive scans of two values per thread over the workgroup of 1024; sums: LDS scratch of 32 ints.
+__device__ __forceinline__ void block_scan2_1024(int v0, int v1, int &ex0, int &ex1, int &tot0, int &tot1, int *sums)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int local = v[0] + v[1] + v[2] + v[3];
-    int inc = local;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int n = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += n;
-    }
-    if (lane == 63) wave_sums[w] = inc;
-    __syncthreads();
-    int base = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) base += i < w ? wave_sums[i] : 0;
-    if (threadIdx.x == DSP_THREADS - 1) *total_out = base + inc;
-    int run = base + inc - local;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        excl[i] = run;
-        run += v[i];
+    const int i0 = wave_scan_incl(v0), i1 = wave_scan_incl(v1);
+    if (lane == 63) {
+        sums[w] = i0;
+        sums[16 + w] = i1;
     }
     __syncthreads();
+    int b0 = 0, b1 = 0;
+    tot0 = tot1 = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int a = sums[i], b = sums[16 + i];
+        b0 += i < w ? a : 0;
+        b1 += i < w ? b : 0;
+        tot0 += a;
+        tot1 += b;
+    }
+    ex0 = b0 + i0 - v0;
+    ex1 = b1 + i1 - v1;
 }
 
 // One workgroup per 1024 tokens.  Every workgroup first rebuilds, from the per-block
@@ -82,7 +92,7 @@ struct PlanArgs {
 };
 
 template <int PPL>
-__global__ __launch_bounds__(DSP_THREADS) void dispatch_permute_kernel(
+__global__ __launch_bounds__(DSP_TOKENS) void dispatch_permute_kernel(
     const int32_t *__restrict__ idx, const int32_t *__restrict__ replicas, int T, int E, int nbits, int C, int nb,
     int max_slots, const int32_t *__restrict__ block_hist, int32_t *__restrict__ counts, int32_t *__restrict__ kept,
     int32_t *__restrict__ expert_offset, int32_t *__restrict__ slot_offset, int32_t *__restrict__ perm,
@@ -90,176 +100,130 @@ __global__ __launch_bounds__(DSP_THREADS) void dispatch_permute_kernel(
 {
     __shared__ unsigned short chunk_cnt[DSP_CHUNKS][MOE_MAX_EXPERTS];
     __shared__ int before_e[MOE_MAX_EXPERTS];   // tokens of e in earlier blocks
+    __shared__ int tot_e[MOE_MAX_EXPERTS];      // and in all
     __shared__ int eoff_e[MOE_MAX_EXPERTS];     // first permuted row of e
     __shared__ int cap_e[MOE_MAX_EXPERTS];      // kept count of e
-    __shared__ int wave_sums[4];
-    __shared__ int total_k, total_p;
+    __shared__ int sums[32];
     __shared__ int plan_hist[PPL > 0 ? MOE_MAX_EXPERTS : 1];
     __shared__ int rep[PPL > 0 ? MOE_MAX_EXPERTS : 1];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int base = blockIdx.x * DSP_TOKENS;
-    for (int i = tid; i < DSP_CHUNKS * E; i += DSP_THREADS) chunk_cnt[i / E][i % E] = 0;
 
-    // ---- tables.  Pass 1: thread per expert (strided), coalesced over the block histograms.
-    for (int e = tid; e < E; e += DSP_THREADS) {
-        int tot = 0, bef = 0;
-        // 16 loads in flight per thread: at 64 blocks this loop is four memory round trips instead of eight
+    // ---- Everything this workgroup reads is asked for up front: its tokens' ids, and the block histograms, (expert, part of the blocks)
+    // per thread.
+    const int t = blockIdx.x * DSP_TOKENS + tid;
+    int id = t < T ? idx[t] : -1;
+    const int given = PPL == 0 && replicas && tid < E ? replicas[tid] : 1;
+    const int n_parts = E <= DSP_TOKENS / 16 ? 16 : E <= DSP_TOKENS / 8 ? 8 : E <= DSP_TOKENS / 4 ? 4 : E <= DSP_TOKENS / 2 ? 2 : 1;
+    const int span = DSP_TOKENS / n_parts, e_own = tid % span, part = tid / span;     // powers of two
+    int tot = 0, bef = 0;
+    if (e_own < E) {
 #pragma unroll 16
-        for (int b = 0; b < nb; ++b) {
-            int v = block_hist[(size_t)b * E + e];
+        for (int b = part; b < nb; b += n_parts) {
+            const int v = block_hist[(size_t)b * E + e_own];
             bef += b < (int)blockIdx.x ? v : 0;
             tot += v;
         }
-        before_e[e] = bef;
-        eoff_e[e] = tot;      // total count, replaced by the offset below
-        if (PPL > 0) {
-            int h = tot;
-            if (pa.plan_partial) {
-                h = 0;
-                for (int b = 0; b < pa.n_partial; ++b) h += pa.plan_partial[(size_t)b * E + e];
-            }
-            plan_hist[e] = h;
-        } else {
-            int r = replicas ? replicas[e] : 1;
-            if (r < 1) r = 1;
-            long long cap = (long long)r * C;
-            cap_e[e] = (long long)tot < cap ? tot : (int)cap;
-        }
     }
-    // ---- ranks inside the block.  With the plan made in here, wavefront 0 is busy with the allocation (a
-    // dependent chain of microseconds) and the other three rank all 16 chunks meanwhile; otherwise all four
-    // wavefronts take four chunks each.
-    constexpr int RANK_WAVES = PPL > 0 ? DSP_THREADS / WAVE - 1 : DSP_THREADS / WAVE;
-    constexpr int RANK_ROUNDS = (DSP_CHUNKS + RANK_WAVES - 1) / RANK_WAVES;
-    const int rank_w = PPL > 0 ? w - 1 : w;          // -1: this wavefront ranks nothing
-    int my_e[RANK_ROUNDS], my_rank[RANK_ROUNDS];
-    auto rank_chunks = [&]() {
-#pragma unroll
-        for (int rd = 0; rd < RANK_ROUNDS; ++rd) {
-            const int c = rd * RANK_WAVES + rank_w;
-            my_e[rd] = -1;
-            my_rank[rd] = 0;
-            if (c >= DSP_CHUNKS) continue;            // uniform per wavefront
-            int t = base + c * WAVE + lane;
-            bool valid = t < T;
-            int e = valid ? idx[t] : 0;
-            valid = valid && e >= 0 && e < E;
-            unsigned long long mask = __ballot(valid);
-            for (int b = 0; b < nbits; ++b) {
-                bool bit = (e >> b) & 1;
-                unsigned long long bal = __ballot(bit);
-                mask &= bit ? bal : ~bal;
-            }
-            int rank = __popcll(mask & ((1ull << lane) - 1ull));
-            if (valid && rank == 0) chunk_cnt[c][e] = (unsigned short)__popcll(mask);
-            my_e[rd] = valid ? e : -1;
-            my_rank[rd] = rank;
-        }
-    };
-    if (PPL > 0) {
-        for (int e = E + tid; e < MOE_MAX_EXPERTS; e += DSP_THREADS) plan_hist[e] = 0;
-        __syncthreads();                  // the chunk table is clear, the plan's histogram complete
-        if (tid < WAVE)
-            plan_allocate_wave<(PPL > 0 ? PPL : 1)>(plan_hist, rep, pa.n_plan_ids, E, pa.R, C, pa.policy, pa.replicas,
-                                                    pa.plan_counts, blockIdx.x == 0);
-        else
-            rank_chunks();
-        __syncthreads();
-        for (int e = tid; e < E; e += DSP_THREADS) {
-            const long long cap = (long long)rep[e] * C;
-            cap_e[e] = (long long)eoff_e[e] < cap ? eoff_e[e] : (int)cap;
-        }
-    }
+    int planned = 0;
+    if (PPL > 0 && pa.plan_partial && e_own < E)
+        for (int b = part; b < pa.n_partial; b += n_parts) planned += pa.plan_partial[(size_t)b * E + e_own];
+    for (int i = tid; i < DSP_CHUNKS * E; i += DSP_TOKENS) chunk_cnt[i / E][i % E] = 0;
+    before_e[tid] = 0;
+    tot_e[tid] = 0;
+    if (PPL > 0) plan_hist[tid] = 0;
     __syncthreads();
-    // Pass 2: thread t owns experts 4t..4t+3 for the scans over experts
-    int n4[4], r4[4], k4[4], off4[4], sb4[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int e = tid * 4 + i;
-        n4[i] = e < E ? eoff_e[e] : 0;
-        k4[i] = e < E ? cap_e[e] : 0;
-        int r = (e < E) ? (PPL > 0 ? rep[e] : (replicas ? replicas[e] : 1)) : 0;
-        if (e < E && r < 1) r = 1;
-        r4[i] = r;
-    }
-    __syncthreads();
-    block_scan4_256(k4, off4, wave_sums, &total_k);
-    block_scan4_256(r4, sb4, wave_sums, &total_p);
-    const int K = total_k, P = total_p;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int e = tid * 4 + i;
-        if (e < E) eoff_e[e] = off4[i];
-    }
-    if (blockIdx.x == 0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            int e = tid * 4 + i;
-            if (e < E) {
-                counts[e] = n4[i];
-                kept[e] = k4[i];
-                expert_offset[e] = off4[i];
-                if (slot_offset) {
-                    int q = k4[i] / r4[i], rem = k4[i] % r4[i];
-                    for (int k = 0; k < r4[i]; ++k) {
-                        int p = sb4[i] + k;
-                        if (p <= max_slots) slot_offset[p] = off4[i] + k * q + (k < rem ? k : rem);
-                    }
-                }
-                if (PPL > 0) {
-                    if (pa.slot_base) pa.slot_base[e] = sb4[i];
-                    if (pa.slot_expert)
-                        for (int k = 0; k < r4[i]; ++k) pa.slot_expert[sb4[i] + k] = e;
-                }
-            }
-        }
-        if (tid == 0) expert_offset[E] = K;
-        if (slot_offset)
-            for (int p = P + tid; p <= max_slots; p += DSP_THREADS) slot_offset[p] = K;
+    if (e_own < E) {
+        if (tot) atomicAdd(&tot_e[e_own], tot);
+        if (bef) atomicAdd(&before_e[e_own], bef);
         if (PPL > 0) {
-            if (tid == 0) {
-                if (pa.slot_base) pa.slot_base[E] = P;
-                if (pa.n_slots) pa.n_slots[0] = P;
-            }
-            if (pa.slot_expert)
-                for (int p = P + tid; p < E + pa.R; p += DSP_THREADS) pa.slot_expert[p] = -1;
+            const int h = pa.plan_partial ? planned : tot;
+            if (h) atomicAdd(&plan_hist[e_own], h);
         }
     }
-    if (T == 0) return;
+    // ---- rank of every token inside its wavefront's 64
+    const bool valid = id >= 0 && id < E;
+    const unsigned long long mask = same_id_lanes(id, valid, nbits);
+    const int rank = __popcll(mask & ((1ull << lane) - 1ull));
+    if (valid && rank == 0) chunk_cnt[w][id] = (unsigned short)__popcll(mask);
+    __syncthreads();
 
-    if (PPL == 0) rank_chunks();
-    __syncthreads();
-    for (int e = tid; e < E; e += DSP_THREADS) {
-        int run = 0;
+    // ---- wavefront 0: the plan; the others: per expert, prefix of the chunk counts
+    if (PPL > 0 && tid < WAVE) {
+        plan_allocate_wave<(PPL > 0 ? PPL : 1)>(plan_hist, rep, pa.n_plan_ids, E, pa.R, C, pa.policy, pa.replicas, pa.plan_counts,
+                                                blockIdx.x == 0);
+    } else {
+        constexpr int FIRST = PPL > 0 ? WAVE : 0;
+        for (int e = tid - FIRST; e < E; e += DSP_TOKENS - FIRST) {
+            int v[DSP_CHUNKS];
 #pragma unroll
-        for (int c = 0; c < DSP_CHUNKS; ++c) {
-            int v = chunk_cnt[c][e];
-            chunk_cnt[c][e] = (unsigned short)run;
-            run += v;
+            for (int c = 0; c < DSP_CHUNKS; ++c) v[c] = chunk_cnt[c][e];
+            int run = 0;
+#pragma unroll
+            for (int c = 0; c < DSP_CHUNKS; ++c) {
+                chunk_cnt[c][e] = (unsigned short)run;
+                run += v[c];
+            }
         }
     }
+    if (PPL > 0) __syncthreads();
+    // ---- thread e owns expert e
+    const int r_e = tid < E ? (PPL > 0 ? rep[tid] : given < 1 ? 1 : given) : 0;
+    const int n_e = tid < E ? tot_e[tid] : 0;
+    const long long cap = (long long)r_e * C;
+    const int k_e = (long long)n_e < cap ? n_e : (int)cap;
+    int off_e, sb_e, K, P;
+    block_scan2_1024(k_e, r_e, off_e, sb_e, K, P, sums);
+    if (tid < E) {
+        eoff_e[tid] = off_e;
+        cap_e[tid] = k_e;
+    }
     __syncthreads();
-#pragma unroll
-    for (int rd = 0; rd < RANK_ROUNDS; ++rd) {
-        int c = rd * RANK_WAVES + rank_w;
-        if (rank_w < 0 || c >= DSP_CHUNKS) continue;
-        int t = base + c * WAVE + lane;
+    if (T > 0) {
         int dest = -1;
-        int e = my_e[rd];
-        if (e >= 0) {
-            int j = before_e[e] + chunk_cnt[c][e] + my_rank[rd];
-            if (j < cap_e[e]) dest = eoff_e[e] + j;
+        if (valid) {
+            const int j = before_e[id] + chunk_cnt[w][id] + rank;
+            if (j < cap_e[id]) dest = eoff_e[id] + j;
         }
         if (t < T) {
             inv[t] = dest;
             if (dest >= 0) perm[dest] = t;
             if (t >= K) perm[t] = -1;
-            if (row_token) {        // top-k: entry t is assignment (t / n_tokens, t % n_tokens)
+            if (row_token) {            // top-k: entry t is assignment (t / n_tokens, t % n_tokens)
                 if (dest >= 0) row_token[dest] = t % n_tokens;
                 if (t >= K) row_token[t] = -1;
             }
         }
     }
+    if (blockIdx.x != 0) return;
+    if (tid < E) {
+        counts[tid] = n_e;
+        kept[tid] = k_e;
+        expert_offset[tid] = off_e;
+        if (PPL > 0 && pa.slot_base) pa.slot_base[tid] = sb_e;
+    }
+    // slot tables: an expert's slots are written by its whole wavefront, 64 at a time
+    const int q = r_e > 0 ? k_e / r_e : 0, rem = r_e > 0 ? k_e % r_e : 0;
+    auto write_slot = [&](int e, int p, int k, int first, int quot, int rest) {
+        if (slot_offset && p <= max_slots) slot_offset[p] = first + k * quot + (k < rest ? k : rest);
+        if (PPL > 0 && pa.slot_expert) pa.slot_expert[p] = e;
+    };
+    if (r_e > 0) write_slot(tid, sb_e, 0, off_e, q, rem);
+    for (unsigned long long more = __ballot(r_e > 1); more; more &= more - 1) {
+        const int l = __builtin_ctzll(more);                     // uniform
+        const int r = __builtin_amdgcn_readlane(r_e, l), p0 = __builtin_amdgcn_readlane(sb_e, l);
+        const int first = __builtin_amdgcn_readlane(off_e, l), quot = __builtin_amdgcn_readlane(q, l);
+        const int rest = __builtin_amdgcn_readlane(rem, l);
+        for (int k = 1 + lane; k < r; k += WAVE) write_slot(w * WAVE + l, p0 + k, k, first, quot, rest);
+    }
+    if (tid == 0) {
+        expert_offset[E] = K;
+        if (PPL > 0 && pa.slot_base) pa.slot_base[E] = P;
+        if (PPL > 0 && pa.n_slots) pa.n_slots[0] = P;
+    }
+    if (slot_offset)
+        for (int p = P + tid; p <= max_slots; p += DSP_TOKENS) slot_offset[p] = K;
+    if (PPL > 0 && pa.slot_expert)
+        for (int p = P + tid; p < E + pa.R; p += DSP_TOKENS) pa.slot_expert[p] = -1;
 }
 
 // x_perm[pos] = x[perm[pos]] for pos < K (K is not read: the permutation ends in -1 entries).  32 lanes per row, 8 rows per workgroup, 16-byte
@@ -314,16 +278,16 @@ int dispatch_planned_launch(const int32_t *expert_idx, int T, int n_tokens, int 
                             int32_t *row_token, hipStream_t st, const char *who)
 {
     const int nb = ceil_div(T, DSP_TOKENS);
-    if (nb > 0) {
-        hipLaunchKernelGGL(dispatch_hist_kernel, dim3(nb), dim3(DSP_THREADS), 0, st, expert_idx, T, E, block_hist);
-        MOE_CHECK_LAUNCH(who);
-    }
     int nbits = 0;
     while ((1 << nbits) < E) ++nbits;
+    if (nb > 0) {
+        hipLaunchKernelGGL(dispatch_hist_kernel, dim3(nb), dim3(DSP_TOKENS), 0, st, expert_idx, T, E, nbits, block_hist);
+        MOE_CHECK_LAUNCH(who);
+    }
     PlanArgs pa{plan_partial, n_partial, n_plan_ids, budget, policy, plan_counts, replicas, slot_base, slot_expert,
                 n_slots};
     auto kern = E <= 128 ? dispatch_permute_kernel<2> : E <= 256 ? dispatch_permute_kernel<4> : dispatch_permute_kernel<16>;
-    hipLaunchKernelGGL(kern, dim3(nb > 0 ? nb : 1), dim3(DSP_THREADS), 0, st, expert_idx, (const int32_t *)nullptr, T, E,
+    hipLaunchKernelGGL(kern, dim3(nb > 0 ? nb : 1), dim3(DSP_TOKENS), 0, st, expert_idx, (const int32_t *)nullptr, T, E,
                        nbits, slot_capacity, nb, E + budget, block_hist, counts, kept, expert_offset, slot_offset, perm,
                        inv, n_tokens > 0 ? n_tokens : 1, row_token, pa);
     MOE_CHECK_LAUNCH(who);
@@ -409,14 +373,14 @@ static int dispatch_checked(const char *who, const void *x, const int32_t *exper
     hipStream_t st = (hipStream_t)stream;
     int nb = ceil_div(T, DSP_TOKENS);
     int32_t *block_hist = (int32_t *)ws;
+    int nbits = 0;
+    while ((1 << nbits) < E) ++nbits;
     if (nb > 0) {
-        hipLaunchKernelGGL(dispatch_hist_kernel, dim3(nb), dim3(DSP_THREADS), 0, st, expert_idx, T, E, block_hist);
+        hipLaunchKernelGGL(dispatch_hist_kernel, dim3(nb), dim3(DSP_TOKENS), 0, st, expert_idx, T, E, nbits, block_hist);
         MOE_CHECK_LAUNCH(who);
     }
     {
-        int nbits = 0;
-        while ((1 << nbits) < E) ++nbits;
-        hipLaunchKernelGGL(dispatch_permute_kernel<0>, dim3(nb > 0 ? nb : 1), dim3(DSP_THREADS), 0, st, expert_idx,
+        hipLaunchKernelGGL(dispatch_permute_kernel<0>, dim3(nb > 0 ? nb : 1), dim3(DSP_TOKENS), 0, st, expert_idx,
                            replicas, T, E, nbits, slot_capacity, nb, max_slots, block_hist, counts, kept,
                            expert_offset, slot_offset, perm, inv, n_tokens > 0 ? n_tokens : 1, row_token, PlanArgs{});
         MOE_CHECK_LAUNCH(who);

@@ -23,19 +23,6 @@ __device__ __forceinline__ int tile_cost(int rows) { return TILE_COST_TILE + TIL
 // a row tile side by side.  The order is cut into 8 ranges of equal COST, one per XCD; ranges of equal length left the XCDs that
 // drew the full tiles of the hot experts with 1.5 times the work of the others.  Each XCD's workgroups with work come first in
 // the grid: two tiles on one CU take twice as long as on two, and the launch order is what spreads them.
-// inclusive sums over the wavefront, on the data-parallel-primitive path: rows of 16 by shifts, then the last lane of a row (of the
-// first two) added to the lanes after it
-__device__ __forceinline__ int wave_scan_incl(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
-    return v;
-}
-
 template <int BM>
 struct TileShare {
     // this thread's slots and the tiles and cost before them

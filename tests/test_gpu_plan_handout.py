@@ -1,0 +1,61 @@
+"""The hand-out of the slots that the floors of the plan leave, several per step, and the dispatch tables made beside it, against the oracle: equal
+loads (ties by id), one expert far ahead (several slots in a row), more experts above the bar than slots, every size class of the allocating
+wavefront, plan and dispatch apart and in one call, one block of tokens to many."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+def _ids(kind, T, E, rng):
+    if kind == "equal":
+        return np.arange(T) % E
+    if kind == "one":
+        return np.where(rng.random(T) < 0.7, E // 2, rng.integers(0, E, T))
+    w = np.arange(1, E + 1.0) ** -{"zipf": 1.0, "steep": 2.0}[kind]
+    return rng.permutation(E)[rng.choice(E, T, p=w / w.sum())]
+
+
+@pytest.mark.parametrize("kind", ["equal", "one", "zipf", "steep"])
+@pytest.mark.parametrize("T,E,R,C", [
+    (500, 5, 3, 7), (4096, 128, 16, 40), (8192, 256, 200, 9), (8193, 60, 31, 30), (12288, 128, 16, 120), (20000, 64, 100, 50),
+    (30000, 256, 64, 70), (9000, 500, 90, 11), (17000, 1024, 333, 10),
+])
+def test_plan_and_dispatch(T, E, R, C, kind):
+    import paper_2605_11537_amd as moe
+    rng = np.random.default_rng(T + E)
+    ids = _ids(kind, T, E, rng).astype(np.int32)
+    other = np.roll(ids, 3)[: T // 2].copy()
+    for plan_ids in (ids, other):
+        ref = oracle.plan(plan_ids, E, R, C)
+        dev = to_dev(ids)
+        same = dev if plan_ids is ids else to_dev(plan_ids)
+        pl, dp = moe.moe_plan_dispatch(same, dev, E, R, C)
+        alone = moe.replica_plan(same, E, R, C)
+        apart = moe.moe_dispatch(None, dev, alone["replicas"], E, C, E + R, shape=(T, 8), dtype=torch.float32)
+        for got in (pl, alone):
+            assert (to_host(got["replicas"]) == ref["replicas"]).all() and (to_host(got["plan_counts"]) == ref["counts"]).all()
+            assert (to_host(got["slot_base"]) == ref["slot_base"]).all() and int(got["n_slots"][0]) == ref["n_slots"]
+            assert (to_host(got["slot_expert"]) == ref["slot_expert"]).all()
+        counts = np.bincount(ids, minlength=E)
+        kept = np.minimum(counts, ref["replicas"].astype(np.int64) * C)
+        first = np.concatenate([[0], np.cumsum(kept)])
+        order = np.argsort(ids, kind="stable")
+        rank = np.empty(T, np.int64)
+        rank[order] = np.arange(T) - np.repeat(np.concatenate([[0], np.cumsum(counts)[:-1]]), counts)
+        inv = np.where(rank < kept[ids], first[ids] + rank, -1)
+        perm = np.full(T, -1, np.int64)
+        perm[inv[inv >= 0]] = np.nonzero(inv >= 0)[0]
+        slots = [first[-1]] * (E + R + 1)
+        for e in range(E):
+            q, rem = divmod(int(kept[e]), int(ref["replicas"][e]))
+            for j in range(ref["replicas"][e]):
+                slots[ref["slot_base"][e] + j] = first[e] + j * q + min(j, rem)
+        for got in (dp, apart):
+            for key, want in (("counts", counts), ("kept", kept), ("expert_offset", first), ("inv", inv), ("perm", perm),
+                              ("slot_offset", slots)):
+                assert (to_host(got[key]) == np.asarray(want)).all(), key
