@@ -270,11 +270,18 @@ static inline bool ffn_use_dense(int max_rows, int max_slots, int K, int N, int 
 // leave less of the chip idle.  Both products, us, this kernel and the one taken instead: 16384 rows over 16 experts, 768 x 3072 (192 tiles) 198, 229;
 // 16384 over 8, 512 x 2048 (128) 95, 85; 10032 over 16, 768 x 3072 (117) 139, 113; 16384 over 8, 256 x 1024 (64) 47, 34; 8192 over 64, 512 x 2048
 // (128) 84, 78.  At d = 1024 half of the CUs are enough: 8192 rows over 8, 1024 x 4096 (128), dealt by Zipf's law 160, 177, evenly 155, 141.
-static inline bool ffn_dense_fills(int max_rows, int max_slots, int d, int F)
+// Nor is it taken where the weight stream binds (ffn_weight_stream) and a slot is a tile of the 128-column kernel: that one keeps more weights in
+// flight.  Both products, us, this kernel and that: 768 x 3072, 128 experts, 12288 rows of which a plan keeps 7834 299, 262; 64 experts,
+// 8192 rows, 4705 kept 166, 141; 256 experts, 30000 rows, 14826 kept 546, 519; 512 x 2048, 256 experts, 20000 rows, 12567 kept 262, 227; 1024 x 4096,
+// 32 experts, 4096 rows, 2548 kept 163, 141.  At d = 1024 with a tile for every CU they are even (64 experts, 8192 rows: 246, 238 and 245, 267),
+// with more than 128 rows per slot a second tile reads the weights again (64 x 140 rows: 170, 210).
+static inline bool ffn_dense_fills(int max_rows, int max_slots, int E, int d, int F)
 {
     const long long ranges = max_rows / DENSE_BM > max_slots ? max_rows / DENSE_BM : max_slots;
     const int n = d < F ? d : F;
-    return ranges * (n / DENSE_BN) >= (n >= 1024 ? 128 : 160);
+    const long long tiles = ranges * (n / DENSE_BN);
+    if (ffn_weight_stream(E, d, F) && (long long)max_rows <= 128LL * max_slots && (n < 1024 || tiles < 256)) return false;
+    return tiles >= (n >= 1024 ? 128 : 160);
 }
 
 }  // namespace moe
@@ -365,7 +372,7 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
 
     // both products must take the dense route or neither: the lists split the rows once
     const bool dense = dtype == MOE_BF16 && ffn_use_dense(max_rows, max_slots, d, F, schedule) &&
-                       ffn_use_dense(max_rows, max_slots, F, d, schedule) && ffn_dense_fills(max_rows, max_slots, d, F);
+                       ffn_use_dense(max_rows, max_slots, F, d, schedule) && ffn_dense_fills(max_rows, max_slots, E, d, F);
     const bool mid = dtype == MOE_BF16 && !dense && ffn_mid(max_rows, max_slots, E, d, F, schedule);
     // Without the dense kernel (small batches, short slots on average, shapes outside its tiling, the
     // experts schedule) the 128-column kernel cuts work items 128 rows high and picks the tile height per
