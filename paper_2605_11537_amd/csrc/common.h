@@ -99,6 +99,49 @@ __device__ __forceinline__ bool grouped_tile_of(int bid, int n_items, int n_nt, 
     return true;
 }
 
+// Value of the partner lane in the steps of a reduction over aligned groups of 8, 16, 32 or 64 lanes: lane ^ 1, lane ^ 2 inside quads, the
+// mirror image inside 8 and inside 16 lanes (data-parallel-primitive moves: no LDS round trip), then lane ^ 16 and lane ^ 32.  After each step
+// every lane of the group so far holds the same result, so which lane of the other half is met does not matter.
+template <int STEP>
+__device__ __forceinline__ int group_exchange(int x)
+{
+    if (STEP == 0) return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false);
+    if (STEP == 1) return __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, false);
+    if (STEP == 2) return __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);
+    if (STEP == 3) return __builtin_amdgcn_update_dpp(0, x, 0x140, 0xf, 0xf, false);
+    return __shfl_xor(x, 1 << STEP, 64);
+}
+template <int STEP>
+__device__ __forceinline__ float group_exchange(float x)
+{
+    return __int_as_float(group_exchange<STEP>(__float_as_int(x)));
+}
+
+// larger value, lower index among equals
+__device__ __forceinline__ void argmax_merge(float &v, int &i, float ov, int oi)
+{
+    if (ov > v || (ov == v && oi < i)) {
+        v = ov;
+        i = oi;
+    }
+}
+template <int LANES, int STEP = 0>
+__device__ __forceinline__ void argmax_over(float &v, int &i)
+{
+    if constexpr ((1 << STEP) < LANES) {
+        const float ov = group_exchange<STEP>(v);
+        const int oi = group_exchange<STEP>(i);
+        argmax_merge(v, i, ov, oi);
+        argmax_over<LANES, STEP + 1>(v, i);
+    }
+}
+template <int LANES, int STEP = 0>
+__device__ __forceinline__ float sum_over(float v)
+{
+    if constexpr ((1 << STEP) < LANES) return sum_over<LANES, STEP + 1>(v + group_exchange<STEP>(v));
+    else return v;
+}
+
 // inclusive sums over the wavefront, on the data-parallel-primitive path: rows of 16 by shifts, then the last lane of a row (of the
 // first two) added to the lanes after it
 __device__ __forceinline__ int wave_scan_incl(int v)

@@ -16,14 +16,6 @@ namespace moe {
 constexpr int RT_DEPTH = 128;   // d is a multiple of this
 constexpr int RT_BK = 64;       // k chunk
 
-__device__ __forceinline__ void argmax_merge(float &v, int &i, float ov, int oi)
-{
-    if (ov > v || (ov == v && oi < i)) {
-        v = ov;
-        i = oi;
-    }
-}
-
 // in [K][N] bf16 row-major -> packed image, 16-byte piece ((n/32)*(K/8) + k/8)*32 + n%32
 __global__ __launch_bounds__(256) void pack_matrix_kernel(const bf16_t *__restrict__ in, int K, int N,
                                                           uint4 *__restrict__ out)
@@ -96,18 +88,16 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void route_mfma_kernel(const bf16_
         float best = lv[0];
         int bi = sub;
 #pragma unroll
-        for (int i = 1; i < PER; ++i) argmax_merge(best, bi, lv[i], sub + 8 * i);
-#pragma unroll
-        for (int o = 1; o < 8; o <<= 1) {
-            float ov = __shfl_xor(best, o, 64);
-            int oi = __shfl_xor(bi, o, 64);
-            argmax_merge(best, bi, ov, oi);
-        }
+        for (int i = 1; i < PER; ++i)
+            if (lv[i] > best) {                          // columns ascend: the lower one stays among equals
+                best = lv[i];
+                bi = sub + 8 * i;
+            }
+        argmax_over<8>(best, bi);
         float z = 0.f;
 #pragma unroll
         for (int i = 0; i < PER; ++i) z += expf(lv[i] - best);
-#pragma unroll
-        for (int o = 1; o < 8; o <<= 1) z += __shfl_xor(z, o, 64);
+        z = sum_over<8>(z);
         const int grow = row0 + mb * 32 + r;
         if (top_k == 1) {
             if (sub == 0 && mb * 32 + r < nrows) {
@@ -133,12 +123,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void route_mfma_kernel(const bf16_
                         const int c = sub + 8 * i;
                         if (t < pv || (t == pv && c > pi)) argmax_merge(v, vi, t, c);
                     }
-#pragma unroll
-                    for (int o = 1; o < 8; o <<= 1) {
-                        float ov = __shfl_xor(v, o, 64);
-                        int oi = __shfl_xor(vi, o, 64);
-                        argmax_merge(v, vi, ov, oi);
-                    }
+                    argmax_over<8>(v, vi);
                     ci[j] = vi;
                     cw[j] = expf(v - best) / z;
                     wsum += cw[j];

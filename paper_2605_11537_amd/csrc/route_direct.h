@@ -267,28 +267,13 @@ __global__ __launch_bounds__(NW * WAVE, 1) void route_direct_kernel(const void *
                 if (col_of(i) < E) f(lv[i], col_of(i));
         }
     };
-    auto merge = [](float &v, int &i, float ov, int oi) {
-        if (ov > v || (ov == v && oi < i)) {
-            v = ov;
-            i = oi;
-        }
-    };
-    auto merge_over_row = [&](float &v, int &i) {
-#pragma unroll
-        for (int o = 1; o < TPR; o <<= 1) {
-            const float ov = __shfl_xor(v, o, 64);
-            const int oi = __shfl_xor(i, o, 64);
-            merge(v, i, ov, oi);
-        }
-    };
     float best = -INFINITY;
     int bi = 0x7fffffff;
-    each([&](float t, int c) { merge(best, bi, t, c); });
-    merge_over_row(best, bi);
+    each([&](float t, int c) { argmax_merge(best, bi, t, c); });
+    argmax_over<TPR>(best, bi);
     float z = 0.f;
     each([&](float t, int) { z += expf(t - best); });
-#pragma unroll
-    for (int o = 1; o < TPR; o <<= 1) z += __shfl_xor(z, o, 64);
+    z = sum_over<TPR>(z);
     const bool writer = sub == 0 && live;
     if (top_k == 1) {
         if (writer) {
@@ -310,9 +295,9 @@ __global__ __launch_bounds__(NW * WAVE, 1) void route_direct_kernel(const void *
             float v = -INFINITY;
             int vi = 0x7fffffff;
             each([&](float t, int c) {
-                if (t < pv || (t == pv && c > pi)) merge(v, vi, t, c);
+                if (t < pv || (t == pv && c > pi)) argmax_merge(v, vi, t, c);
             });
-            merge_over_row(v, vi);
+            argmax_over<TPR>(v, vi);
             ci[q] = vi;
             cw[q] = expf(v - best) / z;
             wsum += cw[q];

@@ -36,14 +36,6 @@ constexpr int RR_STAGE_BYTES = RR_BM * RR_BKS * 2;
 constexpr int RR_LDL = RR_E + 32;      // rows 32 banks apart: two rows x 8 threads x 16 bytes cover all 64 banks
 constexpr int RR_LDS_BYTES = RR_NS * RR_STAGE_BYTES + 32 * RR_LDL * 4;
 
-__device__ __forceinline__ void rr_argmax_merge(float &v, int &i, float ov, int oi)
-{
-    if (ov > v || (ov == v && oi < i)) {
-        v = ov;
-        i = oi;
-    }
-}
-
 // LDS accesses with the offset as an immediate: one address register for all of them (a computed address
 // per access is loop invariant, and the compiler keeps every one of them in a register across the tiles)
 template <int OFF>
@@ -62,35 +54,6 @@ __device__ __forceinline__ void rr_ds_read128(u32x4_t &dst, unsigned addr)
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF));
 }
 #define RR_LGKM0() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
-
-// value of the partner lane in three exchange steps that together connect the 8 lanes of a group (lanes
-// 8g .. 8g+7): lane ^ 1, lane ^ 2 inside quads, then the mirror image inside the half row (lane 7 - i of the
-// group, which lies in the other quad).  Data-parallel-primitive moves: no LDS round trip.
-template <int STEP>
-__device__ __forceinline__ int rr_dpp8(int x)
-{
-    if (STEP == 0) return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false);
-    if (STEP == 1) return __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xf, 0xf, false);
-    return __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);
-}
-__device__ __forceinline__ void rr_argmax_over8(float &v, int &i)
-{
-#define RR_AM(S)                                                                  \
-    {                                                                             \
-        const float ov = __builtin_bit_cast(float, rr_dpp8<S>(__builtin_bit_cast(int, v))); \
-        const int oi = rr_dpp8<S>(i);                                             \
-        rr_argmax_merge(v, i, ov, oi);                                            \
-    }
-    RR_AM(0) RR_AM(1) RR_AM(2)
-#undef RR_AM
-}
-__device__ __forceinline__ float rr_sum_over8(float v)
-{
-    v += __builtin_bit_cast(float, rr_dpp8<0>(__builtin_bit_cast(int, v)));
-    v += __builtin_bit_cast(float, rr_dpp8<1>(__builtin_bit_cast(int, v)));
-    v += __builtin_bit_cast(float, rr_dpp8<2>(__builtin_bit_cast(int, v)));
-    return v;
-}
 
 template <class F, int... I>
 __device__ __forceinline__ void rr_static_for_impl(F &&f, std::integer_sequence<int, I...>)
@@ -247,7 +210,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void route_resident_kernel(
         e_bi = lvf(j) == e_max ? 64 * c + 32 * (j >> 2) + (j & 3) : e_bi;      // the column without its 4*sub
     };
     auto ep_end = [&]() {
-        e_z = rr_sum_over8(e_z);
+        e_z = sum_over<8>(e_z);
         e_bi += 4 * sub;
 #pragma unroll
         for (int stp = 0; stp < 3; ++stp) {
@@ -289,10 +252,10 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void route_resident_kernel(
                     for (int q = 0; q < 8; ++q) {
                         const float t = lvf(q);
                         const int col = ep_col(c, q);
-                        if (t < pv || (t == pv && col > pi)) rr_argmax_merge(v, vi, t, col);
+                        if (t < pv || (t == pv && col > pi)) argmax_merge(v, vi, t, col);
                     }
                 });
-                rr_argmax_over8(v, vi);
+                argmax_over<8>(v, vi);
                 const float cw = __builtin_amdgcn_exp2f(fmaf(v, RR_LOG2E, -e_msc)) / e_z;
                 wsum += cw;
                 if (sub == 0 && e_live) {
