@@ -192,9 +192,9 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void route_resident_kernel(
     auto ep_mid = [&]() {                // the row maximum over the 8 threads of the row
 #pragma unroll
         for (int stp = 0; stp < 3; ++stp) {
-            const int o = stp == 0 ? rr_dpp8<0>(__builtin_bit_cast(int, e_max))
-                          : stp == 1 ? rr_dpp8<1>(__builtin_bit_cast(int, e_max))
-                                     : rr_dpp8<2>(__builtin_bit_cast(int, e_max));
+            const int o = stp == 0 ? group_exchange<0>(__builtin_bit_cast(int, e_max))
+                          : stp == 1 ? group_exchange<1>(__builtin_bit_cast(int, e_max))
+                                     : group_exchange<2>(__builtin_bit_cast(int, e_max));
             e_max = fmaxf(e_max, __builtin_bit_cast(float, o));
         }
         e_msc = e_max * RR_LOG2E;
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void route_resident_kernel(
         e_bi += 4 * sub;
 #pragma unroll
         for (int stp = 0; stp < 3; ++stp) {
-            const int o = stp == 0 ? rr_dpp8<0>(e_bi) : stp == 1 ? rr_dpp8<1>(e_bi) : rr_dpp8<2>(e_bi);
+            const int o = stp == 0 ? group_exchange<0>(e_bi) : stp == 1 ? group_exchange<1>(e_bi) : group_exchange<2>(e_bi);
             e_bi = o < e_bi ? o : e_bi;
         }
         if (sub == 0 && e_live) {
