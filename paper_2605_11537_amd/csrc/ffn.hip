@@ -274,14 +274,16 @@ static inline bool ffn_use_dense(int max_rows, int max_slots, int K, int N, int 
 // flight.  Both products, us, this kernel and that: 768 x 3072, 128 experts, 12288 rows of which a plan keeps 7834 299, 262; 64 experts,
 // 8192 rows, 4705 kept 166, 141; 256 experts, 30000 rows, 14826 kept 546, 519; 512 x 2048, 256 experts, 20000 rows, 12567 kept 262, 227; 1024 x 4096,
 // 32 experts, 4096 rows, 2548 kept 163, 141.  At d = 1024 with a tile for every CU they are even (64 experts, 8192 rows: 246, 238 and 245, 267),
-// with more than 128 rows per slot a second tile reads the weights again (64 x 140 rows: 170, 210).
+// with more than 128 rows per slot a second tile reads the weights again (64 x 140 rows: 170, 210; 32 experts, 8192 rows, 768 x 3072, from 96 tiles
+// on: 149, 158 on the LDS tiles).
 static inline bool ffn_dense_fills(int max_rows, int max_slots, int E, int d, int F)
 {
     const long long ranges = max_rows / DENSE_BM > max_slots ? max_rows / DENSE_BM : max_slots;
     const int n = d < F ? d : F;
     const long long tiles = ranges * (n / DENSE_BN);
-    if (ffn_weight_stream(E, d, F) && (long long)max_rows <= 128LL * max_slots && (n < 1024 || tiles < 256)) return false;
-    return tiles >= (n >= 1024 ? 128 : 160);
+    const bool stream = ffn_weight_stream(E, d, F);
+    if (stream && (long long)max_rows <= 128LL * max_slots && (n < 1024 || tiles < 256)) return false;
+    return tiles >= (n >= 1024 ? 128 : stream ? 96 : 160);
 }
 
 }  // namespace moe
@@ -371,9 +373,13 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     int32_t *n_items = (int32_t *)p;
 
     // both products must take the dense route or neither: the lists split the rows once
-    const bool dense = dtype == MOE_BF16 && ffn_use_dense(max_rows, max_slots, d, F, schedule) &&
-                       ffn_use_dense(max_rows, max_slots, F, d, schedule) && ffn_dense_fills(max_rows, max_slots, E, d, F);
-    const bool mid = dtype == MOE_BF16 && !dense && ffn_mid(max_rows, max_slots, E, d, F, schedule);
+    const bool dense_fits = dtype == MOE_BF16 && ffn_use_dense(max_rows, max_slots, d, F, schedule) &&
+                            ffn_use_dense(max_rows, max_slots, F, d, schedule);
+    const bool dense = dense_fits && ffn_dense_fills(max_rows, max_slots, E, d, F);
+    // With 64 rows per slot on average or fewer a slot is one tile, give or take -- unless the batch is one the 256 x 256 kernel could take: its
+    // slots may be long.
+    const bool short_slots = !dense_fits && (long long)max_rows <= 64LL * max_slots;
+    const bool mid = dtype == MOE_BF16 && !dense && !short_slots && ffn_mid(max_rows, max_slots, E, d, F, schedule);
     // Without the dense kernel (small batches, short slots on average, shapes outside its tiling, the
     // experts schedule) the 128-column kernel cuts work items 128 rows high and picks the tile height per
     // item; with it, the 128-column kernel is not launched at all.
@@ -381,7 +387,7 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     // then reads the slot tables itself and the list kernel (a launch of ~5 us in front of the first
     // product) is skipped.  Long slots without the dense kernel keep the list: it cuts them into tiles
     // that run side by side.
-    const bool listless = mid || dtype == MOE_F32 || (!dense && (long long)max_rows <= 64LL * max_slots);
+    const bool listless = mid || dtype == MOE_F32 || (!dense && short_slots);
     if (!listless) {
         hipLaunchKernelGGL(ffn_worklist_kernel, dim3(1), dim3(1024), 0, st, slot_offset, slot_expert, n_slots,
                            max_slots, max_items, schedule, E, dense ? 1 : 0, max_dense, items, dtiles,

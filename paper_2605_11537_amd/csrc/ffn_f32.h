@@ -225,7 +225,6 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
             if (row_index) {
 #pragma unroll
                 for (int m = 0; m < LOADS; ++m) src[m] = row_index[src[m]];
-                __builtin_amdgcn_sched_barrier(0);
             }
             const int blocks = (nrows + 15) >> 4;
             auto tile = [&](auto BLOCKS, auto STREAM) {

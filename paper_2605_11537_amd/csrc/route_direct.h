@@ -105,15 +105,16 @@ __global__ __launch_bounds__(NW * WAVE, 1) void route_direct_kernel(const void *
             const int kk = k < d ? k : 0;                        // lanes past the end in the last step
             l.a = *reinterpret_cast<const uint4 *>(xp + (size_t)kk * ESZ);
 #pragma unroll
-            for (int i = 0; i < KL; ++i)
+            for (int g = 0; g < NG; ++g) {
+                const char *p = wp[g] + (size_t)kk * w_stride;   // one product per run, the rest are additions
 #pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    const char *p = wp[g] + (size_t)(kk + i) * w_stride;
+                for (int i = 0; i < KL; ++i) {
                     if constexpr (BF16 && VEC == 1)
-                        l.b[i][g][0] = *reinterpret_cast<const uint16_t *>(p);
+                        l.b[i][g][0] = *reinterpret_cast<const uint16_t *>(p + i * w_stride);
                     else
-                        rd_load_words<Loads::BW>(l.b[i][g], p);
+                        rd_load_words<Loads::BW>(l.b[i][g], p + i * w_stride);
                 }
+            }
         };
         constexpr int ACC = BM * BM / WAVE, STRIPS = VEC * NG;
         typedef float acc_t __attribute__((ext_vector_type(ACC)));

@@ -38,6 +38,7 @@ def _run(so, se, x, w1, w2, index, E, F):
     (512, 4096, 16, [200] * 16, None, True),                             # 256 columns in the first product
     (256, 2048, 8, [190 + i for i in range(8)], None, False),
     (128, 128, 260, [70] * 260, None, False),                            # more slots than threads
+    (256, 512, 64, [1030] + [49] * 62 + [28], None, True),               # 64 rows per slot on average, one long slot
 ])
 def test_ffn_lds_tile(d, F, E, rows, se, gather):
     so, se, n, T, x, w1, w2, index = _case(d, F, E, rows, se, gather, d + F)
