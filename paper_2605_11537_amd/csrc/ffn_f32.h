@@ -27,18 +27,29 @@ constexpr int F32_BN = 64, F32_NARROW_BN = 32;
 constexpr int F32_LD = F32_BN + 4;
 constexpr int F32_STAGED = 2;          // D of the kernel that stages its tokens: two steps of 32 k
 
+// First k of wavefront w's step of 16.  It hangs on k alone, so that every kernel here sums a row in the same order: both schedules
+// and every batch size give the same bits.  Past 256 the steps are dealt in pairs, where that comes out even: the four wavefronts then
+// read on in neighbouring lines.  Else, and where a wavefront has no more than two pairs, each has a quarter of k.
+// QUARTERS: k is known to be one of those.
+template <bool QUARTERS>
+__device__ __forceinline__ int f32_k(int K, int w, int step)
+{
+    if (QUARTERS) return w * (K / 4) + step * 16;
+    const bool dealt = K > 256 && K % 128 == 0;                  // uniform
+    return w * (dealt ? 32 : K / 4) + (step >> 1) * (dealt ? 128 : 32) + (step & 1) * 16;
+}
+
 // part[w] <- this wavefront's share of k of (16 * MB rows) x 64 columns.  D: steps of 16 k in flight (f32_depth below)
-template <int MB, bool STREAM, int D, int BLOCKS>
+template <int MB, bool STREAM, int D, bool QUARTERS, int BLOCKS>
 __device__ __forceinline__ void f32_tile(const float *const (&a_row)[BLOCKS], const float *__restrict__ B, int K, int N,
                                          float (*__restrict__ part)[F32_LD])
 {
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 15, g = lane >> 4;
     const int steps = K / 64;                                    // per wavefront
-    const int k_wave = w * (K / 4);                              // scalar, as are the weight rows' addresses
     const unsigned b_lane = (unsigned)(4 * g) * N + 4 * c;
     const float *a_src[MB];
 #pragma unroll
-    for (int m = 0; m < MB; ++m) a_src[m] = a_row[m] + k_wave + 4 * g;
+    for (int m = 0; m < MB; ++m) a_src[m] = a_row[m] + 4 * g;
     f32x4_t a[D][MB], b[D][4], acc[MB][4];
 #pragma unroll
     for (int m = 0; m < MB; ++m)
@@ -46,14 +57,14 @@ __device__ __forceinline__ void f32_tile(const float *const (&a_row)[BLOCKS], co
         for (int s = 0; s < 4; ++s) acc[m][s] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
     // every load is unconditional (past the end: a harmless re-read), so that the waits can be counts
     auto load = [&](int step, int j) {
-        const int s = step < steps ? step : steps - 1;
+        const int k0 = f32_k<QUARTERS>(K, w, step < steps ? step : steps - 1);      // scalar, as are the weight rows' addresses
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const f32x4_t *p = reinterpret_cast<const f32x4_t *>(B + (size_t)(k_wave + s * 16 + i) * N + b_lane);
+            const f32x4_t *p = reinterpret_cast<const f32x4_t *>(B + (size_t)(k0 + i) * N + b_lane);
             b[j][i] = STREAM ? __builtin_nontemporal_load(p) : *p;
         }
 #pragma unroll
-        for (int m = 0; m < MB; ++m) a[j][m] = *reinterpret_cast<const f32x4_t *>(a_src[m] + s * 16);
+        for (int m = 0; m < MB; ++m) a[j][m] = *reinterpret_cast<const f32x4_t *>(a_src[m] + k0);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto multiply = [&](int j) {
@@ -90,11 +101,10 @@ __device__ __forceinline__ void f32_tile(const float *const (&a_row)[BLOCKS], co
 // The same share of k with the tokens staged through the wavefront's own piece of LDS (its part of `part`, which is written after the
 // last step): a step is 32 k, a token load takes eight rows' 128 consecutive bytes, and the fragments (lane (g, c): row c, 4 k) are
 // read back from there.  Loaded straight from memory a fragment touches 16 lines per 16 lanes and holds the load path four times as
-// long as its bytes need.  Wavefront w takes the steps w, w + 4, ..: the four of a workgroup read on in neighbouring lines.
+// long as its bytes need.
 constexpr int F32_LDA = 32 + 4;
 
-//
-// src: the rows this lane loads (tile rows lane / 8 + 8 i), possibly still on their way: the first weights do not wait for them.
+// src: the rows this lane loads (tile rows lane / 8 + 8 i).
 // gathered: they come from an index, a bad one reads row 0.
 template <int MB, int NS, bool STREAM, int D, int ROWS>
 __device__ __forceinline__ void f32_tile_staged(const float *__restrict__ A, const int (&src)[ROWS], bool gathered, int n_src_rows,
@@ -113,7 +123,7 @@ __device__ __forceinline__ void f32_tile_staged(const float *__restrict__ A, con
     for (int m = 0; m < MB; ++m)
 #pragma unroll
         for (int s = 0; s < NS; ++s) acc[m][s] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-    auto k_of = [&](int step) { return ((step < steps ? step : steps - 1) * 4 + w) * 32; };     // past the end: a harmless re-read
+    auto k_of = [&](int step) { return f32_k<false>(K, w, 2 * (step < steps ? step : steps - 1)); };     // past the end: a harmless re-read
     auto load_b = [&](int step, int j) {
         const int k0 = k_of(step);
 #pragma unroll
@@ -237,7 +247,7 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
 #pragma unroll
                     for (int m = 0; m < LOADS; ++m)              // a bad index reads row 0
                         a_row[m] = A + (size_t)(!row_index || (src[m] >= 0 && src[m] < n_src_rows) ? src[m] : 0) * K;
-                    f32_tile<M, S, D>(a_row, B, K, N, part[w]);
+                    f32_tile<M, S, D, SEVERAL>(a_row, B, K, N, part[w]);
                 }
             };
             using std::integral_constant;
