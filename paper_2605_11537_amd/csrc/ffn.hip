@@ -470,16 +470,17 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
         const int bm1 = height(d), bm2 = height(F);
         auto narrow = [&](int K, int N) { return f32_narrow(max_rows, max_slots, E, schedule, K, N); };
         const bool narrow1 = narrow(d, F), narrow2 = narrow(F, d);
+        auto staged = [&](int bm, int K, int N) { return f32_staged(bm, max_rows, max_slots, E, schedule, K, N); };
 #define MOE_F32_BM(RELU, BM, D, SEVERAL) \
     (BM == 64 ? ffn_gemm_f32_kernel<RELU, 64, F32_BN, D, SEVERAL> : ffn_gemm_f32_kernel<RELU, 32, F32_BN, D, SEVERAL>)
-#define MOE_F32_KERNEL(RELU, BM, NARROW, K)                                                       \
+#define MOE_F32_KERNEL(RELU, BM, NARROW, K, N)                                                    \
     (NARROW            ? ffn_gemm_f32_kernel<RELU, 32, F32_NARROW_BN, F32_STAGED, false>          \
      : BM == 0         ? ffn_gemm_f32_kernel<RELU, 32, F32_BN, 1, true>                           \
-     : f32_staged(K)   ? MOE_F32_BM(RELU, BM, F32_STAGED, false)                                  \
+     : staged(BM, K, N) ? MOE_F32_BM(RELU, BM, F32_STAGED, false)                                 \
      : f32_several(K)  ? MOE_F32_BM(RELU, BM, 4, true)                                            \
                        : MOE_F32_BM(RELU, BM, 4, false))
-        auto gemm1 = MOE_F32_KERNEL(true, bm1, narrow1, d);
-        auto gemm2 = MOE_F32_KERNEL(false, bm2, narrow2, F);
+        auto gemm1 = MOE_F32_KERNEL(true, bm1, narrow1, d, F);
+        auto gemm2 = MOE_F32_KERNEL(false, bm2, narrow2, F, d);
 #undef MOE_F32_KERNEL
 #undef MOE_F32_BM
         auto grid = [&](int bm, bool few, int K, int N) {

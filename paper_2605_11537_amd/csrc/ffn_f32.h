@@ -168,9 +168,10 @@ __device__ __forceinline__ void f32_tile_staged(const float *__restrict__ A, con
         __builtin_amdgcn_sched_barrier(0);
     };
 
+    const unsigned limit = gathered ? (unsigned)n_src_rows : 0x80000000u;       // a select per row, not a branch
 #pragma unroll
     for (int i = 0; i < 2 * MB; ++i) {
-        const int r = !gathered || (src[i] >= 0 && src[i] < n_src_rows) ? src[i] : 0;
+        const int r = (unsigned)src[i] < limit ? src[i] : 0;
         a_row[i] = A + (size_t)r * K + (lane & 7) * 4;
     }
 #pragma unroll
@@ -235,6 +236,10 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
             if (row_index) {
 #pragma unroll
                 for (int m = 0; m < LOADS; ++m) src[m] = row_index[src[m]];
+                if constexpr (D != F32_STAGED) {                 // a bad index reads row 0 (the staged tile sees to it itself)
+#pragma unroll
+                    for (int m = 0; m < LOADS; ++m) src[m] = src[m] >= 0 && src[m] < n_src_rows ? src[m] : 0;
+                }
             }
             const int blocks = (nrows + 15) >> 4;
             auto tile = [&](auto BLOCKS, auto STREAM) {
@@ -245,8 +250,7 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
                 } else {
                     const float *a_row[LOADS];
 #pragma unroll
-                    for (int m = 0; m < LOADS; ++m)              // a bad index reads row 0
-                        a_row[m] = A + (size_t)(!row_index || (src[m] >= 0 && src[m] < n_src_rows) ? src[m] : 0) * K;
+                    for (int m = 0; m < LOADS; ++m) a_row[m] = A + (size_t)src[m] * K;
                     f32_tile<M, S, D, SEVERAL>(a_row, B, K, N, part[w]);
                 }
             };
@@ -311,7 +315,19 @@ static inline int f32_grid(int bm, int max_rows, int max_slots, int schedule, in
 
 // Tokens through LDS wherever a wavefront's share of k is whole steps of 32.  At k = 256 there are two of them, and the loads they save
 // are no longer than what the second unit of a workgroup needs (256 -> 1024 -> 256, 32 x 64 rows: 37.2 us without, 39.1 with).
-static inline bool f32_staged(int K) { return !f32_several(K) && K % 128 == 0; }
+// Nor where units of 64 rows, or (experts schedule) of several tiles, are so few that each has a CU for itself: then the load path is
+// not what binds, and loads straight to registers come back sooner.  Both products, us, with LDS and without: 512 -> 2048 -> 512,
+// 1 expert, 256 rows 55.4, 52.1, 512 rows 56.7, 52.6; 1024 -> 1024 -> 1024, 512 rows over 2 46.8, 43.8; experts schedule, 512 -> 2048 -> 512,
+// 1024 rows over 8 302, 283.  The line of the slot schedule is low because the last tiles of the experts are cheap and crowd an XCD: 768 ->
+// 3072 -> 768, 300 rows of 1 expert (240 units) 85, 89; 384 -> 1536 -> 384, 400 rows over 2 (192) 46.7, 52.4; 1024 -> 1024 -> 1024, 800 over 4 (256)
+// 67, 98.
+static inline bool f32_staged(int bm, int max_rows, int max_slots, int E, int schedule, int K, int N)
+{
+    if (f32_several(K) || K % 128 != 0) return false;
+    const long long experts = max_slots < E ? max_slots : E;
+    if (schedule == MOE_SCHEDULE_SLOTS) return bm == 32 || (max_rows / bm + experts) * (N / F32_BN) > 160;
+    return max_rows <= 32 || experts * (N / F32_BN) > 256;
+}
 
 // 32 columns where 64 would leave at least half of the CUs without a unit: half the work per unit, but every token row is loaded twice as often.
 // Both products, 64 and 32 columns, us: 256 -> 1024 -> 256, 300 rows over 8 experts 21.4 and 17.0; 512 -> 2048 -> 512, 200 over 16

@@ -34,7 +34,8 @@ def test_schedules_and_batch_sizes_give_the_same_bits(d, F):
     slots = run(x, rows, moe.SCHEDULE_SLOTS)
     few = [min(c, 20) for c in rows]
     first = torch.cat([p[:n] for p, n in zip(torch.split(x, rows), few)])
-    for other, n in ((run(x, rows, moe.SCHEDULE_EXPERTS), rows), (run(x, rows, moe.SCHEDULE_SLOTS, 8), rows),
-                     (run(first, few, moe.SCHEDULE_SLOTS), few), (run(first, few, moe.SCHEDULE_EXPERTS), few)):
+    for other, n in ((run(x, rows, moe.SCHEDULE_EXPERTS), rows), (run(x, rows, moe.SCHEDULE_SLOTS, 2), rows),
+                     (run(x, rows, moe.SCHEDULE_SLOTS, 8), rows), (run(first, few, moe.SCHEDULE_SLOTS), few),
+                     (run(first, few, moe.SCHEDULE_EXPERTS), few)):
         for e in range(E):
             assert torch.equal(other[e], slots[e][:n[e]]), f"expert {e}"

@@ -15,8 +15,9 @@ pytestmark = pytest.mark.gpu
     (384, 512, 2, [1, 33], None, True),                                    # both products narrow, odd numbers of steps
     (256, 128, 3, [32, 0, 17, 64], [0, 1, 2, 2], False),                   # narrow at k = 256; k = 128 is short
     (512, 4096, 8, [31, 32, 33, 15, 16, 17, 48, 1], list(range(8)), True), # wide first, narrow second product
-    (640, 1024, 3, [130, 200, 70], [0, 1, 2], True),                       # several tiles of one expert, cost ranges inside it
-    (512, 384, 2, [300, 290], [0, 1], True),                               # tiles of 64 rows, staged
+    (640, 1024, 3, [430, 500, 270], [0, 1, 2], True),                      # several tiles of one expert, cost ranges inside it
+    (512, 1536, 2, [610, 700], [0, 1], True),                              # tiles of 64 rows, staged
+    (512, 384, 2, [300, 290], [0, 1], True),                               # and too few of them to be
     (384, 448, 30, [(5 * i) % 9 for i in range(300)], None, False),        # more slots than threads; k = 448 is not staged
 ])
 def test_ffn_f32_staged(d, F, E, rows, se, gather):
