@@ -5,7 +5,7 @@
 // ids in LDS (ids that share a wavefront load are pre-counted with ballots, so a hot expert does
 // not serialise the LDS atomics).  Wavefront 0 then runs the integer allocation entirely in
 // registers: lane l owns experts l, l+64, ..., sums and arg-max searches are wavefront reductions,
-// so the one-by-one hand-out of the slots left by the floors needs no barrier.  All threads
+// so the hand-out of the slots left by the floors needs no barrier.  All threads
 // finally scan the replica counts into slot_base and write the slot -> expert table.
 #include "plan_alloc.h"
 #include "route.h"

@@ -1,6 +1,6 @@
 """The hand-out of the slots that the floors of the plan leave, several per step, and the dispatch tables made beside it, against the oracle: equal
-loads (ties by id), one expert far ahead (several slots in a row), more experts above the bar than slots, every size class of the allocating
-wavefront, plan and dispatch apart and in one call, one block of tokens to many."""
+loads (ties by id), loads that binary32 cannot tell apart, one expert far ahead (several slots in a row), more experts above the bar than slots,
+every size class of the allocating wavefront, no slot and one, plan and dispatch apart and in one call, one block of tokens to many."""
 import numpy as np
 import pytest
 import torch
@@ -14,16 +14,21 @@ pytestmark = pytest.mark.gpu
 def _ids(kind, T, E, rng):
     if kind == "equal":
         return np.arange(T) % E
+    if kind == "close":                      # loads that differ by a few in a hundred thousand and more
+        n = T // E + rng.integers(-2, 3, E)
+        return np.repeat(np.arange(E), np.maximum(n, 0))[:T] if n.sum() >= T else np.concatenate(
+            [np.repeat(np.arange(E), np.maximum(n, 0)), np.full(T - n.sum(), E - 1)])
     if kind == "one":
         return np.where(rng.random(T) < 0.7, E // 2, rng.integers(0, E, T))
     w = np.arange(1, E + 1.0) ** -{"zipf": 1.0, "steep": 2.0}[kind]
     return rng.permutation(E)[rng.choice(E, T, p=w / w.sum())]
 
 
-@pytest.mark.parametrize("kind", ["equal", "one", "zipf", "steep"])
+@pytest.mark.parametrize("kind", ["equal", "close", "one", "zipf", "steep"])
 @pytest.mark.parametrize("T,E,R,C", [
     (500, 5, 3, 7), (4096, 128, 16, 40), (8192, 256, 200, 9), (8193, 60, 31, 30), (12288, 128, 16, 120), (20000, 64, 100, 50),
     (30000, 256, 64, 70), (9000, 500, 90, 11), (17000, 1024, 333, 10),
+    (4000, 128, 0, 5), (3000, 200, 1, 5), (5000, 600, 1, 4), (3000000, 7, 3, 1000), (3000000, 12, 40, 20000), (6000000, 300, 500, 3000),
 ])
 def test_plan_and_dispatch(T, E, R, C, kind):
     import paper_2605_11537_amd as moe
