@@ -4,15 +4,16 @@
 // hardware scheduling:
 //   hist     one workgroup per 1024 tokens: LDS histogram of expert ids -> block_hist[b][e]
 //   permute  one workgroup of 1024 threads per 1024 tokens: per expert, total and prefix over the earlier token blocks
-//            (the blocks dealt to 4 .. 16 threads per expert, so that their histograms are one memory round trip),
+//            (the blocks dealt to 1 .. 16 threads per expert, 16 blocks in flight each: one memory round trip up to
+//            256 blocks with 64 experts, 64 with 256, 16 with 1024),
 //            kept counts, expert offsets (scan over experts), slot offsets (balanced split
 //            per expert); then the rank of every token among the tokens of its expert
 //            = prefix over earlier blocks + prefix over earlier 64-token chunks of the block
 //            (LDS table) + rank inside the chunk (wavefront ballots, one per id bit);
 //            writes inv / perm
 //            Latency is all it is (one round trip for the loads, one for the stores, a dozen steps in LDS between): with 256 threads, whose
-//            histogram sums were four trips and whose ranks four rounds, 65536 ids over 256 experts took 22.8 us with the plan and
-//            16.6 without, hist included; now 15.0 and 10.1.
+//            histogram sums were four trips and whose ranks four rounds, 65536 ids over 256 experts took 20.8 us with the plan (64 slots) and
+//            16.6 without, hist included; now 14.2 and 10.1.
 //   gather   whole-chip copy of the kept rows, x_perm[pos] = x[perm[pos]], 16-byte accesses
 #include <mutex>
 
@@ -172,7 +173,8 @@ __global__ __launch_bounds__(DSP_TOKENS) void dispatch_permute_kernel(
     const long long cap = (long long)r_e * C;
     const int k_e = (long long)n_e < cap ? n_e : (int)cap;
     int off_e, sb_e, K, P;
-    block_scan2_1024(k_e, r_e, off_e, sb_e, K, P, sums);
+    // more replicas than the slot tables hold count as one more: a caller's may be any number, and their sum has to fit
+    block_scan2_1024(k_e, r_e > max_slots ? max_slots + 1 : r_e, off_e, sb_e, K, P, sums);
     if (tid < E) {
         eoff_e[tid] = off_e;
         cap_e[tid] = k_e;
@@ -201,19 +203,20 @@ __global__ __launch_bounds__(DSP_TOKENS) void dispatch_permute_kernel(
         expert_offset[tid] = off_e;
         if (PPL > 0 && pa.slot_base) pa.slot_base[tid] = sb_e;
     }
-    // slot tables: an expert's slots are written by its whole wavefront, 64 at a time
+    // slot tables: an expert's slots are written by its whole wavefront, 64 at a time, those that the tables hold
     const int q = r_e > 0 ? k_e / r_e : 0, rem = r_e > 0 ? k_e % r_e : 0;
     auto write_slot = [&](int e, int p, int k, int first, int quot, int rest) {
-        if (slot_offset && p <= max_slots) slot_offset[p] = first + k * quot + (k < rest ? k : rest);
+        if (slot_offset) slot_offset[p] = first + k * quot + (k < rest ? k : rest);
         if (PPL > 0 && pa.slot_expert) pa.slot_expert[p] = e;
     };
-    if (r_e > 0) write_slot(tid, sb_e, 0, off_e, q, rem);
+    if (r_e > 0 && sb_e <= max_slots) write_slot(tid, sb_e, 0, off_e, q, rem);
     for (unsigned long long more = __ballot(r_e > 1); more; more &= more - 1) {
         const int l = __builtin_ctzll(more);                     // uniform
         const int r = __builtin_amdgcn_readlane(r_e, l), p0 = __builtin_amdgcn_readlane(sb_e, l);
         const int first = __builtin_amdgcn_readlane(off_e, l), quot = __builtin_amdgcn_readlane(q, l);
         const int rest = __builtin_amdgcn_readlane(rem, l);
-        for (int k = 1 + lane; k < r; k += WAVE) write_slot(w * WAVE + l, p0 + k, k, first, quot, rest);
+        const int last = p0 > max_slots ? 0 : r - 1 < max_slots - p0 ? r - 1 : max_slots - p0;
+        for (unsigned k = 1 + lane; k <= (unsigned)last; k += WAVE) write_slot(w * WAVE + l, p0 + (int)k, (int)k, first, quot, rest);
     }
     if (tid == 0) {
         expert_offset[E] = K;

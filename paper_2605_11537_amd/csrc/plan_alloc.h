@@ -191,9 +191,9 @@ __device__ __forceinline__ void plan_allocate_wave(const int *hist, int *rep, in
             }
         }
         // The slots still left go to the most loaded expert per slot, one after another; many at a time where the order among them
-        // cannot matter.  us of moe_plan_dispatch one by one, by steps of exact keys, now: 4096 ids, 128 experts, 16 slots 10.1, 8.9, 8.5; 1000
-        // ids, 256 experts, 1 slot 6.7, 7.0, 6.7, 64 slots with half of the ids on one 12.7, 13.5, 11.5; 4096 ids, 1024 experts, 128
-        // slots 59.7, 39.0, 28.8.
+        // cannot matter.  us of moe_plan_dispatch one by one, by steps of exact keys, now: 4096 ids, 128 experts, 16 slots 10.1, 8.9, 8.4; 1000
+        // ids, 256 experts, 1 slot 6.6, 7.0, 6.7, 64 slots with half of the ids on one 12.6, 13.6, 12.0; 4096 ids, 1024 experts, 128
+        // slots 59.7, 39.2, 31.2.
         if (n_ids < (1 << 24)) {
             // Counts below 2^24, exact in binary32.  Exact keys: load per slot and expert id in ONE 64-bit integer, so a fold step is an
             // unsigned maximum.  q = floor(RN(n 2^28 / r)) is monotone in n / r, equal for equal fractions,

@@ -64,3 +64,31 @@ def test_plan_and_dispatch(T, E, R, C, kind):
             for key, want in (("counts", counts), ("kept", kept), ("expert_offset", first), ("inv", inv), ("perm", perm),
                               ("slot_offset", slots)):
                 assert (to_host(got[key]) == np.asarray(want)).all(), key
+
+
+@pytest.mark.parametrize("replicas,max_slots", [
+    ([2**31 - 1, 1, 1], 3),                         # "as many as it takes"
+    ([2, 2**31 - 1, 5, 2**31 - 1], 9),              # their sum does not fit an int
+    ([1, 70, 2**31 - 64, 1], 200),
+    ([1] * 70 + [2**31 - 1] + [3] * 5, 90),         # past the first wavefront of experts
+    ([3, 4, 2], 9),
+])
+def test_replicas_beyond_the_slot_table(replicas, max_slots):
+    """Replica counts of a caller's own, however large: every slot that the table holds, nothing behind it."""
+    import paper_2605_11537_amd as moe
+    E, C, T = len(replicas), 3, 1500
+    rng = np.random.default_rng(E)
+    ids = rng.integers(0, E, T).astype(np.int32)
+    room = to_dev(np.full(max_slots + 1 + 64, -7, np.int32))
+    i32 = lambda n: torch.empty(n, dtype=torch.int32, device="cuda")  # noqa: E731
+    out = dict(counts=i32(E), kept=i32(E), expert_offset=i32(E + 1), slot_offset=room[: max_slots + 1], perm=i32(T), inv=i32(T), x_perm=None)
+    moe.moe_dispatch(None, to_dev(ids), to_dev(np.array(replicas, np.int32)), E, C, max_slots, out=out, shape=(T, 8), dtype=torch.float32)
+    kept = np.minimum(np.bincount(ids, minlength=E), np.array(replicas, np.int64) * C)
+    first = np.concatenate([[0], np.cumsum(kept)])
+    slots = []
+    for e in range(E):
+        q, rem = divmod(int(kept[e]), replicas[e])
+        slots += [first[e] + j * q + min(j, rem) for j in range(min(replicas[e], max_slots + 1))]
+    slots = (slots + [first[-1]] * (max_slots + 1))[: max_slots + 1]
+    assert (to_host(out["kept"]) == kept).all() and (to_host(out["expert_offset"]) == first).all()
+    assert (to_host(room) == np.array(slots + [-7] * 64)).all()
