@@ -17,6 +17,10 @@ pytestmark = pytest.mark.gpu
     (50, 2056, 128, synth.F32, 1),
     (40, 64, 22, synth.F32, 8),
     (8190, 16, 8, synth.F32, 1),             # 16 wavefronts, 32 tokens
+    (1024, 1024, 16, synth.F32, 2),          # the last depths with 16 wavefronts, and the next
+    (1025, 512, 3, synth.F32, 1),
+    (1025, 520, 16, synth.F32, 1),
+    (7, 1032, 16, synth.F32, 1),
     (1, 8, 8, synth.BF16, 1),
     (8192, 40, 32, synth.BF16, 3),
     (8193, 40, 32, synth.BF16, 1),
