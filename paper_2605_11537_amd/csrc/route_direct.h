@@ -14,9 +14,9 @@
 // VEC grows with E (1, 2, 4, 8 for up to 32, 64, 128, 256 experts, as far as E's divisibility keeps the loads
 // aligned); more experts than 32 * VEC are walked in groups whose logits collect in LDS.
 //
-// Measured (kernel time): 3001 tokens x 768, 64 experts, bf16: 82.6 -> 7.5 us; 1500 x 512, 32 experts, f32: 165 ->
-// 9.0 us, against one wavefront per token with the experts over the lanes (a serial chain of d multiply-adds behind 2- or
-// 4-byte loads).
+// Measured (a call in a captured graph), us: 3001 tokens x 768, 64 experts, bf16 81 -> 6.2; 1500 x 512, 32 experts, f32 167 -> 5.0, against
+// one wavefront per token with the experts over the lanes (a serial chain of d multiply-adds behind 2- or 4-byte loads); of it the wavefronts
+// past four and the tiles of 16 tokens 7.3 -> 6.2 and 7.8 -> 5.0.
 #pragma once
 #include "gemm_bf16.h"
 
@@ -69,9 +69,8 @@ __global__ __launch_bounds__(NW * WAVE, 1) void route_direct_kernel(const void *
     constexpr int KL = Loads::KL, KS = WAVE / BM * KL, ESZ = BF16 ? 2 : 4, GW = BM * VEC * NG;   // GW: columns per group
     // steps in flight: twice U with four wavefronts, U with more (16 of them have 128 registers each, and hide each other's waits)
     constexpr int U = NW > 4 ? (BM == 16 && VEC * NG <= 4 ? 8 : 4) : VEC <= 2 ? 6 : VEC == 4 ? 4 : 2;
-    // partial tiles that fit beside each other; the wavefronts past them hand theirs over first
-    constexpr int SLOTS = GROUPS ? 1 : NW * VEC > 32 ? 32 / VEC : NW;
-    static_assert(GROUPS || NW == SLOTS || NW == 2 * SLOTS, "one hand-over");
+    static_assert(GROUPS || NW * VEC <= 32, "a partial tile per wavefront fits");
+    constexpr int SLOTS = GROUPS ? 1 : NW;
     constexpr int LD = (GROUPS ? MOE_MAX_EXPERTS : GW) + 4;
     __shared__ __attribute__((aligned(16))) float part[SLOTS][BM][LD];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, j = lane % BM, h = lane / BM;
@@ -134,11 +133,9 @@ __global__ __launch_bounds__(NW * WAVE, 1) void route_direct_kernel(const void *
                 for (int i = 0; i < KL; ++i)
 #pragma unroll
                     for (int q = 0; q < Loads::BW; ++q)
-                        {
 #pragma unroll
                         for (int g = 0; g < NG; ++g)
                             if (past) l.b[i][g][q] = 0;
-                    }
             }
             if constexpr (BF16) {
 #pragma unroll
@@ -210,28 +207,10 @@ __global__ __launch_bounds__(NW * WAVE, 1) void route_direct_kernel(const void *
                 __syncthreads();
             }
         } else {
-            if (NW > SLOTS) {
-                if (w >= SLOTS) {
 #pragma unroll
-                    for (int v = 0; v < ACC; ++v)
+            for (int v = 0; v < ACC; ++v)
 #pragma unroll
-                        for (int c = 0; c < STRIPS; ++c) part[w - SLOTS][row_of(v)][column_of(c)] = acc[c][v];
-                }
-                __syncthreads();
-                if (w < SLOTS) {
-#pragma unroll
-                    for (int v = 0; v < ACC; ++v)
-#pragma unroll
-                        for (int c = 0; c < STRIPS; ++c) acc[c][v] += part[w][row_of(v)][column_of(c)];
-                }
-                __syncthreads();
-            }
-            if (w < SLOTS) {
-#pragma unroll
-                for (int v = 0; v < ACC; ++v)
-#pragma unroll
-                    for (int c = 0; c < STRIPS; ++c) part[w][row_of(v)][column_of(c)] = acc[c][v];
-            }
+                for (int c = 0; c < STRIPS; ++c) part[w][row_of(v)][column_of(c)] = acc[c][v];
             __syncthreads();
         }
     }
