@@ -21,7 +21,7 @@
 #include "gemm_dense_bf16.h"
 #include "ffn_f32.h"
 #include "ffn_few_rows.h"
-#include "ffn_lds_tile.h"
+#include "ffn_rules.h"
 
 namespace moe {
 
@@ -258,34 +258,6 @@ static inline int ffn_max_items(int max_rows, int max_slots) { return max_slots 
 // every dense tile but the last of a slot has 256 rows
 static inline int ffn_max_dense(int max_rows, int max_slots) { return max_rows / DENSE_BM + max_slots + 1; }
 
-// The 256 x 256 tile pays off when slots are long: it is launched when the rows could fill slots of
-// 64 and more on average, the matrix sizes fit its tiling, and its tiles fill the chip.
-static inline bool ffn_use_dense(int max_rows, int max_slots, int K, int N, int schedule)
-{
-    return schedule == MOE_SCHEDULE_SLOTS && N % DENSE_BN == 0 && K % DENSE_BK == 0 && K >= DENSE_MIN_K &&
-           (long long)max_rows >= 64LL * max_slots && max_rows >= 4096;
-}
-
-// Tiles of the product with fewer columns that can be expected (a slot has one at least): under five eighths of the CUs the others
-// leave less of the chip idle.  Both products, us, this kernel and the one taken instead: 16384 rows over 16 experts, 768 x 3072 (192 tiles) 198, 229;
-// 16384 over 8, 512 x 2048 (128) 95, 85; 10032 over 16, 768 x 3072 (117) 139, 113; 16384 over 8, 256 x 1024 (64) 47, 34; 8192 over 64, 512 x 2048
-// (128) 84, 78.  At d = 1024 half of the CUs are enough: 8192 rows over 8, 1024 x 4096 (128), dealt by Zipf's law 160, 177, evenly 155, 141.
-// Nor is it taken where the weight stream binds (ffn_weight_stream) and a slot is a tile of the 128-column kernel: that one keeps more weights in
-// flight.  Both products, us, this kernel and that: 768 x 3072, 128 experts, 12288 rows of which a plan keeps 7834 299, 262; 64 experts,
-// 8192 rows, 4705 kept 166, 141; 256 experts, 30000 rows, 14826 kept 546, 519; 512 x 2048, 256 experts, 20000 rows, 12567 kept 262, 227; 1024 x 4096,
-// 32 experts, 4096 rows, 2548 kept 163, 141.  At d = 1024 with a tile for every CU they are even (64 experts, 8192 rows: 246, 238 and 245, 267),
-// with more than 128 rows per slot a second tile reads the weights again (64 x 140 rows: 170, 210; 32 experts, 8192 rows, 768 x 3072, from 96 tiles
-// on: 149, 158 on the LDS tiles).
-static inline bool ffn_dense_fills(int max_rows, int max_slots, int E, int d, int F)
-{
-    const long long ranges = max_rows / DENSE_BM > max_slots ? max_rows / DENSE_BM : max_slots;
-    const int n = d < F ? d : F;
-    const long long tiles = ranges * (n / DENSE_BN);
-    const bool stream = ffn_weight_stream(E, d, F);
-    if (stream && (long long)max_rows <= 128LL * max_slots && (n < 1024 || tiles < 256)) return false;
-    return tiles >= (n >= 1024 ? 128 : stream ? 96 : 160);
-}
-
 }  // namespace moe
 
 using namespace moe;
@@ -372,22 +344,10 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     p += align_up((size_t)max_dense * sizeof(DenseTile), 256);
     int32_t *n_items = (int32_t *)p;
 
-    // both products must take the dense route or neither: the lists split the rows once
-    const bool dense_fits = dtype == MOE_BF16 && ffn_use_dense(max_rows, max_slots, d, F, schedule) &&
-                            ffn_use_dense(max_rows, max_slots, F, d, schedule);
-    const bool dense = dense_fits && ffn_dense_fills(max_rows, max_slots, E, d, F);
-    // With 64 rows per slot on average or fewer a slot is one tile, give or take -- unless the batch is one the 256 x 256 kernel could take: its
-    // slots may be long.
-    const bool short_slots = !dense_fits && (long long)max_rows <= 64LL * max_slots;
-    const bool mid = dtype == MOE_BF16 && !dense && !short_slots && ffn_mid(max_rows, max_slots, E, d, F, schedule);
-    // Without the dense kernel (small batches, short slots on average, shapes outside its tiling, the
-    // experts schedule) the 128-column kernel cuts work items 128 rows high and picks the tile height per
-    // item; with it, the 128-column kernel is not launched at all.
-    // Slots that hold 64 rows on average at most are one tile each, give or take: the 128-column kernel
-    // then reads the slot tables itself and the list kernel (a launch of ~5 us in front of the first
-    // product) is skipped.  Long slots without the dense kernel keep the list: it cuts them into tiles
-    // that run side by side.
-    const bool listless = mid || dtype == MOE_F32 || (!dense && short_slots);
+    // binary32 finds its tiles itself, at any batch
+    const FfnRoute route = ffn_route(max_rows, max_slots, E, d, F, schedule);
+    const bool dense = dtype == MOE_BF16 && route.kernel == FFN_DENSE, mid = route.kernel == FFN_LDS_TILE;
+    const bool listless = dtype == MOE_F32 || !route.list;
     if (!listless) {
         hipLaunchKernelGGL(ffn_worklist_kernel, dim3(1), dim3(1024), 0, st, slot_offset, slot_expert, n_slots,
                            max_slots, max_items, schedule, E, dense ? 1 : 0, max_dense, items, dtiles,
@@ -434,7 +394,7 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
             // the dense kernel took every row
         } else if (mid)
             mid_launch(ffn_lds_tile_bf16_kernel<true, 2>, ffn_lds_tile_bf16_kernel<true, 4>, x_perm, row_index, n_x_rows, w1, d, F, h);
-        else if (listless && ffn_few_rows(max_rows, max_slots, d, F))
+        else if (route.few_rows[0])
             hipLaunchKernelGGL((by_slots ? ffn_few_rows_bf16_kernel<true, false> : ffn_few_rows_bf16_kernel<true, true>),
                                dim3(few_rows_grid(max_rows, max_slots, schedule, F)), dim3(SHARE_THREADS), 0, st,
                                (const bf16_t *)x_perm, (const bf16_t *)w1, row_index, n_x_rows, d, F, E, slot_offset, slot_expert,
@@ -454,7 +414,7 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
         if (dense) {
         } else if (mid)
             mid_launch(ffn_lds_tile_bf16_kernel<false, 2>, ffn_lds_tile_bf16_kernel<false, 4>, h, nullptr, max_rows, w2, F, d, y_perm);
-        else if (listless && ffn_few_rows(max_rows, max_slots, F, d))
+        else if (route.few_rows[1])
             hipLaunchKernelGGL((by_slots ? ffn_few_rows_bf16_kernel<false, false> : ffn_few_rows_bf16_kernel<false, true>),
                                dim3(few_rows_grid(max_rows, max_slots, schedule, d)), dim3(SHARE_THREADS), 0, st, (const bf16_t *)h,
                                (const bf16_t *)w2, (const int32_t *)nullptr, max_rows, F, d, E, slot_offset, slot_expert, n_slots,

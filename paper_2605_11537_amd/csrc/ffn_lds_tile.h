@@ -217,15 +217,4 @@ static inline int mid_strips(int max_rows, int max_slots, int N)
     return N % 256 == 0 && tiles * (N / 256) >= 256 ? 4 : 2;
 }
 
-// From 128 MB of weights per product on, their stream binds at the few hundred rows per slot that these kernels see.
-static inline bool ffn_weight_stream(int E, int d, int F) { return (long long)E * d * F >= (64LL << 20); }
-
-// Where this kernel takes the products (of batches whose slots are not all short): the slot schedule, and no weight stream that binds
-// (128 MB per product under 128 rows per slot belong to the 128-column kernel: 64 experts x 128 rows, 768 x 3072, 160 us against 175;
-// 512 x 2048, 64 x 128, 78 both, 32 x 128 47 against 43).
-static inline bool ffn_mid(int max_rows, int max_slots, int E, int d, int F, int schedule)
-{
-    return schedule == MOE_SCHEDULE_SLOTS && (!ffn_weight_stream(E, d, F) || (long long)max_rows > 128LL * max_slots);
-}
-
 }  // namespace moe

@@ -11,15 +11,19 @@ from gpu_util import f64, to_dev, to_host
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,F,E,rows,se,gather", [
-    (384, 512, 2, [1, 33], None, True),                                    # both products narrow, odd numbers of steps
-    (256, 128, 3, [32, 0, 17, 64], [0, 1, 2, 2], False),                   # narrow at k = 256; k = 128 is short
-    (512, 4096, 8, [31, 32, 33, 15, 16, 17, 48, 1], list(range(8)), True), # wide first, narrow second product
-    (640, 1024, 3, [430, 500, 270], [0, 1, 2], True),                      # several tiles of one expert, cost ranges inside it
-    (512, 1536, 2, [610, 700], [0, 1], True),                              # tiles of 64 rows, staged
-    (512, 384, 2, [300, 290], [0, 1], True),                               # and too few of them to be
-    (384, 448, 30, [(5 * i) % 9 for i in range(300)], None, False),        # more slots than threads; k = 448 is not staged
-])
+# shape: d, F, E, rows and expert per slot, gathered;  what it takes: rows of a tile, first and second product with 32 columns, and staged
+SHAPES = [
+    ((384, 512, 2, [1, 33], None, True), (32, (1, 1), (1, 1))),                                   # odd numbers of steps
+    ((256, 128, 3, [32, 0, 17, 64], [0, 1, 2, 2], False), (32, (1, 0), (0, 0))),                  # k = 256; k = 128 is short
+    ((512, 4096, 8, [31, 32, 33, 15, 16, 17, 48, 1], list(range(8)), True), (32, (0, 1), (1, 1))),
+    ((640, 1024, 3, [430, 500, 270], [0, 1, 2], True), (64, (0, 0), (1, 1))),                     # cost ranges inside an expert
+    ((512, 1536, 2, [610, 700], [0, 1], True), (64, (0, 0), (1, 1))),
+    ((512, 384, 2, [300, 290], [0, 1], True), (64, (0, 0), (0, 0))),                              # too few tiles
+    ((384, 448, 30, [(5 * i) % 9 for i in range(300)], None, False), (32, (0, 0), (1, 0))),       # more slots than threads; k = 448
+]
+
+
+@pytest.mark.parametrize("d,F,E,rows,se,gather", [s for s, _ in SHAPES])
 def test_ffn_f32_staged(d, F, E, rows, se, gather):
     import paper_2605_11537_amd as moe
     rng = np.random.default_rng(d * F)

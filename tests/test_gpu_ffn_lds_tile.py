@@ -31,7 +31,7 @@ def _run(so, se, x, w1, w2, index, E, F):
     return to_host(y)
 
 
-@pytest.mark.parametrize("d,F,E,rows,se,gather", [
+SHAPES = [
     (128, 256, 4, [65, 96, 97, 128], None, True),                        # 3, 3, 4, 4 blocks; k = 128
     (384, 128, 3, [129, 160, 31], None, False),                          # a second tile of one row, of 32 rows; 128 columns
     (256, 512, 2, [300, 20, 0, 150], [0, 0, 1, 1], True),                # tiles over the slots of an expert
@@ -39,7 +39,10 @@ def _run(so, se, x, w1, w2, index, E, F):
     (256, 2048, 8, [190 + i for i in range(8)], None, False),
     (128, 128, 260, [70] * 260, None, False),                            # more slots than threads
     (256, 512, 64, [1030] + [49] * 62 + [28], None, True),               # 64 rows per slot on average, one long slot
-])
+]
+
+
+@pytest.mark.parametrize("d,F,E,rows,se,gather", SHAPES)
 def test_ffn_lds_tile(d, F, E, rows, se, gather):
     so, se, n, T, x, w1, w2, index = _case(d, F, E, rows, se, gather, d + F)
     src = x[:n]

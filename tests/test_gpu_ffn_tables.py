@@ -7,6 +7,7 @@ import torch
 
 import oracle
 import synth
+from ffn_shapes import BAD_ROWS, BAD_TABLES
 from gpu_util import f64, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
@@ -41,14 +42,8 @@ def test_rows_past_the_batch(dtype, max_rows, rows, schedule):
         assert (np.abs(got - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-3 * np.abs(ref).max()).all()
 
 
-# rows per slot and the shape that takes each kernel: binary32 (both tile heights, short and long k), bf16 for few rows, 128 columns, 256 x 256
-KERNELS = [
-    pytest.param(synth.F32, 64, 320, 1, 0, id="f32-short"),
-    pytest.param(synth.F32, 320, 448, 12, 0, id="f32-64rows"),
-    pytest.param(synth.BF16, 128, 1024, 1, 200, id="few-rows"),
-    pytest.param(synth.BF16, 128, 256, 4, 0, id="128-columns"),
-    pytest.param(synth.BF16, 256, 512, 100, 0, id="256x256"),
-]
+# every kernel: its shape, and what it does to the rows per slot
+KERNELS = [pytest.param(synth.F32 if name.startswith("f32") else synth.BF16, *shape, id=name.replace(" ", "-")) for name, *shape in BAD_TABLES]
 
 
 def _run(dtype, d, F, E, rows, se, used, schedule, index=None, n_src=None):
@@ -57,8 +52,9 @@ def _run(dtype, d, F, E, rows, se, used, schedule, index=None, n_src=None):
     so = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
     T = int(so[-1])
     x = synth.normal_tensor((n_src or T, d), 1.0, [94, d, T], dtype)
-    w1 = synth.normal_tensor((E, d, F), 0.05, [95, d, F], dtype)
-    w2 = synth.normal_tensor((E, F, d), 0.05, [96, d, F], dtype)
+    # weights of six experts, the same ones again for the rest
+    w1 = np.resize(synth.normal_tensor((min(E, 6), d, F), 0.05, [95, d, F], dtype), (E, d, F))
+    w2 = np.resize(synth.normal_tensor((min(E, 6), F, d), 0.05, [96, d, F], dtype), (E, F, d))
     good = (se >= 0) & (se < E)
     src = x if index is None else np.ascontiguousarray(x[np.clip(index, 0, len(x) - 1)])
     ref = f64(oracle.ffn(src, w1, w2, so, np.where(good, se, 0).astype(np.int32), len(rows)))
@@ -82,10 +78,10 @@ def _close(got, ref, dtype):
 
 
 @pytest.mark.parametrize("schedule", [0, 1])
-@pytest.mark.parametrize("dtype,d,F,scale,empty", KERNELS)
-def test_slots_that_are_none(dtype, d, F, scale, empty, schedule):
-    E = 6
-    rows = [5, 3, 4, 0, 33, 6, 2, 9, 4]
+@pytest.mark.parametrize("dtype,d,F,scale,empty,experts", KERNELS)
+def test_slots_that_are_none(dtype, d, F, scale, empty, experts, schedule):
+    E = max(6, experts)
+    rows = BAD_ROWS[0]
     se = [0, E, 0, 2, 2, -1, 4, 4, 5]           # ids that are no expert's, one between two slots of an expert
     used = 7                                    # the second slot of expert 4 and expert 5's are not slots
     rows, se = [r * scale for r in rows] + [0] * empty, np.array(se + [5] * empty, np.int32)
@@ -96,10 +92,10 @@ def test_slots_that_are_none(dtype, d, F, scale, empty, schedule):
 
 
 @pytest.mark.parametrize("schedule", [0, 1])
-@pytest.mark.parametrize("dtype,d,F,scale,empty", KERNELS)
-def test_row_numbers_out_of_range(dtype, d, F, scale, empty, schedule):
-    E = 4
-    rows = [r * scale for r in (7, 40, 1, 18)] + [0] * empty
+@pytest.mark.parametrize("dtype,d,F,scale,empty,experts", KERNELS)
+def test_row_numbers_out_of_range(dtype, d, F, scale, empty, experts, schedule):
+    E = max(4, experts)
+    rows = [r * scale for r in BAD_ROWS[1]] + [0] * empty
     se = np.array([0, 1, 2, 3] + [3] * empty, np.int32)
     T = sum(rows)
     n_src = T // 2 + 1

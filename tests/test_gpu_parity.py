@@ -12,6 +12,7 @@ import torch
 
 import oracle
 import synth
+from ffn_shapes import FFN_SHAPES
 from gpu_util import assert_close, check_ids_margin, f64, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
@@ -285,26 +286,28 @@ def test_ffn_bf16_long_slots(schedule):
     assert torch.equal(y[:K], y2[:K])
 
 
-@pytest.mark.parametrize("case", ["ragged", "long", "dense"])
+def _shape(name):
+    """E, d, F, slot tables, rows in slots and in all of a shape meant for one kernel (tests/test_ffn_routes.py checks that it takes it)."""
+    E, d, F, rows, experts, behind = FFN_SHAPES[name]
+    so, se = _slots_for(rows, experts)
+    return E, d, F, rows, so, se, int(so[-1]), int(so[-1]) + behind
+
+
+def _weights(E, d, F, seeds, se):
+    """Drawn for the experts that have slots; any that come after them repeat these."""
+    n = int(se.max()) + 1
+    return (np.resize(synth.normal_tensor((n, d, F), 0.05, [seeds[0]], synth.BF16), (E, d, F)),
+            np.resize(synth.normal_tensor((n, F, d), 0.05, [seeds[1]], synth.BF16), (E, F, d)))
+
+
+@pytest.mark.parametrize("case", ["ragged", "long", "listed", "dense"])
 def test_ffn_first_product_h(case):
     """The first product on its own: h = relu(x_perm W1[e]) as left in the head of the workspace, element by
-    element against the oracle, for the three kernels that can write it (64/128-row tiles of the 128-column
-    kernel reading the slot tables, the same with a work list, the 256 x 256 tile kernel)."""
-    if case == "ragged":
-        E, d, F = 5, 128, 256
-        rows, experts = [3, 0, 64, 65, 1, 130, 40, 0, 17], [0, 0, 1, 2, 2, 3, 3, 3, 4]
-    elif case == "long":
-        E, d, F = 3, 256, 512
-        rows, experts = [300, 129, 0, 128, 1, 700], [0, 0, 1, 1, 2, 2]
-    else:
-        E, d, F = 4, 256, 512
-        rows, experts = [1500, 129, 0, 256, 257, 1, 385, 2000, 63], [0, 0, 1, 1, 2, 2, 3, 3, 3]
-    so, se = _slots_for(rows, experts)
-    K = int(so[-1])
-    T = K + 9
+    element against the oracle, for the kernels that can write it (64/128-row tiles of the 128-column kernel
+    reading the slot tables, 128-row tiles through LDS, the 128-column kernel with a work list, the 256 x 256 tile kernel)."""
+    E, d, F, rows, so, se, K, T = _shape(case)
     x = synth.normal_tensor((T, d), 1.0, [51], synth.BF16)
-    w1 = synth.normal_tensor((E, d, F), 0.05, [52], synth.BF16)
-    w2 = synth.normal_tensor((E, F, d), 0.05, [53], synth.BF16)
+    w1, w2 = _weights(E, d, F, (52, 53), se)
     ref_y, ref_h = oracle.ffn(x, w1, w2, so, se, len(rows), want_h=True)
     ws = torch.zeros(moe.lib().moe_expert_ffn_workspace_bytes(T, len(rows), d, F, moe.MOE_BF16), dtype=torch.uint8,
                      device="cuda")
@@ -347,16 +350,9 @@ def test_ffn_bf16_dense_tiles():
     """Enough rows that the 256 x 256 tile kernel takes the slots: lengths around its cut points
     (pieces of 1..256 rows use 1..8 row blocks of the tile), short and empty slots beside them, and
     the fused gather."""
-    E, d, F = 7, 256, 512
-    rows = [1500, 129, 0, 256, 257, 1, 385, 2000, 128, 513, 384, 64, 65, 96, 289, 320, 321, 32, 160, 224, 97]
-    experts = [0, 0, 1, 1, 2, 2, 3, 3, 3, 4, 4, 4, 5, 5, 5, 5, 6, 6, 6, 6, 6]
-    so, se = _slots_for(rows, experts)
-    K = int(so[-1])
-    T = K + 3
-    assert T >= 4096 and T >= 64 * len(rows)        # the sizes at which the library uses that kernel
+    E, d, F, rows, so, se, K, T = _shape("dense tiles")
     x = synth.normal_tensor((T, d), 1.0, [31], synth.BF16)
-    w1 = synth.normal_tensor((E, d, F), 0.05, [32], synth.BF16)
-    w2 = synth.normal_tensor((E, F, d), 0.05, [33], synth.BF16)
+    w1, w2 = _weights(E, d, F, (32, 33), se)
     ref = oracle.ffn(x, w1, w2, so, se, len(rows))
     args = (moe.moe_pack_weights(to_dev(w1)), moe.moe_pack_weights(to_dev(w2)), to_dev(so), to_dev(se),
             torch.tensor([len(rows)], dtype=torch.int32, device="cuda"), E, F)
@@ -380,24 +376,13 @@ def test_ffn_bf16_dense_tiles():
 def test_ffn_bf16_many_short_slots_beside_long_ones():
     """The tile kernel on matrices other than the small test's (d = 512, F = 768: two and three column tiles,
     16 and 24 k stages): rests of 1..128 rows with 1..4 row blocks beside full 256-row ranges and rests above
-    128 rows, 32 single-slot experts of 1..128 rows (tiles that only stream their weights), an expert with two
+    128 rows, 60 single-slot experts of 1..128 rows (tiles that only stream their weights), an expert with two
     short slots (shared weights), empty slots, the fused gather.  Every element of h and of the output against
     the oracle, and bit for bit against the experts schedule, which runs the 128-column kernel alone and
     accumulates in the same order."""
-    E, d, F = 40, 512, 768
-    rng = np.random.default_rng(7)
-    rows = [1500, 129, 0, 256, 257, 1, 385, 2000, 128, 513, 384, 64, 65, 96, 289, 320, 321, 32, 160, 224, 97, 127, 33]
-    experts = [0, 0, 1, 1, 2, 2, 3, 3, 3, 4, 4, 4, 5, 5, 5, 5, 6, 6, 6, 6, 6, 7, 7]
-    for e in range(8, E):                         # many single-slot experts with short rows
-        rows.append(int(rng.integers(1, 129)))
-        experts.append(e)
-    so, se = _slots_for(rows, experts)
-    K = int(so[-1])
-    T = K + 5
-    assert T >= 4096 and T >= 64 * len(rows)        # the sizes at which the library uses the tile kernels
+    E, d, F, rows, so, se, K, T = _shape("many short slots")
     x = synth.normal_tensor((T, d), 1.0, [71], synth.BF16)
-    w1 = synth.normal_tensor((E, d, F), 0.05, [72], synth.BF16)
-    w2 = synth.normal_tensor((E, F, d), 0.05, [73], synth.BF16)
+    w1, w2 = _weights(E, d, F, (72, 73), se)
     ref_y, ref_h = oracle.ffn(x, w1, w2, so, se, len(rows), want_h=True)
     args = (moe.moe_pack_weights(to_dev(w1)), moe.moe_pack_weights(to_dev(w2)), to_dev(so), to_dev(se),
             torch.tensor([len(rows)], dtype=torch.int32, device="cuda"), E, F)
@@ -422,27 +407,17 @@ def test_ffn_bf16_many_short_slots_beside_long_ones():
     assert torch.equal(y[:K], y3[:K])
 
 
-def test_ffn_bf16_short_tiles_several_per_workgroup():
+@pytest.mark.parametrize("case", ["short tiles", "short tiles, listed"])
+def test_ffn_bf16_short_tiles_several_per_workgroup(case):
     """More short row ranges x column tiles than the chip has compute units: every persistent workgroup of the
     tile kernel walks several tiles of at most 128 rows (loads of the next tile's first stages and its row
-    numbers issued during the current one, epilogue stores in flight while the next tile starts), at the
-    d = 768 of the workloads.  128 experts of 64..128 rows, some with a second slot; with and without the gather."""
-    E, d, F = 128, 768, 1536
-    rng = np.random.default_rng(11)
-    rows, experts = [], []
-    for e in range(E):
-        rows.append(int(rng.integers(64, 129)))
-        experts.append(e)
-        if e % 17 == 3:
-            rows.append(int(rng.integers(64, 129)))
-            experts.append(e)
-    so, se = _slots_for(rows, experts)
-    K = int(so[-1])
-    T = K + 2
-    assert T >= 4096 and T >= 64 * len(rows) and len(rows) * (F // 256) > 3 * 256
+    numbers issued during the current one, epilogue stores in flight while the next tile starts); 60 experts of 64..128 rows, most with a
+    second slot.  And where the weight stream binds, the 128-column kernel with its list: 128 experts at the d = 768 of the workloads,
+    some with a second slot; with and without the gather."""
+    E, d, F, rows, so, se, K, T = _shape(case)
+    assert len(rows) * (F // 256) > 3 * 256
     x = synth.normal_tensor((T, d), 1.0, [81], synth.BF16)
-    w1 = synth.normal_tensor((E, d, F), 0.05, [82], synth.BF16)
-    w2 = synth.normal_tensor((E, F, d), 0.05, [83], synth.BF16)
+    w1, w2 = _weights(E, d, F, (82, 83), se)
     ref = oracle.ffn(x, w1, w2, so, se, len(rows))
     args = (moe.moe_pack_weights(to_dev(w1)), moe.moe_pack_weights(to_dev(w2)), to_dev(so), to_dev(se),
             torch.tensor([len(rows)], dtype=torch.int32, device="cuda"), E, F)
@@ -463,12 +438,7 @@ def test_ffn_bf16_dense_tiles_persistent():
     kernel walk several tiles each (prefetch across tiles, epilogue stores still in flight).  The
     oracle checks sampled rows; every row must equal the experts schedule bit for bit, which runs
     the 128-column kernel alone and accumulates in the same order."""
-    E, d, F = 4, 256, 512
-    rows = [30000, 20000, 130, 15000, 257, 15001]
-    experts = [0, 1, 1, 2, 3, 3]
-    so, se = _slots_for(rows, experts)
-    K = int(so[-1])
-    T = K
+    E, d, F, rows, so, se, K, T = _shape("persistent")
     x = synth.normal_tensor((T, d), 1.0, [41], synth.BF16)
     w1 = synth.normal_tensor((E, d, F), 0.05, [42], synth.BF16)
     w2 = synth.normal_tensor((E, F, d), 0.05, [43], synth.BF16)

@@ -64,15 +64,17 @@ def _most_units(rows_of_expert, bm, n_nt, schedule):
 def test_grid_holds_every_range(share_grid):
     rng = np.random.default_rng(5)
     asked, want = [], []
-    for _ in range(3000):
-        bm, n_nt, schedule = int(rng.choice([32, 64])), int(rng.integers(1, 9)), int(rng.integers(0, 2))
+    for _ in range(6000):
+        # 128 rows: the LDS tiles, which take the slot schedule only; 32 columns: binary32 with few units
+        bm, bn, n_nt = int(rng.choice([32, 64, 128])), int(rng.choice([32, 64, 128, 256])), int(rng.integers(1, 9))
+        schedule = int(rng.integers(0, 2)) if bm < 128 else SLOTS
         S = int(rng.integers(1, 60))
         kind = rng.integers(0, 4)
         rows = (rng.integers(0, 3, S) if kind == 0 else rng.integers(0, 130, S) if kind == 1
                 else (rng.pareto(1.0, S) * 20).astype(int) % 3000 if kind == 2 else np.eye(S, dtype=int)[0] * 2000)
         expert = np.sort(rng.integers(0, S, S))                      # some experts own several slots
         per_expert = np.bincount(expert, weights=rows, minlength=S).astype(int)
-        asked.append([bm, 64, max(1, int(rows.sum())), S, schedule, 64 * n_nt])
+        asked.append([bm, bn, max(1, int(rows.sum())), S, schedule, bn * n_nt])
         want.append(_most_units(per_expert, bm, n_nt, schedule))
     for a, w, (got,) in zip(asked, want, share_grid(asked)):
         assert got % 8 == 0 and got // 8 >= w, (a, w, got)
