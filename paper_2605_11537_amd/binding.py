@@ -493,7 +493,8 @@ class MoeLayerTopK:
     def forward(self, x, w_router, b_router, w1, w2, plan_ids=None, schedule=SCHEDULE_SLOTS, residual=0,
                 out=None, router_layout=LAYOUT_PLAIN, marks=None, ffn_events=None):
         """marks, ffn_events: as in MoeLayer.forward."""
-        if marks is None and ffn_events is None and x.shape == (self.T, self.d) and (plan_ids is None or plan_ids.numel()):
+        if (marks is None and ffn_events is None and self.k >= 1 and x.shape == (self.T, self.d)
+                and (plan_ids is None or plan_ids.numel())):
             return _layer_forward(self, x, w_router, b_router, w1, w2, plan_ids, schedule, residual, out, router_layout, int(self.k),
                                   self.renormalize)
         if marks is not None:

@@ -42,6 +42,10 @@ def test_one_call_refuses_what_the_calls_refuse():
         layer.forward(args[0], args[1].float(), *args[2:])                   # router in another type
     with pytest.raises(ValueError):
         layer.forward(*args, out=torch.empty(args[0].shape, dtype=torch.bfloat16))   # not on the device
+    for T in (0, 300):                                               # no choice at all
+        none = moe.MoeLayerTopK(T, 128, 256, 16, 0, 4, 20, torch.bfloat16)
+        with pytest.raises(moe.MoeError):
+            none.forward(args[0][:T], *args[1:])
     layer.ffn_ws = layer.ffn_ws[:256]
     with pytest.raises(moe.MoeError, match="moe_expert_ffn: workspace"):
         layer.forward(*args)
