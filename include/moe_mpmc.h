@@ -69,7 +69,8 @@ const char *moe_build_id(void);
  *   expert_idx[s]  = argmax_e logit[s][e]          (lowest e on an exact tie)
  *   expert_prob[s] = softmax(logit[s])[expert_idx[s]]
  * x [T,d]; w_router [d,E]; b_router [E] binary32 or NULL (= 0); logits_opt [T,E] binary32
- * or NULL.  Sums, exponentials and the argmax are taken in binary32 for both dtypes.
+ * or NULL.  Sums, exponentials and the argmax are taken in binary32 for both dtypes; the order of a
+ * sum depends on the shape (T among it), so a token's last bits may differ between batch sizes.
  * w_layout: MOE_LAYOUT_PLAIN = row-major [d,E] (re-laid into the workspace on every call), or
  * MOE_LAYOUT_PACKED = the image moe_pack_weights writes for a [1,d,E] tensor (static router
  * weights packed once; bf16 with E = 128 or 256 and d a multiple of 128 only).
@@ -259,7 +260,9 @@ int moe_pack_weights(const void *w, int E, int K, int N, int dtype, void *w_pack
  * the rows of an expert's neighbouring slots into tiles together), so the replicas of a hot expert run side by side; MOE_SCHEDULE_EXPERTS makes one work item per
  * (expert, column tile) walk all rows of that expert one tile after another (tokens queue on
  * the one physical expert).  Both produce the same y_perm.  max_rows bounds the rows
- * (normally T), max_slots the slot tables, E the expert count of W1/W2 (slots naming an
+ * (normally T), max_slots the slot tables: slot_expert has max_slots entries and slot_offset
+ * max_slots + 1, all of them readable whatever n_slots[0] is (those past it are read and may
+ * hold anything); E the expert count of W1/W2 (slots naming an
  * expert outside [0,E) are skipped).  Rows outside all slots are not written.
  * row_index (may be NULL): fused gather.  When given, row r of the permuted row space is read
  * from x_perm[row_index[r]] -- pass the token matrix x as x_perm and moe_dispatch's perm as
