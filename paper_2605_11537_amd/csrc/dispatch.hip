@@ -289,6 +289,8 @@ int dispatch_planned_launch(const int32_t *expert_idx, int T, int n_tokens, int 
     }
     PlanArgs pa{plan_partial, n_partial, n_plan_ids, budget, policy, plan_counts, replicas, slot_base, slot_expert,
                 n_slots};
+    // With 16 experts per lane the plan keeps 49 of its registers in scratch (1024 threads leave 128 each; with 256 it had 206), and is ahead
+    // all the same: 30000 ids, 512 experts, 64 slots 43.9 us with 256 threads and slots one by one, 26.4 now.
     auto kern = E <= 128 ? dispatch_permute_kernel<2> : E <= 256 ? dispatch_permute_kernel<4> : dispatch_permute_kernel<16>;
     hipLaunchKernelGGL(kern, dim3(nb > 0 ? nb : 1), dim3(DSP_TOKENS), 0, st, expert_idx, (const int32_t *)nullptr, T, E,
                        nbits, slot_capacity, nb, E + budget, block_hist, counts, kept, expert_offset, slot_offset, perm,

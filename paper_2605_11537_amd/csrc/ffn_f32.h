@@ -12,8 +12,8 @@
 // Bound: few rows per expert by the weight stream (32 experts x 32 rows, 512 x 2048: 4.4 TB/s, 4.9 with no matrix work), many by the
 // matrix pipes (8 x 512 rows, 768 x 3072: 100 of 120 TFLOP/s that the loop reaches without loads); between them by what the tiles load
 // twice.  Both products, tokens straight from memory and as now, us (of the gain 1 .. 1.5 us per product are the search of ffn_share.h):
-//   512 x 2048: 32 experts x 32 rows 68, 58; 40 slots of 10 .. 59 rows 111, 92; 8 x 256 rows 107, 94; 16 x 94 rows 112, 91
-//   768 x 3072, 8 x 512 rows: 498, 395       256 x 1024, 8 experts, 300 rows 22.5, 17.0       64 x 256, 8 x 64 rows 12.9, 10.1
+//   512 x 2048: 32 experts x 32 rows 69, 61; 40 slots of 10 .. 59 rows 119, 101; 8 x 256 rows 107, 95; 16 x 94 rows 112, 91
+//   768 x 3072, 8 x 512 rows: 493, 400       256 x 1024, 8 experts, 300 rows 22.3, 16.7       64 x 256, 8 x 64 rows 12.9, 10.1
 #pragma once
 #include "ffn_share.h"
 #include <type_traits>
@@ -297,9 +297,9 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
 static inline int f32_depth(int K) { return K < 256 ? 1 : 4; }
 
 // Tile height of the others.  64 rows load a third less per multiply-add, 32 rows leave no CU with twice the tiles of another: few
-// rows per expert make few tiles, and from 128 on average on there are enough of them (8 experts x 512 rows, 768 x 3072:
-// 215, 279 us against 248, 318 with 32 rows; 512 x 2048, both products: 40 slots of 10 .. 59 rows 94 against 91, 1300 rows by Zipf's law over
-// 32 experts 136 against 116).
+// rows per expert make few tiles, and from 128 on average on there are enough of them (both products, us, with 64 and 32 rows:
+// 768 x 3072, 8 experts x 512 rows 399, 428; 512 x 2048, 8 x 256 95, 102; 40 slots of 10 .. 59 rows 94, 91; 1300 rows by Zipf's law over
+// 32 experts 136, 116).
 static inline int f32_rows(int max_rows, int E) { return (long long)max_rows >= 128LL * E ? 64 : 32; }
 
 // A workgroup per unit, except up to k = 256, where a unit is short beside its search: there twice as many as are resident (two with 64
