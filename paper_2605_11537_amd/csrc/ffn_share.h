@@ -41,7 +41,9 @@ struct TileShare {
         if (p > 0 && slot_expert[p - 1] == e) return 0;
         int last = p;
         while (last + 1 < P && slot_expert[last + 1] == e) ++last;
-        const int r0 = slot_offset[p], left = max_rows - r0;
+        const int r0 = slot_offset[p];
+        if (r0 < 0) return 0;                     // nor go through rows that are none
+        const int left = max_rows - r0;
         int n = slot_offset[last + 1] - r0;
         if (n > left) n = left;
         return n > 0 ? n : 0;
@@ -97,7 +99,7 @@ struct TileShare {
             p0 = tid < P ? tid : P;
             p1 = tid < P ? tid + 1 : P;
             own_rows = 0;
-            if (tid < P && own_expert >= 0 && own_expert < E && (tid == 0 || before != own_expert)) {
+            if (tid < P && own_expert >= 0 && own_expert < E && own_row >= 0 && (tid == 0 || before != own_expert)) {
                 unsigned long long m = ends & (~0ull << lane);
                 int word = w;
                 while (m == 0) m = last_lds[++word];  // ends: the bit of slot P - 1 is set

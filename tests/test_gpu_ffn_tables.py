@@ -107,3 +107,30 @@ def test_row_numbers_out_of_range(dtype, d, F, scale, empty, experts, schedule):
     got, ref, _ = _run(dtype, d, F, E, rows, se, len(rows), schedule, index, n_src)
     assert np.isfinite(got).all()
     assert _close(got[~bad], ref[~bad], dtype)
+
+
+# the kernels that cut an expert's rows into tiles themselves (the LDS tiles in the slot schedule only)
+@pytest.mark.parametrize("dtype,d,F,scale,empty,experts,schedule", [
+    pytest.param(*k.values, schedule, id=f"{k.id}-{schedule}") for k in KERNELS for schedule in (0, 1)
+    if k.id in ("f32-short", "f32-64-rows", "f32-staged") or k.id == "lds" and schedule == 0])
+@pytest.mark.parametrize("slots", [9, 300])          # a slot per thread of the search, and two
+def test_slots_that_begin_before_the_rows(dtype, d, F, scale, empty, experts, schedule, slots):
+    """Such a slot is none, however far before (its tiles are not walked one by one up to the first row)."""
+    import paper_2605_11537_amd as moe
+    E, n = 9, 40 * scale
+    rows = [n // 2, n // 2] + [0] * (slots - 2)
+    so = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    se = np.minimum(np.arange(slots), E - 1).astype(np.int32)
+    so[0] = -2 ** 30                                 # slot 0 runs from there to the middle
+    # the sizes that the kernels want: many rows per slot and no 256 x 256 tiles for the LDS tiles, 128 rows per expert for 64-row tiles
+    T, F = (65 * slots + 1, 640) if dtype == synth.BF16 else (n if scale == 1 else 1200, F)
+    x = synth.normal_tensor((T, d), 1.0, [97, d], dtype)
+    w1, w2 = synth.normal_tensor((E, d, F), 0.05, [98, d], dtype), synth.normal_tensor((E, F, d), 0.05, [99, d], dtype)
+    ref = f64(oracle.ffn(x, w1, w2, np.array([0, n // 2, n], np.int32), np.array([0, 1], np.int32), 2))
+    pack = (lambda w: w) if dtype == synth.F32 else moe.moe_pack_weights
+    y = torch.full((T, d), 7.0, dtype=torch.float32 if dtype == synth.F32 else torch.bfloat16, device="cuda")
+    moe.moe_expert_ffn(to_dev(x), pack(to_dev(w1)), pack(to_dev(w2)), to_dev(so), to_dev(se),
+                       torch.tensor([slots], dtype=torch.int32, device="cuda"), E, F, schedule=schedule, out=y)
+    got = f64(to_host(y))
+    assert (got[: n // 2] == 7.0).all() and (got[n:] == 7.0).all()
+    assert _close(got[n // 2: n], ref[n // 2: n], dtype)
