@@ -92,3 +92,18 @@ def test_replicas_beyond_the_slot_table(replicas, max_slots):
     slots = (slots + [first[-1]] * (max_slots + 1))[: max_slots + 1]
     assert (to_host(out["kept"]) == kept).all() and (to_host(out["expert_offset"]) == first).all()
     assert (to_host(room) == np.array(slots + [-7] * 64)).all()
+
+
+@pytest.mark.parametrize("E", [3, 40, 128, 200, 700])
+def test_random_plans(E):
+    """Plans of random sizes, loads and capacities, in both policies: few ids (many equal loads) to many (loads close together)."""
+    import paper_2605_11537_amd as moe
+    rng = np.random.default_rng(E)
+    for i in range(60):
+        T = int(np.exp(rng.uniform(np.log(E), np.log(200000 if i % 6 == 0 else 6000))))
+        w = rng.pareto(rng.uniform(0.5, 4.0), E) + rng.choice([0.0, 0.2, 5.0, 500.0])
+        ids = rng.choice(E, T, p=w / w.sum()).astype(np.int32)
+        R, C, policy = int(rng.integers(0, 2 * E)), max(1, int(T / E * rng.uniform(0.1, 2.0))), int(i % 4 == 3)
+        ref, got = oracle.plan(ids, E, R, C, policy), moe.replica_plan(to_dev(ids), E, R, C, policy)
+        assert (to_host(got["replicas"]) == ref["replicas"]).all(), (i, T, R, C, policy)
+        assert (to_host(got["slot_expert"]) == ref["slot_expert"]).all() and int(got["n_slots"][0]) == ref["n_slots"]
