@@ -67,29 +67,19 @@ typedef unsigned att_u32x4_t __attribute__((ext_vector_type(4)));
 // NKS = features / 16.  PER: scores per lane and row, L <= 64 * PER.  FRAG: h is the fragment image of the states, else row-major.
 template <int NKS, int PER, bool FRAG>
 __global__ __launch_bounds__(ATT_THREADS, 1) void sru_attention_kernel(const bf16_t *__restrict__ h,
-                                                                        const bf16_t *__restrict__ hp, int L, int Lp,
-                                                                        bf16_t *__restrict__ z)
+                                                                        const bf16_t *__restrict__ hp, int n_units, int L,
+                                                                        int Lp, bf16_t *__restrict__ z)
 {
     constexpr int n = NKS * 16, LDQ = n + 8, LDS_S = 64 * PER + 4;
     __shared__ __attribute__((aligned(16))) float s_lds[ATT_QT * LDS_S];
     __shared__ __attribute__((aligned(16))) bf16_t q_lds[ATT_QT * LDQ];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Workgroup i runs on XCD i % 8; all query blocks of a sequence read the same keys and packed states,
-    // so whole sequences go to one XCD (sequence b to XCD b % 8) when their number allows: an XCD's L2 then
-    // holds 1/8 of the states instead of cycling through all of them.
+    // All query blocks of a sequence read the same keys and packed states: 8 contiguous ranges of the (sequence, query block) pairs, one per
+    // XCD, so that an XCD's L2 holds the states of about 1/8 of the sequences instead of cycling through all of them.
     const int n_kb = (L + 31) / 32;              // blocks of 32 positions: query blocks and key blocks
-    int seq, qblk;
-    {
-        const int nseq = gridDim.x / n_kb;
-        if (nseq % 8 == 0) {
-            const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-            seq = xcd + 8 * (slot / n_kb);
-            qblk = slot % n_kb;
-        } else {
-            seq = blockIdx.x / n_kb;
-            qblk = blockIdx.x % n_kb;
-        }
-    }
+    const int unit = xcd_remap(blockIdx.x, n_units);
+    if (unit < 0) return;
+    const int seq = unit / n_kb, qblk = unit - seq * n_kb;
     const int q0 = qblk * ATT_QT;
     const bf16_t *hs = h + (size_t)seq * L * n;
     const att_u32x4_t *frag = reinterpret_cast<const att_u32x4_t *>(h) + (size_t)seq * n_kb * NKS * 64;
@@ -320,8 +310,9 @@ int sru_attention_launch(const void *h, bool fragments, int B, int L, int n, voi
                 : sru_attention_kernel<NKS, 16, true>)
     auto kern = n == 128 ? MOE_ATT(8) : MOE_ATT(16);
 #undef MOE_ATT
-    hipLaunchKernelGGL(kern, dim3(ceil_div(L, ATT_QT) * B), dim3(ATT_THREADS), 0, st, (const bf16_t *)h,
-                       (const bf16_t *)ht_ws, L, Lp, (bf16_t *)z);
+    const int units = ceil_div(L, ATT_QT) * B;
+    hipLaunchKernelGGL(kern, dim3((int)align_up((size_t)units, 8)), dim3(ATT_THREADS), 0, st, (const bf16_t *)h,
+                       (const bf16_t *)ht_ws, units, L, Lp, (bf16_t *)z);
     MOE_CHECK_LAUNCH(who);
     return MOE_OK;
 }
