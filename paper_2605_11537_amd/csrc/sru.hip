@@ -281,127 +281,139 @@ __global__ __launch_bounds__(FUS_THREADS, NRB == 1 ? 4 : 1) void sru_layer_fused
     }
     // ---- projections: U[t][c], c = gate * 8 + channel
     {
-        // Token rows: a wavefront fetches its own row blocks in whole 128-byte lines (8 lanes per row, 8 rows
-        // per load; half lines for the longest sequences), turns them into A fragments through a private piece of LDS (row stride 72 elements, no
-        // barrier: LDS operations of one wavefront execute in order).  A lane
-        // loading its fragment straight from memory touches 32 bytes of 32 different lines per load, and
-        // the kernel was bound by those transactions.
-        bf16_t *stage = reinterpret_cast<bf16_t *>(u_lds + W_FLOATS) + (size_t)w * (SB * 32 * LDA);
-        u32x4s_t *w_lds = reinterpret_cast<u32x4s_t *>(u_lds);
-        const int r = lane & 31, kh = lane >> 5;
-        constexpr int PPR = KC / 8, RPL = 64 / PPR, NSB = 32 / RPL;      // pieces per row, rows per load, loads per row block
-        const int lrow = lane / PPR, lpiece = lane % PPR;
-        // this lane's pieces of its rows, elements from the sequence's first; or the first fragment of its row blocks
-        unsigned a_off[NRB][NSB];
-        const u32x4s_t *a_frag[NRB];
-#pragma unroll
-        for (int i = 0; i < NRB; ++i)
-#pragma unroll
-            for (int sb = 0; sb < NSB; ++sb) {
-                const int t = (w + FUS_WAVES * i) * 32 + sb * RPL + lrow;   // row blocks dealt to the eight wavefronts in turn
-                a_off[i][sb] = (unsigned)(t < L ? t : L - 1) * K + lpiece * 8;
-            }
-#pragma unroll
-        for (int i = 0; i < NRB; ++i) {
-            const int blk = w + FUS_WAVES * i < n_blocks ? w + FUS_WAVES * i : n_blocks - 1;
-            a_frag[i] = Xp + ((size_t)b * n_blocks + blk) * (K >> 4) * 64;
-        }
-        const int gate = r >> 3 < kgates ? r >> 3 : 0;
-        const int col = gate * n_h + cb * FUS_CH + (r & 7);
-        const u32x4s_t *b_ptr = reinterpret_cast<const u32x4s_t *>(Wp) + ((size_t)(col >> 5) * KG + kh) * 32 + (col & 31);
+        const int r = lane & 31;
         f32x16_t acc[NRB][1];
         zero_acc<NRB, 1>(acc);
-        constexpr int KS = KC / 16;
-        // Chunks in flight, of which D - 1 are asked for past the end.  Short row-major sequences: two, which leaves room for a second
-        // workgroup per CU (see the launch bounds).  Narrow first layers have 1 .. 8 chunks, and the other wavefront's loads to hide
-        // behind: 2 x 300, 64 -> 128, with the head, three, two, one chunk: 10.8, 10.5, 9.9 us; 16 x 1024, 256 -> 256: 46.1, 44.3, 43.5.
-        constexpr int D = PIN ? 3 : WF == 2 ? 1 : NRB == 1 ? 2 : 3;
-        constexpr int AR = PIN ? KS : NSB;             // 16-byte pieces per lane, row block and chunk (the same number)
-        u32x4s_t ga[D][NRB][AR], fb[WF ? 1 : D][KS], wf[WF ? WF : 1];
-        const int nkc = K / KC;
-        auto load = [&](int kc, int buf) {
-            const int k0 = (kc < nkc ? kc : nkc - 1) * KC;         // past the end: a harmless re-read
-            if constexpr (WF == 0) {
+        // One body per number of row blocks a wavefront has.  With NRB for everybody, the blocks that a wavefront does not have were up to a third of
+        // the loads: 6 x 600, 256 -> 256, four layers with the head, 57.6 -> 47.4 us (with the recurrence's steps below); 8 x 300, 768 -> 256, one
+        // layer 19.5 -> 16.3; 5 x 777, 768 -> 256, two layers 46.9 -> 42.4.
+        auto product = [&](auto BLOCKS) {
+            constexpr int MB = decltype(BLOCKS)::value;
+            // Token rows: a wavefront fetches its own row blocks in whole 128-byte lines (8 lanes per row, 8 rows
+            // per load; half lines for the longest sequences), turns them into A fragments through a private piece of LDS (row stride 72 elements, no
+            // barrier: LDS operations of one wavefront execute in order).  A lane
+            // loading its fragment straight from memory touches 32 bytes of 32 different lines per load, and
+            // the kernel was bound by those transactions.
+            bf16_t *stage = reinterpret_cast<bf16_t *>(u_lds + W_FLOATS) + (size_t)w * (SB * 32 * LDA);
+            u32x4s_t *w_lds = reinterpret_cast<u32x4s_t *>(u_lds);
+            const int kh = lane >> 5;
+            constexpr int PPR = KC / 8, RPL = 64 / PPR, NSB = 32 / RPL;      // pieces per row, rows per load, loads per row block
+            const int lrow = lane / PPR, lpiece = lane % PPR;
+            // this lane's pieces of its rows, elements from the sequence's first; or the first fragment of its row blocks
+            unsigned a_off[MB][NSB];
+            const u32x4s_t *a_frag[MB];
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) fb[buf][ks] = b_ptr[(size_t)((k0 >> 3) + ks * 2) * 32];
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int sb = 0; sb < NSB; ++sb) {
+                    const int t = (w + FUS_WAVES * i) * 32 + sb * RPL + lrow;   // row blocks dealt to the eight wavefronts in turn
+                    a_off[i][sb] = (unsigned)(t < L ? t : L - 1) * K + lpiece * 8;
+                }
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                const int blk = w + FUS_WAVES * i < n_blocks ? w + FUS_WAVES * i : n_blocks - 1;
+                a_frag[i] = Xp + ((size_t)b * n_blocks + blk) * (K >> 4) * 64;
             }
+            const int gate = r >> 3 < kgates ? r >> 3 : 0;
+            const int col = gate * n_h + cb * FUS_CH + (r & 7);
+            const u32x4s_t *b_ptr = reinterpret_cast<const u32x4s_t *>(Wp) + ((size_t)(col >> 5) * KG + kh) * 32 + (col & 31);
+            constexpr int KS = KC / 16;
+            // Chunks in flight, of which D - 1 are asked for past the end.  Short row-major sequences: two, which leaves room for a second
+            // workgroup per CU (see the launch bounds).  Narrow first layers have 1 .. 8 chunks, and the other wavefront's loads to hide
+            // behind: 2 x 300, 64 -> 128, with the head, three, two, one chunk: 10.8, 10.5, 9.9 us; 16 x 1024, 256 -> 256: 46.1, 44.3, 43.5.
+            constexpr int D = PIN ? 3 : WF == 2 ? 1 : NRB == 1 ? 2 : 3;
+            constexpr int AR = PIN ? KS : NSB;             // 16-byte pieces per lane, row block and chunk (the same number)
+            u32x4s_t ga[D][MB][AR], fb[WF ? 1 : D][KS], wf[WF ? WF : 1];
+            const int nkc = K / KC;
+            auto load = [&](int kc, int buf) {
+                const int k0 = (kc < nkc ? kc : nkc - 1) * KC;         // past the end: a harmless re-read
+                if constexpr (WF == 0) {
 #pragma unroll
-            for (int i = 0; i < NRB; ++i)
+                    for (int ks = 0; ks < KS; ++ks) fb[buf][ks] = b_ptr[(size_t)((k0 >> 3) + ks * 2) * 32];
+                }
 #pragma unroll
-                for (int sb = 0; sb < AR; ++sb)
-                    ga[buf][i][sb] = PIN ? a_frag[i][((k0 >> 4) + sb) * 64 + lane]
-                                         : *reinterpret_cast<const u32x4s_t *>(Xs + k0 + a_off[i][sb]);
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        auto compute = [&](int kc, int buf) {
-            const int fbuf = WF ? 0 : buf;
+                for (int i = 0; i < MB; ++i)
+#pragma unroll
+                    for (int sb = 0; sb < AR; ++sb)
+                        ga[buf][i][sb] = PIN ? a_frag[i][((k0 >> 4) + sb) * 64 + lane]
+                                             : *reinterpret_cast<const u32x4s_t *>(Xs + k0 + a_off[i][sb]);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto compute = [&](int kc, int buf) {
+                const int fbuf = WF ? 0 : buf;
+                if constexpr (WF > 0) {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) fb[0][ks] = w_lds[(kc * KS + ks) * 64 + lane];
+                }
+                if constexpr (PIN) {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                        for (int i = 0; i < MB; ++i)
+                            acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ga[buf][i][ks]),
+                                                                                __builtin_bit_cast(bf16x8_t, fb[fbuf][ks]),
+                                                                                acc[i][0], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    return;
+                }
+#pragma unroll
+                for (int i0 = 0; i0 < MB; i0 += SB) {
+#pragma unroll
+                    for (int i = 0; i < SB && i0 + i < MB; ++i)
+#pragma unroll
+                        for (int sb = 0; sb < NSB; ++sb)
+                            *reinterpret_cast<u32x4s_t *>(stage + (i * 32 + sb * RPL + lrow) * LDA + lpiece * 8) = ga[buf][i0 + i][sb];
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                        for (int i = 0; i < SB && i0 + i < MB; ++i) {
+                            const u32x4s_t av = *reinterpret_cast<const u32x4s_t *>(stage + (i * 32 + r) * LDA + ks * 16 + kh * 8);
+                            acc[i0 + i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av),
+                                                                                     __builtin_bit_cast(bf16x8_t, fb[fbuf][ks]),
+                                                                                     acc[i0 + i][0], 0, 0, 0);
+                        }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            if constexpr (WF > 0) {
+                const int n_frag = K >> 4;
+#pragma unroll
+                for (int i = 0; i < WF; ++i) {
+                    const int fr = w + FUS_WAVES * i < n_frag ? w + FUS_WAVES * i : n_frag - 1;
+                    wf[i] = b_ptr[(size_t)(fr * 2) * 32];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // A wavefront whose first row block lies past the sequence multiplies nothing: eight of them loaded the same rows at 7 positions.
+            // (Where weights are shared the loads stay unconditional, the wait for the weights is a count over them.)
+            const bool rows = WF > 0 || w * 32 < L;
+            if (rows) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) load(d, d);
+            }
             if constexpr (WF > 0) {
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) fb[0][ks] = w_lds[(kc * KS + ks) * 64 + lane];
+                for (int i = 0; i < WF; ++i) w_lds[(w + FUS_WAVES * i) * 64 + lane] = wf[i];
+                __syncthreads();
             }
-            if constexpr (PIN) {
+            const int n_chunks = rows ? nkc : 0;
+            int kc = 0;
+            for (; kc + D < n_chunks; kc += D) {
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                    for (int i = 0; i < NRB; ++i)
-                        acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ga[buf][i][ks]),
-                                                                            __builtin_bit_cast(bf16x8_t, fb[fbuf][ks]),
-                                                                            acc[i][0], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                return;
+                for (int d = 0; d < D; ++d) {
+                    compute(kc + d, d);
+                    load(kc + D + d, d);
+                }
             }
 #pragma unroll
-            for (int i0 = 0; i0 < NRB; i0 += SB) {
-#pragma unroll
-                for (int i = 0; i < SB; ++i)
-#pragma unroll
-                    for (int sb = 0; sb < NSB; ++sb)
-                        *reinterpret_cast<u32x4s_t *>(stage + (i * 32 + sb * RPL + lrow) * LDA + lpiece * 8) = ga[buf][i0 + i][sb];
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                    for (int i = 0; i < SB; ++i) {
-                        const u32x4s_t av = *reinterpret_cast<const u32x4s_t *>(stage + (i * 32 + r) * LDA + ks * 16 + kh * 8);
-                        acc[i0 + i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, av),
-                                                                                 __builtin_bit_cast(bf16x8_t, fb[fbuf][ks]),
-                                                                                 acc[i0 + i][0], 0, 0, 0);
-                    }
-            }
-            __builtin_amdgcn_sched_barrier(0);
+            for (int d = 0; d < D; ++d)
+                if (kc + d < n_chunks) compute(kc + d, d); // uniform
         };
-        if constexpr (WF > 0) {
-            const int n_frag = K >> 4;
-#pragma unroll
-            for (int i = 0; i < WF; ++i) {
-                const int fr = w + FUS_WAVES * i < n_frag ? w + FUS_WAVES * i : n_frag - 1;
-                wf[i] = b_ptr[(size_t)(fr * 2) * 32];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // A wavefront whose first row block lies past the sequence multiplies nothing: eight of them loaded the same rows at 7 positions.
-        // (Where weights are shared the loads stay unconditional, the wait for the weights is a count over them.)
-        const bool rows = WF > 0 || w * 32 < L;
-        if (rows) {
-#pragma unroll
-            for (int d = 0; d < D; ++d) load(d, d);
-        }
-        if constexpr (WF > 0) {
-#pragma unroll
-            for (int i = 0; i < WF; ++i) w_lds[(w + FUS_WAVES * i) * 64 + lane] = wf[i];
-            __syncthreads();
-        }
-        const int n_chunks = rows ? nkc : 0;
-        int kc = 0;
-        for (; kc + D < n_chunks; kc += D) {
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                compute(kc + d, d);
-                load(kc + D + d, d);
-            }
-        }
-#pragma unroll
-        for (int d = 0; d < D; ++d)
-            if (kc + d < n_chunks) compute(kc + d, d); // uniform
+        using std::integral_constant;
+        const int n_own = (n_blocks - w + FUS_WAVES - 1) / FUS_WAVES;            // NRB / 2 and more
+        if (NRB == 1 || n_own == NRB) product(integral_constant<int, NRB>{});
+        else if (NRB == 4 && n_own == 3) product(integral_constant<int, NRB == 4 ? 3 : NRB>{});
+        else product(integral_constant<int, (NRB > 1 ? NRB / 2 : 1)>{});
         __syncthreads();           // the staging pieces alias the tile written next
         if (r < kgates * FUS_CH) {
 #pragma unroll
@@ -485,9 +497,17 @@ __global__ __launch_bounds__(FUS_THREADS, NRB == 1 ? 4 : 1) void sru_layer_fused
             if (i < cl && t0 + i < L) h_lds[(t0 + i) * FUS_CH + ch] = f32_to_bf16(r[i] * tanhf_(c) + (1.f - r[i]) * hw[i]);
         }
     };
-    // short sequences: the steps they have
+    // the steps that the chunks have, to the next even number (a step past the chunk costs as much as one inside)
     using std::integral_constant;
-    if (NRB > 1) recurrence(integral_constant<int, MAX_L / FUS_CHUNKS>{});
+    if (NRB == 4) {
+        if (cl > 14) recurrence(integral_constant<int, NRB == 4 ? 16 : 1>{});
+        else if (cl > 12) recurrence(integral_constant<int, NRB == 4 ? 14 : 1>{});
+        else if (cl > 10) recurrence(integral_constant<int, NRB == 4 ? 12 : 1>{});
+        else recurrence(integral_constant<int, NRB == 4 ? 10 : 1>{});
+    } else if (NRB == 2) {
+        if (cl > 6) recurrence(integral_constant<int, NRB == 2 ? 8 : 1>{});
+        else recurrence(integral_constant<int, NRB == 2 ? 6 : 1>{});
+    }
     else if (cl == 1) recurrence(integral_constant<int, 1>{});
     else if (cl == 2) recurrence(integral_constant<int, 2>{});
     else recurrence(integral_constant<int, 4>{});
@@ -649,7 +669,7 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
             // sequences keeps its LDS small, two to four of its workgroups share a CU)
 #define MOE_FUS(N)                                                                                                     \
     (pin ? (nin <= 256            ? sru_layer_fused_kernel<N, true, 2>                                                 \
-            : N > 2 && nin <= 768 ? sru_layer_fused_kernel<N, true, (N > 2 ? 6 : 2)>                                   \
+            : N > 1 && nin <= 768 ? sru_layer_fused_kernel<N, true, (N > 1 ? 6 : 2)>                                   \
                                   : sru_layer_fused_kernel<N, true, 0>)                                                \
          : (N > 1 && nin <= 256   ? sru_layer_fused_kernel<N, false, (N > 1 ? 2 : 0)>                                  \
             : N > 1 && nin <= 768 ? sru_layer_fused_kernel<N, false, (N > 1 ? 6 : 0)>                                  \
