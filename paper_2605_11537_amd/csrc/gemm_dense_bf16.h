@@ -20,7 +20,11 @@
 //       lanes that the LDS serves per clock over all banks when a fragment (32 rows x 16 k) is read.
 // One wavefront with no partner on its SIMD must hide everything itself: the LDS reads of the next
 // fragments and the global->LDS loads of a later stage are placed by hand between the matrix
-// instructions (each occupies the pipe for 32 clocks but issues in 4).  LDS reads are inline
+// instructions (each occupies the pipe for 32 clocks but issues in 4).  A load of 1 KB holds the CU's address path for 16 clocks, the four
+// wavefronts ask for theirs together: one after each of eight matrix instructions in a row, they stalled the wavefronts for about 250 clocks per stage of
+// 1024.  So the loads of a stage go out one per four matrix instructions, the tokens behind the barrier that frees their buffer, the weights in
+// the first half of the next stage (768 x 3072, both products, us: 64 experts x 512 rows 387 -> 358, 8 x 4096 361 -> 334, one of 32760 367 -> 345;
+// 256 x 256, half bound by memory, 761 -> 738; the same bits).  LDS reads are inline
 // assembly: the compiler cannot tell which LDS bytes an in-flight global->LDS load will write and
 // would wait for every outstanding load before any LDS read it can see.  The waits are explicit:
 // vector memory operations complete in issue order, so "at most P outstanding" means every load
@@ -137,11 +141,12 @@ __device__ __forceinline__ void dense_tiles_bf16(const bf16_t *__restrict__ A, c
         }
     };
     auto checked = [&](int v) { return (v >= 0 && v < n_src_rows) ? v : 0; };   // a bad index reads row 0
-    auto issue = [&](int kc, int buf) {
+    auto issue = [&](int kc, int buf, bool tokens_only) {
         uint4 *base = smem + buf * STAGE + (w * 4) * 64;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             __builtin_amdgcn_global_load_lds((glb_void_t *)(a_src[i] + kc * BK), (lds_void_t *)(base + i * 64), 16, 0, 0);
+        if (tokens_only) return;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             __builtin_amdgcn_global_load_lds((glb_void_t *)(b_src[i] + (size_t)kc * 4 * 32),
@@ -163,7 +168,9 @@ __device__ __forceinline__ void dense_tiles_bf16(const bf16_t *__restrict__ A, c
     int buf = 0;                       // ring position of the current tile's stage 0
     int prev_stores = 0;               // stores of the previous tile's epilogue, younger than this tile's first loads
 #pragma unroll
-    for (int s = 0; s < NS; ++s) issue(s, s);
+    for (int s = 0; s < NS; ++s) issue(s, s, s + 1 == NS);
+    int late_k = NS - 1;               // stage of the loads that are still to be issued, and its buffer
+    uint4 *late_base = smem + (NS - 1) * STAGE + (w * 4) * 64;
 
     u32x4_t fx[8], fy[8];              // fragments of the two 16-deep steps: [0..3] token row blocks, [4..7] weight strips
 #pragma unroll
@@ -187,9 +194,9 @@ __device__ __forceinline__ void dense_tiles_bf16(const bf16_t *__restrict__ A, c
         f32x16_t acc[4][4];
         zero_acc<4, 4>(acc);
         {
-            // stage 0 landed: everything but the NS-1 younger stages -- and the stores of the previous
-            // tile's epilogue, which are younger still
-            MOE_VMCNT_PLUS((NS - 1) * 8, prev_stores);
+            // stage 0 landed: everything but the NS-1 younger stages (the weights of the last of them are still to be asked for) --
+            // and the stores of the previous tile's epilogue, which are younger still
+            MOE_VMCNT_PLUS((NS - 1) * 8 - 4, prev_stores);
             __builtin_amdgcn_s_barrier();
             const unsigned a = a_addr[0] + buf * (STAGE * 16), b = b_addr[0] + buf * (STAGE * 16);
             if (0 < MYB) MOE_DS_READ128(fx[0], a, 0); if (1 < MYB) MOE_DS_READ128(fx[1], a, 4096); if (2 < MYB) MOE_DS_READ128(fx[2], a, 8192); if (3 < MYB) MOE_DS_READ128(fx[3], a, 12288);
@@ -197,19 +204,27 @@ __device__ __forceinline__ void dense_tiles_bf16(const bf16_t *__restrict__ A, c
             MOE_WAIT_LGKM0_8(fx);
         }
         for (int kc = 0; kc < nk; ++kc) {
-            {   // first 16-deep step of the stage; fetch the fragments of the second
+            {   // first 16-deep step of the stage; fetch the fragments of the second, ask for the weights of the stage whose tokens went out last
+#define MOE_LB(i) __builtin_amdgcn_global_load_lds((glb_void_t *)(b_src[i] + (size_t)late_k * 4 * 32), (lds_void_t *)(late_base + 16 * 64 + i * 64), 16, 0, 0)
                 const unsigned a = a_addr[1] + buf * (STAGE * 16), b = b_addr[1] + buf * (STAGE * 16);
                 MOE_MF(fx, 0, 0); if (0 < MYB) MOE_DS_READ128(fy[0], a, 0); MOE_SB();
                 MOE_MF(fx, 0, 1); MOE_DS_READ128(fy[4], b, 0); MOE_SB();
-                MOE_MF(fx, 0, 2); MOE_DS_READ128(fy[5], b, 2048); MOE_SB();
+                MOE_MF(fx, 0, 2); MOE_DS_READ128(fy[5], b, 2048); MOE_LB(0); MOE_SB();
                 MOE_MF(fx, 0, 3); MOE_DS_READ128(fy[6], b, 4096); MOE_SB();
                 MOE_MF(fx, 1, 0); MOE_DS_READ128(fy[7], b, 6144); MOE_SB();
                 MOE_MF(fx, 1, 1); if (1 < MYB) MOE_DS_READ128(fy[1], a, 4096); MOE_SB();
-                MOE_MF(fx, 1, 2); if (2 < MYB) MOE_DS_READ128(fy[2], a, 8192); MOE_SB();
+                MOE_MF(fx, 1, 2); if (2 < MYB) MOE_DS_READ128(fy[2], a, 8192); MOE_LB(1); MOE_SB();
                 MOE_MF(fx, 1, 3); if (3 < MYB) MOE_DS_READ128(fy[3], a, 12288); MOE_SB();
-                MOE_MF(fx, 2, 0); MOE_MF(fx, 2, 1); MOE_MF(fx, 2, 2); MOE_MF(fx, 2, 3);
-                MOE_MF(fx, 3, 0); MOE_MF(fx, 3, 1); MOE_MF(fx, 3, 2); MOE_MF(fx, 3, 3); MOE_SB();
+                MOE_MF(fx, 2, 0); MOE_SB();
+                MOE_MF(fx, 2, 1); MOE_SB();
+                MOE_MF(fx, 2, 2); MOE_LB(2); MOE_SB();
+                MOE_MF(fx, 2, 3); MOE_SB();
+                MOE_MF(fx, 3, 0); MOE_SB();
+                MOE_MF(fx, 3, 1); MOE_SB();
+                MOE_MF(fx, 3, 2); MOE_LB(3); MOE_SB();
+                MOE_MF(fx, 3, 3); MOE_SB();
             }
+#undef MOE_LB
             // the loads issued below belong to the next tile from stage nk on: switch the sources first
             if (kc + NS == nk && has_next) {
                 int src_row[4];
@@ -232,9 +247,9 @@ __device__ __forceinline__ void dense_tiles_bf16(const bf16_t *__restrict__ A, c
             }
             MOE_WAIT_LGKM0_8(fy);
             // stage kc+1 landed (this wavefront's part); the barrier makes that true for all four and
-            // tells that everyone has read stage kc, whose buffer is refilled below.  Stages up to NS-1
-            // of a tile were issued before the previous epilogue's stores.
-            if (kc + 2 > NS) MOE_VMCNT((NS - 2) * 8);
+            // tells that everyone has read stage kc, whose buffer is refilled below.  Stages up to NS-2
+            // of a tile were issued before the previous epilogue's stores, the weights of stage NS-1 behind them.
+            if (kc + 3 > NS) MOE_VMCNT((NS - 2) * 8);
             else MOE_VMCNT_PLUS((NS - 2) * 8, prev_stores);
             __builtin_amdgcn_s_barrier();
             MOE_SB();
@@ -252,26 +267,26 @@ __device__ __forceinline__ void dense_tiles_bf16(const bf16_t *__restrict__ A, c
                 uint4 *base = smem + buf * STAGE + (w * 4) * 64;
                 buf = buf + 1 == NS ? 0 : buf + 1;
                 const unsigned a = a_addr[0] + buf * (STAGE * 16), b = b_addr[0] + buf * (STAGE * 16);
+                late_k = nx;
+                late_base = base;
 #define MOE_LA(i) __builtin_amdgcn_global_load_lds((glb_void_t *)(a_src[i] + nx * BK), (lds_void_t *)(base + i * 64), 16, 0, 0)
-#define MOE_LB(i) __builtin_amdgcn_global_load_lds((glb_void_t *)(b_src[i] + (size_t)nx * 4 * 32), (lds_void_t *)(base + 16 * 64 + i * 64), 16, 0, 0)
                 MOE_MF(fy, 0, 0); MOE_LA(0); MOE_SB();
-                MOE_MF(fy, 0, 1); MOE_LA(1); MOE_SB();
-                MOE_MF(fy, 0, 2); MOE_LA(2); MOE_SB();
-                MOE_MF(fy, 0, 3); MOE_LA(3); MOE_SB();
-                MOE_MF(fy, 1, 0); MOE_LB(0); MOE_SB();
-                MOE_MF(fy, 1, 1); MOE_LB(1); MOE_SB();
-                MOE_MF(fy, 1, 2); MOE_LB(2); MOE_SB();
-                MOE_MF(fy, 1, 3); MOE_LB(3); MOE_SB();
-                MOE_MF(fy, 2, 0); if (0 < MYB) MOE_DS_READ128(fx[0], a, 0); MOE_SB();
+                MOE_MF(fy, 0, 1); MOE_SB();
+                MOE_MF(fy, 0, 2); MOE_SB();
+                MOE_MF(fy, 0, 3); MOE_SB();
+                MOE_MF(fy, 1, 0); MOE_LA(1); MOE_SB();
+                MOE_MF(fy, 1, 1); MOE_SB();
+                MOE_MF(fy, 1, 2); MOE_SB();
+                MOE_MF(fy, 1, 3); MOE_SB();
+                MOE_MF(fy, 2, 0); if (0 < MYB) MOE_DS_READ128(fx[0], a, 0); MOE_LA(2); MOE_SB();
                 MOE_MF(fy, 2, 1); MOE_DS_READ128(fx[4], b, 0); MOE_SB();
                 MOE_MF(fy, 2, 2); MOE_DS_READ128(fx[5], b, 2048); MOE_SB();
                 MOE_MF(fy, 2, 3); MOE_DS_READ128(fx[6], b, 4096); MOE_SB();
-                MOE_MF(fy, 3, 0); MOE_DS_READ128(fx[7], b, 6144); MOE_SB();
+                MOE_MF(fy, 3, 0); MOE_DS_READ128(fx[7], b, 6144); MOE_LA(3); MOE_SB();
                 MOE_MF(fy, 3, 1); if (1 < MYB) MOE_DS_READ128(fx[1], a, 4096); MOE_SB();
                 MOE_MF(fy, 3, 2); if (2 < MYB) MOE_DS_READ128(fx[2], a, 8192); MOE_SB();
                 MOE_MF(fy, 3, 3); if (3 < MYB) MOE_DS_READ128(fx[3], a, 12288); MOE_SB();
 #undef MOE_LA
-#undef MOE_LB
             }
             MOE_WAIT_LGKM0_8(fx);
         }
