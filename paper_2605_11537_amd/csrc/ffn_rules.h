@@ -9,7 +9,7 @@ namespace moe {
 // 64 and more on average and the matrix sizes fit its tiling (and is where its tiles fill the chip, see ffn_dense_fills).
 static inline bool ffn_use_dense(int max_rows, int max_slots, int K, int N, int schedule)
 {
-    return schedule == MOE_SCHEDULE_SLOTS && N % DENSE_BN == 0 && K % DENSE_BK == 0 && K >= DENSE_MIN_K &&
+    return schedule == MOE_SCHEDULE_SLOTS && N % DENSE_BN == 0 && N <= DENSE_MAX_N && K % DENSE_BK == 0 && K >= DENSE_MIN_K &&
            (long long)max_rows >= 64LL * max_slots && max_rows >= 4096;
 }
 

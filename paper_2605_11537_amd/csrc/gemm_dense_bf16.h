@@ -48,6 +48,7 @@ constexpr int DENSE_STAGE = 32 * 64;                          // 16-byte pieces 
 constexpr int DENSE_LDE = 64 + 8;                             // epilogue strip (32 rows x 64 columns) row stride, elements
 constexpr int DENSE_IDX_OFFSET = DENSE_NS * DENSE_STAGE * 16 + 4 * 32 * DENSE_LDE * 2;   // 256 gathered row numbers
 constexpr int DENSE_LDS_BYTES = DENSE_IDX_OFFSET + 256 * 4;
+constexpr int DENSE_MAX_N = 1 << 22;                          // byte offsets inside a tile's rows fit 32 bits
 constexpr int DENSE_MIN_K = 256;                              // the pipeline needs a few stages per tile
 
 struct DenseTile {
@@ -290,56 +291,68 @@ __device__ __forceinline__ void dense_tiles_bf16(const bf16_t *__restrict__ A, c
             }
             MOE_WAIT_LGKM0_8(fx);
         }
-        // epilogue: this wavefront's 128 x 128 part, 32 token rows x 64 columns at a time through its own
-        // LDS strip (transposes lane-per-column into 16-byte row pieces)
+        // Epilogue: this wavefront's 128 x 128 part, 32 token rows x 64 columns at a time through its own LDS strip (transposes
+        // lane-per-column into 16-byte row pieces).  LDS operations of one wavefront execute in order, so a part's reads need no wait behind its
+        // writes, nor the next part's writes behind them: the only wait is for the reads, one part late, in front of its stores.  With a wait behind
+        // the writes and one behind the reads of each part, the epilogue was 14 % of a 768 deep tile (64 x 512 rows, both products: 366 -> 358 us).
         const unsigned strip = lds0 + NS * STAGE * 16 + w * (32 * LDE * 2);
         const unsigned wr_addr = strip + ((lane & 31) * LDE + 4 * (lane >> 5)) * 2;
         const unsigned rd_addr = strip + ((lane >> 3) * LDE + (lane & 7) * 8) * 2;
+        typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+        typedef float f32x2_t __attribute__((ext_vector_type(2)));
+        u32x4_t o[2][4];               // rows 8i + lane/8 of the strip: row stride 8 * LDE * 2 = 1152 bytes
+        char *const c_part = reinterpret_cast<char *>(C + (size_t)cur_row0 * N + cur_nt * DENSE_BN + wn * 128);      // scalar
+        const unsigned row_bytes = (unsigned)N * 2;      // 256 rows lie within 32 bits (DENSE_MAX_N)
+        auto store = [&](int part, u32x4_t (&v)[4]) {
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-            if (mb >= MYB) continue;
-            typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-            typedef float f32x2_t __attribute__((ext_vector_type(2)));
-// volatile asm: an ordinary max here is hoisted by the compiler onto the whole accumulator array right
-// after the k loop, which needs 256 more registers and spills
-#define MOE_RELU_BITS(f) ({ float r_; asm volatile("v_max_i32 %0, 0, %1" : "=v"(r_) : "v"((float)(f))); r_; })
+            for (int i = 0; i < 4; ++i) {
+                const int gr = (part & ~1) * 32 + wm * 32 + i * 8 + (lane >> 3);
+                // always 8 stores per block, so the counted waits of the next tile hold: rows past the
+                // tile rewrite its last row with the same values (the clamped loads duplicated it)
+                const int sr = gr < cur_nrows ? gr : cur_nrows - 1;
+                *reinterpret_cast<u32x4_t *>(c_part + ((unsigned)sr * row_bytes + (unsigned)((part & 1) * 128 + (lane & 7) * 16))) = v[i];
+            }
+        };
+#pragma unroll
+        for (int part = 0; part < 2 * MYB; ++part) {     // row block part / 2, columns 64 * (part % 2) ..
+// as signed 16-bit integers, a pair at a time: anything with the sign bit set becomes +0.  Volatile assembly: an ordinary max is hoisted by
+// the compiler onto the whole accumulator array right after the k loop, which needs 256 more registers and spills
+#define MOE_PK1(x, y)                                                                                                \
+    ({                                                                                                               \
+        const f32x2_t two_ = {x, y};                                                                                 \
+        unsigned r_ = __builtin_bit_cast(unsigned, __builtin_convertvector(two_, bf16x2_t));                         \
+        if (RELU) asm volatile("v_pk_max_i16 %0, %0, 0" : "+v"(r_));                                                 \
+        r_;                                                                                                          \
+    })
 #define MOE_PK(nb, q)                                                                                                \
     ({                                                                                                               \
-        f32x2_t lo = {acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1]}, hi = {acc[mb][nb][4 * q + 2], acc[mb][nb][4 * q + 3]}; \
-        if (RELU) { /* as signed integers: anything with the sign bit set becomes +0 */                             \
-            lo.x = MOE_RELU_BITS(lo.x); lo.y = MOE_RELU_BITS(lo.y); hi.x = MOE_RELU_BITS(hi.x); hi.y = MOE_RELU_BITS(hi.y); \
-        }                                                                                                            \
         uint2 pk;                                                                                                    \
-        pk.x = __builtin_bit_cast(unsigned, __builtin_convertvector(lo, bf16x2_t));                                  \
-        pk.y = __builtin_bit_cast(unsigned, __builtin_convertvector(hi, bf16x2_t));                                  \
+        pk.x = MOE_PK1(acc[part / 2][nb][4 * q], acc[part / 2][nb][4 * q + 1]);                                      \
+        pk.y = MOE_PK1(acc[part / 2][nb][4 * q + 2], acc[part / 2][nb][4 * q + 3]);                                  \
         pk;                                                                                                          \
     })
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                {
-                    uint2 v;   // block nb, group q -> columns (nb%2)*32 + 8q + 4*(lane/32) .. +3 of token row lane%32
-                    v = MOE_PK(2 * half, 0); MOE_DS_WRITE64(wr_addr, v, 0);       v = MOE_PK(2 * half, 1); MOE_DS_WRITE64(wr_addr, v, 16);
-                    v = MOE_PK(2 * half, 2); MOE_DS_WRITE64(wr_addr, v, 32);      v = MOE_PK(2 * half, 3); MOE_DS_WRITE64(wr_addr, v, 48);
-                    v = MOE_PK(2 * half + 1, 0); MOE_DS_WRITE64(wr_addr, v, 64);  v = MOE_PK(2 * half + 1, 1); MOE_DS_WRITE64(wr_addr, v, 80);
-                    v = MOE_PK(2 * half + 1, 2); MOE_DS_WRITE64(wr_addr, v, 96);  v = MOE_PK(2 * half + 1, 3); MOE_DS_WRITE64(wr_addr, v, 112);
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                u32x4_t o[4];      // rows 8i + lane/8 of the strip: row stride 8 * LDE * 2 = 1152 bytes
-                MOE_DS_READ128(o[0], rd_addr, 0);    MOE_DS_READ128(o[1], rd_addr, 1152);
-                MOE_DS_READ128(o[2], rd_addr, 2304); MOE_DS_READ128(o[3], rd_addr, 3456);
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3])::"memory");
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int gr = (2 * mb + wm) * 32 + i * 8 + (lane >> 3);
-                    // always 8 stores per block, so the counted waits of the next tile hold: rows past the
-                    // tile rewrite its last row with the same values (the clamped loads duplicated it)
-                    const int sr = gr < cur_nrows ? gr : cur_nrows - 1;
-                    *reinterpret_cast<u32x4_t *>(C + (size_t)(cur_row0 + sr) * N + cur_nt * DENSE_BN + wn * 128 + half * 64 +
-                                                 (lane & 7) * 8) = o[i];
-                }
+            const int nb0 = 2 * (part & 1);
+            uint2 v;       // block nb, group q -> columns (nb%2)*32 + 8q + 4*(lane/32) .. +3 of token row lane%32
+            v = MOE_PK(nb0, 0); MOE_DS_WRITE64(wr_addr, v, 0);       v = MOE_PK(nb0, 1); MOE_DS_WRITE64(wr_addr, v, 16);
+            v = MOE_PK(nb0, 2); MOE_DS_WRITE64(wr_addr, v, 32);      v = MOE_PK(nb0, 3); MOE_DS_WRITE64(wr_addr, v, 48);
+            v = MOE_PK(nb0 + 1, 0); MOE_DS_WRITE64(wr_addr, v, 64);  v = MOE_PK(nb0 + 1, 1); MOE_DS_WRITE64(wr_addr, v, 80);
+            v = MOE_PK(nb0 + 1, 2); MOE_DS_WRITE64(wr_addr, v, 96);  v = MOE_PK(nb0 + 1, 3); MOE_DS_WRITE64(wr_addr, v, 112);
+            u32x4_t (&r)[4] = o[part & 1];
+            MOE_DS_READ128(r[0], rd_addr, 0);    MOE_DS_READ128(r[1], rd_addr, 1152);
+            MOE_DS_READ128(r[2], rd_addr, 2304); MOE_DS_READ128(r[3], rd_addr, 3456);
+            MOE_SB();
+            if (part > 0) {                              // all but this part's 8 writes and 4 reads
+                u32x4_t (&d)[4] = o[(part & 1) ^ 1];
+                asm volatile("s_waitcnt lgkmcnt(12)" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3])::"memory");
+                store(part - 1, d);
             }
 #undef MOE_PK
-#undef MOE_RELU_BITS
+#undef MOE_PK1
+        }
+        if (MYB > 0) {
+            u32x4_t (&d)[4] = o[1];                      // an even number of parts
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]), "+v"(d[3])::"memory");
+            store(2 * MYB - 1, d);
         }
         };   // run_tile
         switch (my_blocks) {
