@@ -3,7 +3,9 @@
 //
 // 128 rows of one expert x 64 * NB columns per workgroup (128 or 256), two workgroups per CU.  Both operands go global -> LDS directly
 // into a ring of 32-k stages, as in the 256 x 256 kernel; the four wavefronts are a 2 x 2 grid of 64 x 32 NB outputs.  The fragments of the
-// next 16-deep step are read while the current ones are multiplied, one barrier per stage.  A workgroup finds
+// next 16-deep step are read while the current ones are multiplied, one barrier per stage.  The loads of a stage are spread over the matrix
+// instructions as there (all behind the barrier, both products, us: 768 x 3072, 16 experts x 627 rows 119, now 112, 8 x 1024 107, 99; 512 x 2048, 16 x
+// 480 57, 55; no change where tiles are few).  A workgroup finds
 // its tile in the slot tables (ffn_share.h), so there is no list kernel in front.
 //
 // Bound: what a CU gets from beyond its L2, about 50 GB/s, as first readers of weights and of h (8 experts x 90 rows, k = 4096, 64
@@ -95,26 +97,21 @@ __global__ __launch_bounds__(SHARE_THREADS, 2) void ffn_lds_tile_bf16_kernel(
 #pragma unroll
     for (int i = 0; i < AU; ++i) a_src[i] = A + (size_t)src[i] * K + ld_kg * 8;
     MOE_VMCNT(0);                                            // from here on only the stages' loads are counted
-    auto issue = [&](int kc, int buf) {
-        uint4 *base = ring + buf * STAGE;
-        const int k = kc < nk ? kc : nk - 1;                 // past the end: a harmless re-read
-        if (own_rows) {
-#pragma unroll
-            for (int i = 0; i < AU; ++i)
-                __builtin_amdgcn_global_load_lds((glb_void_t *)(a_src[i] + k * BK), (lds_void_t *)(base + (AU * w + i) * 64), 16, 0,
-                                                 0);
-        }
-#pragma unroll
-        for (int i = 0; i < BU; ++i)
-            __builtin_amdgcn_global_load_lds((glb_void_t *)(b_src[i] + (size_t)k * (BK / 8) * 32),
-                                             (lds_void_t *)(base + (Tile::A_UNITS + w * BU + i) * 64), 16, 0, 0);
-        MOE_SB();
+    // stage kc's loads, tokens and weights apart; past the end: a harmless re-read
+    auto load_a = [&](int kc, int buf, int i) {
+        const int k = kc < nk ? kc : nk - 1;
+        __builtin_amdgcn_global_load_lds((glb_void_t *)(a_src[i] + k * BK), (lds_void_t *)(ring + buf * STAGE + (AU * w + i) * 64), 16, 0, 0);
+    };
+    auto load_b = [&](int kc, int buf, int i) {
+        const int k = kc < nk ? kc : nk - 1;
+        __builtin_amdgcn_global_load_lds((glb_void_t *)(b_src[i] + (size_t)k * (BK / 8) * 32),
+                                         (lds_void_t *)(ring + buf * STAGE + (Tile::A_UNITS + w * BU + i) * 64), 16, 0, 0);
     };
     // all but the newest `young` stages have landed, for everybody behind the barrier
     auto landed = [&](auto YOUNG) {
-        constexpr int young = decltype(YOUNG)::value;
-        if (own_rows) MOE_VMCNT(young * (BU + AU));
-        else MOE_VMCNT(young * BU);
+        constexpr int young = decltype(YOUNG)::value, late = young == NS - 1 ? BU : 0;   // the prologue leaves the last stage's weights to the loop
+        if (own_rows) MOE_VMCNT(young * (BU + AU) - late);
+        else MOE_VMCNT(young * BU - late);
         __builtin_amdgcn_s_barrier();
         MOE_SB();
     };
@@ -147,31 +144,52 @@ __global__ __launch_bounds__(SHARE_THREADS, 2) void ffn_lds_tile_bf16_kernel(
             MOE_SB();
         };
         // (weights, tokens): the transposed block, a lane holds 4 consecutive columns of one token
-        auto multiply = [&](const u32x4_t (&f)[2 + NB]) {
+        // between(i) follows matrix instruction i
+        auto multiply = [&](const u32x4_t (&f)[2 + NB], auto between) {
 #pragma unroll
             for (int mb = 0; mb < MYB; ++mb)
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
+                for (int nb = 0; nb < NB; ++nb) {
                     acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, f[2 + nb]),
                                                                           __builtin_bit_cast(bf16x8_t, f[mb]), acc[mb][nb], 0, 0, 0);
+                    between(mb * NB + nb);
+                    MOE_SB();
+                }
+            if (MYB == 0)
+                for (int i = 0; i < NB; ++i) between(i);
             MOE_SB();
         };
+        constexpr int EVERY = MYB > 1 ? 2 : 1;               // a load per EVERY matrix instructions
 #pragma unroll
-        for (int s = 0; s < NS; ++s) issue(s, s);
+        for (int s = 0; s < NS; ++s) {
+            if (own_rows) {
+#pragma unroll
+                for (int i = 0; i < AU; ++i) load_a(s, s, i);
+            }
+            if (s + 1 < NS) {
+#pragma unroll
+                for (int i = 0; i < BU; ++i) load_b(s, s, i);
+            }
+            MOE_SB();
+        }
         landed(std::integral_constant<int, NS - 1>{});
-        int buf = 0;
+        int buf = 0, late_buf = NS - 1;
         read(fx, 0, 0);
         wait(fx);
         for (int kc = 0; kc < nk; ++kc) {
             read(fy, 1, buf);
-            multiply(fx);
+            multiply(fx, [&](int i) {                        // the weights of the stage whose tokens went out last
+                if (i % EVERY == 0 && i / EVERY < BU) load_b(kc + NS - 1, late_buf, i / EVERY);
+            });
             wait(fy);
             // behind the barrier stage kc + 1 is there and stage kc has been read by all
             landed(std::integral_constant<int, NS - 2>{});
-            issue(kc + NS, buf);
+            late_buf = buf;
             buf = buf + 1 == NS ? 0 : buf + 1;
             read(fx, 0, buf);
-            multiply(fy);
+            multiply(fy, [&](int i) {
+                if (own_rows && i % EVERY == 0 && i / EVERY < AU) load_a(kc + NS, late_buf, i / EVERY);
+            });
             wait(fx);
         }
         MOE_VMCNT(0);                                            // the re-reads past the end
