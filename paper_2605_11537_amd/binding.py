@@ -1,15 +1,16 @@
-"""ctypes binding of ``libmoe_mpmc.so``: the library's calls under the same names (the six steps
+"""Binding of ``libmoe_mpmc.so``: the library's calls under the same names (the six steps
 of the layer, weight packing, the fused plan + dispatch front end, the top-k variants) on torch
 tensors, and three small classes that hold preallocated buffers and issue the calls in order.
-Argument marshalling only -- every step of the path runs in the HIP kernels.  Torch is used for
+Argument marshalling only -- every step of the path runs in the HIP kernels.  The library is loaded through ctypes;
+the calls that enqueue work go through the extension ``_marshal`` (csrc/marshal.cpp), which reads the tensors' pointers itself.  Torch is used for
 device memory and the current stream, nothing else.  There is no CPU fallback: if the library is
 missing or a call fails, an exception is raised.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib
 import os
-import struct
 
 import torch
 
@@ -20,6 +21,7 @@ SCHEDULE_SLOTS, SCHEDULE_EXPERTS = 0, 1
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmoe_mpmc.so")
 _lib = None
+_calls = None                    # the extension, bound to the library's functions
 
 EXPORTS = (
     "moe_last_error", "moe_version", "moe_build_id",
@@ -34,6 +36,12 @@ EXPORTS = (
     "moe_plan_dispatch_workspace_bytes", "moe_plan_dispatch", "moe_layer_forward",
     "moe_measure_sink_bytes", "moe_measure_stream_read", "moe_measure_mfma_bf16_flops", "moe_measure_mfma_bf16",
 )
+
+
+# the calls that go through the extension
+MARSHALLED = ("moe_route", "moe_route_topk", "sru_predict", "replica_plan", "moe_dispatch", "moe_dispatch_static", "moe_dispatch_topk",
+              "moe_plan_dispatch", "moe_pack_weights", "moe_expert_ffn", "moe_expert_ffn_rows", "moe_combine", "moe_combine_topk",
+              "moe_layer_forward")
 
 
 class MoeError(RuntimeError):
@@ -52,10 +60,10 @@ class SruWeightsC(C.Structure):
 def lib():
     """Load the built library (build it first if it was never built); fail loudly otherwise -- also when
     the binary on disk was compiled from other sources than the ones beside it (no silent rebuild)."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
-        from .build import build_library, source_id
-        if not os.path.exists(LIB_PATH):
+        from .build import MARSHAL, build_library, source_id
+        if not (os.path.exists(LIB_PATH) and os.path.exists(MARSHAL)):
             build_library()
         loaded = C.CDLL(LIB_PATH)
         try:
@@ -67,7 +75,13 @@ def lib():
             raise RuntimeError(
                 f"{LIB_PATH} was built from sources {built_from}, the sources here are {source_id()}: rebuild it "
                 "(python -m paper_2605_11537_amd.build)")
-        _lib = loaded
+        calls = importlib.import_module("._marshal", __package__)
+        if calls.build_id != built_from:
+            raise RuntimeError(f"{MARSHAL} was built from sources {calls.build_id}, {LIB_PATH} from {built_from}: rebuild them "
+                               "(python -m paper_2605_11537_amd.build)")
+        for n in MARSHALLED:
+            calls.bind(n, C.cast(getattr(loaded, n), C.c_void_p).value)
+        _lib, _calls = loaded, calls
         _lib.moe_last_error.restype = C.c_char_p
         for n in EXPORTS:
             f = getattr(_lib, n)
@@ -103,6 +117,13 @@ def lib():
         _lib.moe_plan_dispatch.argtypes = [P, I, P, I, I, I, I, I, I] + [P] * 12 + [P, S, P]
         _lib.moe_layer_forward.argtypes = [C.c_char_p, P]
     return _lib
+
+
+def _c():
+    """The calls with tensors for their pointers (None for a null one), ints, and a raw stream handle; they return the error code."""
+    if _calls is None:
+        lib()
+    return _calls
 
 
 def _check(rc: int):
@@ -160,8 +181,8 @@ def moe_route(x, w_router, b_router=None, want_logits=False, out=None, ws=None, 
     idx, prob = out if out is not None else (_i32(T, dev), torch.empty(T, dtype=torch.float32, device=dev))
     logits = torch.empty(T, E, dtype=torch.float32, device=dev) if want_logits else None
     ws = ws if ws is not None else _ws(lib().moe_route_workspace_bytes(T, d, E, dt), dev)
-    _check(lib().moe_route(_ptr(x), _ptr(w_router), w_layout, _ptr(b_router), T, d, E, dt, _ptr(idx), _ptr(prob),
-                           _ptr(logits), _ptr(ws), ws.numel(), _stream()))
+    _check(_c().moe_route(x, w_router, w_layout, b_router, T, d, E, dt, idx, prob,
+                           logits, ws, ws.numel(), _stream()))
     return idx, prob, logits
 
 
@@ -206,8 +227,7 @@ def sru_predict(emb, weights: SruWeights, want_logits=False, out=None, ws=None):
             # tensors, so that its validation names what is wrong
             _check(lib().sru_predict(None, C.byref(weights.c), B, L, dt, None, None, None, 0, None) or -2)
         ws = _ws(need, dev)
-    _check(lib().sru_predict(_ptr(emb), C.byref(weights.c), B, L, dt, _ptr(pred), _ptr(logits), _ptr(ws),
-                             ws.numel(), _stream()))
+    _check(_c().sru_predict(emb, C.addressof(weights.c), B, L, dt, pred, logits, ws, ws.numel(), _stream()))
     return pred, logits
 
 
@@ -220,9 +240,9 @@ def replica_plan(idx, E, budget, slot_capacity, policy=0, out=None, ws=None):
     o = out if out is not None else dict(plan_counts=_i32(E, dev), replicas=_i32(E, dev),
                                          slot_base=_i32(E + 1, dev), slot_expert=_i32(E + budget, dev),
                                          n_slots=_i32(1, dev))
-    _check(lib().replica_plan(_ptr(idx), idx.shape[0], E, budget, slot_capacity, policy, _ptr(o["plan_counts"]),
-                              _ptr(o["replicas"]), _ptr(o["slot_base"]), _ptr(o["slot_expert"]),
-                              _ptr(o["n_slots"]), _ptr(ws), ws.numel() if ws is not None else 0, _stream()))
+    _check(_c().replica_plan(idx, idx.shape[0], E, budget, slot_capacity, policy, o["plan_counts"],
+                              o["replicas"], o["slot_base"], o["slot_expert"],
+                              o["n_slots"], ws, ws.numel() if ws is not None else 0, _stream()))
     return o
 
 
@@ -238,9 +258,9 @@ def moe_dispatch(x, expert_idx, replicas, E, slot_capacity, max_slots, out=None,
                                          inv=_i32(T, dev), x_perm=torch.empty_like(x) if x is not None else None)
     ws = ws if ws is not None else _ws(lib().moe_dispatch_workspace_bytes(T, E), dev)
     xp = o["x_perm"] if x is not None else None
-    _check(lib().moe_dispatch(_ptr(x), _ptr(expert_idx), _ptr(replicas), T, d, E, slot_capacity, max_slots, dt,
-                              _ptr(o["counts"]), _ptr(o["kept"]), _ptr(o["expert_offset"]), _ptr(o["slot_offset"]),
-                              _ptr(o["perm"]), _ptr(o["inv"]), _ptr(xp), _ptr(ws), ws.numel(), _stream()))
+    _check(_c().moe_dispatch(x, expert_idx, replicas, T, d, E, slot_capacity, max_slots, dt,
+                              o["counts"], o["kept"], o["expert_offset"], o["slot_offset"],
+                              o["perm"], o["inv"], xp, ws, ws.numel(), _stream()))
     return o
 
 
@@ -250,9 +270,9 @@ def moe_dispatch_static(x, expert_idx, replicas, E, slot_capacity, max_slots, ou
     T, d = x.shape if x is not None else shape
     dt = _dt(x) if x is not None else (MOE_BF16 if dtype == torch.bfloat16 else MOE_F32)
     xp = out["x_perm"] if x is not None else None
-    _check(lib().moe_dispatch_static(_ptr(x), _ptr(expert_idx), _ptr(replicas), T, d, E, slot_capacity, max_slots,
-                                     dt, _ptr(out["counts"]), _ptr(out["kept"]), _ptr(out["expert_offset"]),
-                                     _ptr(out["slot_offset"]), _ptr(out["perm"]), _ptr(out["inv"]), _ptr(xp),
+    _check(_c().moe_dispatch_static(x, expert_idx, replicas, T, d, E, slot_capacity, max_slots,
+                                     dt, out["counts"], out["kept"], out["expert_offset"],
+                                     out["slot_offset"], out["perm"], out["inv"], xp,
                                      _stream()))
     return out
 
@@ -261,7 +281,7 @@ def moe_pack_weights(w, out=None):
     """[E,K,N] bf16 row-major -> packed image for the matrix-core kernels (same byte size)."""
     E, K, N = w.shape
     out = out if out is not None else torch.empty_like(w)
-    _check(lib().moe_pack_weights(_ptr(w), E, K, N, _dt(w), _ptr(out), _stream()))
+    _check(_c().moe_pack_weights(w, E, K, N, _dt(w), out, _stream()))
     return out
 
 
@@ -286,17 +306,17 @@ def moe_expert_ffn(x_perm, w1, w2, slot_offset, slot_expert, n_slots, E, F, max_
                                           d, F, dt, schedule, _ptr(y), _ptr(ws), ws.numel(), _stream(),
                                           *[C.c_void_p(e.cuda_event) for e in events]))
         return y
-    _check(lib().moe_expert_ffn(_ptr(x_perm), _ptr(row_index), _ptr(w1), _ptr(w2), weight_layout, _ptr(slot_offset),
-                                _ptr(slot_expert), _ptr(n_slots), max_rows, max_slots, E, d, F, dt, schedule,
-                                _ptr(y), _ptr(ws), ws.numel(), _stream()))
+    _check(_c().moe_expert_ffn(x_perm, row_index, w1, w2, weight_layout, slot_offset,
+                                slot_expert, n_slots, max_rows, max_slots, E, d, F, dt, schedule,
+                                y, ws, ws.numel(), _stream()))
     return y
 
 
 def moe_combine(y_perm, x, inv, expert_prob, residual=0, out=None):
     T, d = x.shape
     o = out if out is not None else torch.empty_like(x)
-    _check(lib().moe_combine(_ptr(y_perm), _ptr(x), _ptr(inv), _ptr(expert_prob), T, d, _dt(x), int(residual),
-                             _ptr(o), _stream()))
+    _check(_c().moe_combine(y_perm, x, inv, expert_prob, T, d, _dt(x), int(residual),
+                             o, _stream()))
     return o
 
 
@@ -321,17 +341,13 @@ def moe_plan_dispatch(plan_idx, expert_idx, E, budget, slot_capacity, policy=0, 
     if ws is None:
         need = lib().moe_plan_dispatch_workspace_bytes(n_plan, T, k, E)
         ws = _ws(need, dev) if need else None
-    _check(lib().moe_plan_dispatch(_ptr(plan_idx), n_plan, _ptr(expert_idx), T, k, E, budget, slot_capacity, policy,
-                                   _ptr(po["plan_counts"]), _ptr(po["replicas"]), _ptr(po["slot_base"]),
-                                   _ptr(po["slot_expert"]), _ptr(po["n_slots"]), _ptr(do["counts"]), _ptr(do["kept"]),
-                                   _ptr(do["expert_offset"]), _ptr(do["slot_offset"]), _ptr(do["perm"]),
-                                   _ptr(do["inv"]), _ptr(do.get("row_token")), _ptr(ws),
+    _check(_c().moe_plan_dispatch(plan_idx, n_plan, expert_idx, T, k, E, budget, slot_capacity, policy,
+                                   po["plan_counts"], po["replicas"], po["slot_base"],
+                                   po["slot_expert"], po["n_slots"], do["counts"], do["kept"],
+                                   do["expert_offset"], do["slot_offset"], do["perm"],
+                                   do["inv"], do.get("row_token"), ws,
                                    ws.numel() if ws is not None else 0, _stream()))
     return po, do
-
-
-# struct moe_layer_args: 25 pointers, 3 sizes, 16 ints in the machine's own layout
-_layer_args = struct.Struct("@25P3N16i")
 
 
 def _layer_forward(layer, x, w_router, b_router, w1, w2, plan_ids, schedule, residual, out, router_layout, top_k, renormalize):
@@ -342,15 +358,14 @@ def _layer_forward(layer, x, w_router, b_router, w1, w2, plan_ids, schedule, res
     pl, dp = layer.plan_out, layer.disp_out
     out = layer.out if out is None else out
     idx, prob = layer.route_out
-    ptrs = [_ptr(t) or 0 for t in (
-        x, w_router, b_router, w1, w2, plan_ids, idx, prob, pl["plan_counts"], pl["replicas"], pl["slot_base"],
-        pl["slot_expert"], pl["n_slots"], dp["counts"], dp["kept"], dp["expert_offset"], dp["slot_offset"], dp["perm"], dp["inv"],
-        dp.get("row_token"), layer.y_perm, out, layer.route_ws, layer.front_ws, layer.ffn_ws)]
-    _check(lib().moe_layer_forward(_layer_args.pack(
-        *ptrs, layer.route_ws.numel(), layer.front_ws.numel(), layer.ffn_ws.numel(), layer.T,
-        0 if plan_ids is None else plan_ids.numel(), top_k, int(bool(renormalize)), layer.d, layer.F, w_router.shape[1], layer.E, layer.R,
-        layer.C, layer.policy, dt, router_layout, LAYOUT_PACKED if dt == MOE_BF16 else LAYOUT_PLAIN, schedule, int(residual)),
-        _stream()))
+    # the fields of moe_layer_args in their order
+    _check(_c().moe_layer_forward(
+        x, w_router, b_router, w1, w2, plan_ids, idx, prob, pl["plan_counts"], pl["replicas"], pl["slot_base"], pl["slot_expert"],
+        pl["n_slots"], dp["counts"], dp["kept"], dp["expert_offset"], dp["slot_offset"], dp["perm"], dp["inv"], dp.get("row_token"),
+        layer.y_perm, out, layer.route_ws, layer.front_ws, layer.ffn_ws, layer.route_ws.numel(), layer.front_ws.numel(),
+        layer.ffn_ws.numel(), layer.T, 0 if plan_ids is None else plan_ids.numel(), top_k, int(bool(renormalize)), layer.d, layer.F,
+        w_router.shape[1], layer.E, layer.R, layer.C, layer.policy, dt, router_layout,
+        LAYOUT_PACKED if dt == MOE_BF16 else LAYOUT_PLAIN, schedule, int(residual), _stream()))
     return out
 
 
@@ -404,8 +419,8 @@ def moe_route_topk(x, w_router, b_router, k, renormalize=False, want_logits=Fals
                                             torch.empty(k, T, dtype=torch.float32, device=dev))
     logits = torch.empty(T, E, dtype=torch.float32, device=dev) if want_logits else None
     ws = ws if ws is not None else _ws(lib().moe_route_workspace_bytes(T, d, E, dt), dev)
-    _check(lib().moe_route_topk(_ptr(x), _ptr(w_router), w_layout, _ptr(b_router), T, d, E, dt, int(k),
-                                int(bool(renormalize)), _ptr(idx), _ptr(wgt), _ptr(logits), _ptr(ws), ws.numel(),
+    _check(_c().moe_route_topk(x, w_router, w_layout, b_router, T, d, E, dt, int(k),
+                                int(bool(renormalize)), idx, wgt, logits, ws, ws.numel(),
                                 _stream()))
     return idx, wgt, logits
 
@@ -426,10 +441,10 @@ def moe_dispatch_topk(x, expert_idx, replicas, E, slot_capacity, max_slots, out=
         x_perm=torch.empty(A, d, dtype=x.dtype, device=dev) if x is not None else None)
     ws = ws if ws is not None else _ws(lib().moe_dispatch_workspace_bytes(A, E), dev)
     xp = o["x_perm"] if x is not None else None
-    _check(lib().moe_dispatch_topk(_ptr(x), _ptr(expert_idx), _ptr(replicas), T, k, d, E, slot_capacity, max_slots,
-                                   dt, _ptr(o["counts"]), _ptr(o["kept"]), _ptr(o["expert_offset"]),
-                                   _ptr(o["slot_offset"]), _ptr(o["perm"]), _ptr(o["inv"]), _ptr(o["row_token"]),
-                                   _ptr(xp), _ptr(ws), ws.numel(), _stream()))
+    _check(_c().moe_dispatch_topk(x, expert_idx, replicas, T, k, d, E, slot_capacity, max_slots,
+                                   dt, o["counts"], o["kept"], o["expert_offset"],
+                                   o["slot_offset"], o["perm"], o["inv"], o["row_token"],
+                                   xp, ws, ws.numel(), _stream()))
     return o
 
 
@@ -446,13 +461,13 @@ def moe_expert_ffn_rows(x, row_index, max_rows, w1, w2, slot_offset, slot_expert
         max_slots = slot_expert.shape[0]
     y = out if out is not None else torch.empty(max_rows, d, dtype=x.dtype, device=dev)
     ws = ws if ws is not None else _ws(lib().moe_expert_ffn_workspace_bytes(max_rows, max_slots, d, F, dt), dev)
-    args = (_ptr(x), n_x_rows, _ptr(row_index), _ptr(w1), _ptr(w2), weight_layout, _ptr(slot_offset),
-            _ptr(slot_expert), _ptr(n_slots), max_rows, max_slots, E, d, F, dt, schedule, _ptr(y), _ptr(ws),
-            ws.numel(), _stream())
     if events is not None:
-        _check(lib().moe_expert_ffn_timed(*args, *[C.c_void_p(e.cuda_event) for e in events]))
+        _check(lib().moe_expert_ffn_timed(_ptr(x), n_x_rows, _ptr(row_index), _ptr(w1), _ptr(w2), weight_layout, _ptr(slot_offset),
+                                          _ptr(slot_expert), _ptr(n_slots), max_rows, max_slots, E, d, F, dt, schedule, _ptr(y),
+                                          _ptr(ws), ws.numel(), _stream(), *[C.c_void_p(e.cuda_event) for e in events]))
     else:
-        _check(lib().moe_expert_ffn_rows(*args))
+        _check(_c().moe_expert_ffn_rows(x, n_x_rows, row_index, w1, w2, weight_layout, slot_offset, slot_expert, n_slots, max_rows,
+                                        max_slots, E, d, F, dt, schedule, y, ws, ws.numel(), _stream()))
     return y
 
 
@@ -461,8 +476,8 @@ def moe_combine_topk(y_perm, x, inv, expert_weight, residual=0, out=None):
     T, d = x.shape
     k = inv.shape[0]
     o = out if out is not None else torch.empty_like(x)
-    _check(lib().moe_combine_topk(_ptr(y_perm), _ptr(x), _ptr(inv), _ptr(expert_weight), T, k, d, _dt(x),
-                                  int(residual), _ptr(o), _stream()))
+    _check(_c().moe_combine_topk(y_perm, x, inv, expert_weight, T, k, d, _dt(x),
+                                  int(residual), o, _stream()))
     return o
 
 

@@ -1,4 +1,5 @@
-"""Compile the HIP sources of the library for gfx950 into ``libmoe_mpmc.so`` next to this file."""
+"""Compile the HIP sources of the library for gfx950 into ``libmoe_mpmc.so`` next to this file, and the Python extension that
+marshals its calls' arguments into ``_marshal.so``."""
 from __future__ import annotations
 
 import glob
@@ -8,6 +9,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmoe_mpmc.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")            # the Python extension (csrc/marshal.cpp, host code)
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -35,8 +37,11 @@ def source_id() -> str:
 
 
 def build_library(verbose: bool = False) -> str:
-    """One hipcc -c per source, side by side, then one link."""
+    """One hipcc -c per source, side by side, then one link; beside them the Python extension."""
+    import sysconfig
     from concurrent.futures import ThreadPoolExecutor
+
+    import torch
 
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     obj_dir = os.path.join(HERE, "_build")
@@ -50,15 +55,20 @@ def build_library(verbose: bool = False) -> str:
         msgs = "\n".join(l for l in (r.stdout + r.stderr).splitlines()
                          if "packed-fp32-ops" not in l and l.strip())
         if r.returncode != 0:
-            raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + msgs)
+            raise RuntimeError("the compiler failed:\n" + " ".join(cmd) + "\n" + msgs)
         if verbose and msgs:
             print(msgs)
 
     srcs = sources()
     objs = [os.path.join(obj_dir, os.path.basename(p)[:-4] + ".o") for p in srcs]
-    jobs = min(len(srcs), max(1, min(8, os.cpu_count() or 1)))
+    tdir = os.path.dirname(torch.__file__)
+    marshal = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", f'-DMOE_BUILD_ID="{source_id()}"',
+               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(tdir, "include"),
+               "-I" + os.path.join(tdir, "include", "torch", "csrc", "api", "include"), "-I" + sysconfig.get_paths()["include"],
+               os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-L" + os.path.join(tdir, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    jobs = min(len(srcs) + 1, max(1, min(8, os.cpu_count() or 1)))
     with ThreadPoolExecutor(max_workers=jobs) as pool:
-        list(pool.map(lambda so: run([hipcc] + compile_flags + [so[0], "-o", so[1]]), zip(srcs, objs)))
+        list(pool.map(run, [marshal] + [[hipcc] + compile_flags + [s, "-o", o] for s, o in zip(srcs, objs)]))
     run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB])
     return LIB
 
