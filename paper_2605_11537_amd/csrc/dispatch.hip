@@ -1,6 +1,7 @@
 // moe_dispatch: capacity-limited, stable dispatch of tokens to expert slots.
 //
-// Three kernels, no global atomics, so the permutation is the stable one whatever the
+// Batches of a few thousand entries take the one workgroup of dispatch_small (front.hip) for the tables.  Others:
+// three kernels, no global atomics, so the permutation is the stable one whatever the
 // hardware scheduling:
 //   hist     one workgroup per 1024 tokens: LDS histogram of expert ids -> block_hist[b][e]
 //   permute  one workgroup of 1024 threads per 1024 tokens: per expert, total and prefix over the earlier token blocks
@@ -380,24 +381,28 @@ static int dispatch_checked(const char *who, const void *x, const int32_t *exper
     int32_t *block_hist = (int32_t *)ws;
     int nbits = 0;
     while ((1 << nbits) < E) ++nbits;
-    if (nb > 0) {
-        hipLaunchKernelGGL(dispatch_hist_kernel, dim3(nb), dim3(DSP_TOKENS), 0, st, expert_idx, T, E, nbits, block_hist);
-        MOE_CHECK_LAUNCH(who);
-    }
-    {
+    if (dispatch_small(T, E)) {
+        const int rc = dispatch_small_launch(expert_idx, replicas, T, n_tokens, E, slot_capacity, max_slots, counts, kept, expert_offset,
+                                             slot_offset, perm, inv, row_token, st, who);
+        if (rc != MOE_OK) return rc;
+    } else {
+        if (nb > 0) {
+            hipLaunchKernelGGL(dispatch_hist_kernel, dim3(nb), dim3(DSP_TOKENS), 0, st, expert_idx, T, E, nbits, block_hist);
+            MOE_CHECK_LAUNCH(who);
+        }
         hipLaunchKernelGGL(dispatch_permute_kernel<0>, dim3(nb > 0 ? nb : 1), dim3(DSP_TOKENS), 0, st, expert_idx,
                            replicas, T, E, nbits, slot_capacity, nb, max_slots, block_hist, counts, kept,
                            expert_offset, slot_offset, perm, inv, n_tokens > 0 ? n_tokens : 1, row_token, PlanArgs{});
         MOE_CHECK_LAUNCH(who);
-        if (x && nb > 0) {
-            int vec_per_row = (int)((size_t)d * esz / 16);
-            int grid = ceil_div(T, GATHER_ROWS);
-            auto gather = (size_t)T * vec_per_row * 16 >= GATHER_STREAM_BYTES ? dispatch_gather_kernel<true>
-                                                                              : dispatch_gather_kernel<false>;
-            hipLaunchKernelGGL(gather, dim3(grid), dim3(DSP_THREADS), 0, st, (const dsp_u32x4_t *)x, perm, T, n_tokens,
-                               vec_per_row, (dsp_u32x4_t *)x_perm);
-            MOE_CHECK_LAUNCH(who);
-        }
+    }
+    if (x && nb > 0) {
+        int vec_per_row = (int)((size_t)d * esz / 16);
+        int grid = ceil_div(T, GATHER_ROWS);
+        auto gather = (size_t)T * vec_per_row * 16 >= GATHER_STREAM_BYTES ? dispatch_gather_kernel<true>
+                                                                          : dispatch_gather_kernel<false>;
+        hipLaunchKernelGGL(gather, dim3(grid), dim3(DSP_THREADS), 0, st, (const dsp_u32x4_t *)x, perm, T, n_tokens,
+                           vec_per_row, (dsp_u32x4_t *)x_perm);
+        MOE_CHECK_LAUNCH(who);
     }
     return MOE_OK;
 }

@@ -12,6 +12,7 @@
 //   C  per expert: kept = min(total, replicas * C); scans over experts for the first row of every expert
 //      and the first slot; slot tables
 //   D  per token: row = first row of its expert + prefix of its chunk + rank in the chunk, if kept
+// moe_dispatch takes the same kernel without a plan, for at most DISPATCH_SMALL entries.
 // Larger inputs: block histograms of the ids, then the dispatch's permute kernel with the plan made inside it
 // (every workgroup for itself), two or three launches instead of four.  Same tables, bit for bit, either way.
 #include "plan_alloc.h"
@@ -23,6 +24,12 @@ constexpr int FRONT_MAX_TOKENS = 8192;
 constexpr int FRONT_MAX_EXPERTS = 256;
 constexpr int FRONT_CHUNKS = FRONT_MAX_TOKENS / WAVE;              // 128
 constexpr int FRONT_ROUNDS = FRONT_MAX_TOKENS / PLAN_THREADS;      // chunks per wavefront
+// Entries of a moe_dispatch that one workgroup takes.  What it saves is a launch (3 us of the host, a memory round trip or two in the stream),
+// what it costs is that one CU passes over all ids.  Tables, histogram and permute launches -> one workgroup, us in the stream, entries dealt by
+// Zipf's law: E = 64: 16 6.7 -> 4.8, 300 6.7 -> 5.1, 1000 6.8 -> 5.4, 2048 7.3 -> 6.2 (half of them on one expert 7.3 -> 6.6); E = 256: 16 10.9 ->
+// 8.1, 2048 11.4 -> 9.6 (11.3 -> 10.0).  With a kernel for 8192 entries: 2000 7.3 -> 7.0, 3000 7.4 -> 7.5, 4096 7.4 -> 8.3, 8192 7.6 -> 11.
+// From the host, tables, row copy and combine of 300 rows: 15.4 -> 11.3.
+constexpr int DISPATCH_SMALL = 2048;
 
 constexpr int FRONT_SEG = 8;                                       // chunks per segment of the two-level prefix
 constexpr int FRONT_SEGS = FRONT_CHUNKS / FRONT_SEG;               // 16
@@ -64,16 +71,21 @@ __device__ __forceinline__ void expert_scan2(int v0, int v1, int &ex0, int &ex1,
 
 // SAME: the plan is made from the routed ids themselves (no predictor): their histogram is gathered
 // along with the chunk counts, the plan ids are not read a second time.
+// PLAN_PER_LANE 0: no plan; the replica counts are given (moe_dispatch's: any numbers, or NULL for one each), and an expert's slots are written by
+// its whole wavefront.
 template <int PLAN_PER_LANE, bool SAME>
 __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
     const int32_t *__restrict__ plan_idx, int n_plan, const int32_t *__restrict__ idx, int T, int n_tokens, int E,
-    int R, int C, int policy, int max_slots, int32_t *__restrict__ plan_counts,
+    int R, int C, int policy, int max_slots, const int32_t *__restrict__ given, int32_t *__restrict__ plan_counts,
     int32_t *__restrict__ replicas, int32_t *__restrict__ slot_base, int32_t *__restrict__ slot_expert,
     int32_t *__restrict__ n_slots, int32_t *__restrict__ counts, int32_t *__restrict__ kept,
     int32_t *__restrict__ expert_offset, int32_t *__restrict__ slot_offset, int32_t *__restrict__ perm,
     int32_t *__restrict__ inv, int32_t *__restrict__ row_token)
 {
-    __shared__ unsigned short chunk_cnt[FRONT_CHUNKS][FRONT_LD];   // count, then prefix inside its segment
+    constexpr bool GIVEN = PLAN_PER_LANE == 0;
+    constexpr int ROUNDS = GIVEN ? DISPATCH_SMALL / PLAN_THREADS : FRONT_ROUNDS;
+    static_assert(!GIVEN || SAME, "there are no plan ids");
+    __shared__ unsigned short chunk_cnt[ROUNDS * (PLAN_THREADS / WAVE)][FRONT_LD];   // count, then prefix inside its segment
     __shared__ int seg_tot[FRONT_MAX_EXPERTS][FRONT_SEGS + 1];     // per expert: segment totals, then their prefix
     __shared__ unsigned long long match[PLAN_THREADS / WAVE][FRONT_MAX_EXPERTS];   // per wavefront and expert: lanes
     __shared__ int hist[MOE_MAX_EXPERTS];
@@ -83,11 +95,12 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n_chunks = (T + WAVE - 1) / WAVE;
     const int n_segs = (n_chunks + FRONT_SEG - 1) / FRONT_SEG;
+    const int given_e = GIVEN && given && tid < E ? given[tid] : 1;
 
     // all ids of this thread are fetched up front, so both sets are one memory round trip
-    int my_e[FRONT_ROUNDS], my_rank[FRONT_ROUNDS], plan_e[FRONT_ROUNDS];
+    int my_e[ROUNDS], my_rank[ROUNDS], plan_e[ROUNDS];
 #pragma unroll
-    for (int rd = 0; rd < FRONT_ROUNDS; ++rd) {
+    for (int rd = 0; rd < ROUNDS; ++rd) {
         const int t = (rd * 16 + w) * WAVE + lane;
         my_e[rd] = t < T ? idx[t] : -1;
         plan_e[rd] = (!SAME && t < n_plan) ? plan_idx[t] : -1;
@@ -113,7 +126,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
         return m;
     };
 #pragma unroll
-    for (int rd = 0; rd < FRONT_ROUNDS; ++rd) {
+    for (int rd = 0; rd < ROUNDS; ++rd) {
         const int c = rd * 16 + w;
         if (!SAME && c * WAVE < n_plan) {           // uniform per wavefront
             const int e = plan_e[rd];
@@ -129,7 +142,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
             const int rank = __popcll(mask & ((1ull << lane) - 1ull));
             if (valid && rank == 0) {
                 chunk_cnt[c][e] = (unsigned short)__popcll(mask);
-                if (SAME) atomicAdd(&hist[e], __popcll(mask));      // the plan's histogram is the same count
+                if (SAME && !GIVEN) atomicAdd(&hist[e], __popcll(mask));    // the plan's histogram is the same count
             }
             my_e[rd] = valid ? e : -1;
             my_rank[rd] = rank;
@@ -139,10 +152,11 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
 
     // ---- B: wavefront 0 runs the allocation; the others the prefix of the chunk counts inside segments of
     // 8 chunks (one expert and segment per thread)
-    if (tid < WAVE) {
-        plan_allocate_wave<PLAN_PER_LANE>(hist, rep, SAME ? T : n_plan, E, R, C, policy, replicas, plan_counts);
+    if (!GIVEN && tid < WAVE) {
+        plan_allocate_wave<(GIVEN ? 1 : PLAN_PER_LANE)>(hist, rep, SAME ? T : n_plan, E, R, C, policy, replicas, plan_counts);
     } else {
-        for (int i = tid - WAVE; i < E * n_segs; i += PLAN_THREADS - WAVE) {
+        constexpr int FIRST = GIVEN ? 0 : WAVE;
+        for (int i = tid - FIRST; i < E * n_segs; i += PLAN_THREADS - FIRST) {
             const int e = i % E, g = i / E;
             int v[FRONT_SEG];
 #pragma unroll
@@ -173,12 +187,13 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
     __syncthreads();
 
     // ---- C: thread e owns expert e
-    const int r_e = tid < E ? rep[tid] : 0;
+    const int r_e = tid >= E ? 0 : GIVEN ? (given_e < 1 ? 1 : given_e) : rep[tid];
     const int n_e = tid < E ? tot_e[tid] : 0;
     const long long cap = (long long)r_e * C;
     const int k_e = (long long)n_e < cap ? n_e : (int)cap;
     int off_e, sb_e, K, P;
-    expert_scan2(k_e, r_e, off_e, sb_e, K, P, wave_sums);
+    // more given replicas than the slot tables hold count as one more: their sum has to fit
+    expert_scan2(k_e, GIVEN && r_e > max_slots ? max_slots + 1 : r_e, off_e, sb_e, K, P, wave_sums);
     if (tid < E) {
         eoff_e[tid] = off_e;
         cap_e[tid] = k_e;
@@ -187,10 +202,22 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
         expert_offset[tid] = off_e;
         if (slot_base) slot_base[tid] = sb_e;
         const int q = k_e / r_e, rem = k_e % r_e;      // r_e >= 1 for every expert
-        for (int j = 0; j < r_e; ++j) {
+        for (int j = 0; !GIVEN && j < r_e; ++j) {
             const int p = sb_e + j;
             if (slot_expert) slot_expert[p] = tid;
             if (slot_offset && p <= max_slots) slot_offset[p] = off_e + j * q + (j < rem ? j : rem);
+        }
+    }
+    if (GIVEN && slot_offset && tid < FRONT_MAX_EXPERTS) {             // whole wavefronts
+        const int q = r_e > 0 ? k_e / r_e : 0, rem = r_e > 0 ? k_e % r_e : 0;
+        if (r_e > 0 && sb_e <= max_slots) slot_offset[sb_e] = off_e;
+        for (unsigned long long more = __ballot(r_e > 1); more; more &= more - 1) {
+            const int l = __builtin_ctzll(more);                     // uniform
+            const int r = __builtin_amdgcn_readlane(r_e, l), p0 = __builtin_amdgcn_readlane(sb_e, l);
+            const int first = __builtin_amdgcn_readlane(off_e, l), quot = __builtin_amdgcn_readlane(q, l);
+            const int rest = __builtin_amdgcn_readlane(rem, l);
+            const int last = p0 > max_slots ? 0 : r - 1 < max_slots - p0 ? r - 1 : max_slots - p0;
+            for (int j = 1 + lane; j <= last; j += WAVE) slot_offset[p0 + j] = first + j * quot + (j < rest ? j : rest);
         }
     }
     if (tid == 0) {
@@ -206,7 +233,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
 
     // ---- D
 #pragma unroll
-    for (int rd = 0; rd < FRONT_ROUNDS; ++rd) {
+    for (int rd = 0; rd < ROUNDS; ++rd) {
         const int c = rd * 16 + w;
         const int t = c * WAVE + lane;
         if (t >= T) continue;
@@ -224,6 +251,20 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
             if (t >= K) row_token[t] = -1;
         }
     }
+}
+
+bool dispatch_small(int T, int E) { return T <= DISPATCH_SMALL && E <= FRONT_MAX_EXPERTS; }
+
+int dispatch_small_launch(const int32_t *expert_idx, const int32_t *replicas, int T, int n_tokens, int E, int slot_capacity, int max_slots,
+                          int32_t *counts, int32_t *kept, int32_t *expert_offset, int32_t *slot_offset, int32_t *perm, int32_t *inv,
+                          int32_t *row_token, hipStream_t st, const char *who)
+{
+    int32_t *const none = nullptr;
+    hipLaunchKernelGGL((plan_dispatch_small_kernel<0, true>), dim3(1), dim3(PLAN_THREADS), 0, st, (const int32_t *)none, 0, expert_idx, T,
+                       n_tokens > 0 ? n_tokens : 1, E, 0, slot_capacity, 0, max_slots, replicas, none, none, none, none, none, counts, kept,
+                       expert_offset, slot_offset, perm, inv, row_token);
+    MOE_CHECK_LAUNCH(who);
+    return MOE_OK;
 }
 
 }  // namespace moe
@@ -292,7 +333,7 @@ extern "C" int moe_plan_dispatch(const int32_t *plan_idx, int n_plan, const int3
     auto kern = E <= 128 ? (same ? plan_dispatch_small_kernel<2, true> : plan_dispatch_small_kernel<2, false>)
                          : (same ? plan_dispatch_small_kernel<4, true> : plan_dispatch_small_kernel<4, false>);
     hipLaunchKernelGGL(kern, dim3(1), dim3(PLAN_THREADS), 0, (hipStream_t)stream, plan_idx, n_plan, expert_idx, A,
-                       T > 0 ? T : 1, E, budget, slot_capacity, policy, max_slots, plan_counts, replicas,
+                       T > 0 ? T : 1, E, budget, slot_capacity, policy, max_slots, (const int32_t *)nullptr, plan_counts, replicas,
                        slot_base, slot_expert, n_slots, counts, kept, expert_offset, slot_offset, perm, inv,
                        row_token);
     MOE_CHECK_LAUNCH("moe_plan_dispatch");

@@ -28,4 +28,9 @@ int dispatch_planned_launch(const int32_t *expert_idx, int T, int n_tokens, int 
                             int32_t *slot_expert, int32_t *n_slots, int32_t *counts, int32_t *kept,
                             int32_t *expert_offset, int32_t *slot_offset, int32_t *perm, int32_t *inv,
                             int32_t *row_token, hipStream_t st, const char *who);
+// front.hip: moe_dispatch's tables of a small batch in one workgroup, and whether a batch is one
+bool dispatch_small(int T, int E);
+int dispatch_small_launch(const int32_t *expert_idx, const int32_t *replicas, int T, int n_tokens, int E, int slot_capacity, int max_slots,
+                          int32_t *counts, int32_t *kept, int32_t *expert_offset, int32_t *slot_offset, int32_t *perm, int32_t *inv,
+                          int32_t *row_token, hipStream_t st, const char *who);
 }  // namespace moe
