@@ -12,9 +12,12 @@
 //   C  per expert: kept = min(total, replicas * C); scans over experts for the first row of every expert
 //      and the first slot; slot tables
 //   D  per token: row = first row of its expert + prefix of its chunk + rank in the chunk, if kept
+// Latency is all it is: the steps are a chain, and the instructions of a kernel that runs once come from memory as well.
 // moe_dispatch takes the same kernel without a plan, for at most DISPATCH_SMALL entries.
 // Larger inputs: block histograms of the ids, then the dispatch's permute kernel with the plan made inside it
 // (every workgroup for itself), two or three launches instead of four.  Same tables, bit for bit, either way.
+#include <type_traits>
+
 #include "plan_alloc.h"
 #include "route.h"
 
@@ -72,8 +75,8 @@ __device__ __forceinline__ void expert_scan2(int v0, int v1, int &ex0, int &ex1,
 // SAME: the plan is made from the routed ids themselves (no predictor): their histogram is gathered
 // along with the chunk counts, the plan ids are not read a second time.
 // PLAN_PER_LANE 0: no plan; the replica counts are given (moe_dispatch's: any numbers, or NULL for one each), and an expert's slots are written by
-// its whole wavefront.
-template <int PLAN_PER_LANE, bool SAME>
+// its whole wavefront.  ROUNDS: passes of the 1024 threads over the ids.
+template <int PLAN_PER_LANE, bool SAME, int ROUNDS>
 __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
     const int32_t *__restrict__ plan_idx, int n_plan, const int32_t *__restrict__ idx, int T, int n_tokens, int E,
     int R, int C, int policy, int max_slots, const int32_t *__restrict__ given, int32_t *__restrict__ plan_counts,
@@ -83,7 +86,6 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
     int32_t *__restrict__ inv, int32_t *__restrict__ row_token)
 {
     constexpr bool GIVEN = PLAN_PER_LANE == 0;
-    constexpr int ROUNDS = GIVEN ? DISPATCH_SMALL / PLAN_THREADS : FRONT_ROUNDS;
     static_assert(!GIVEN || SAME, "there are no plan ids");
     __shared__ unsigned short chunk_cnt[ROUNDS * (PLAN_THREADS / WAVE)][FRONT_LD];   // count, then prefix inside its segment
     __shared__ int seg_tot[FRONT_MAX_EXPERTS][FRONT_SEGS + 1];     // per expert: segment totals, then their prefix
@@ -260,7 +262,7 @@ int dispatch_small_launch(const int32_t *expert_idx, const int32_t *replicas, in
                           int32_t *row_token, hipStream_t st, const char *who)
 {
     int32_t *const none = nullptr;
-    hipLaunchKernelGGL((plan_dispatch_small_kernel<0, true>), dim3(1), dim3(PLAN_THREADS), 0, st, (const int32_t *)none, 0, expert_idx, T,
+    hipLaunchKernelGGL((plan_dispatch_small_kernel<0, true, DISPATCH_SMALL / PLAN_THREADS>), dim3(1), dim3(PLAN_THREADS), 0, st, (const int32_t *)none, 0, expert_idx, T,
                        n_tokens > 0 ? n_tokens : 1, E, 0, slot_capacity, 0, max_slots, replicas, none, none, none, none, none, counts, kept,
                        expert_offset, slot_offset, perm, inv, row_token);
     MOE_CHECK_LAUNCH(who);
@@ -270,6 +272,9 @@ int dispatch_small_launch(const int32_t *expert_idx, const int32_t *replicas, in
 }  // namespace moe
 
 using namespace moe;
+
+template <int N>
+using int_c = std::integral_constant<int, N>;
 
 static inline bool front_fused(int n_plan, int A, int E)
 {
@@ -330,8 +335,17 @@ extern "C" int moe_plan_dispatch(const int32_t *plan_idx, int n_plan, const int3
                                        n_slots, counts, kept, expert_offset, slot_offset, perm, inv, row_token,
                                        (hipStream_t)stream, "moe_plan_dispatch");
     }
-    auto kern = E <= 128 ? (same ? plan_dispatch_small_kernel<2, true> : plan_dispatch_small_kernel<2, false>)
-                         : (same ? plan_dispatch_small_kernel<4, true> : plan_dispatch_small_kernel<4, false>);
+    // a kernel that has no passes but those its ids need is shorter to fetch and to run.  Eight passes for all -> this, us, plan ids = routed ids,
+    // E = 64: 64 ids 4.78 -> 4.43, 1000 6.42 -> 5.90, 2000 7.04 -> 6.67, 4096 8.01 -> 7.77; E = 256: 64 5.34 -> 4.82, 4096 9.68 -> 9.53
+    const int rounds = ceil_div(A > n_plan ? A : n_plan, PLAN_THREADS);
+    auto pick = [&](auto per_lane, auto rounds_c) {
+        constexpr int P = decltype(per_lane)::value, N = decltype(rounds_c)::value;
+        return same ? plan_dispatch_small_kernel<P, true, N> : plan_dispatch_small_kernel<P, false, N>;
+    };
+    auto pick_rounds = [&](auto per_lane) {
+        return rounds <= 2 ? pick(per_lane, int_c<2>{}) : rounds <= 4 ? pick(per_lane, int_c<4>{}) : pick(per_lane, int_c<FRONT_ROUNDS>{});
+    };
+    auto kern = E <= 128 ? pick_rounds(int_c<2>{}) : pick_rounds(int_c<4>{});
     hipLaunchKernelGGL(kern, dim3(1), dim3(PLAN_THREADS), 0, (hipStream_t)stream, plan_idx, n_plan, expert_idx, A,
                        T > 0 ? T : 1, E, budget, slot_capacity, policy, max_slots, (const int32_t *)nullptr, plan_counts, replicas,
                        slot_base, slot_expert, n_slots, counts, kept, expert_offset, slot_offset, perm, inv,
