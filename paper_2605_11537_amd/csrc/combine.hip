@@ -1,6 +1,7 @@
 // moe_combine: scale expert outputs by the gate probability and scatter them back to token
 // order; tokens over capacity are copied through bit for bit.  HBM-bound: every 16-byte
 // piece of x, y_perm and out is touched once.
+#include "route.h"
 #include "row_groups.h"
 
 namespace moe {
@@ -144,8 +145,8 @@ __global__ __launch_bounds__(CMB_THREADS) void combine_topk_kernel(const cmb_u32
 
 using namespace moe;
 
-extern "C" int moe_combine(const void *y_perm, const void *x, const int32_t *inv, const float *expert_prob,
-                           int T, int d, int dtype, int residual, void *out, void *stream)
+int moe::combine_check(const void *y_perm, const void *x, const int32_t *inv, const float *expert_prob, int T, int d, int dtype,
+                       int residual, const void *out)
 {
     MOE_REQUIRE(T >= 0 && d > 0, MOE_ERR_INVALID_ARG, "moe_combine: T=%d d=%d out of range", T, d);
     MOE_REQUIRE(dtype == MOE_F32 || dtype == MOE_BF16, MOE_ERR_INVALID_ARG, "moe_combine: unknown dtype %d",
@@ -159,6 +160,15 @@ extern "C" int moe_combine(const void *y_perm, const void *x, const int32_t *inv
                 "moe_combine: row size %zu bytes is not a multiple of 16", (size_t)d * esz);
     MOE_REQUIRE(aligned16(y_perm) && aligned16(x) && aligned16(out), MOE_ERR_INVALID_ARG,
                 "moe_combine: tensor misaligned");
+    return MOE_OK;
+}
+
+extern "C" int moe_combine(const void *y_perm, const void *x, const int32_t *inv, const float *expert_prob,
+                           int T, int d, int dtype, int residual, void *out, void *stream)
+{
+    const int rc = combine_check(y_perm, x, inv, expert_prob, T, d, dtype, residual, out);
+    if (rc != MOE_OK || T == 0) return rc;
+    const size_t esz = dtype == MOE_F32 ? 4 : 2;
     int vec_per_row = (int)((size_t)d * esz / 16);
     hipStream_t st = (hipStream_t)stream;
     const bool big = (size_t)T * vec_per_row * 16 >= CMB_STREAM_BYTES;

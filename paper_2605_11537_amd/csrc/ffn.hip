@@ -22,6 +22,7 @@
 #include "ffn_f32.h"
 #include "ffn_few_rows.h"
 #include "ffn_rules.h"
+#include "route.h"
 
 namespace moe {
 
@@ -299,7 +300,7 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
                               const void *w2, int weight_layout, const int32_t *slot_offset,
                               const int32_t *slot_expert, const int32_t *n_slots, int max_rows, int max_slots, int E,
                               int d, int F, int dtype, int schedule, void *y_perm, void *ws, size_t ws_bytes,
-                              void *stream, void *const *timing_events = nullptr)
+                              void *stream, void *const *timing_events = nullptr, const LayerOut *layer = nullptr)
 {
     MOE_REQUIRE(max_rows >= 0 && max_slots > 0 && E > 0 && d > 0 && F > 0, MOE_ERR_INVALID_ARG,
                 "moe_expert_ffn: max_rows=%d max_slots=%d E=%d d=%d F=%d out of range", max_rows, max_slots, E, d,
@@ -330,6 +331,11 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     size_t need = moe_expert_ffn_workspace_bytes(max_rows, max_slots, d, F, dtype);
     MOE_REQUIRE(ws && aligned16(ws) && ws_bytes >= need, MOE_ERR_WORKSPACE,
                 "moe_expert_ffn: workspace of %zu bytes needed, %zu given", need, ws_bytes);
+    if (layer) {
+        const int rc = combine_check(y_perm, layer->x, layer->inv, layer->prob, layer->T, d, dtype, layer->residual, layer->out);
+        if (rc != MOE_OK) return rc;
+    }
+    const LayerOut out = layer ? *layer : LayerOut{};
 
     hipStream_t st = (hipStream_t)stream;
     size_t esz = dtype == MOE_F32 ? 4 : 2;
@@ -431,16 +437,16 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
         auto narrow = [&](int K, int N) { return f32_narrow(max_rows, max_slots, E, schedule, K, N); };
         const bool narrow1 = narrow(d, F), narrow2 = narrow(F, d);
         auto staged = [&](int bm, int K, int N) { return f32_staged(bm, max_rows, max_slots, E, schedule, K, N); };
-#define MOE_F32_BM(RELU, BM, D, SEVERAL) \
-    (BM == 64 ? ffn_gemm_f32_kernel<RELU, 64, F32_BN, D, SEVERAL> : ffn_gemm_f32_kernel<RELU, 32, F32_BN, D, SEVERAL>)
-#define MOE_F32_KERNEL(RELU, BM, NARROW, K, N)                                                    \
-    (NARROW            ? ffn_gemm_f32_kernel<RELU, 32, F32_NARROW_BN, F32_STAGED, false>          \
-     : BM == 0         ? ffn_gemm_f32_kernel<RELU, 32, F32_BN, 1, true>                           \
-     : staged(BM, K, N) ? MOE_F32_BM(RELU, BM, F32_STAGED, false)                                 \
-     : f32_several(K)  ? MOE_F32_BM(RELU, BM, 4, true)                                            \
-                       : MOE_F32_BM(RELU, BM, 4, false))
-        auto gemm1 = MOE_F32_KERNEL(true, bm1, narrow1, d, F);
-        auto gemm2 = MOE_F32_KERNEL(false, bm2, narrow2, F, d);
+#define MOE_F32_BM(RELU, BM, D, SEVERAL, OUT) \
+    (BM == 64 ? ffn_gemm_f32_kernel<RELU, 64, F32_BN, D, SEVERAL, OUT> : ffn_gemm_f32_kernel<RELU, 32, F32_BN, D, SEVERAL, OUT>)
+#define MOE_F32_KERNEL(RELU, BM, NARROW, K, N, OUT)                                               \
+    (NARROW            ? ffn_gemm_f32_kernel<RELU, 32, F32_NARROW_BN, F32_STAGED, false, OUT>     \
+     : BM == 0         ? ffn_gemm_f32_kernel<RELU, 32, F32_BN, 1, true, OUT>                      \
+     : staged(BM, K, N) ? MOE_F32_BM(RELU, BM, F32_STAGED, false, OUT)                            \
+     : f32_several(K)  ? MOE_F32_BM(RELU, BM, 4, true, OUT)                                       \
+                       : MOE_F32_BM(RELU, BM, 4, false, OUT))
+        auto gemm1 = MOE_F32_KERNEL(true, bm1, narrow1, d, F, false);
+        auto gemm2 = layer ? MOE_F32_KERNEL(false, bm2, narrow2, F, d, true) : MOE_F32_KERNEL(false, bm2, narrow2, F, d, false);
 #undef MOE_F32_KERNEL
 #undef MOE_F32_BM
         auto grid = [&](int bm, bool few, int K, int N) {
@@ -448,16 +454,35 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
         };
         hipLaunchKernelGGL(gemm1, grid(bm1, narrow1, d, F), dim3(F32_THREADS), 0, st,
                            (const float *)x_perm, (const float *)w1, row_index, n_x_rows, d, F, E, slot_offset, slot_expert,
-                           n_slots, max_slots, schedule, max_rows, (float *)h);
+                           n_slots, max_slots, schedule, max_rows, (float *)h, LayerOut{});
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm1");
         if (ev[1]) (void)hipEventRecord(ev[1], st);
         hipLaunchKernelGGL(gemm2, grid(bm2, narrow2, F, d), dim3(F32_THREADS), 0, st,
                            (const float *)h, (const float *)w2, (const int32_t *)nullptr, max_rows, F, d, E, slot_offset,
-                           slot_expert, n_slots, max_slots, schedule, max_rows, (float *)y_perm);
+                           slot_expert, n_slots, max_slots, schedule, max_rows, (float *)y_perm, out);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm2");
     }
     if (ev[2]) (void)hipEventRecord(ev[2], st);
     return MOE_OK;
+}
+
+// Where the second product of a binary32 layer makes the output: a launch less, and y is not read back.  Captured layers, us, with
+// moe_combine and so: 64 -> 256, 32 experts, 100 rows 19.7, 17.6; 256 -> 1024, 8 experts, 16 rows 22.8, 20.5, 1500 rows 58.7, 53.0, 32 experts,
+// 4096 rows 75.9, 71.2; 512 -> 2048, 32 experts, 1500 rows 117, 114.  The rows then leave scattered from a workgroup that still computes,
+// which costs more than the launch where there are many: 64 -> 256, 8 experts, 4096 rows 29.8, 30.9; 64 -> 1024, 128 experts, 16384 rows 82, 85;
+// 512 -> 2048 is even from 3000 rows on (0.98 .. 1.02).  Nor in the experts schedule, whose few workgroups write one after another (64 -> 256, 32
+// experts, 2048 rows 98, 105), nor in bf16: the kernel for few rows has no registers left for it (37 rows, 128 experts 56.5, 57.4).
+bool moe::ffn_makes_output(int T, int d, int dtype, int schedule)
+{
+    return dtype == MOE_F32 && schedule == MOE_SCHEDULE_SLOTS && T > 0 && T <= (d >= 128 && d <= 256 ? 6000 : 2048);
+}
+
+int moe::ffn_layer(const moe_layer_args *a, int max_slots, void *stream)
+{
+    const LayerOut out{a->perm, a->inv, a->expert_prob, a->x, a->out, a->T, a->residual};
+    return expert_ffn_checked(a->x, a->T, a->perm, a->w1, a->w2, a->weight_layout, a->slot_offset, a->slot_expert, a->n_slots, a->T,
+                              max_slots, a->E, a->d, a->F, a->dtype, a->schedule, a->y_perm, a->ffn_ws, a->ffn_ws_bytes, stream, nullptr,
+                              &out);
 }
 
 extern "C" int moe_expert_ffn(const void *x_perm, const int32_t *row_index, const void *w1, const void *w2,

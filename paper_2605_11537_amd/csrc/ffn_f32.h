@@ -199,11 +199,12 @@ __device__ __forceinline__ void f32_tile_staged(const float *__restrict__ A, con
 }
 
 // SEVERAL: units per workgroup (f32_grid); else one, which is up to 5 % faster with nothing kept for the next
-template <bool RELU, int BM, int BN, int D, bool SEVERAL>
+// OUT: the layer's output too (LayerOut); the token of a row is asked for before the product, its probability and x after it
+template <bool RELU, int BM, int BN, int D, bool SEVERAL, bool OUT = false>
 __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_kernel(
     const float *__restrict__ A, const float *__restrict__ W, const int32_t *__restrict__ row_index, int n_src_rows, int K,
     int N, int E, const int32_t *__restrict__ slot_offset, const int32_t *__restrict__ slot_expert,
-    const int32_t *__restrict__ n_slots_p, int max_slots, int schedule, int max_rows, float *__restrict__ C)
+    const int32_t *__restrict__ n_slots_p, int max_slots, int schedule, int max_rows, float *__restrict__ C, LayerOut layer)
 {
     __shared__ __attribute__((aligned(16))) float part[4][BM][BN + 4];
     __shared__ TileItem found;
@@ -212,8 +213,10 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
     share.schedule = schedule;
     share.n_nt = N / BN;
     share.max_rows = max_rows;
-    share.find(slot_offset, slot_expert, n_slots_p, max_slots, &found);
     const int tid = threadIdx.x, w = tid >> 6, c = tid & 15;
+    const bool gone = OUT && layer.dropped(blockIdx.x * (F32_THREADS / WAVE) + __builtin_amdgcn_readfirstlane(w));
+    share.find(slot_offset, slot_expert, n_slots_p, max_slots, &found);
+    if constexpr (OUT) layer.copy_dropped(gone, N / 4);
     for (int unit = share.first + (int)(blockIdx.x >> 3); unit < share.end; unit += (int)(gridDim.x >> 3)) {      // uniform
         share.write_item(slot_offset, slot_expert, unit, &found);
         __syncthreads();
@@ -239,6 +242,16 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
                 if constexpr (D != F32_STAGED) {                 // a bad index reads row 0 (the staged tile sees to it itself)
 #pragma unroll
                     for (int m = 0; m < LOADS; ++m) src[m] = src[m] >= 0 && src[m] < n_src_rows ? src[m] : 0;
+                }
+            }
+            constexpr int ROWS_AT_ONCE = F32_THREADS / (BN / 4), ROWS = BM / ROWS_AT_ONCE;      // of the tile's epilogue
+            const int r_first = tid / (BN / 4);
+            int token[ROWS];
+            if constexpr (OUT) {
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i) {
+                    const int r = r_first + i * ROWS_AT_ONCE;
+                    token[i] = layer.perm[r0 + (r < nrows ? r : nrows - 1)];
                 }
             }
             const int blocks = (nrows + 15) >> 4;
@@ -269,7 +282,21 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
 #undef MOE_F32_TILE
             __syncthreads();
             const int col = tid % (BN / 4) * 4;
-            for (int r = tid / (BN / 4); r < nrows; r += F32_THREADS / (BN / 4)) {
+            float prob[ROWS];
+            f32x4_t base[ROWS];
+            if constexpr (OUT) {
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i) {
+                    token[i] = (unsigned)token[i] < (unsigned)layer.T ? token[i] : 0;
+                    prob[i] = layer.prob[token[i]];
+                    base[i] = layer.residual ? *reinterpret_cast<const f32x4_t *>(static_cast<const float *>(layer.x) + (size_t)token[i] * N + nt * BN + col)
+                                             : (f32x4_t){0.f, 0.f, 0.f, 0.f};
+                }
+            }
+#pragma unroll
+            for (int n = 0; n < ROWS; ++n) {
+                const int r = r_first + n * ROWS_AT_ONCE;
+                if (r >= nrows) break;
                 f32x4_t p[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) p[q] = *reinterpret_cast<const f32x4_t *>(&part[q][r][col]);
@@ -280,6 +307,12 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
                     o[i] = RELU ? fmaxf(v, 0.f) : v;
                 }
                 *reinterpret_cast<f32x4_t *>(C + (size_t)(r0 + r) * N + nt * BN + col) = o;
+                if constexpr (OUT) {
+                    f32x4_t v;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = fmaf(prob[n], o[i], base[n][i]);
+                    *reinterpret_cast<f32x4_t *>(static_cast<float *>(layer.out) + (size_t)token[n] * N + nt * BN + col) = v;
+                }
             }
             __syncthreads();
         }

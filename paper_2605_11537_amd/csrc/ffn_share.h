@@ -12,6 +12,35 @@ struct TileItem {
     int expert, row_begin, row_end, column, reuse;
 };
 
+// A layer's last step, made by its second product (top-1 routing): what moe_combine does, row by row as the rows come out.
+// The tables are those of the same batch: perm[row] is the token of a row, inv[token] < 0 a token without one.
+struct LayerOut {
+    const int32_t *perm, *inv;
+    const float *prob;
+    const void *x;
+    void *out;
+    int T, residual;
+
+    // a token that has no row; asked for before the search of the units, so that the answer comes with the slot tables
+    __device__ __forceinline__ bool dropped(int s) const { return s < T && inv[s] < 0; }
+    // out <- x for the tokens without a row, dealt to all wavefronts of the launch; `first`: dropped(this wavefront's first token)
+    __device__ __forceinline__ void copy_dropped(bool first, int vec_per_row) const
+    {
+        typedef unsigned vec_t __attribute__((ext_vector_type(4)));
+        const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int step = gridDim.x * (SHARE_THREADS / WAVE);
+        bool gone = first;
+        for (long long s = blockIdx.x * (SHARE_THREADS / WAVE) + w; s < T; s += step) {
+            if (gone) {
+                const vec_t *src = static_cast<const vec_t *>(x) + (size_t)s * vec_per_row;
+                vec_t *dst = static_cast<vec_t *>(out) + (size_t)s * vec_per_row;
+                for (int c = lane; c < vec_per_row; c += WAVE) dst[c] = src[c];
+            }
+            gone = s + step < T && inv[s + step] < 0;
+        }
+    }
+};
+
 // Relative cost of a row tile: its 16-row blocks, and what every tile pays for its weights.
 __device__ __forceinline__ int tile_cost(int rows) { return TILE_COST_TILE + TILE_COST_BLOCK * ((rows + 15) >> 4); }
 

@@ -1,6 +1,7 @@
-// moe_layer_forward: the four calls of a layer in turn on one stream.  Nothing runs here that the calls do not do; what it saves is
-// four crossings of a foreign-function boundary (a Python program issues a layer in 15 instead of 29 us, which bounded small layers).
-#include "common.h"
+// moe_layer_forward: the four calls of a layer in turn on one stream, the last two as one where the second product can make the output
+// (ffn_makes_output).  The results are those of the calls; what it saves is four crossings of a foreign-function boundary (a Python program
+// issues a layer in 15 instead of 29 us, which bounded small layers) and there a launch.
+#include "route.h"
 
 static_assert(sizeof(moe_layer_args) == 28 * 8 + 16 * 4, "no padding: callers pack it field by field");
 
@@ -24,6 +25,7 @@ extern "C" int moe_layer_forward(const moe_layer_args *a, void *stream)
                            a->counts, a->kept, a->expert_offset, a->slot_offset, a->perm, a->inv, a->row_token, a->front_ws,
                            a->front_ws_bytes, stream);
     if (rc != MOE_OK) return rc;
+    if (a->top_k == 0 && moe::ffn_makes_output(a->T, a->d, a->dtype, a->schedule)) return moe::ffn_layer(a, max_slots, stream);
     rc = a->top_k > 0 ? moe_expert_ffn_rows(a->x, a->T, a->row_token, a->w1, a->w2, a->weight_layout, a->slot_offset, a->slot_expert,
                                             a->n_slots, n, max_slots, a->E, a->d, a->F, a->dtype, a->schedule, a->y_perm, a->ffn_ws,
                                             a->ffn_ws_bytes, stream)

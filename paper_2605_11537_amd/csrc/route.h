@@ -33,4 +33,10 @@ bool dispatch_small(int T, int E);
 int dispatch_small_launch(const int32_t *expert_idx, const int32_t *replicas, int T, int n_tokens, int E, int slot_capacity, int max_slots,
                           int32_t *counts, int32_t *kept, int32_t *expert_offset, int32_t *slot_offset, int32_t *perm, int32_t *inv,
                           int32_t *row_token, hipStream_t st, const char *who);
+// combine.hip: what moe_combine asks of its arguments
+int combine_check(const void *y_perm, const void *x, const int32_t *inv, const float *expert_prob, int T, int d, int dtype, int residual,
+                  const void *out);
+// ffn.hip: moe_expert_ffn and moe_combine of a top-1 layer with the output made by the second product, and whether it takes a layer
+bool ffn_makes_output(int T, int d, int dtype, int schedule);
+int ffn_layer(const moe_layer_args *a, int max_slots, void *stream);
 }  // namespace moe

@@ -1,0 +1,54 @@
+"""A top-1 layer whose second product makes the output: the same bits as the product and moe_combine by themselves, tokens without a
+row included, in every kernel that does it."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# dtype, T, d, F, E, R, capacity
+CASES = [
+    ("f32", 512, 64, 256, 8, 4, 80),            # one step of k in flight, several units per workgroup, 32 columns
+    ("f32", 1, 64, 64, 4, 0, 1),
+    ("f32", 33, 256, 256, 8, 2, 3),             # 32 rows, several units
+    ("f32", 700, 256, 192, 5, 3, 90),
+    ("f32", 1500, 256, 256, 4, 3, 260),         # 64 rows, several units
+    ("f32", 1500, 512, 512, 32, 8, 59),         # 32 rows, tokens through LDS
+    ("f32", 1500, 512, 512, 4, 2, 300),         # 64 rows, tokens through LDS
+    ("f32", 700, 128, 320, 16, 4, 40),          # 32 and 64 rows straight from memory
+    ("f32", 900, 128, 320, 2, 4, 100),
+    ("f32", 2048, 64, 256, 16, 0, 60),          # the longest batches that it takes, most tokens without a row
+    ("f32", 6000, 128, 256, 16, 2, 100),
+    ("f32", 6001, 128, 256, 16, 2, 100),        # and layers whose output moe_combine makes
+    ("f32", 2049, 64, 256, 16, 0, 60),
+    ("bf16", 37, 256, 1024, 64, 8, 4),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(str(v) for v in c))
+def test_same_bits_as_the_calls(case):
+    import paper_2605_11537_amd as moe
+    name, T, d, F, E, R, C = case
+    dt = dict(f32=torch.float32, bf16=torch.bfloat16)[name]
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+
+    def rand(*shape, std=1.0):
+        return (torch.randn(*shape, generator=g, device="cuda") * std).to(dt)
+    x, wr, b = rand(T, d), rand(d, E, std=0.1), torch.zeros(E, device="cuda")
+    b[0] = 1.0
+    w1, w2 = rand(E, d, F, std=0.05), rand(E, F, d, std=0.05)
+    if dt == torch.bfloat16:
+        w1, w2 = moe.moe_pack_weights(w1), moe.moe_pack_weights(w2)
+    layer = moe.MoeLayer(T, d, F, E, R, C, dt)
+    ev = [torch.cuda.Event() for _ in range(5)]
+    for residual in (0, 1):
+        for schedule in (0, 1):
+            got = []
+            for how in (dict(), dict(marks=ev)):                 # one call, call by call
+                layer.y_perm.fill_(float("nan"))
+                layer.out.fill_(float("nan"))
+                out = layer.forward(x, wr, b, w1, w2, residual=residual, schedule=schedule, **how)
+                kept = int(layer.disp_out["expert_offset"][-1])
+                got.append((out.clone(), layer.y_perm[:kept].clone()))
+            assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), (residual, schedule)
+            dropped = layer.disp_out["inv"] < 0
+            assert torch.equal(got[0][0][dropped], x[dropped])
