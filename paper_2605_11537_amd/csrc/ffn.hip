@@ -160,13 +160,14 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) void ffn_dense_bf16_kernel(
 // weight-streaming shapes.  65..128 rows: 4 row blocks per wavefront, k chunks of 64, so a weight
 // byte fetched from L2/HBM feeds twice the rows.  (Three or four workgroups per CU instead of two, tried with a k chunk of 64 to
 // fit the registers, changed the HBM-bound launches by under 1%: two it stays.)
-template <bool RELU>
+// OUT: the layer's output too (LayerOut)
+template <bool RELU, bool OUT = false>
 __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
     const bf16_t *__restrict__ A, const int32_t *__restrict__ row_index, int n_src_rows,
     const bf16_t *__restrict__ Wp, int K, int N, int E, const WorkItem *__restrict__ items,
     const int32_t *__restrict__ n_items, const int32_t *__restrict__ slot_offset,
     const int32_t *__restrict__ slot_expert, const int32_t *__restrict__ n_slots_p, int max_slots, int schedule,
-    int max_rows, bf16_t *__restrict__ C)
+    int max_rows, bf16_t *__restrict__ C, LayerOut layer)
 {
     constexpr int TM = FFN_BM;                               // rows per pass over a work item
     constexpr int MBT = TM / 32;
@@ -174,10 +175,14 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
     constexpr int S0 = gemm_lds_elems<2, FFN_BK>(), S1 = gemm_lds_elems<4, FFN_BK_TALL>(), S2 = TM * LDC;
     __shared__ __attribute__((aligned(16))) bf16_t lds[(S0 > S1 ? S0 : S1) > S2 ? (S0 > S1 ? S0 : S1) : S2];
     const int n_nt = N / FFN_BN;
+    const bool gone = OUT && layer.dropped(blockIdx.x * (GEMM_THREADS / WAVE) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    auto copy_dropped = [&]() {
+        if constexpr (OUT) layer.copy_dropped(gone, N / 8);
+    };
     int item, nt;
     WorkItem it;
     if (items) {
-        if (!grouped_tile_of(blockIdx.x, n_items[0], n_nt, n_items[1], item, nt)) return;
+        if (!grouped_tile_of(blockIdx.x, n_items[0], n_nt, n_items[1], item, nt)) return copy_dropped();
         it = items[item];
     } else {
         // No list: one work item per slot (per expert in the experts schedule), read straight from the
@@ -186,7 +191,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
         int P = n_slots_p[0];
         if (P > max_slots) P = max_slots;
         const int lid = xcd_remap(blockIdx.x, P * n_nt);
-        if (lid < 0) return;
+        if (lid < 0) return copy_dropped();
         item = lid / n_nt;
         nt = lid - item * n_nt;
         const int e = slot_expert[item];
@@ -195,13 +200,14 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
         const bool after_same = item > 0 && slot_expert[item - 1] == e;
         int last = item;
         if (schedule == MOE_SCHEDULE_EXPERTS) {
-            if (after_same) return;                       // the expert's first slot walks all its rows
+            if (after_same) return copy_dropped();                       // the expert's first slot walks all its rows
             while (last + 1 < P && slot_expert[last + 1] == e) ++last;
         }
         it.row_end = slot_offset[last + 1];
         it.reuse = it.row_end - it.row_begin > TM || (schedule == MOE_SCHEDULE_SLOTS &&
                                                      (after_same || (item + 1 < P && slot_expert[item + 1] == e)));
     }
+    copy_dropped();
     if (it.expert < 0 || it.expert >= E || it.row_begin < 0) return;  // never index weights with a bad id
     const bf16_t *Bp = Wp + (size_t)it.expert * K * N;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -228,6 +234,16 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
             else MOE_TILE(4, FFN_BK_TALL, true);
         }
 #undef MOE_TILE
+        constexpr int PIECES = TM * (FFN_BN / 8) / GEMM_THREADS;
+        const int c8 = threadIdx.x % (FFN_BN / 8), r_first = threadIdx.x / (FFN_BN / 8);       // of this thread's pieces, 16 rows apart
+        int token[PIECES];
+        if constexpr (OUT) {
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i) {
+                const int r = r_first + i * (TM / PIECES);
+                token[i] = layer.perm[r0 + (r < nrows ? r : nrows - 1)];
+            }
+        }
         // Epilogue through LDS: an accumulator lane holds single columns of 16 different rows,
         // and 2-byte stores that cover a quarter of a cache line each are slow.  The tile is
         // transposed in LDS (the A buffers are free after the last barrier of the product) and
@@ -242,14 +258,29 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
                     lds[(mb * 32 + acc_row(v, lane)) * LDC + w * 32 + (lane & 31)] = f32_to_bf16(val);
                 }
             }
+        float prob[PIECES];
+        uint4 base[PIECES];
+        if constexpr (OUT) {
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i) {
+                token[i] = (unsigned)token[i] < (unsigned)layer.T ? token[i] : 0;
+                prob[i] = layer.prob[token[i]];
+                base[i] = layer.residual ? *reinterpret_cast<const uint4 *>(static_cast<const bf16_t *>(layer.x) + (size_t)token[i] * N +
+                                                                            nt * FFN_BN + c8 * 8)
+                                         : make_uint4(0, 0, 0, 0);
+            }
+        }
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < TM * (FFN_BN / 8) / GEMM_THREADS; ++i) {
-            int p = threadIdx.x + i * GEMM_THREADS;
-            int r = p / (FFN_BN / 8), c8 = p % (FFN_BN / 8);
-            if (r < nrows)
-                *reinterpret_cast<uint4 *>(C + (size_t)(r0 + r) * N + nt * FFN_BN + c8 * 8) =
-                    *reinterpret_cast<const uint4 *>(lds + r * LDC + c8 * 8);
+        for (int i = 0; i < PIECES; ++i) {
+            const int r = r_first + i * (TM / PIECES);
+            if (r < nrows) {
+                const uint4 y = *reinterpret_cast<const uint4 *>(lds + r * LDC + c8 * 8);
+                *reinterpret_cast<uint4 *>(C + (size_t)(r0 + r) * N + nt * FFN_BN + c8 * 8) = y;
+                if constexpr (OUT)
+                    *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(layer.out) + (size_t)token[i] * N + nt * FFN_BN + c8 * 8) =
+                        LayerOut::scaled(y, prob[i], base[i]);
+            }
         }
         __syncthreads();
     }
@@ -408,7 +439,7 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
         else
             hipLaunchKernelGGL(ffn_gemm_bf16_kernel<true>, dim3(g1), dim3(GEMM_THREADS), 0, st, (const bf16_t *)x_perm, row_index,
                                n_x_rows, (const bf16_t *)w1, d, F, E, list, n_items, slot_offset, slot_expert, n_slots,
-                               max_slots, schedule, max_rows, (bf16_t *)h);
+                               max_slots, schedule, max_rows, (bf16_t *)h, LayerOut{});
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm1");
         if (ev[1]) (void)hipEventRecord(ev[1], st);
         if (dense) {
@@ -426,9 +457,9 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
                                (const bf16_t *)w2, (const int32_t *)nullptr, max_rows, F, d, E, slot_offset, slot_expert, n_slots,
                                max_slots, max_rows, (bf16_t *)y_perm);
         else
-            hipLaunchKernelGGL(ffn_gemm_bf16_kernel<false>, dim3(g2), dim3(GEMM_THREADS), 0, st, (const bf16_t *)h,
+            hipLaunchKernelGGL((layer ? ffn_gemm_bf16_kernel<false, true> : ffn_gemm_bf16_kernel<false>), dim3(g2), dim3(GEMM_THREADS), 0, st, (const bf16_t *)h,
                                (const int32_t *)nullptr, max_rows, (const bf16_t *)w2, F, d, E, list, n_items, slot_offset,
-                               slot_expert, n_slots, max_slots, schedule, max_rows, (bf16_t *)y_perm);
+                               slot_expert, n_slots, max_slots, schedule, max_rows, (bf16_t *)y_perm, out);
         MOE_CHECK_LAUNCH("moe_expert_ffn/gemm2");
     } else {
         // tile height of a product of depth K (0: 32 rows and a short k); the results are the same
@@ -466,15 +497,23 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     return MOE_OK;
 }
 
-// Where the second product of a binary32 layer makes the output: a launch less, and y is not read back.  Captured layers, us, with
-// moe_combine and so: 64 -> 256, 32 experts, 100 rows 19.7, 17.6; 256 -> 1024, 8 experts, 16 rows 22.8, 20.5, 1500 rows 58.7, 53.0, 32 experts,
-// 4096 rows 75.9, 71.2; 512 -> 2048, 32 experts, 1500 rows 117, 114.  The rows then leave scattered from a workgroup that still computes,
-// which costs more than the launch where there are many: 64 -> 256, 8 experts, 4096 rows 29.8, 30.9; 64 -> 1024, 128 experts, 16384 rows 82, 85;
-// 512 -> 2048 is even from 3000 rows on (0.98 .. 1.02).  Nor in the experts schedule, whose few workgroups write one after another (64 -> 256, 32
-// experts, 2048 rows 98, 105), nor in bf16: the kernel for few rows has no registers left for it (37 rows, 128 experts 56.5, 57.4).
-bool moe::ffn_makes_output(int T, int d, int dtype, int schedule)
+// Where the second product of a layer makes the output: a launch less, and y is not read back; but the rows then leave scattered from
+// workgroups that still compute, which costs more than the launch where there are many.  Captured layers, us, with moe_combine and so.
+//   binary32: 64 -> 256, 32 experts, 100 rows 19.7, 17.6; 256 -> 1024, 8 experts, 16 rows 22.8, 20.5, 1500 rows 58.7, 53.0, 32 experts,
+//     4096 rows 75.9, 71.2; 512 -> 2048, 32 experts, 1500 rows 117, 114.  Past the lines: 64 -> 256, 8 experts, 4096 rows 29.8, 30.9; 64 -> 1024, 128
+//     experts, 16384 rows 82, 85; 512 -> 2048 is even from 3000 rows on (0.98 .. 1.02).
+//   bf16, 128-column kernel: 256 -> 1024, 64 experts, 200 rows 25.9, 24.4, 1000 rows 31.8, 30.3; 512 -> 2048, 32 experts, 200 rows 40.1, 38.2; on
+//     average 1.5 % up to 1000 rows over 64 .. 768 columns and more, none from 2000 on (768 -> 3072, 64 experts, 2048 rows 124.3, 125.7).
+//   The others lost or gained nothing: the 128-row tiles 256 -> 1024, 8 experts, 2000 rows 32.4, 33.6; the kernel for few rows has no registers
+//     left for it (37 rows, 128 experts 56.5, 57.4).
+// Nor in the experts schedule, whose few workgroups write one after another (64 -> 256, 32 experts, 2048 fp32 rows 98, 105).
+bool moe::ffn_makes_output(int T, int max_slots, int E, int d, int F, int dtype, int schedule)
 {
-    return dtype == MOE_F32 && schedule == MOE_SCHEDULE_SLOTS && T > 0 && T <= (d >= 128 && d <= 256 ? 6000 : 2048);
+    if (schedule != MOE_SCHEDULE_SLOTS || T <= 0 || max_slots <= 0 || E <= 0 || d <= 0 || F <= 0) return false;
+    if (dtype == MOE_F32) return T <= (d >= 128 && d <= 256 ? 6000 : 2048);
+    if (dtype != MOE_BF16 || T > 1500) return false;
+    const FfnRoute route = ffn_route(T, max_slots, E, d, F, schedule);
+    return route.kernel == FFN_COLUMNS && !route.few_rows[1];
 }
 
 int moe::ffn_layer(const moe_layer_args *a, int max_slots, void *stream)

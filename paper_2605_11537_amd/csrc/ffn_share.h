@@ -21,6 +21,15 @@ struct LayerOut {
     void *out;
     int T, residual;
 
+    // a 16-byte piece of bf16: y scaled, on x or on zero
+    __device__ __forceinline__ static uint4 scaled(uint4 y, float p, uint4 base)
+    {
+        auto two = [&](uint32_t v, uint32_t b) {
+            return pack_bf16x2(fmaf(p, __uint_as_float(v << 16), __uint_as_float(b << 16)),
+                               fmaf(p, __uint_as_float(v & 0xffff0000u), __uint_as_float(b & 0xffff0000u)));
+        };
+        return make_uint4(two(y.x, base.x), two(y.y, base.y), two(y.z, base.z), two(y.w, base.w));
+    }
     // a token that has no row; asked for before the search of the units, so that the answer comes with the slot tables
     __device__ __forceinline__ bool dropped(int s) const { return s < T && inv[s] < 0; }
     // out <- x for the tokens without a row, dealt to all wavefronts of the launch; `first`: dropped(this wavefront's first token)

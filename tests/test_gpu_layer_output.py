@@ -20,7 +20,13 @@ CASES = [
     ("f32", 6000, 128, 256, 16, 2, 100),
     ("f32", 6001, 128, 256, 16, 2, 100),        # and layers whose output moe_combine makes
     ("f32", 2049, 64, 256, 16, 0, 60),
-    ("bf16", 37, 256, 1024, 64, 8, 4),
+    ("bf16", 37, 256, 1024, 64, 8, 4),          # the kernel for few rows
+    ("bf16", 1, 128, 256, 1, 0, 1),             # the 128-column kernel: a row,
+    ("bf16", 200, 256, 384, 24, 3, 9),          # tiles of 32 rows,
+    ("bf16", 900, 128, 128, 16, 2, 56),         # of 64
+    ("bf16", 500, 256, 256, 9, 6, 200),         # and 128 rows, slots of several tiles
+    ("bf16", 1500, 128, 128, 64, 0, 20),        # the longest batch that it takes, most tokens without a row
+    ("bf16", 1501, 128, 128, 64, 0, 20),
 ]
 
 
