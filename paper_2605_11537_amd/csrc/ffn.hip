@@ -362,10 +362,6 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     size_t need = moe_expert_ffn_workspace_bytes(max_rows, max_slots, d, F, dtype);
     MOE_REQUIRE(ws && aligned16(ws) && ws_bytes >= need, MOE_ERR_WORKSPACE,
                 "moe_expert_ffn: workspace of %zu bytes needed, %zu given", need, ws_bytes);
-    if (layer) {
-        const int rc = combine_check(y_perm, layer->x, layer->inv, layer->prob, layer->T, d, dtype, layer->residual, layer->out);
-        if (rc != MOE_OK) return rc;
-    }
     const LayerOut out = layer ? *layer : LayerOut{};
 
     hipStream_t st = (hipStream_t)stream;
@@ -516,6 +512,7 @@ bool moe::ffn_makes_output(int T, int max_slots, int E, int d, int F, int dtype,
     return route.kernel == FFN_COLUMNS && !route.few_rows[1];
 }
 
+// the arguments have passed combine_check
 int moe::ffn_layer(const moe_layer_args *a, int max_slots, void *stream)
 {
     const LayerOut out{a->perm, a->inv, a->expert_prob, a->x, a->out, a->T, a->residual};

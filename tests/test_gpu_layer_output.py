@@ -58,3 +58,16 @@ def test_same_bits_as_the_calls(case):
             assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), (residual, schedule)
             dropped = layer.disp_out["inv"] < 0
             assert torch.equal(got[0][0][dropped], x[dropped])
+
+
+def test_refused_output_is_an_error_behind_the_products():
+    """Arguments of the last step are refused as it refuses them, with the steps before it enqueued."""
+    import paper_2605_11537_amd as moe
+    T, d, F, E = 64, 64, 64, 4
+    layer = moe.MoeLayer(T, d, F, E, 0, T, torch.float32)
+    x, wr, b = torch.randn(T, d, device="cuda"), torch.randn(d, E, device="cuda"), torch.zeros(E, device="cuda")
+    w1, w2 = torch.randn(E, d, F, device="cuda"), torch.randn(E, F, d, device="cuda")
+    layer.y_perm.fill_(float("nan"))
+    with pytest.raises(moe.MoeError, match="moe_combine: out aliases"):
+        layer.forward(x, wr, b, w1, w2, out=x)
+    assert torch.isfinite(layer.y_perm).all()
