@@ -2,10 +2,13 @@
 //
 // What a small call costs a Python program is its marshalling: through ctypes a tensor takes about 0.5 us (three attribute look-ups in Python and
 // a conversion) and an int 0.1 us, a dozen of them per call.  Here a tensor's pointer is read from the tensor itself.  The calls keep
-// their argument order and return their error code; what a tensor has to be (on the device, contiguous) and the errors are the same.
+// their argument order and return their error code.  A tensor has to be on the device and contiguous (ValueError else).  An int may be any whole
+// number, numpy's too (TypeError else).  The fields of a layer have to fit the struct's (OverflowError else); arguments of the other calls are
+// reduced to their parameter's width, as ctypes does.
 // Functions are typed by the C header and bound to the addresses of the library that binding.lib() has loaded and checked.
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <climits>
 #include <cstring>
 #include <exception>
 #include <tuple>
@@ -50,15 +53,42 @@ void *pointer_of(PyObject *o)
 
 unsigned long long integer_of(PyObject *o)
 {
-    if (!PyLong_Check(o)) {
-        PyErr_Format(PyExc_TypeError, "int expected instead of %s instance", Py_TYPE(o)->tp_name);
-        throw Failed();
-    }
-    return PyLong_AsUnsignedLongLongMask(o);        // reduced to the parameter's width, as ctypes does
+    const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);      // takes what has __index__
+    if (v == (unsigned long long)-1 && PyErr_Occurred()) throw Failed();
+    return v;
 }
 
-// what is no tensor comes as an address: a stream, a struct in host memory
-void *address_of(PyObject *o) { return o == Py_None ? nullptr : reinterpret_cast<void *>(integer_of(o)); }
+// a whole number that the field holds
+void fit(PyObject *o, size_t &field)
+{
+    PyObject *whole = PyNumber_Index(o);
+    if (!whole) throw Failed();
+    field = PyLong_AsSize_t(whole);
+    Py_DECREF(whole);
+    if (field == (size_t)-1 && PyErr_Occurred()) throw Failed();
+}
+void fit(PyObject *o, int &field)
+{
+    int over = 0;
+    const long v = PyLong_AsLongAndOverflow(o, &over);                  // takes what has __index__
+    if (v == -1 && PyErr_Occurred()) throw Failed();
+    if (over || v < INT_MIN || v > INT_MAX) {
+        PyErr_Format(PyExc_OverflowError, "%R does not fit an int", o);
+        throw Failed();
+    }
+    field = (int)v;
+}
+
+// what is no tensor comes as an address, an int itself: a stream, a struct in host memory
+void *address_of(PyObject *o)
+{
+    if (o == Py_None) return nullptr;
+    if (!PyLong_Check(o)) {
+        PyErr_Format(PyExc_TypeError, "an address expected instead of %s instance", Py_TYPE(o)->tp_name);
+        throw Failed();
+    }
+    return reinterpret_cast<void *>(integer_of(o));
+}
 
 template <class T, bool STREAM>
 struct Arg {
@@ -156,8 +186,8 @@ PyObject *py_moe_layer_forward(PyObject *, PyObject *const *args, Py_ssize_t n)
         } fields;
         PyObject *const *at = args;
         for (void *&p : fields.pointers) p = pointer_of(*at++);
-        for (size_t &s : fields.sizes) s = static_cast<size_t>(integer_of(*at++));
-        for (int &i : fields.ints) i = static_cast<int>(integer_of(*at++));
+        for (size_t &s : fields.sizes) fit(*at++, s);
+        for (int &i : fields.ints) fit(*at++, i);
         moe_layer_args layer;
         memcpy(&layer, &fields, sizeof layer);
         void *stream = address_of(*at);

@@ -1,6 +1,7 @@
 """What the extension takes and refuses for the arguments of the library's calls (no GPU: the calls stop at their own checks or have nothing to do)."""
 import ctypes
 
+import numpy as np
 import pytest
 import torch
 
@@ -22,6 +23,13 @@ class _OnDevice:
         return 16
 
 
+class _Whole:
+    """A whole number of no type that is known."""
+
+    def __index__(self):
+        return 8
+
+
 def _combine(y, x=None, T=0, d=8, dtype=0, residual=0, out=None, stream=0):
     return binding._c().moe_combine(y, x, None, None, T, d, dtype, residual, out, stream)
 
@@ -39,17 +47,52 @@ def test_what_a_tensor_may_be():
 def test_ints_and_the_stream():
     assert _combine(None, T=False, residual=True) == 0                   # a bool is an int
     assert _combine(None, T=2 ** 32) == 0 and _combine(None, stream=None) == 0       # taken to 32 bits, as by ctypes
-    for bad in (1.0, "1", None, torch.tensor(1)):
+    for whole in (np.int64(8), np.uint8(8), torch.tensor(8), _Whole()):  # as any whole number is
+        assert _combine(None, d=whole) == 0
+    for bad in (1.0, "1", None, np.float32(8), torch.tensor(8.0), torch.tensor([8, 8])):
         with pytest.raises(TypeError):
             _combine(None, d=bad)
-    with pytest.raises(TypeError):
-        _combine(None, stream=torch.zeros(1))
+    for no_address in (torch.zeros(1), np.int64(16), _Whole(), 1.5):
+        with pytest.raises(TypeError):
+            _combine(None, stream=no_address)
     with pytest.raises(TypeError):
         binding._c().moe_combine(None)
     with pytest.raises(TypeError):
         binding._c().moe_layer_forward(*[None] * 44)
     with pytest.raises(ValueError):
         binding._c().bind("no_such_call", 0)
+
+
+INT_FIELDS = ("T", "n_plan", "top_k", "renormalize", "d", "F", "router_E", "E", "budget", "slot_capacity", "policy", "dtype", "router_layout",
+              "weight_layout", "schedule", "residual")
+SIZE_FIELDS = ("route_ws_bytes", "front_ws_bytes", "ffn_ws_bytes")
+
+
+def _layer(**fields):
+    """top_k = -1: the call stops at its first check, whose message names T and top_k."""
+    values = {**dict.fromkeys(SIZE_FIELDS, 0), **dict.fromkeys(INT_FIELDS, 1), "top_k": -1, **fields}
+    return binding._c().moe_layer_forward(*[None] * 25, *values.values(), 0)
+
+
+@pytest.mark.parametrize("name", INT_FIELDS + SIZE_FIELDS)
+def test_the_fields_of_a_layer_keep_their_value(name):
+    """A field takes any whole number that fits it, and none that would become another one."""
+    size = name in SIZE_FIELDS
+    lowest, highest = (0, 2 ** 64 - 1) if size else (-2 ** 31, 2 ** 31 - 1)
+    for bad in (lowest - 1, highest + 1, 2 ** 32 + 4 if not size else 2 ** 64 + 4, 2 ** 70, -2 ** 70):
+        with pytest.raises(OverflowError):
+            _layer(**{name: bad})
+    for bad in (1.0, "1", None, np.float64(1), torch.tensor(1.0)):
+        with pytest.raises(TypeError):
+            _layer(**{name: bad})
+    one = -1 if name == "top_k" else 1
+    for fits in (one, np.int64(one), np.int16(one), torch.tensor(one)):
+        assert _layer(**{name: fits}) == -1 and b"T=1 top_k=-1 out of range" in moe.lib().moe_last_error()
+    if name != "top_k":
+        assert _layer(**{name: highest}) == -1 and _layer(**{name: lowest}) == -1
+    else:
+        assert _layer(top_k=lowest) == -1 and b"top_k=-2147483648 " in moe.lib().moe_last_error()
+    assert _layer(T=np.int64(2 ** 31 - 1)) == -1 and b"T=2147483647 " in moe.lib().moe_last_error()
 
 
 def test_errors_are_the_library_s():
