@@ -503,13 +503,19 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
 //   The others lost or gained nothing: the 128-row tiles 256 -> 1024, 8 experts, 2000 rows 32.4, 33.6; the kernel for few rows has no registers
 //     left for it (37 rows, 128 experts 56.5, 57.4).
 // Nor in the experts schedule, whose few workgroups write one after another (64 -> 256, 32 experts, 2048 fp32 rows 98, 105).
-bool moe::ffn_makes_output(int T, int max_slots, int E, int d, int F, int dtype, int schedule)
+static bool output_pays(int T, int max_slots, int E, int d, int F, int dtype, int schedule)
 {
     if (schedule != MOE_SCHEDULE_SLOTS || T <= 0 || max_slots <= 0 || E <= 0 || d <= 0 || F <= 0) return false;
     if (dtype == MOE_F32) return T <= (d >= 128 && d <= 256 ? 6000 : 2048);
     if (dtype != MOE_BF16 || T > 1500) return false;
     const FfnRoute route = ffn_route(T, max_slots, E, d, F, schedule);
     return route.kernel == FFN_COLUMNS && !route.few_rows[1];
+}
+
+bool moe::ffn_makes_output(const moe_layer_args *a, int max_slots)
+{
+    return output_pays(a->T, max_slots, a->E, a->d, a->F, a->dtype, a->schedule) &&
+           ffn_output_apart(a, max_slots, moe_expert_ffn_workspace_bytes(a->T, max_slots, a->d, a->F, a->dtype));
 }
 
 // the arguments have passed combine_check

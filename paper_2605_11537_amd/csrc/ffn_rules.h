@@ -69,4 +69,19 @@ static inline FfnRoute ffn_route(int max_rows, int max_slots, int E, int d, int 
             {short_slots && ffn_few_rows(max_rows, max_slots, d, F), short_slots && ffn_few_rows(max_rows, max_slots, F, d)}};
 }
 
+// Whether the second product of a layer can write the output: it then reads its own operands while it writes, moe_combine does not read
+// them any more.  An output that lies in one of them (its caller has no more use for h, say) is made behind the product.  ws_bytes: of
+// the products' workspace, the part that they use.
+static inline bool ffn_output_apart(const moe_layer_args *a, int max_slots, size_t ws_bytes)
+{
+    const size_t esz = a->dtype == MOE_F32 ? 4 : 2, bytes = (size_t)a->T * a->d * esz;
+    const uintptr_t out = reinterpret_cast<uintptr_t>(a->out);
+    auto apart = [&](const void *p, size_t n) {
+        const uintptr_t at = reinterpret_cast<uintptr_t>(p);
+        return at >= out ? at - out >= bytes : out - at >= n;
+    };
+    return apart(a->ffn_ws, ws_bytes) && apart(a->w2, (size_t)a->E * a->F * a->d * esz) && apart(a->perm, (size_t)a->T * 4) &&
+           apart(a->slot_offset, ((size_t)max_slots + 1) * 4) && apart(a->slot_expert, (size_t)max_slots * 4) && apart(a->n_slots, 4);
+}
+
 }  // namespace moe

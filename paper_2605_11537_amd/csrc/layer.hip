@@ -26,7 +26,7 @@ extern "C" int moe_layer_forward(const moe_layer_args *a, void *stream)
                            a->front_ws_bytes, stream);
     if (rc != MOE_OK) return rc;
     // (arguments that moe_combine refuses go step by step: the products are enqueued in front of the error)
-    if (a->top_k == 0 && moe::ffn_makes_output(a->T, max_slots, a->E, a->d, a->F, a->dtype, a->schedule) &&
+    if (a->top_k == 0 && moe::ffn_makes_output(a, max_slots) &&
         moe::combine_check(a->y_perm, a->x, a->inv, a->expert_prob, a->T, a->d, a->dtype, a->residual, a->out) == MOE_OK)
         return moe::ffn_layer(a, max_slots, stream);
     rc = a->top_k > 0 ? moe_expert_ffn_rows(a->x, a->T, a->row_token, a->w1, a->w2, a->weight_layout, a->slot_offset, a->slot_expert,

@@ -37,6 +37,6 @@ int dispatch_small_launch(const int32_t *expert_idx, const int32_t *replicas, in
 int combine_check(const void *y_perm, const void *x, const int32_t *inv, const float *expert_prob, int T, int d, int dtype, int residual,
                   const void *out);
 // ffn.hip: moe_expert_ffn and moe_combine of a top-1 layer with the output made by the second product, and whether it takes a layer
-bool ffn_makes_output(int T, int max_slots, int E, int d, int F, int dtype, int schedule);
+bool ffn_makes_output(const moe_layer_args *a, int max_slots);
 int ffn_layer(const moe_layer_args *a, int max_slots, void *stream);
 }  // namespace moe

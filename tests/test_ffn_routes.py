@@ -71,3 +71,44 @@ def test_lds_shapes(rules):
     from test_gpu_ffn_lds_tile import SHAPES
     for d, F, E, rows, *_ in SHAPES:
         assert rules(sum(rows) + 3, len(rows), E, d, F)[0] == "lds", (d, F, rows)
+
+
+APART = """
+#include "ffn_rules.h"
+#include <stdio.h>
+int main()
+{
+    // a layer whose buffers stand one after another, and an output at a byte of that row
+    int T, d, F, E, budget, f32, which;
+    long long shift;
+    while (scanf("%d %d %d %d %d %d %d %lld", &T, &d, &F, &E, &budget, &f32, &which, &shift) == 8) {
+        const size_t esz = f32 ? 4 : 2, slots = E + budget, ws = (size_t)T * F * esz + 4096;
+        const size_t bytes[] = {ws, (size_t)E * F * d * esz, (size_t)T * 4, (slots + 1) * 4, slots * 4, 4, (size_t)T * 4, (size_t)E * F * d * esz};
+        char *at[8], *next = (char *)(1ull << 40);
+        for (int i = 0; i < 8; ++i) {
+            at[i] = next;
+            next += bytes[i] + 2 * (size_t)T * d * esz;
+        }
+        moe_layer_args a = {};
+        a.T = T, a.d = d, a.F = F, a.E = E, a.budget = budget, a.dtype = f32 ? MOE_F32 : MOE_BF16;
+        a.ffn_ws = at[0], a.w2 = at[1], a.perm = (int32_t *)at[2], a.slot_offset = (int32_t *)at[3], a.slot_expert = (int32_t *)at[4];
+        a.n_slots = (int32_t *)at[5], a.replicas = (int32_t *)at[6], a.w1 = at[7];
+        // shift < 0: that many bytes of the output in front of the buffer; >= 0: the output begins there, from its end if beyond 1 << 40
+        a.out = at[which] + (shift >= 1ll << 40 ? (long long)bytes[which] + (shift - (1ll << 41)) : shift);
+        a.ffn_ws_bytes = 1ull << 60;
+        printf("%d\\n", moe::ffn_output_apart(&a, (int)slots, ws));
+    }
+}
+"""
+
+
+@pytest.mark.parametrize("T,d,F,E,budget,f32", [(64, 64, 256, 8, 2, 1), (1500, 128, 128, 64, 0, 0), (1, 128, 64, 1, 0, 1)])
+def test_an_output_in_the_second_product_s_operands(tmp_path_factory, T, d, F, E, budget, f32):
+    """Workspace, second weights, the permutation and the slot tables: an output that meets one of them by a byte is not made by the product."""
+    ask = _compiled(tmp_path_factory, "apart", APART)
+    end, out = 1 << 41, T * d * (4 if f32 else 2)
+    for which in range(8):
+        read = which < 6                                 # the others are free: replica counts, first weights
+        at = [0, -out + 1, -1, end - 1, -out, end]
+        got = [v for v, in ask([[T, d, F, E, budget, f32, which, a] for a in at])]
+        assert got == [int(not read)] * 4 + [1, 1], (which, got)

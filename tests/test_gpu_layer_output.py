@@ -71,3 +71,25 @@ def test_refused_output_is_an_error_behind_the_products():
     with pytest.raises(moe.MoeError, match="moe_combine: out aliases"):
         layer.forward(x, wr, b, w1, w2, out=x)
     assert torch.isfinite(layer.y_perm).all()
+
+
+@pytest.mark.parametrize("dt,T,d,F,E,R,C", [(torch.float32, 512, 64, 256, 8, 4, 80), (torch.float32, 1500, 256, 256, 4, 3, 260),
+                                            (torch.bfloat16, 200, 256, 384, 24, 3, 9), (torch.bfloat16, 1500, 128, 128, 64, 0, 20)])
+def test_output_in_what_the_products_read(dt, T, d, F, E, R, C):
+    """An output in the products' workspace or in the second weights, which a caller with no more use for them may name: as that of the calls."""
+    import paper_2605_11537_amd as moe
+    g = torch.Generator(device="cuda").manual_seed(T)
+
+    def rand(*shape, std=1.0):
+        return (torch.randn(*shape, generator=g, device="cuda") * std).to(dt)
+    x, wr, b = rand(T, d), rand(d, E, std=0.1), torch.zeros(E, device="cuda")
+    w1, w2 = rand(E, d, F, std=0.05), rand(E, F, d, std=0.05)
+    if dt == torch.bfloat16:
+        w1, w2 = moe.moe_pack_weights(w1), moe.moe_pack_weights(w2)
+    layer = moe.MoeLayer(T, d, F, E, R, C, dt)
+    want = layer.forward(x, wr, b, w1, w2, marks=[torch.cuda.Event() for _ in range(5)]).clone()
+    in_ws = layer.ffn_ws[: T * d * want.element_size()].view(dt).view(T, d)
+    assert torch.equal(layer.forward(x, wr, b, w1, w2, out=in_ws), want)
+    last = w2.clone()
+    if last.numel() >= T * d:
+        assert torch.equal(layer.forward(x, wr, b, w1, last, out=last.view(-1)[-T * d:].view(T, d)), want)
