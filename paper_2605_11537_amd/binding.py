@@ -59,10 +59,11 @@ class SruWeightsC(C.Structure):
 
 def lib():
     """Load the built library (build it first if it was never built); fail loudly otherwise -- also when
-    the binary on disk was compiled from other sources than the ones beside it (no silent rebuild)."""
+    a binary on disk was compiled from other sources than the ones beside it, or the extension for another torch or
+    Python (no silent rebuild)."""
     global _lib, _calls
     if _lib is None:
-        from .build import MARSHAL, build_library, source_id
+        from .build import MARSHAL, build_library, marshal_host, source_id
         if not (os.path.exists(LIB_PATH) and os.path.exists(MARSHAL)):
             build_library()
         loaded = C.CDLL(LIB_PATH)
@@ -78,6 +79,10 @@ def lib():
         calls = importlib.import_module("._marshal", __package__)
         if calls.build_id != built_from:
             raise RuntimeError(f"{MARSHAL} was built from sources {calls.build_id}, {LIB_PATH} from {built_from}: rebuild them "
+                               "(python -m paper_2605_11537_amd.build)")
+        built_for = getattr(calls, "built_for", "another")
+        if built_for != marshal_host():
+            raise RuntimeError(f"{MARSHAL} was built for {built_for}, this is {marshal_host()}: rebuild it "
                                "(python -m paper_2605_11537_amd.build)")
         for n in MARSHALLED:
             calls.bind(n, C.cast(getattr(loaded, n), C.c_void_p).value)

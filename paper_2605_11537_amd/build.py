@@ -36,6 +36,15 @@ def source_id() -> str:
     return h.hexdigest()[:16]
 
 
+def marshal_host() -> str:
+    """The torch and the Python whose objects the extension reads through their headers' layout.  build_library() compiles it into the
+    extension (built_for); binding.lib() refuses one that was built for others."""
+    import sys
+
+    import torch
+    return f"torch {torch.__version__} {torch.version.git_version}, python {sys.hexversion >> 24}.{sys.hexversion >> 16 & 255}"
+
+
 def build_library(verbose: bool = False) -> str:
     """One hipcc -c per source, side by side, then one link; beside them the Python extension."""
     import sysconfig
@@ -63,7 +72,7 @@ def build_library(verbose: bool = False) -> str:
     objs = [os.path.join(obj_dir, os.path.basename(p)[:-4] + ".o") for p in srcs]
     tdir = os.path.dirname(torch.__file__)
     marshal = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", f'-DMOE_BUILD_ID="{source_id()}"',
-               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(tdir, "include"),
+               f'-DMOE_BUILT_FOR="{marshal_host()}"', f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(tdir, "include"),
                "-I" + os.path.join(tdir, "include", "torch", "csrc", "api", "include"), "-I" + sysconfig.get_paths()["include"],
                os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-L" + os.path.join(tdir, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"]
     jobs = min(len(srcs) + 1, max(1, min(8, os.cpu_count() or 1)))

@@ -227,7 +227,7 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 PyMODINIT_FUNC PyInit__marshal(void)
 {
     PyObject *m = PyModule_Create(&module);
-    if (m && PyModule_AddStringConstant(m, "build_id", MOE_BUILD_ID) < 0) {
+    if (m && (PyModule_AddStringConstant(m, "build_id", MOE_BUILD_ID) < 0 || PyModule_AddStringConstant(m, "built_for", MOE_BUILT_FOR) < 0)) {
         Py_DECREF(m);
         return nullptr;
     }

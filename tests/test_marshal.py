@@ -1,5 +1,6 @@
 """What the extension takes and refuses for the arguments of the library's calls (no GPU: the calls stop at their own checks or have nothing to do)."""
 import ctypes
+import importlib
 
 import numpy as np
 import pytest
@@ -106,3 +107,27 @@ def test_every_call_is_bound():
     for n in binding.MARSHALLED:
         with pytest.raises(TypeError, match="arguments"):                # bound, and counted
             getattr(binding._c(), n)()
+
+
+@pytest.fixture
+def unloaded(monkeypatch):
+    """The binding as in a process that has not loaded the library."""
+    moe.lib()
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_calls", None)
+
+
+@pytest.mark.parametrize("other", ["torch", "python", "none"])
+def test_an_extension_of_another_torch_or_python_is_refused(unloaded, monkeypatch, other):
+    """It reads torch's objects by the layout that its headers gave them."""
+    if other == "torch":
+        monkeypatch.setattr(torch.version, "git_version", "0" * 40)
+    elif other == "python":
+        monkeypatch.setattr("sys.hexversion", 0x030900F0)
+    else:
+        monkeypatch.delattr(importlib.import_module("paper_2605_11537_amd._marshal"), "built_for", raising=False)
+    with pytest.raises(RuntimeError, match="rebuild"):
+        moe.lib()
+    assert binding._lib is None and binding._calls is None
+    monkeypatch.undo()
+    assert moe.lib() is not None
