@@ -493,28 +493,9 @@ static int expert_ffn_checked(const void *x_perm, int n_x_rows, const int32_t *r
     return MOE_OK;
 }
 
-// Where the second product of a layer makes the output: a launch less, and y is not read back; but the rows then leave scattered from
-// workgroups that still compute, which costs more than the launch where there are many.  Captured layers, us, with moe_combine and so.
-//   binary32: 64 -> 256, 32 experts, 100 rows 19.7, 17.6; 256 -> 1024, 8 experts, 16 rows 22.8, 20.5, 1500 rows 58.7, 53.0, 32 experts,
-//     4096 rows 75.9, 71.2; 512 -> 2048, 32 experts, 1500 rows 117, 114.  Past the lines: 64 -> 256, 8 experts, 4096 rows 29.8, 30.9; 64 -> 1024, 128
-//     experts, 16384 rows 82, 85; 512 -> 2048 is even from 3000 rows on (0.98 .. 1.02).
-//   bf16, 128-column kernel: 256 -> 1024, 64 experts, 200 rows 25.9, 24.4, 1000 rows 31.8, 30.3; 512 -> 2048, 32 experts, 200 rows 40.1, 38.2; on
-//     average 1.5 % up to 1000 rows over 64 .. 768 columns and more, none from 2000 on (768 -> 3072, 64 experts, 2048 rows 124.3, 125.7).
-//   The others lost or gained nothing: the 128-row tiles 256 -> 1024, 8 experts, 2000 rows 32.4, 33.6; the kernel for few rows has no registers
-//     left for it (37 rows, 128 experts 56.5, 57.4).
-// Nor in the experts schedule, whose few workgroups write one after another (64 -> 256, 32 experts, 2048 fp32 rows 98, 105).
-static bool output_pays(int T, int max_slots, int E, int d, int F, int dtype, int schedule)
-{
-    if (schedule != MOE_SCHEDULE_SLOTS || T <= 0 || max_slots <= 0 || E <= 0 || d <= 0 || F <= 0) return false;
-    if (dtype == MOE_F32) return T <= (d >= 128 && d <= 256 ? 6000 : 2048);
-    if (dtype != MOE_BF16 || T > 1500) return false;
-    const FfnRoute route = ffn_route(T, max_slots, E, d, F, schedule);
-    return route.kernel == FFN_COLUMNS && !route.few_rows[1];
-}
-
 bool moe::ffn_makes_output(const moe_layer_args *a, int max_slots)
 {
-    return output_pays(a->T, max_slots, a->E, a->d, a->F, a->dtype, a->schedule) &&
+    return ffn_output_pays(a->T, max_slots, a->E, a->d, a->F, a->dtype, a->schedule) &&
            ffn_output_apart(a, max_slots, moe_expert_ffn_workspace_bytes(a->T, max_slots, a->d, a->F, a->dtype));
 }
 

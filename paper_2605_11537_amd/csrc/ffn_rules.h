@@ -69,6 +69,25 @@ static inline FfnRoute ffn_route(int max_rows, int max_slots, int E, int d, int 
             {short_slots && ffn_few_rows(max_rows, max_slots, d, F), short_slots && ffn_few_rows(max_rows, max_slots, F, d)}};
 }
 
+// Where the second product of a layer makes the output: a launch less, and y is not read back; but the rows then leave scattered from
+// workgroups that still compute, which costs more than the launch where there are many.  Captured layers, us, with moe_combine and so.
+//   binary32: 64 -> 256, 32 experts, 100 rows 19.7, 17.6; 256 -> 1024, 8 experts, 16 rows 22.8, 20.5, 1500 rows 58.7, 53.0, 32 experts,
+//     4096 rows 75.9, 71.2; 512 -> 2048, 32 experts, 1500 rows 117, 114.  Past the lines: 64 -> 256, 8 experts, 4096 rows 29.8, 30.9; 64 -> 1024, 128
+//     experts, 16384 rows 82, 85; 512 -> 2048 is even from 3000 rows on (0.98 .. 1.02).
+//   bf16, 128-column kernel: 256 -> 1024, 64 experts, 200 rows 25.9, 24.4, 1000 rows 31.8, 30.3; 512 -> 2048, 32 experts, 200 rows 40.1, 38.2; on
+//     average 1.5 % up to 1000 rows over 64 .. 768 columns and more, none from 2000 on (768 -> 3072, 64 experts, 2048 rows 124.3, 125.7).
+//   The others lost or gained nothing: the 128-row tiles 256 -> 1024, 8 experts, 2000 rows 32.4, 33.6; the kernel for few rows has no registers
+//     left for it (37 rows, 128 experts 56.5, 57.4).
+// Nor in the experts schedule, whose few workgroups write one after another (64 -> 256, 32 experts, 2048 fp32 rows 98, 105).
+static inline bool ffn_output_pays(int T, int max_slots, int E, int d, int F, int dtype, int schedule)
+{
+    if (schedule != MOE_SCHEDULE_SLOTS || T <= 0 || max_slots <= 0 || E <= 0 || d <= 0 || F <= 0) return false;
+    if (dtype == MOE_F32) return T <= (d >= 128 && d <= 256 ? 6000 : 2048);
+    if (dtype != MOE_BF16 || T > 1500) return false;
+    const FfnRoute route = ffn_route(T, max_slots, E, d, F, schedule);
+    return route.kernel == FFN_COLUMNS && !route.few_rows[1];
+}
+
 // Whether the second product of a layer can write the output: it then reads its own operands while it writes, moe_combine does not read
 // them any more.  An output that lies in one of them (its caller has no more use for h, say) is made behind the product.  ws_bytes: of
 // the products' workspace, the part that they use.

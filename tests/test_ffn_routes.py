@@ -15,9 +15,10 @@ int main()
     while (scanf("%d %d %d %d %d %d", &r, &s, &E, &d, &F, &sched) == 6) {
         const moe::FfnRoute b = moe::ffn_route(r, s, E, d, F, sched);
         const int bm = moe::f32_rows(r, E);
-        printf("%d %d %d %d %d %d %d %d %d\\n", (int)b.kernel, b.list, b.few_rows[0], b.few_rows[1], bm,
+        printf("%d %d %d %d %d %d %d %d %d %d %d %d %d\\n", (int)b.kernel, b.list, b.few_rows[0], b.few_rows[1], bm,
                moe::f32_narrow(r, s, E, sched, d, F), moe::f32_narrow(r, s, E, sched, F, d),
-               moe::f32_staged(bm, r, s, E, sched, d, F), moe::f32_staged(bm, r, s, E, sched, F, d));
+               moe::f32_staged(bm, r, s, E, sched, d, F), moe::f32_staged(bm, r, s, E, sched, F, d), moe::f32_depth(F), moe::f32_several(F),
+               moe::ffn_output_pays(r, s, E, d, F, MOE_F32, sched), moe::ffn_output_pays(r, s, E, d, F, MOE_BF16, sched));
     }
 }
 """
@@ -28,9 +29,12 @@ def rules(tmp_path_factory):
     ask = _compiled(tmp_path_factory, "rules", RULES)
 
     def of(rows, slots, E, d, F, schedule=SLOTS):
-        (kernel, listed, few1, few2, bm, narrow1, narrow2, staged1, staged2), = ask([[rows, slots, E, d, F, schedule]])
+        (kernel, listed, few1, few2, bm, narrow1, narrow2, staged1, staged2, depth2, several2, out32, out16), = ask(
+            [[rows, slots, E, d, F, schedule]])
         bf16 = {0: "columns listed" if listed else "few rows" if few1 and few2 else "columns", 1: "dense", 2: "lds"}[kernel]
-        return bf16, dict(bm=bm, narrow=(narrow1, narrow2), staged=(staged1, staged2), few=(few1, few2))
+        second = ("32 columns" if narrow2 else "32 rows, short k" if depth2 == 1 else f"{bm} rows, staged" if staged2
+                  else f"{bm} rows, several units" if several2 else f"{bm} rows")
+        return bf16, dict(bm=bm, narrow=(narrow1, narrow2), staged=(staged1, staged2), few=(few1, few2), second=second, output=(out32, out16))
     return of
 
 
@@ -71,6 +75,21 @@ def test_lds_shapes(rules):
     from test_gpu_ffn_lds_tile import SHAPES
     for d, F, E, rows, *_ in SHAPES:
         assert rules(sum(rows) + 3, len(rows), E, d, F)[0] == "lds", (d, F, rows)
+
+
+def test_layer_output_cases(rules):
+    """The layers of the output tests: the second product's kernel, and whether it makes the output; every kernel that can is there."""
+    from test_gpu_layer_output import CASES
+    made = set()
+    for (name, T, d, F, E, R, _), kernel, makes in CASES:
+        bf16, more = rules(T, E + R, E, d, F)
+        takes = more["second"] if name == "f32" else "few rows" if more["few"][1] else bf16
+        assert takes == kernel and more["output"][name == "bf16"] == makes, (name, T, d, F, E, R, takes, more["output"])
+        assert rules(T, E + R, E, d, F, EXPERTS)[1]["output"] == (0, 0)
+        if makes:
+            made.add((name, kernel))
+    assert made == {("f32", k) for k in ("32 columns", "32 rows, short k", "32 rows, staged", "64 rows, staged", "32 rows, several units",
+                                         "64 rows, several units", "32 rows", "64 rows")} | {("bf16", "columns"), ("bf16", "columns listed")}
 
 
 APART = """

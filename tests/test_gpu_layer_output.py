@@ -5,32 +5,36 @@ import torch
 
 pytestmark = pytest.mark.gpu
 
-# dtype, T, d, F, E, R, capacity
+# dtype, T, d, F, E, R, capacity; the second product's kernel; whether it makes the output (a host test asks the library's rules for both)
 CASES = [
-    ("f32", 512, 64, 256, 8, 4, 80),            # one step of k in flight, several units per workgroup, 32 columns
-    ("f32", 1, 64, 64, 4, 0, 1),
-    ("f32", 33, 256, 256, 8, 2, 3),             # 32 rows, several units
-    ("f32", 700, 256, 192, 5, 3, 90),
-    ("f32", 1500, 256, 256, 4, 3, 260),         # 64 rows, several units
-    ("f32", 1500, 512, 512, 32, 8, 59),         # 32 rows, tokens through LDS
-    ("f32", 1500, 512, 512, 4, 2, 300),         # 64 rows, tokens through LDS
-    ("f32", 700, 128, 320, 16, 4, 40),          # 32 and 64 rows straight from memory
-    ("f32", 900, 128, 320, 2, 4, 100),
-    ("f32", 2048, 64, 256, 16, 0, 60),          # the longest batches that it takes, most tokens without a row
-    ("f32", 6000, 128, 256, 16, 2, 100),
-    ("f32", 6001, 128, 256, 16, 2, 100),        # and layers whose output moe_combine makes
-    ("f32", 2049, 64, 256, 16, 0, 60),
-    ("bf16", 37, 256, 1024, 64, 8, 4),          # the kernel for few rows
-    ("bf16", 1, 128, 256, 1, 0, 1),             # the 128-column kernel: a row,
-    ("bf16", 200, 256, 384, 24, 3, 9),          # tiles of 32 rows,
-    ("bf16", 900, 128, 128, 16, 2, 56),         # of 64
-    ("bf16", 500, 256, 256, 9, 6, 200),         # and 128 rows, slots of several tiles
-    ("bf16", 1500, 128, 128, 64, 0, 20),        # the longest batch that it takes, most tokens without a row
-    ("bf16", 1501, 128, 128, 64, 0, 20),
+    (("f32", 512, 64, 256, 8, 4, 80), "32 columns", True),
+    (("f32", 33, 256, 256, 8, 2, 3), "32 columns", True),
+    (("f32", 1, 64, 64, 4, 0, 1), "32 rows, short k", True),
+    (("f32", 700, 256, 192, 5, 3, 90), "32 rows, short k", True),
+    (("f32", 1500, 256, 256, 32, 8, 59), "32 rows, several units", True),
+    (("f32", 1500, 256, 256, 4, 3, 260), "64 rows, several units", True),
+    (("f32", 1500, 512, 512, 32, 8, 59), "32 rows, staged", True),
+    (("f32", 1500, 512, 512, 4, 2, 300), "64 rows, staged", True),
+    (("f32", 700, 128, 320, 16, 4, 40), "32 rows", True),
+    (("f32", 900, 128, 320, 2, 4, 100), "64 rows", True),
+    (("f32", 2048, 64, 256, 16, 0, 60), "64 rows, several units", True),            # the longest batches, most tokens without a row
+    (("f32", 6000, 128, 256, 16, 2, 100), "64 rows, several units", True),
+    (("f32", 6001, 128, 256, 16, 2, 100), "64 rows, several units", False),         # and layers whose output moe_combine makes
+    (("f32", 2049, 64, 256, 16, 0, 60), "64 rows, several units", False),
+    (("bf16", 37, 256, 1024, 64, 8, 4), "few rows", False),
+    (("bf16", 1, 128, 256, 1, 0, 1), "columns", True),                              # a row,
+    (("bf16", 200, 256, 384, 24, 3, 9), "columns", True),                           # tiles of 32 rows,
+    (("bf16", 900, 128, 128, 16, 2, 56), "columns", True),                          # of 64
+    (("bf16", 500, 256, 256, 9, 6, 200), "columns", True),                          # and 128 rows, slots of several tiles
+    (("bf16", 1200, 1024, 4096, 16, 2, 90), "columns listed", True),                # weight streams with a work list
+    (("bf16", 1500, 1024, 4096, 16, 0, 200), "columns listed", True),
+    (("bf16", 1500, 128, 128, 64, 0, 20), "columns", True),                         # the longest batch, most tokens without a row
+    (("bf16", 1501, 128, 128, 64, 0, 20), "columns", False),
+    (("bf16", 700, 256, 512, 8, 0, 90), "lds", False),
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(str(v) for v in c))
+@pytest.mark.parametrize("case", [c for c, _, _ in CASES], ids=lambda c: "-".join(str(v) for v in c))
 def test_same_bits_as_the_calls(case):
     import paper_2605_11537_amd as moe
     name, T, d, F, E, R, C = case

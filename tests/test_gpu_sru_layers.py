@@ -29,7 +29,10 @@ pytestmark = pytest.mark.gpu
     (2, 777, 768, 256, 3),        # embeddings packed first, their image overwritten by the second layer
     (1, 1024, 832, 256, 1),       # the same without room for the weights in LDS, one layer
     (2, 200, 128, 384, 2),        # fragments with weights too wide for LDS, one row block per wavefront
-    (1, 400, 128, 384, 2),        # and two
+    (1, 400, 128, 384, 2),        # fragments of more than 256 channels whose weights fit, two row blocks
+    (1, 400, 128, 896, 2),        # and whose weights do not
+    (1, 288, 128, 896, 2),        # the same with wavefronts that have one row block and one that has two
+    (2, 288, 128, 768, 2),        # the widest whose weights fit, likewise
     (1, 1024, 128, 384, 3),       # the longest; later layers too wide for their weights in LDS
     (1, 1025, 128, 128, 2),       # the two-kernel form
     (1, 600, 1024, 256, 2),       # the two-kernel form in front of one kernel: its states as fragments, the last layer's row-major
