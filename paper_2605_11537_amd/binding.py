@@ -120,7 +120,7 @@ def lib():
         _lib.moe_measure_mfma_bf16.argtypes = [I, I, P, P]
         _lib.moe_plan_dispatch_workspace_bytes.argtypes = [I, I, I, I]
         _lib.moe_plan_dispatch.argtypes = [P, I, P, I, I, I, I, I, I] + [P] * 12 + [P, S, P]
-        _lib.moe_layer_forward.argtypes = [C.c_char_p, P]
+        _lib.moe_layer_forward.argtypes = [P, P]
     return _lib
 
 

@@ -4,16 +4,16 @@
 // 128 rows of one expert x 64 * NB columns per workgroup (128 or 256), two workgroups per CU.  Both operands go global -> LDS directly
 // into a ring of 32-k stages, as in the 256 x 256 kernel; the four wavefronts are a 2 x 2 grid of 64 x 32 NB outputs.  The fragments of the
 // next 16-deep step are read while the current ones are multiplied, one barrier per stage.  The loads of a stage are spread over the matrix
-// instructions as there (all behind the barrier, both products, us: 768 x 3072, 16 experts x 627 rows 119, now 112, 8 x 1024 107, 99; 512 x 2048, 16 x
-// 480 57, 55; no change where tiles are few).  A workgroup finds
-// its tile in the slot tables (ffn_share.h), so there is no list kernel in front.
+// instructions as there (all behind the barrier and so, both products, us: 768 x 3072, 16 experts x 627 rows 118, 113, 8 x 1024 103, 95; 384 x 1536, 32
+// x 349 57, 54; no change where tiles are few).  A workgroup finds its tile in the slot tables (ffn_share.h), so there is
+// no list kernel in front.
 //
 // Bound: what a CU gets from beyond its L2, about 50 GB/s, as first readers of weights and of h (8 experts x 90 rows, k = 4096, 64
 // workgroups of 1.8 MB each: 36 us), and with two workgroups per CU the load path and LDS together.  More stages in flight (six of 24 KB, nine of 16 KB, one
 // workgroup per CU) and stages of 64 k left the times where they are or lost 10 .. 30 %.
-// Measured, both products with what is launched in front of them, us: 256 x 256 kernel (128-column kernel where that did not apply), now:
-//   512 x 2048, 16 experts x 480 rows: 68 -> 48    768 x 3072, 16 x 627: 137 -> 107    1024 x 4096, 8 x 393: 133 -> 74
-//   256 x 1024, 16 x 512: 43 -> 26                 384 x 1536, 32 x 349: 59 -> 53      1024 x 4096, 8 x 90: 57 -> 50
+// Measured, both products with what is launched in front of them, us: 256 x 256 kernel (128-column kernel where that does not apply), this one:
+//   512 x 2048, 16 experts x 480 rows: 69, 51      768 x 3072, 16 x 627: 132, 112      1024 x 4096, 8 x 393: 136, 78
+//   256 x 1024, 16 x 512: 41, 26                   384 x 1536, 32 x 349: 62, 54        1024 x 4096, 8 x 90: 57, 49
 #pragma once
 #include "ffn_share.h"
 #include "gemm_dense_bf16.h"

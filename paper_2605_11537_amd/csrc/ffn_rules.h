@@ -17,17 +17,19 @@ static inline bool ffn_use_dense(int max_rows, int max_slots, int K, int N, int 
 static inline bool ffn_weight_stream(int E, int d, int F) { return (long long)E * d * F >= (64LL << 20); }
 
 // Tiles of the product with fewer columns that can be expected (a slot has one at least): under five eighths of the CUs the others
-// leave less of the chip idle.  Both products, us, this kernel and the one taken instead: 16384 rows over 16 experts, 768 x 3072 (192 tiles) 198, 229;
-// 16384 over 8, 512 x 2048 (128) 95, 85; 10032 over 16, 768 x 3072 (117) 139, 113; 16384 over 8, 256 x 1024 (64) 47, 34; 8192 over 64, 512 x 2048
-// (128) 84, 78.  The line suits the rows that a plan keeps of max_rows; where it keeps all of them, or a few slots hold most, it lies a little high:
-// 12288 over 8, 768 x 3072 (144), at most 1920 per expert 119, 107, evenly 142, 153; 16384 over 32, 512 x 2048 (128), at most 641 84, 77, evenly 94,
-// 89, by Zipf's law 102, 113; 40000 over 159, 256 x 1024 (159) 68, 73, 87, 103, 106, 106.  At d = 1024 half of the CUs are enough: 8192 rows over 8, 1024 x 4096 (128), dealt by Zipf's law 160, 177, evenly 155, 141.
+// leave less of the chip idle.  Both products, us, this kernel and the 128-row LDS tiles, rows dealt evenly: 16384 rows over 16 experts, 768 x
+// 3072 (192 tiles) 184, 191; 16384 over 8, 512 x 2048 (128) 96, 89; 10032 over 16, 768 x 3072 (117) 132, 112; 16384 over 8, 256 x 1024 (64) 46, 34;
+// 8192 over 64, 512 x 2048 (128) 85, 80.  The line suits the rows that a plan keeps of max_rows; where it keeps all of them, or a few slots hold
+// most, it lies a little high: 12288 over 8, 768 x 3072 (144), 9800 kept of a deal by Zipf's law 131, 112, all of it 141, 151, evenly 141, 148; 16384
+// over 32, 512 x 2048 (128) 10600 kept 82, 77, all 101, 108, evenly 94, 89; and in narrow products by more: 40000 over 159, 256 x 1024 (159) 24000 kept
+// 66, 77, all 91, 106, evenly 87, 102.  At d = 1024 half of the CUs are enough: 8192 rows over 8, 1024 x 4096 (128), by Zipf's law 170, 183, evenly
+// 156, 148.
 // Nor is it taken where the weight stream binds (ffn_weight_stream) and a slot is a tile of the 128-column kernel: that one keeps more weights in
-// flight.  Both products, us, this kernel and that: 768 x 3072, 128 experts, 12288 rows of which a plan keeps 7834 299, 262; 64 experts,
-// 8192 rows, 4705 kept 166, 141; 256 experts, 30000 rows, 14826 kept 546, 519; 512 x 2048, 256 experts, 20000 rows, 12567 kept 262, 227; 1024 x 4096,
-// 32 experts, 4096 rows, 2548 kept 163, 141.  At d = 1024 with a tile for every CU they are even (64 experts, 8192 rows: 246, 238 and 245, 267),
-// with more than 128 rows per slot a second tile reads the weights again (64 x 140 rows: 170, 210; 32 experts, 8192 rows, 768 x 3072, from 96 tiles
-// on: 149, 158 on the LDS tiles).
+// flight.  Both products, us, this kernel and that, rows kept of a deal by Zipf's law: 768 x 3072, 128 experts, 7834 of 12288 rows 323, 259; 64
+// experts, 4705 of 8192 164, 137; 256 experts, 14826 of 30000 542, 521; 512 x 2048, 256 experts, 12567 of 20000 253, 218; 1024 x 4096, 32 experts,
+// 2548 of 4096 158, 140.  At d = 1024 with a tile for every CU they are about even (64 experts, 8192 rows evenly 243, 252, 5000 of them kept 251,
+// 233), with more than 128 rows per slot a second tile reads the weights again (64 x 140 rows: 170, 212).  From 96 tiles on this kernel is taken
+// where the weights stream: 32 experts, 8192 rows, 768 x 3072 141, LDS tiles 138 -- and 126 in the 128-column kernel, for slots of two full tiles.
 static inline bool ffn_dense_fills(int max_rows, int max_slots, int E, int d, int F)
 {
     const long long ranges = max_rows / DENSE_BM > max_slots ? max_rows / DENSE_BM : max_slots;
@@ -39,8 +41,8 @@ static inline bool ffn_dense_fills(int max_rows, int max_slots, int E, int d, in
 }
 
 // Where the 128-row LDS tiles take the products (of batches whose slots are not all short): the slot schedule, and no weight stream that binds
-// (128 MB per product under 128 rows per slot belong to the 128-column kernel: 64 experts x 128 rows, 768 x 3072, 160 us against 175;
-// 512 x 2048, 64 x 128, 78 both, 32 x 128 47 against 43).
+// (128 MB per product under 128 rows per slot belong to the 128-column kernel: 64 experts, 4705 of 8192 rows kept, 768 x 3072 137 us against 182,
+// 128 rows each 162, 164; 512 x 2048, which these take below 64 experts, 64 x 128 79, 80, 32 x 128 50, 40).
 static inline bool ffn_mid(int max_rows, int max_slots, int E, int d, int F, int schedule)
 {
     return schedule == MOE_SCHEDULE_SLOTS && (!ffn_weight_stream(E, d, F) || (long long)max_rows > 128LL * max_slots);
@@ -75,7 +77,10 @@ static inline FfnRoute ffn_route(int max_rows, int max_slots, int E, int d, int 
 //     4096 rows 75.9, 71.2; 512 -> 2048, 32 experts, 1500 rows 117, 114.  Past the lines: 64 -> 256, 8 experts, 4096 rows 29.8, 30.9; 64 -> 1024, 128
 //     experts, 16384 rows 82, 85; 512 -> 2048 is even from 3000 rows on (0.98 .. 1.02).
 //   bf16, 128-column kernel: 256 -> 1024, 64 experts, 200 rows 25.9, 24.4, 1000 rows 31.8, 30.3; 512 -> 2048, 32 experts, 200 rows 40.1, 38.2; on
-//     average 1.5 % up to 1000 rows over 64 .. 768 columns and more, none from 2000 on (768 -> 3072, 64 experts, 2048 rows 124.3, 125.7).
+//     average 1.5 % up to 1000 rows over 64 .. 768 columns and more, none from 2000 on (768 -> 3072, 64 experts, 2048 rows 124.3, 125.7).  Between
+//     them 2.3 % on average over 64 layers of 800 .. 1500 rows, at worst 0.9 % lost (128 -> 256, 24 experts, 1489 rows 26.6, 26.8); 1500 rows: 256 ->
+//     1024, 64 experts 36.8, 35.5, 512 -> 2048, 32 experts 51.8, 49.9.  With a work list: 1024 -> 4096, 16 experts, 1024 rows 83.8, 79.6, 1500 rows
+//     95.4, 92.8; 2048 -> 8192, 8 experts, 1500 rows 236.2, 237.1.
 //   The others lost or gained nothing: the 128-row tiles 256 -> 1024, 8 experts, 2000 rows 32.4, 33.6; the kernel for few rows has no registers
 //     left for it (37 rows, 128 experts 56.5, 57.4).
 // Nor in the experts schedule, whose few workgroups write one after another (64 -> 256, 32 experts, 2048 fp32 rows 98, 105).

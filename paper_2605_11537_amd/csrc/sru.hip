@@ -202,8 +202,8 @@ __global__ __launch_bounds__(SRU_CHUNKS * SRU_CHANNELS) void sru_scan_kernel(
 // has, and only the wavefronts that have rows load any: with one per CU, four steps and all eight wavefronts loading, 64 sequences of
 // 7, 256 -> 256, took 45.7 us with the head where the kernel before took 38.6, now 18; 16 x 16: 15.5, 13.8, now 9.1; 1 x 1: 10.2, 9.2,
 // now 7.6.
-// Measured per layer at 8 x 512, 256 -> 256, in a predictor of ten: 12.4 -> 9.0 us (8.0 .. 8.3 at best); 5 x 777, 768 -> 256 and 256 -> 256, both layers: 46 us in two
-// launches against 53 us in four (projection and scan kernels).
+// Measured per layer at 8 x 512, 256 -> 256, in a predictor of ten: 12.4 -> 9.0 us (8.0 .. 8.3 at best); 5 x 777, 768 -> 256 and 256 -> 256, both layers, packing and
+// head: 42 us against 56 us with projection and scan kernels.
 constexpr int FUS_THREADS = 512;       // 8 wavefronts: 2 per SIMD, so one's loads fly under the other's work
 constexpr int FUS_WAVES = FUS_THREADS / 64;
 constexpr int FUS_CHUNKS = FUS_THREADS / FUS_CH;   // 64 time chunks per sequence
@@ -671,7 +671,9 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
         packed_in_h = two && pout;
         if (!two) {
             // weights through LDS where they fit beside what else is there (K / 16 fragments of 1 KB; the row-major kernel of short
-            // sequences keeps its LDS small, two to four of its workgroups share a CU)
+            // sequences keeps its LDS small, two to four of its workgroups share a CU).  For fragments of 257 .. 768 channels at 257 .. 512 positions that
+            // is 10 % of a predictor on average over 40 of them (2 .. 4 layers, 384 .. 768 channels), us with every wavefront loading them and so:
+            // 2 x 401, 384 channels, two layers 21.1, 20.2; 29 x 408, 640 channels, four 425, 367; 2 x 512, 768 channels, four 62.1, 55.1.
 #define MOE_FUS(N)                                                                                                     \
     (pin ? (nin <= 256            ? sru_layer_fused_kernel<N, true, 2>                                                 \
             : N > 1 && nin <= 768 ? sru_layer_fused_kernel<N, true, (N > 1 ? 6 : 2)>                                   \

@@ -13,8 +13,8 @@ static inline size_t fus_image_bytes(int B, int L, int n) { return (size_t)B * a
 // The longest sequences of wide embeddings have them packed once, where the row-major kernel turns them into fragments in each
 // of the n_hidden / 8 workgroups of a sequence.  The image lies where the second layer's states go afterwards, behind the first's,
 // if the room for the projections holds it.  Measured where the one-kernel form is taken, two layers and the head without and
-// with it: 16 x 1024, 768 -> 256: 109 and 91 us, 512 -> 256: 86 and 80; 8 x 1024, 768 -> 256: 59 and 53; at up to 512
-// positions 2 .. 7 us more with it.
+// with it: 16 x 1024, 768 -> 256: 112 and 95 us, 512 -> 256: 87 and 80; 8 x 1024, 768 -> 256: 57 and 50; 5 x 777: 44 and 42; at up to 512
+// positions 1 .. 3 us more with it.
 static inline bool fus_packs_input(int B, int L, int K, int n_h)
 {
     return L > 512 && L <= FUS_MAX_L && K >= 512 &&
@@ -24,11 +24,13 @@ static inline bool fus_packs_input(int B, int L, int K, int n_h)
 // Projection and scan in two kernels, or the layer in one?  One kernel up to 512 positions, two above 1024.  Between them one
 // workgroup fills a CU and reads all rows of its sequence, so its time grows with K, in steps of 256 workgroups (rounds, of which
 // share is filled), while the two kernels deal the work out evenly but send the projections through memory (dearer from 10 million
-// on, 40 MB).  The estimates (microseconds; K and L in thousands, x in millions of projections) are fitted to 300 layers of 1 .. 200
-// sequences of 513 .. 1024 positions, 64 .. 2048 -> 128 .. 1024 channels, with mean errors of at most 12 and 8 %; taking the form they
-// choose costs 0.3 % on average against always knowing.  Two against one kernel: 1 x 1024, 1024 -> 256: 25 and 35 us;
-// 5 x 777, 1024 -> 1024: 68 and 94; 64 x 600, 1024 -> 1024: 640 and 972; 8 x 1024, 256 -> 256: 29 and 15; 16 x 1024, 768 -> 256:
-// 73 and 60; 64 x 1024, 384 -> 384: 303 and 269.
+// on, 40 MB).  The estimates (microseconds; K and L in thousands, x in millions of projections) were fitted to 300 layers of 1 .. 200
+// sequences of 513 .. 1024 positions, 64 .. 2048 -> 128 .. 1024 channels, with a one-kernel form in which every wavefront had the same number of row
+// blocks and every chunk 16 steps; the present one is faster where a sequence does not fill them.  So the estimate for one kernel is too high
+// there: taking the form they choose costs 3.1 % on average against always knowing (150 predictors of one to three such layers, 86 single ones
+// 3.0 %; 0.3 % with the kernel that was fitted), up to 46 % (170 x 630, 384 -> 768: two kernels 1216 us, one 831), where two are taken
+// and one would do.  One layer and the head, two against one kernel: 1 x 1024, 1024 -> 256: 28 and 40 us; 5 x 777, 1024 -> 1024: 76 and 90; 64 x 600, 1024 ->
+// 1024: 634 and 694; 8 x 1024, 256 -> 256: 34 and 24; 16 x 1024, 768 -> 256: 79 and 63; 64 x 1024, 384 -> 384: 302 and 267.
 // from_fragments: the one-kernel form would read its states as the layer before leaves them.  hands_on: the next layer is one kernel; the
 // scan's states reach it 0.5 us (1 x 1024, 128 channels) to 3.5 us (5 x 777, 256 channels) later than those of a kernel of its own kind.
 static inline bool sru_two_kernels(int B, int L, int K, int n_h, bool from_fragments, bool hands_on)
