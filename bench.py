@@ -33,16 +33,16 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # sru*_cfg3*.md).  Counters cannot be read inside a normal run, so the values are carried here and are
 # refreshed, with those files, whenever these kernels change (roofline.traffic_source says so in the line).
 PMC_TRAFFIC_BYTES = {
-    "cfg1": {"ffn_gemm1": 1.22e6 + 0.52e6, "ffn_gemm2": 1.71e6 + 0.13e6},
-    "cfg2": {"ffn_gemm1": 628.01e6 + 15.12e6, "ffn_gemm2": 625.79e6 + 3.78e6},
-    "cfg2k3": {"ffn_gemm1": 663.06e6 + 52.2e6, "ffn_gemm2": 689.57e6 + 13.05e6},
-    "cfg3": {"ffn_gemm1": 641.14e6 + 24.1e6, "ffn_gemm2": 645.08e6 + 6.02e6},
-    "cfg3x": {"ffn_gemm1": 635.91e6 + 23.25e6, "ffn_gemm2": 649.71e6 + 5.81e6},
-    "cfg4": {"ffn_gemm1": 1248.76e6 + 40.63e6, "ffn_gemm2": 1237.74e6 + 10.16e6},
-    "cfg4b": {"ffn_gemm1": 1262.3e6 + 63.36e6, "ffn_gemm2": 1278.79e6 + 15.84e6},
+    "cfg1": {"ffn_gemm1": 1.23e6 + 0.52e6, "ffn_gemm2": 1.71e6 + 0.13e6},
+    "cfg2": {"ffn_gemm1": 628.16e6 + 15.12e6, "ffn_gemm2": 625.75e6 + 3.78e6},
+    "cfg2k3": {"ffn_gemm1": 662.95e6 + 52.2e6, "ffn_gemm2": 689.53e6 + 13.05e6},
+    "cfg3": {"ffn_gemm1": 641.54e6 + 24.1e6, "ffn_gemm2": 645.79e6 + 6.02e6},
+    "cfg3x": {"ffn_gemm1": 635.65e6 + 23.25e6, "ffn_gemm2": 649.33e6 + 5.81e6},
+    "cfg4": {"ffn_gemm1": 1247.71e6 + 40.63e6, "ffn_gemm2": 1242.38e6 + 10.16e6},
+    "cfg4b": {"ffn_gemm1": 1263.58e6 + 63.36e6, "ffn_gemm2": 1275.95e6 + 15.84e6},
     # cfg5: every row goes through the 256 x 256 tile kernel; cfg5stack runs six such layers per step
-    "cfg5": {"ffn_gemm1": 2083.19e6 + 402.65e6, "ffn_gemm2": 2236.49e6 + 100.66e6},
-    "cfg5stack": {"ffn_gemm1": 2083.19e6 + 402.65e6, "ffn_gemm2": 2236.49e6 + 100.66e6},
+    "cfg5": {"ffn_gemm1": 2066.04e6 + 402.65e6, "ffn_gemm2": 2215.1e6 + 100.66e6},
+    "cfg5stack": {"ffn_gemm1": 2066.04e6 + 402.65e6, "ffn_gemm2": 2215.1e6 + 100.66e6},
 }
 
 
