@@ -297,7 +297,8 @@ int moe_combine(const void *y_perm, const void *x, const int32_t *inv, const flo
  * moe_layer_forward -- moe_route, moe_plan_dispatch, moe_expert_ffn (rows gathered through perm) and
  * moe_combine in turn on one stream; with top_k >= 1 moe_route_topk, moe_plan_dispatch, moe_expert_ffn_rows and
  * moe_combine_topk.  Every field is the argument of that name of those calls; router_E is the router's E,
- * max_slots is E + budget, plan_idx = NULL plans from the routed ids.  Each step checks its arguments before it
+ * max_slots is E + budget, plan_idx = NULL plans from the routed ids.  In small top-1 layers the second product writes out
+ * beside y_perm instead of moe_combine, with the same results.  Each step checks its arguments before it
  * enqueues anything; on error the steps before the failing one have been enqueued.
  */
 typedef struct moe_layer_args {
