@@ -235,7 +235,7 @@ __global__ __launch_bounds__(FUS_THREADS, NRB == 1 ? 4 : 1) void sru_layer_fused
                                                                          const bf16_t *__restrict__ Wp, int L, int K,
                                                                          int n_h, int kgates,
                                                                          const float *__restrict__ b_f,
-                                                                         const float *__restrict__ b_r, int packed_out,
+                                                                         const float *__restrict__ b_r, int packed_out, int xcd_bits, int per_xcd,
                                                                          bf16_t *__restrict__ h_out,
                                                                          bf16_t *__restrict__ ht_out)
 {
@@ -251,11 +251,12 @@ __global__ __launch_bounds__(FUS_THREADS, NRB == 1 ? 4 : 1) void sru_layer_fused
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroup i runs on XCD i % 8.  All channel blocks of a sequence read the same token rows, written a moment ago by the layer before: 8
     // contiguous ranges of the (sequence, channel block) pairs, one per XCD, so that an XCD's L2 fetches about 1/8 of the rows instead of all
-    // of them, and mostly those it wrote (n_h / 8 is a multiple of 16, the ranges are equal).  With the channel blocks of a sequence dealt to all XCDs
+    // of them, and mostly those it wrote (n_h / 8 is a multiple of 16, the ranges are equal).  xcd_bits 0 (3 else, per_xcd: workgroups of a
+    // range): the channel blocks of a sequence go to all XCDs in turn, so that an L2 holds 1/8 of the weights instead (sru_deals_channels).  With the channel blocks of a sequence dealt to all XCDs
     // where the sequences are no multiple of 8, us: 12 x 512, 256 -> 256, four layers 76.0, now 67.8; 5 x 512, 768 -> 256, two 30.5, 28.9.
     int cb, b;
     {
-        const int ncb = n_h / FUS_CH, at = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+        const int ncb = n_h / FUS_CH, at = (blockIdx.x & ((1 << xcd_bits) - 1)) * per_xcd + (blockIdx.x >> xcd_bits);
         b = at / ncb;
         cb = at - b * ncb;
     }
@@ -639,6 +640,8 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
     const bool later_two = !w->attention && sru_two_kernels(B, L, n_h, n_h, true, false);
     const bool first_two = !(w->attention && w->n_layers == 1) &&
                            sru_two_kernels(B, L, nin, n_h, false, w->n_layers > 1 && !later_two);
+    const int xcd_bits = sru_deals_channels(B, L, nin, n_h, w->n_layers, first_two, later_two) ? 0 : 3;
+    const int per_xcd = n_h / FUS_CH * B >> xcd_bits;
     if (!first_two && fus_packs_input(B, L, nin, n_h)) {
         bf16_t *image = (bf16_t *)(base + lay.u + fus_image_bytes(B, L, n_h));
         const int units = ceil_div(L, 32) * (nin / 64) * B;
@@ -684,7 +687,7 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
             auto fused = L <= 256 ? MOE_FUS(1) : L <= 512 ? MOE_FUS(2) : MOE_FUS(4);
 #undef MOE_FUS
             hipLaunchKernelGGL(fused, dim3((n_h / FUS_CH) * B), dim3(FUS_THREADS), 0, st, cur, (const bf16_t *)wl, L, nin, n_h, k,
-                               w->b_f ? w->b_f[l] : nullptr, w->b_r ? w->b_r[l] : nullptr, pout ? 1 : 0, out,
+                               w->b_f ? w->b_f[l] : nullptr, w->b_r ? w->b_r[l] : nullptr, pout ? 1 : 0, xcd_bits, per_xcd, out,
                                last && pout ? (bf16_t *)(base + lay.ht) : nullptr);
             MOE_CHECK_LAUNCH("sru_predict/layer");
             cur = out;

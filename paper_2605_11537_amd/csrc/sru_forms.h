@@ -49,4 +49,29 @@ static inline bool sru_two_kernels(int B, int L, int K, int n_h, bool from_fragm
     return two < one;
 }
 
+// Which XCDs the workgroups of the one-kernel layers go to.  Whole sequences per XCD (ranges of them) have an L2 fetch 1/8 of the rows and all weights, channel
+// blocks dealt to the XCDs 1/8 of the weights and all rows; as long as the weights stay in an XCD's 4 MB L2 from one call to the next, they are no
+// matter.  So the channel blocks are dealt where an XCD's share of the predictor's weights does not fit (beside 3.8 MB of them there is
+// no room) and the weights it would fetch outweigh seven times the rows: those of a layer, once for every XCD that has a sequence, or, past
+// what stays through a layer (3.2 MB), for every sequence.  Captured, head included, us, ranges of sequences and dealt: 14 x 18, 768 -> 512, four
+// layers 43.7, 40.5; 9 x 23, 768 -> 256, ten 71.1, 68.2; 30 x 41, 768 -> 1024, four 196, 172; 38 x 255, 768 -> 1024, three 511, 481; 12 x 512,
+// 256 -> 256, four 67.8, 76.0.  Over 460 predictors whose sequences are no multiple of 8 the choice is at most 1.7 % slower than always dealt and 2.1 % faster on
+// average, 0.3 % off the better of the two.  Where something else has run in between (caches flushed) ranges are 2 .. 4 % ahead with either kind.
+// Multiples of 8 keep their sequences together at any size.
+static inline bool sru_deals_channels(int B, int L, int n_in, int n_h, int n_layers, bool first_two, bool later_two)
+{
+    if (B % 8 == 0) return false;
+    const double mb = 1 << 20, held = B < 8 ? B : 8;
+    double all = 0, fetched = 0, rows = 0;
+    auto layers = [&](int n, int K) {
+        const double weights = (double)K * (K == n_h ? 3 : 4) * n_h * 2 / mb;
+        all += n * weights;
+        fetched += n * weights * (weights > 3.2 ? B : held);
+        rows += n * ((double)B * L * K * 2 / mb);
+    };
+    if (!first_two) layers(1, n_in);
+    if (!later_two) layers(n_layers - 1, n_h);
+    return all * held / 8 > 3.8 && fetched > 7 * rows;
+}
+
 }  // namespace moe

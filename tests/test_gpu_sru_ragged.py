@@ -23,6 +23,9 @@ pytestmark = pytest.mark.gpu
     (6, 769, 128, 256, 2),        # one wavefront with four, fourteen steps
     (3, 896, 512, 256, 2),        # embeddings as an image, the last of fourteen steps
     (3, 897, 256, 128, 2),        # sixteen; the highway from row-major rows
+    (9, 23, 448, 256, 12),        # channel blocks dealt to the XCDs: many layers,
+    (5, 33, 384, 1024, 2),        # wide ones
+    (3, 300, 256, 1024, 3),       # and two row blocks
 ])
 def test_sru_ragged(B, L, n_in, n_h, layers):
     import paper_2605_11537_amd as moe
