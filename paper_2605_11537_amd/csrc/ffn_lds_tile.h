@@ -4,9 +4,9 @@
 // 128 rows of one expert x 64 * NB columns per workgroup (128 or 256), two workgroups per CU.  Both operands go global -> LDS directly
 // into a ring of 32-k stages, as in the 256 x 256 kernel; the four wavefronts are a 2 x 2 grid of 64 x 32 NB outputs.  The fragments of the
 // next 16-deep step are read while the current ones are multiplied, one barrier per stage.  The loads of a stage are spread over the matrix
-// instructions as there (all behind the barrier and so, both products, us: 768 x 3072, 16 experts x 627 rows 118, 113, 8 x 1024 103, 95; 384 x 1536, 32
-// x 349 57, 54; no change where tiles are few).  A workgroup finds its tile in the slot tables (ffn_share.h), so there is
-// no list kernel in front.
+// instructions as there, where a wavefront has two row blocks (all behind the barrier and so, both products, us: 768 x 3072, 16 experts x 627 rows
+// 118, 113, 8 x 1024 103, 95; 384 x 1536, 32 x 349 57, 54; no change where tiles are few).  A workgroup finds its tile in the slot tables
+// (ffn_share.h), so there is no list kernel in front.
 //
 // Bound: what a CU gets from beyond its L2, about 50 GB/s, as first readers of weights and of h (8 experts x 90 rows, k = 4096, 64
 // workgroups of 1.8 MB each: 36 us), and with two workgroups per CU the load path and LDS together.  More stages in flight (six of 24 KB, nine of 16 KB, one
@@ -107,9 +107,9 @@ __global__ __launch_bounds__(SHARE_THREADS, 2) void ffn_lds_tile_bf16_kernel(
         __builtin_amdgcn_global_load_lds((glb_void_t *)(b_src[i] + (size_t)k * (BK / 8) * 32),
                                          (lds_void_t *)(ring + buf * STAGE + (Tile::A_UNITS + w * BU + i) * 64), 16, 0, 0);
     };
-    // all but the newest `young` stages have landed, for everybody behind the barrier
-    auto landed = [&](auto YOUNG) {
-        constexpr int young = decltype(YOUNG)::value, late = young == NS - 1 ? BU : 0;   // the prologue leaves the last stage's weights to the loop
+    // all but the newest `young` stages have landed -- of them `late` loads are still to be asked for --, for everybody behind the barrier
+    auto landed = [&](auto YOUNG, auto LATE) {
+        constexpr int young = decltype(YOUNG)::value, late = decltype(LATE)::value;
         if (own_rows) MOE_VMCNT(young * (BU + AU) - late);
         else MOE_VMCNT(young * BU - late);
         __builtin_amdgcn_s_barrier();
@@ -118,6 +118,11 @@ __global__ __launch_bounds__(SHARE_THREADS, 2) void ffn_lds_tile_bf16_kernel(
     // one body per number of row blocks (2 * mb + wm) a wavefront owns
     auto run_tile = [&](auto BLOCKS) {
         constexpr int MYB = decltype(BLOCKS)::value;
+        // SPREAD: the loads of a stage between the matrix instructions, its weights half a stage after its tokens.  A wavefront with one row block or
+        // none has half the instructions to hide them behind and waits for them: all at once behind the barrier (both products, us, spread and so: 70 rows
+        // of which 56 are kept, 1024 x 4096 41.8, 38.0; 8 x 56, 1024 x 2048 29.8, 27.4; 6 x 44, 512 x 2048 26.0, 23.8).  Every wavefront waits for its
+        // own loads, so both kinds share the ring.
+        constexpr bool SPREAD = MYB > 1;
         f32x16_t acc[MYB ? MYB : 1][NB];
         zero_acc<MYB ? MYB : 1, NB>(acc);
         u32x4_t fx[2 + NB], fy[2 + NB];                          // fragments of two 16-deep steps: two row blocks, NB strips
@@ -144,7 +149,7 @@ __global__ __launch_bounds__(SHARE_THREADS, 2) void ffn_lds_tile_bf16_kernel(
             MOE_SB();
         };
         // (weights, tokens): the transposed block, a lane holds 4 consecutive columns of one token
-        // between(i) follows matrix instruction i
+        // between(i) follows matrix instruction i where the loads are spread
         auto multiply = [&](const u32x4_t (&f)[2 + NB], auto between) {
 #pragma unroll
             for (int mb = 0; mb < MYB; ++mb)
@@ -152,43 +157,46 @@ __global__ __launch_bounds__(SHARE_THREADS, 2) void ffn_lds_tile_bf16_kernel(
                 for (int nb = 0; nb < NB; ++nb) {
                     acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, f[2 + nb]),
                                                                           __builtin_bit_cast(bf16x8_t, f[mb]), acc[mb][nb], 0, 0, 0);
-                    between(mb * NB + nb);
-                    MOE_SB();
+                    if constexpr (SPREAD) {
+                        between(mb * NB + nb);
+                        MOE_SB();
+                    }
                 }
-            if (MYB == 0)
-                for (int i = 0; i < NB; ++i) between(i);
             MOE_SB();
         };
-        constexpr int EVERY = MYB > 1 ? 2 : 1;               // a load per EVERY matrix instructions
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
+        using std::integral_constant;
+        auto load_stage = [&](int kc, int buf, auto WEIGHTS) {
             if (own_rows) {
 #pragma unroll
-                for (int i = 0; i < AU; ++i) load_a(s, s, i);
+                for (int i = 0; i < AU; ++i) load_a(kc, buf, i);
             }
-            if (s + 1 < NS) {
+            if constexpr (decltype(WEIGHTS)::value) {
 #pragma unroll
-                for (int i = 0; i < BU; ++i) load_b(s, s, i);
+                for (int i = 0; i < BU; ++i) load_b(kc, buf, i);
             }
             MOE_SB();
-        }
-        landed(std::integral_constant<int, NS - 1>{});
+        };
+#pragma unroll
+        for (int s = 0; s + 1 < NS; ++s) load_stage(s, s, std::true_type{});
+        load_stage(NS - 1, NS - 1, integral_constant<bool, !SPREAD>{});
+        landed(integral_constant<int, NS - 1>{}, integral_constant<int, SPREAD ? BU : 0>{});
         int buf = 0, late_buf = NS - 1;
         read(fx, 0, 0);
         wait(fx);
         for (int kc = 0; kc < nk; ++kc) {
             read(fy, 1, buf);
-            multiply(fx, [&](int i) {                        // the weights of the stage whose tokens went out last
-                if (i % EVERY == 0 && i / EVERY < BU) load_b(kc + NS - 1, late_buf, i / EVERY);
+            multiply(fx, [&](int i) {                        // a load per two of them: the weights of the stage whose tokens went out last
+                if (i % 2 == 0 && i / 2 < BU) load_b(kc + NS - 1, late_buf, i / 2);
             });
             wait(fy);
             // behind the barrier stage kc + 1 is there and stage kc has been read by all
-            landed(std::integral_constant<int, NS - 2>{});
+            landed(integral_constant<int, NS - 2>{}, integral_constant<int, 0>{});
+            if constexpr (!SPREAD) load_stage(kc + NS, buf, std::true_type{});
             late_buf = buf;
             buf = buf + 1 == NS ? 0 : buf + 1;
             read(fx, 0, buf);
             multiply(fy, [&](int i) {
-                if (own_rows && i % EVERY == 0 && i / EVERY < AU) load_a(kc + NS, late_buf, i / EVERY);
+                if (own_rows && i % 2 == 0 && i / 2 < AU) load_a(kc + NS, late_buf, i / 2);
             });
             wait(fx);
         }
@@ -222,9 +230,10 @@ __global__ __launch_bounds__(SHARE_THREADS, 2) void ffn_lds_tile_bf16_kernel(
     };
     const int my_blocks = (blocks - wm + 1) >> 1;
     using std::integral_constant;
-    if (my_blocks == 2) run_tile(integral_constant<int, 2>{});
-    else if (my_blocks == 1) run_tile(integral_constant<int, 1>{});
-    else run_tile(integral_constant<int, 0>{});
+    // (the short bodies first: behind the long one their instructions arrive later, 1 .. 2 % of tiles of up to 64 rows)
+    if (my_blocks == 1) run_tile(integral_constant<int, 1>{});
+    else if (my_blocks == 0) run_tile(integral_constant<int, 0>{});
+    else run_tile(integral_constant<int, 2>{});
 }
 
 // Columns per workgroup in units of 64: 256 where those tiles fill the chip, else 128 (1024 x 4096, 8 experts x 90 rows: first product 20.9

@@ -39,6 +39,7 @@ SHAPES = [
     (256, 2048, 8, [190 + i for i in range(8)], None, False),
     (128, 128, 260, [70] * 260, None, False),                            # more slots than threads
     (256, 512, 64, [1030] + [49] * 62 + [28], None, True),               # 64 rows per slot on average, one long slot
+    (512, 4096, 24, [97, 33, 64, 1, 96, 128] * 4, None, True),           # wavefronts with no, one and two row blocks, side by side; 256 columns
 ]
 
 
