@@ -34,6 +34,15 @@ static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 constexpr int WAVE = 64;
 
+// A barrier that the wavefronts of a workgroup may reach at different places of the program, once each: s_barrier counts the wavefronts
+// that arrive, at whichever instruction.  __syncthreads has to be reached by the whole workgroup at one place.
+__device__ __forceinline__ void barrier_anywhere()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 // ---------------------------------------------------------------- bf16 <-> f32 on device
 typedef unsigned short bf16_t;  // raw bits
 

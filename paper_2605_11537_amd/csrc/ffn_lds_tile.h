@@ -201,7 +201,7 @@ __global__ __launch_bounds__(SHARE_THREADS, 2) void ffn_lds_tile_bf16_kernel(
             wait(fx);
         }
         MOE_VMCNT(0);                                            // the re-reads past the end
-        __syncthreads();                                         // everybody has read the last stage: the strips take its place
+        barrier_anywhere();                                      // everybody has read the last stage: the strips take its place
         bf16_t *strip = reinterpret_cast<bf16_t *>(ring) + w * (32 * LDE);
 #pragma unroll
         for (int mb = 0; mb < MYB; ++mb) {

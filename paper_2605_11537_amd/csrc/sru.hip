@@ -395,12 +395,9 @@ __global__ __launch_bounds__(FUS_THREADS, NRB == 1 ? 4 : 1) void sru_layer_fused
             if constexpr (WF > 0) {
 #pragma unroll
                 for (int i = 0; i < WF; ++i) w_lds[(w + FUS_WAVES * i) * 64 + lane] = wf[i];
-                // The wavefronts of a workgroup arrive here in different bodies, once each.  s_barrier counts the wavefronts that arrive, at
-                // whichever instruction, so the builtin it is and not __syncthreads, which a whole workgroup has to reach at one place.  (One barrier
-                // between two halves of the body keeps the rows in flight across a join: 178 registers for 148 at best, up to 85 spilled.)
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                __builtin_amdgcn_s_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                // (one __syncthreads between two halves of the body keeps the rows in flight across a join: 178 registers for 148 at best, up to 85
+                // spilled)
+                barrier_anywhere();
             }
             const int n_chunks = rows ? nkc : 0;
             int kc = 0;
