@@ -33,6 +33,10 @@ constexpr int FRONT_ROUNDS = FRONT_MAX_TOKENS / PLAN_THREADS;      // chunks per
 // 8.1, 2048 11.4 -> 9.6 (11.3 -> 10.0).  With a kernel for 8192 entries: 2000 7.3 -> 7.0, 3000 7.4 -> 7.5, 4096 7.4 -> 8.3, 8192 7.6 -> 11.
 // From the host, tables, row copy and combine of 300 rows: 15.4 -> 11.3.
 constexpr int DISPATCH_SMALL = 2048;
+// From here on the lanes that have their first lane's id find each other by a ballot: 64 lanes of one id take their turns at its word in LDS,
+// which made long batches of few ids slower here than in two launches.  Two launches, one workgroup without and with it, us: 2048 entries on one
+// expert 5.8, 6.4, 4.8; 80 % of them on one of 16 6.1, 6.2, 5.2; evenly over 64 6.3, 5.3, 5.4.  Up to here taking turns was never the slower way.
+constexpr int DISPATCH_TURNS = 1280;
 
 constexpr int FRONT_SEG = 8;                                       // chunks per segment of the two-level prefix
 constexpr int FRONT_SEGS = FRONT_CHUNKS / FRONT_SEG;               // 16
@@ -75,8 +79,8 @@ __device__ __forceinline__ void expert_scan2(int v0, int v1, int &ex0, int &ex1,
 // SAME: the plan is made from the routed ids themselves (no predictor): their histogram is gathered
 // along with the chunk counts, the plan ids are not read a second time.
 // PLAN_PER_LANE 0: no plan; the replica counts are given (moe_dispatch's: any numbers, or NULL for one each), and an expert's slots are written by
-// its whole wavefront.  ROUNDS: passes of the 1024 threads over the ids.
-template <int PLAN_PER_LANE, bool SAME, int ROUNDS>
+// its whole wavefront.  ROUNDS: passes of the 1024 threads over the ids.  FIRSTS: see DISPATCH_TURNS.
+template <int PLAN_PER_LANE, bool SAME, int ROUNDS, bool FIRSTS = false>
 __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
     const int32_t *__restrict__ plan_idx, int n_plan, const int32_t *__restrict__ idx, int T, int n_tokens, int E,
     int R, int C, int policy, int max_slots, const int32_t *__restrict__ given, int32_t *__restrict__ plan_counts,
@@ -114,6 +118,13 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
     for (int i = lane; i < E; i += WAVE) match[w][i] = 0ull;
     for (int i = tid; i < n_segs * FRONT_SEG * (FRONT_LD / 2); i += PLAN_THREADS)
         reinterpret_cast<unsigned int *>(&chunk_cnt[0][0])[i] = 0u;
+    bool as_first[ROUNDS];
+    unsigned long long firsts[ROUNDS];
+#pragma unroll
+    for (int rd = 0; rd < ROUNDS; ++rd) {
+        as_first[rd] = FIRSTS && my_e[rd] >= 0 && my_e[rd] < E && my_e[rd] == __builtin_amdgcn_readfirstlane(my_e[rd]);
+        firsts[rd] = FIRSTS ? __ballot(as_first[rd]) : 0ull;
+    }
     __syncthreads();
 
     // ---- A: lanes of a wavefront with equal ids find each other through a 64-bit lane mask per expert in
@@ -140,7 +151,9 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_dispatch_small_kernel(
         if (c < n_chunks) {
             const int e = my_e[rd];
             const bool valid = e >= 0 && e < E;
-            const unsigned long long mask = match_lanes(e, valid);
+            unsigned long long mask = 0ull;
+            if (FIRSTS && as_first[rd]) mask = firsts[rd];
+            else mask = match_lanes(e, valid);
             const int rank = __popcll(mask & ((1ull << lane) - 1ull));
             if (valid && rank == 0) {
                 chunk_cnt[c][e] = (unsigned short)__popcll(mask);
@@ -262,7 +275,9 @@ int dispatch_small_launch(const int32_t *expert_idx, const int32_t *replicas, in
                           int32_t *row_token, hipStream_t st, const char *who)
 {
     int32_t *const none = nullptr;
-    hipLaunchKernelGGL((plan_dispatch_small_kernel<0, true, DISPATCH_SMALL / PLAN_THREADS>), dim3(1), dim3(PLAN_THREADS), 0, st, (const int32_t *)none, 0, expert_idx, T,
+    auto kern = T > DISPATCH_TURNS ? plan_dispatch_small_kernel<0, true, DISPATCH_SMALL / PLAN_THREADS, true>
+                                   : plan_dispatch_small_kernel<0, true, DISPATCH_SMALL / PLAN_THREADS>;
+    hipLaunchKernelGGL(kern, dim3(1), dim3(PLAN_THREADS), 0, st, (const int32_t *)none, 0, expert_idx, T,
                        n_tokens > 0 ? n_tokens : 1, E, 0, slot_capacity, 0, max_slots, replicas, none, none, none, none, none, counts, kept,
                        expert_offset, slot_offset, perm, inv, row_token);
     MOE_CHECK_LAUNCH(who);

@@ -54,6 +54,19 @@ def test_tables(T, E):
             assert np.array_equal(out[k].cpu().numpy(), v), (k, T, E)
 
 
+@pytest.mark.parametrize("T", [1279, 1280, 1281, 1537, 2048])          # lanes of one id one after another, and by a ballot
+@pytest.mark.parametrize("E,share", [(1, 1.0), (2, 0.5), (3, 0.9), (16, 0.8), (64, 0.0), (256, 1.0)])
+def test_ids_that_lanes_share(T, E, share):
+    import paper_2605_11537_amd as moe
+    rng = np.random.default_rng(T + E)
+    ids = rng.integers(0, E, T).astype(np.int32)
+    ids[rng.random(T) < share] = E - 1
+    C = max(1, T // (2 * E))
+    d = moe.moe_dispatch(torch.randn(T, 8, device="cuda"), torch.from_numpy(ids).cuda(), None, E, C, E)
+    for name, v in _tables(ids, np.ones(E, np.int64), E, C, E).items():
+        assert np.array_equal(d[name].cpu().numpy(), v), name
+
+
 @pytest.mark.parametrize("T,k,E", [(682, 3, 64), (683, 3, 64), (100, 2, 256), (40, 8, 10)])     # 2046 and 2049 entries
 def test_topk_rows(T, k, E):
     import paper_2605_11537_amd as moe
