@@ -175,9 +175,10 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void ffn_gemm_bf16_kernel(
     constexpr int S0 = gemm_lds_elems<2, FFN_BK>(), S1 = gemm_lds_elems<4, FFN_BK_TALL>(), S2 = TM * LDC;
     __shared__ __attribute__((aligned(16))) bf16_t lds[(S0 > S1 ? S0 : S1) > S2 ? (S0 > S1 ? S0 : S1) : S2];
     const int n_nt = N / FFN_BN;
-    const bool gone = OUT && layer.dropped(blockIdx.x * (GEMM_THREADS / WAVE) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    LayerOut::Deal dropped;
+    if constexpr (OUT) dropped = layer.deal_dropped(N / 8);
     auto copy_dropped = [&]() {
-        if constexpr (OUT) layer.copy_dropped(gone, N / 8);
+        if constexpr (OUT) layer.copy_dropped(dropped, N / 8);
     };
     int item, nt;
     WorkItem it;

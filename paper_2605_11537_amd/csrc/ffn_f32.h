@@ -214,9 +214,10 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
     share.n_nt = N / BN;
     share.max_rows = max_rows;
     const int tid = threadIdx.x, w = tid >> 6, c = tid & 15;
-    const bool gone = OUT && layer.dropped(blockIdx.x * (F32_THREADS / WAVE) + __builtin_amdgcn_readfirstlane(w));
+    LayerOut::Deal dropped;
+    if constexpr (OUT) dropped = layer.deal_dropped(N / 4);
     share.find(slot_offset, slot_expert, n_slots_p, max_slots, &found);
-    if constexpr (OUT) layer.copy_dropped(gone, N / 4);
+    if constexpr (OUT) layer.copy_dropped(dropped, N / 4);
     for (int unit = share.first + (int)(blockIdx.x >> 3); unit < share.end; unit += (int)(gridDim.x >> 3)) {      // uniform
         share.write_item(slot_offset, slot_expert, unit, &found);
         __syncthreads();

@@ -21,6 +21,10 @@ CASES = [
     (("f32", 6000, 128, 256, 16, 2, 100), "64 rows, several units", True),
     (("f32", 6001, 128, 256, 16, 2, 100), "64 rows, several units", False),         # and layers whose output moe_combine makes
     (("f32", 2049, 64, 256, 16, 0, 60), "64 rows, several units", False),
+    (("f32", 1200, 192, 256, 24, 0, 1), "32 rows, several units", True),            # next to all tokens without a row: 48 pieces in a row,
+    (("f32", 900, 320, 320, 4, 0, 2), "64 rows", True),                             # 80,
+    (("f32", 2048, 64, 192, 32, 0, 1), "32 rows, short k", True),                   # 16
+    (("f32", 4096, 256, 256, 8, 0, 3), "64 rows, several units", True),             # 64, several units
     (("bf16", 37, 256, 1024, 64, 8, 4), "few rows", False),
     (("bf16", 1, 128, 256, 1, 0, 1), "columns", True),                              # a row,
     (("bf16", 200, 256, 384, 24, 3, 9), "columns", True),                           # tiles of 32 rows,
@@ -29,6 +33,8 @@ CASES = [
     (("bf16", 1200, 1024, 4096, 16, 2, 90), "columns listed", True),                # weight streams with a work list
     (("bf16", 1500, 1024, 4096, 16, 0, 200), "columns listed", True),
     (("bf16", 1500, 128, 128, 64, 0, 20), "columns", True),                         # the longest batch, most tokens without a row
+    (("bf16", 1100, 128, 256, 20, 0, 1), "columns", True),                          # next to all tokens without a row: 16 pieces in a row,
+    (("bf16", 1000, 768, 768, 24, 0, 2), "columns", True),                          # 96
     (("bf16", 1501, 128, 128, 64, 0, 20), "columns", False),
     (("bf16", 700, 256, 512, 8, 0, 90), "lds", False),
 ]
