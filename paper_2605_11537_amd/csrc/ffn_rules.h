@@ -76,6 +76,9 @@ static inline FfnRoute ffn_route(int max_rows, int max_slots, int E, int d, int 
 //   binary32: 64 -> 256, 32 experts, 100 rows 19.7, 17.6; 256 -> 1024, 8 experts, 16 rows 22.8, 20.5, 1500 rows 58.7, 53.0, 32 experts,
 //     4096 rows 75.9, 71.2; 512 -> 2048, 32 experts, 1500 rows 117, 114.  Past the lines: 64 -> 256, 8 experts, 4096 rows 29.8, 30.9; 64 -> 1024, 128
 //     experts, 16384 rows 82, 85; 512 -> 2048 is even from 3000 rows on (0.98 .. 1.02).
+//     Outputs of more than 4 MB lose where capacity drops most of the rows, which then are copied in front of the product (kept of rows: 1024 -> 4096, 16
+//     experts, 336 of 1400 127.9, 133.9, 30 experts, 60 of 1322 192.3, 197.1; 768 -> 1536, 83 experts, 562 of 1592 170.1, 175.3; 256 -> 512, 32 experts, 96 of
+//     6000 33.3, 33.7), and gain 1 % at most where it does not.
 //   bf16, 128-column kernel: 256 -> 1024, 64 experts, 200 rows 25.9, 24.4, 1000 rows 31.8, 30.3; 512 -> 2048, 32 experts, 200 rows 40.1, 38.2; on
 //     average 1.5 % up to 1000 rows over 64 .. 768 columns and more, none from 2000 on (768 -> 3072, 64 experts, 2048 rows 124.3, 125.7).  Between
 //     them 2.3 % on average over 64 layers of 800 .. 1500 rows, at worst 0.9 % lost (128 -> 256, 24 experts, 1489 rows 26.6, 26.8); 1500 rows: 256 ->
@@ -87,7 +90,7 @@ static inline FfnRoute ffn_route(int max_rows, int max_slots, int E, int d, int 
 static inline bool ffn_output_pays(int T, int max_slots, int E, int d, int F, int dtype, int schedule)
 {
     if (schedule != MOE_SCHEDULE_SLOTS || T <= 0 || max_slots <= 0 || E <= 0 || d <= 0 || F <= 0) return false;
-    if (dtype == MOE_F32) return T <= (d >= 128 && d <= 256 ? 6000 : 2048);
+    if (dtype == MOE_F32) return T <= (d >= 128 && d <= 256 ? 6000 : 2048) && (long long)T * d <= 1 << 20;
     if (dtype != MOE_BF16 || T > 1500) return false;
     const FfnRoute route = ffn_route(T, max_slots, E, d, F, schedule);
     return route.kernel == FFN_COLUMNS && !route.few_rows[1];

@@ -24,7 +24,8 @@ CASES = [
     (("f32", 1200, 192, 256, 24, 0, 1), "32 rows, several units", True),            # next to all tokens without a row: 48 pieces in a row,
     (("f32", 900, 320, 320, 4, 0, 2), "64 rows", True),                             # 80,
     (("f32", 2048, 64, 192, 32, 0, 1), "32 rows, short k", True),                   # 16
-    (("f32", 4096, 256, 256, 8, 0, 3), "64 rows, several units", True),             # 64, several units
+    (("f32", 4096, 256, 256, 8, 0, 3), "64 rows, several units", True),             # the largest output
+    (("f32", 4097, 256, 256, 8, 0, 3), "64 rows, several units", False),
     (("bf16", 37, 256, 1024, 64, 8, 4), "few rows", False),
     (("bf16", 1, 128, 256, 1, 0, 1), "columns", True),                              # a row,
     (("bf16", 200, 256, 384, 24, 3, 9), "columns", True),                           # tiles of 32 rows,
