@@ -45,10 +45,10 @@ struct LayerOut {
         asm volatile("" : "+v"(tid));              // a copy of its own: what comes of it is not kept through the product
         const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
         const unsigned wave = blockIdx.x * (SHARE_THREADS / WAVE) + w, waves = gridDim.x * (SHARE_THREADS / WAVE);
-        const int lanes = vec_per_row < WAVE ? vec_per_row : WAVE, rows = WAVE / lanes, r = lane / lanes;       // lanes per row, rows per pass
+        const int sh = vec_per_row < WAVE ? 31 - __builtin_clz(2 * vec_per_row - 1) : 6, rows = WAVE >> sh;      // 2^sh lanes per row, rows per pass
         // (T is some thousands at most: a product with it fits)
-        const int token = r < rows && wave < (unsigned)T ? (int)wave * rows + r : T, step = (int)(waves < (unsigned)T ? waves : T) * rows;
-        f(token, step, lane - r * lanes, lanes);
+        const int token = wave < (unsigned)T ? (int)wave * rows + (lane >> sh) : T, step = (int)(waves < (unsigned)T ? waves : T) * rows;
+        f(token, step, lane & ((1 << sh) - 1), 1 << sh);
     }
     __device__ __forceinline__ void ask(Deal &deal, int token, int step) const
     {
@@ -67,7 +67,10 @@ struct LayerOut {
         typedef unsigned vec_t __attribute__((ext_vector_type(4)));
         dealt(vec_per_row, [&](int token, int step, int piece, int lanes) {
             while (token < T) {
-                for (int c = piece; c < vec_per_row; c += lanes) {
+                int none = 0;                          // negative: one of them has no row
+#pragma unroll
+                for (int p = 0; p < AHEAD; ++p) none |= deal.row[p];
+                for (int c = none < 0 ? piece : vec_per_row; c < vec_per_row; c += lanes) {
                     vec_t v[AHEAD];
 #pragma unroll
                     for (int p = 0; p < AHEAD; ++p)
