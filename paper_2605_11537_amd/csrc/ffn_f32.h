@@ -294,10 +294,7 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
                                              : (f32x4_t){0.f, 0.f, 0.f, 0.f};
                 }
             }
-#pragma unroll
-            for (int n = 0; n < ROWS; ++n) {
-                const int r = r_first + n * ROWS_AT_ONCE;
-                if (r >= nrows) break;
+            auto finish = [&](int r, int n) {                        // n: of this thread's rows
                 f32x4_t p[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) p[q] = *reinterpret_cast<const f32x4_t *>(&part[q][r][col]);
@@ -314,6 +311,16 @@ __global__ __launch_bounds__(F32_THREADS, BM == 32 ? 3 : 2) void ffn_gemm_f32_ke
                     for (int i = 0; i < 4; ++i) v[i] = fmaf(prob[n], o[i], base[n][i]);
                     *reinterpret_cast<f32x4_t *>(static_cast<float *>(layer.out) + (size_t)token[n] * N + nt * BN + col) = v;
                 }
+            };
+            if constexpr (OUT) {
+#pragma unroll
+                for (int n = 0; n < ROWS; ++n) {
+                    const int r = r_first + n * ROWS_AT_ONCE;
+                    if (r >= nrows) break;
+                    finish(r, n);
+                }
+            } else {                                                 // rolled up: unrolled, these builds took up to 4 registers more or spilled 2
+                for (int r = r_first; r < nrows; r += ROWS_AT_ONCE) finish(r, 0);
             }
             __syncthreads();
         }
