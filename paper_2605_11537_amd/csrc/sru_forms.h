@@ -55,8 +55,11 @@ static inline bool sru_two_kernels(int B, int L, int K, int n_h, bool from_fragm
 // no room) and the weights it would fetch outweigh seven times the rows: those of a layer, once for every XCD that has a sequence, or, past
 // what stays through a layer (3.2 MB), for every sequence.  Captured, head included, us, ranges of sequences and dealt: 14 x 18, 768 -> 512, four
 // layers 43.7, 40.5; 9 x 23, 768 -> 256, ten 71.1, 68.2; 30 x 41, 768 -> 1024, four 196, 172; 38 x 255, 768 -> 1024, three 511, 481; 12 x 512,
-// 256 -> 256, four 67.8, 76.0.  Over 460 predictors whose sequences are no multiple of 8 the choice is at most 1.7 % slower than always dealt and 2.1 % faster on
-// average, 0.3 % off the better of the two.  Where something else has run in between (caches flushed) ranges are 2 .. 4 % ahead with either kind.
+// 256 -> 256, four 67.8, 76.0.  Where they outweigh the rows sixteen times, sooner: the rows that dealing fetches 8 times are next to nothing there, and
+// from 2.8 MB on some of an XCD's weights are gone by the next call (9 x 16, 960 -> 512, one layer 18.6, 17.2; 3 x 19, 1024 -> 768, two 19.3, 18.3; one
+// sequence has its channel blocks on all XCDs either way).  Over 460 predictors whose sequences are no multiple of 8, and 250 next to these lines, the
+// choice is at most 1.7 % slower than always dealt and 2.1 % (1.3 % next to the lines) faster on average.  Where something else has run in between (caches flushed)
+// ranges are 2 .. 4 % ahead with either kind.
 // Multiples of 8 keep their sequences together at any size.
 static inline bool sru_deals_channels(int B, int L, int n_in, int n_h, int n_layers, bool first_two, bool later_two)
 {
@@ -71,7 +74,8 @@ static inline bool sru_deals_channels(int B, int L, int n_in, int n_h, int n_lay
     };
     if (!first_two) layers(1, n_in);
     if (!later_two) layers(n_layers - 1, n_h);
-    return all * held / 8 > 3.8 && fetched > 7 * rows;
+    const double share = all * held / 8;
+    return (share > 3.8 && fetched > 7 * rows) || (B > 1 && share > 2.8 && fetched > 16 * rows);
 }
 
 }  // namespace moe
