@@ -31,7 +31,8 @@ constexpr int FRONT_ROUNDS = FRONT_MAX_TOKENS / PLAN_THREADS;      // chunks per
 // what it costs is that one CU passes over all ids.  Tables, histogram and permute launches -> one workgroup, us in the stream, entries dealt by
 // Zipf's law: E = 64: 16 6.7 -> 4.8, 300 6.7 -> 5.1, 1000 6.8 -> 5.4, 2048 7.3 -> 6.2 (half of them on one expert 7.3 -> 6.6); E = 256: 16 10.9 ->
 // 8.1, 2048 11.4 -> 9.6 (11.3 -> 10.0).  With a kernel for 8192 entries: 2000 7.3 -> 7.0, 3000 7.4 -> 7.5, 4096 7.4 -> 8.3, 8192 7.6 -> 11.
-// From the host, tables, row copy and combine of 300 rows: 15.4 -> 11.3.
+// From the host, tables, row copy and combine of 300 rows: 15.4 -> 11.3.  (One workgroup without DISPATCH_TURNS, which takes another 0.8 off 2048 entries
+// of which half are on one expert, and nothing off the others.)
 constexpr int DISPATCH_SMALL = 2048;
 // From here on the lanes that have their first lane's id find each other by a ballot: 64 lanes of one id take their turns at its word in LDS,
 // which made long batches of few ids slower here than in two launches.  Two launches, one workgroup without and with it, us: 2048 entries on one
