@@ -230,12 +230,14 @@ __global__ __launch_bounds__(256) void sru_pack_input_kernel(const uint4 *__rest
 // WF > 0: the weight fragments (K / 16 <= 8 * WF of them) are fetched once per workgroup, WF per wavefront, and read from LDS;
 // loaded by every wavefront for itself they are a third of what the CU's load path carries (45 bytes per clock, the bound of the
 // product here).
-template <int NRB, bool PIN, int WF>
+// DEALT: see below; a build of its own, for every argument and instruction in front of the first load is one of each layer (as arguments: a predictor of ten
+// layers 113 -> 114 us).
+template <int NRB, bool PIN, int WF, bool DEALT>
 __global__ __launch_bounds__(FUS_THREADS, NRB == 1 ? 4 : 1) void sru_layer_fused_kernel(const bf16_t *__restrict__ X,
                                                                          const bf16_t *__restrict__ Wp, int L, int K,
                                                                          int n_h, int kgates,
                                                                          const float *__restrict__ b_f,
-                                                                         const float *__restrict__ b_r, int packed_out, int xcd_bits, int per_xcd,
+                                                                         const float *__restrict__ b_r, int packed_out,
                                                                          bf16_t *__restrict__ h_out,
                                                                          bf16_t *__restrict__ ht_out)
 {
@@ -251,12 +253,12 @@ __global__ __launch_bounds__(FUS_THREADS, NRB == 1 ? 4 : 1) void sru_layer_fused
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroup i runs on XCD i % 8.  All channel blocks of a sequence read the same token rows, written a moment ago by the layer before: 8
     // contiguous ranges of the (sequence, channel block) pairs, one per XCD, so that an XCD's L2 fetches about 1/8 of the rows instead of all
-    // of them, and mostly those it wrote (n_h / 8 is a multiple of 16, the ranges are equal).  xcd_bits 0 (3 else, per_xcd: workgroups of a
-    // range): the channel blocks of a sequence go to all XCDs in turn, so that an L2 holds 1/8 of the weights instead (sru_deals_channels).  With the channel blocks of a sequence dealt to all XCDs
+    // of them, and mostly those it wrote (n_h / 8 is a multiple of 16, the ranges are equal).  DEALT: the channel blocks of a sequence go to all
+    // XCDs in turn, so that an L2 holds 1/8 of the weights instead (sru_deals_channels).  With the channel blocks of a sequence dealt to all XCDs
     // where the sequences are no multiple of 8, us: 12 x 512, 256 -> 256, four layers 76.0, now 67.8; 5 x 512, 768 -> 256, two 30.5, 28.9.
     int cb, b;
     {
-        const int ncb = n_h / FUS_CH, at = (blockIdx.x & ((1 << xcd_bits) - 1)) * per_xcd + (blockIdx.x >> xcd_bits);
+        const int ncb = n_h / FUS_CH, at = DEALT ? blockIdx.x : (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
         b = at / ncb;
         cb = at - b * ncb;
     }
@@ -637,8 +639,7 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
     const bool later_two = !w->attention && sru_two_kernels(B, L, n_h, n_h, true, false);
     const bool first_two = !(w->attention && w->n_layers == 1) &&
                            sru_two_kernels(B, L, nin, n_h, false, w->n_layers > 1 && !later_two);
-    const int xcd_bits = sru_deals_channels(B, L, nin, n_h, w->n_layers, first_two, later_two) ? 0 : 3;
-    const int per_xcd = n_h / FUS_CH * B >> xcd_bits;
+    const bool dealt = sru_deals_channels(B, L, nin, n_h, w->n_layers, first_two, later_two);
     if (!first_two && fus_packs_input(B, L, nin, n_h)) {
         bf16_t *image = (bf16_t *)(base + lay.u + fus_image_bytes(B, L, n_h));
         const int units = ceil_div(L, 32) * (nin / 64) * B;
@@ -674,17 +675,19 @@ extern "C" int sru_predict(const void *emb, const sru_weights *w, int B, int L, 
             // sequences keeps its LDS small, two to four of its workgroups share a CU).  For fragments of 257 .. 768 channels at 257 .. 512 positions that
             // is 10 % of a predictor on average over 40 of them (2 .. 4 layers, 384 .. 768 channels), us with every wavefront loading them and so:
             // 2 x 401, 384 channels, two layers 21.1, 20.2; 29 x 408, 640 channels, four 425, 367; 2 x 512, 768 channels, four 62.1, 55.1.
-#define MOE_FUS(N)                                                                                                     \
-    (pin ? (nin <= 256            ? sru_layer_fused_kernel<N, true, 2>                                                 \
-            : N > 1 && nin <= 768 ? sru_layer_fused_kernel<N, true, (N > 1 ? 6 : 2)>                                   \
-                                  : sru_layer_fused_kernel<N, true, 0>)                                                \
-         : (N > 1 && nin <= 256   ? sru_layer_fused_kernel<N, false, (N > 1 ? 2 : 0)>                                  \
-            : N > 1 && nin <= 768 ? sru_layer_fused_kernel<N, false, (N > 1 ? 6 : 0)>                                  \
-                                  : sru_layer_fused_kernel<N, false, 0>))
+#define MOE_FUS_BUILD(N, PIN, WF) (dealt ? sru_layer_fused_kernel<N, PIN, WF, true> : sru_layer_fused_kernel<N, PIN, WF, false>)
+#define MOE_FUS(N)                                                                                    \
+    (pin ? (nin <= 256            ? MOE_FUS_BUILD(N, true, 2)                                         \
+            : N > 1 && nin <= 768 ? MOE_FUS_BUILD(N, true, (N > 1 ? 6 : 2))                           \
+                                  : MOE_FUS_BUILD(N, true, 0))                                        \
+         : (N > 1 && nin <= 256   ? MOE_FUS_BUILD(N, false, (N > 1 ? 2 : 0))                          \
+            : N > 1 && nin <= 768 ? MOE_FUS_BUILD(N, false, (N > 1 ? 6 : 0))                          \
+                                  : MOE_FUS_BUILD(N, false, 0)))
             auto fused = L <= 256 ? MOE_FUS(1) : L <= 512 ? MOE_FUS(2) : MOE_FUS(4);
 #undef MOE_FUS
+#undef MOE_FUS_BUILD
             hipLaunchKernelGGL(fused, dim3((n_h / FUS_CH) * B), dim3(FUS_THREADS), 0, st, cur, (const bf16_t *)wl, L, nin, n_h, k,
-                               w->b_f ? w->b_f[l] : nullptr, w->b_r ? w->b_r[l] : nullptr, pout ? 1 : 0, xcd_bits, per_xcd, out,
+                               w->b_f ? w->b_f[l] : nullptr, w->b_r ? w->b_r[l] : nullptr, pout ? 1 : 0, out,
                                last && pout ? (bf16_t *)(base + lay.ht) : nullptr);
             MOE_CHECK_LAUNCH("sru_predict/layer");
             cur = out;
